@@ -694,7 +694,7 @@ int psgd_build_mixing_device(int topology, int n, uint64_t seed, uint64_t* step_
     const size_t tb = (size_t)n * 3 * 4;
     if (overlaps(nbr, tb, w, tb) || (step_dev && (overlaps(step_dev, 8, nbr, tb) || overlaps(step_dev, 8, w, tb))))
         return fail(PSGD_EALIAS, "psgd_build_mixing_device: nbr, w and step_dev overlap");
-    hipLaunchKernelGGL(build_mixing_kernel, dim3(1), dim3(kThreads), 0, static_cast<hipStream_t>(stream),
+    hipLaunchKernelGGL(build_mixing_kernel, dim3(1), dim3((n + 63) / 64 * 64), 0, static_cast<hipStream_t>(stream),
                        topology == PSGD_TOPO_RAND_RING ? 1 : 0, n, seed, step_dev, step_offset, (uint64_t)advance, nbr, w);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "build_mixing_kernel");
