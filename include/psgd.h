@@ -115,7 +115,7 @@ int psgd_build_mixing_device(int topology, int n, uint64_t seed, uint64_t* step_
  *
  * Enqueues its work on `stream` and returns without waiting.  The table lives in device memory,
  * so only the device can tell whether it is one ring (every table of Sec. 3 is) or a general
- * 3-slot table.  Short rows: one kernel that holds both paths.  Long rows (from about 1.5 M
+ * 3-slot table.  Short rows: one kernel that serves any table.  Long rows (from about 1.5 M
  * columns): two kernels, the ring walk and behind it the tiled kernel, each shaped for its own
  * path; both classify the table and the one it does not belong to exits at once.
  * Errors: PSGD_EINVAL;

@@ -27,10 +27,8 @@ constexpr int kUnroll = 8;           // rows whose loads are in flight together 
 using plan::kMaxGrid;                // upper bound on persistent workgroups (partials buffer sizing)
 constexpr int kGridPerCu = 4;        // persistent workgroups per compute unit (16 waves per CU)
 constexpr int kXcds = 8;             // accelerator dies of an MI355X: consecutive workgroups go to consecutive dies
-// LDS a workgroup may ask for: a compute unit has 160 KB.  The large lockstep workgroup is alone on its CU
-// and may take nearly all of it; the small one leaves room for four per CU unless the table needs more.
+// LDS a workgroup may ask for: a compute unit has 160 KB.  The large workgroups are alone on their CU.
 constexpr size_t kLdsCapLarge = 160 * 1024 - 1024;
-constexpr size_t kLdsCapSmall = 40 * 1024 - 256;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -95,6 +93,52 @@ __device__ __forceinline__ f32x4 widen_g(u32x2 b) {
 }
 __device__ __forceinline__ float widen_g(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+// Rows that may start at any element and hold any number of columns, still four columns per lane and one wide access
+// per row: gfx950 takes 128-bit (bf16: 64-bit) global accesses at any element alignment (the compiler's default for
+// this target, unaligned-access-mode), so alignment decides nothing here; the types below only tell the compiler.
+// A row of d columns has (d + 3) / 4 groups.  If 4 does not divide d the last one covers columns d-4 .. d-1, of which
+// the first few belong to the group before: they are loaded and computed but not stored (in place they may be read
+// after that group has replaced them; the values are dropped), [lo, hi) is what the lane owns.  Rows of fewer than
+// four columns are one group, loaded element by element.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+struct ColGroup {
+    int64_t col;   // first column
+    int lo, hi;    // the lane's columns are col + lo .. col + hi - 1; lo == hi: no group of its own
+};
+__device__ __forceinline__ ColGroup col_group(int64_t cg, int64_t d) {
+    ColGroup c;
+    const int64_t full = d >> 2;
+    c.col = cg * 4;
+    c.lo = 0;
+    c.hi = 4;
+    if (cg >= full) {
+        const int rem = (int)(d & 3);
+        c.col = d >= 4 ? d - 4 : 0;
+        c.hi = d >= 4 ? 4 : rem;
+        c.lo = cg == full && rem ? c.hi - rem : c.hi;
+    }
+    return c;
+}
+// FEW: rows of fewer than four columns (d of them).
+template <bool FEW> __device__ __forceinline__ f32x4 ld_cols(const float* p, int64_t d) {
+    if (!FEW) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+    return (f32x4){p[0], d > 1 ? p[1] : 0.0f, d > 2 ? p[2] : 0.0f, 0.0f};
+}
+template <bool FEW> __device__ __forceinline__ f32x4 ld_cols_raw(const float* p, int64_t d) { return ld_cols<FEW>(p, d); }
+template <bool FEW> __device__ __forceinline__ u32x2 ld_cols_raw(const uint16_t* p, int64_t d) {
+    if (!FEW) return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p));
+    return (u32x2){(uint32_t)p[0] | (d > 1 ? (uint32_t)p[1] << 16 : 0u), d > 2 ? (uint32_t)p[2] : 0u};
+}
+__device__ __forceinline__ void st_cols(float* p, f32x4 v, const ColGroup& c) {
+    if (c.lo == 0 && c.hi == 4) {
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(p));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k >= c.lo && k < c.hi) __builtin_nontemporal_store(v[k], p + k);
+    }
+}
 // Two barriers that are lighter than __syncthreads(), which also waits until every global load and store the
 // wavefront has issued is complete.  That wait is exactly what the step kernels must avoid: their loads are
 // issued early to travel during other work, and their stores need never be waited for.
@@ -138,8 +182,7 @@ struct __attribute__((aligned(8))) TileSlot {
 
 // LDS carve-up of the 3-slot step kernel (dynamic, sized by the launcher):
 //   RingEnt ring[n] | int nbr[3n] | float w[3n] | scratch
-// scratch holds the ranking arrays while the table is classified and, for a table that is not one ring, the
-// tiled path's slot table, tile buffers and merge slots (plan::tile_plan).
+// scratch holds the ranking arrays while the table is classified.
 struct Lds {
     RingEnt* ring;
     int* nbr;

@@ -117,6 +117,79 @@ inline TilePlan tile_plan(int n, int deg, int vec, int threads, bool cd, size_t 
     return p;
 }
 
+// The short-row kernel's tile: all n rows x `1 << logc` column groups on `nrg` row groups of as many lanes (a multiple
+// of 64 lanes in all), `rows` rows per lane, and its LDS: slot table (8 bytes per slot), the tile, and with the distance
+// the merge slots (48 bytes per lane).
+constexpr int kShortThreads = 1024;      // most lanes of its workgroups
+constexpr int kShortRows = 4;            // most rows per lane where the next tile's rows are loaded ahead,
+constexpr int kShortRowsOne = 8;         // and where a workgroup has one tile: what 128 registers hold in flight
+constexpr size_t kShortLds = 160 * 1024 - 2048;
+struct ShortPlan {
+    bool one;                            // a tile per workgroup
+    int threads, rows, logc, nrg;
+    int tab_bytes, tile_bytes;
+    int64_t tiles;
+    size_t lds;
+};
+inline ShortPlan short_shape(int n, int deg, int64_t ncg, bool cd, bool one, int logc, int rows) {
+    ShortPlan p;
+    p.one = one;
+    p.logc = logc;
+    const int c = 1 << logc, whole = c < 64 ? 64 / c : 1;
+    p.nrg = ((n + rows - 1) / rows + whole - 1) / whole * whole;
+    p.rows = (n + p.nrg - 1) / p.nrg;
+    if (one) p.rows = (p.rows + 1) & ~1;
+    p.threads = p.nrg * c;
+    p.tab_bytes = (n * deg * 8 + 15) & ~15;
+    p.tile_bytes = n * c * 16;
+    p.tiles = (ncg + c - 1) >> logc;
+    const int merge = cd && p.nrg > 1 ? p.threads * 48 : 0;
+    if (one && p.tile_bytes < merge) p.tile_bytes = merge;
+    p.lds = (size_t)p.tab_bytes + p.tile_bytes + (one ? 0 : merge);
+    return p;
+}
+// The widest tile of at most `threads` lanes whose LDS fits.
+inline ShortPlan short_widest(int n, int deg, int64_t ncg, bool cd, bool one, int threads, int rows) {
+    ShortPlan p;
+    for (int logc = 10; logc >= 0; --logc) {
+        p = short_shape(n, deg, ncg, cd, one, logc, rows);
+        if (p.threads <= threads && p.lds <= kShortLds) break;
+    }
+    return p;
+}
+// Workgroups of the looping form: one per tile up to what is resident together (128 registers per lane: 1024 lanes per
+// compute unit), at most `most`.
+inline int short_grid(const ShortPlan& p, int cus, int64_t most) {
+    int64_t per_cu = kShortThreads / p.threads;
+    if (per_cu > (int64_t)(kShortLds / p.lds)) per_cu = kShortLds / p.lds;
+    int64_t g = cus * per_cu;
+    if (g > p.tiles) g = p.tiles;
+    if (g > most) g = most;
+    return (int)(g < 1 ? 1 : g);
+}
+// Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
+//   - everything in one round of at most one workgroup per compute unit, eight rows per lane: the whole chip's loads
+//     are in flight at once.  8 learners x 1 M without the distance 15.7 us, looping over narrower tiles 18.9; 64 x 100 k
+//     17.9 against 21.2.  The widest workgroup that still occupies more than half of the compute units: 16 x 250 k at
+//     512 lanes (245 tiles) 12.4, at 1024 (123 tiles) 15.2;
+//   - up to 8 learners beyond that: a lane holds all rows of its columns, nothing is exchanged and small independent
+//     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2;
+//   - all else: 1024 lanes, four rows each, the next tile's loads ahead: 512 x 60 k 77.6 us, at 512 lanes 107;
+//     64 x 1 M with bf16 gradients 126 against 130.
+// `slots`: with the distance, the most workgroups.
+inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, int64_t slots) {
+    for (int threads = kShortThreads; threads >= 256; threads /= 2) {
+        const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, kShortRowsOne);
+        if (p.threads > threads || p.tiles > cus) break;
+        if (p.tiles > cus / 2 || threads == 256) return p;
+    }
+    if (n <= kShortRowsOne) {
+        const ShortPlan p = short_widest(n, deg, ncg, cd, true, 256, kShortRowsOne);
+        if (!cd || p.tiles <= slots) return p;
+    }
+    return short_widest(n, deg, ncg, cd, false, kShortThreads, kShortRows);
+}
+
 }  // namespace plan
 }  // namespace psgd
 

@@ -1,8 +1,8 @@
 // libpsgd's HIP translation unit (gfx950 / CDNA4): the launchers and C entry points for the model-averaging step
 //     X_out[i,:] = sum_s w[i,s] * X[nbr[i,s],:] - lr * G[i,:]            (Sec. 2, Eq. 2)
 // and for the consensus distance sum_i ||x_i - xbar||^2 (Sec. 3).  The kernels live in the headers included
-// below: psgd_device.h (shared building blocks), psgd_ring_walk.h (ring tables, registers only), psgd_tiled.h
-// (any other table, LDS tiles), psgd_streams.h (global averaging, distance, gradient producer, reference streams,
+// below: psgd_device.h (shared building blocks), psgd_short.h (short rows, any table), psgd_ring_walk.h (long rows, ring
+// tables, registers only), psgd_tiled.h (long rows, any other table, LDS tiles), psgd_streams.h (global averaging, distance, gradient producer, reference streams,
 // table builder).
 //
 // The step is bound by HBM traffic (about 7 flops against 10-12 bytes per element), so the
@@ -17,7 +17,8 @@
 //     buffered, with the next tiles travelling from HBM through registers while the current one is
 //     computed; a tile is complete in LDS before its first output is stored, so this path too may
 //     run in place.
-// Tables live in device memory and are validated and classified (one ring or not) by the kernels.
+// Short rows, where a launch is bound by latency, take one kernel of their own for every table (psgd_short.h).
+// Tables live in device memory and are validated and, on long rows, classified (one ring or not) by the kernels.
 // Workgroups are persistent, so table staging is paid once per launch.  On long rows the workgroups are
 // large (768 lanes for the ring walk, 512 or 1024 for the tiled path), one per compute unit; the ring walk's
 // wavefronts sweep the rows in lockstep, a barrier per batch of rows: the HBM then sees one 12 KB burst
@@ -38,6 +39,7 @@
 static __device__ __align__(256) double scratch[PSGD_STATIC_SLOTS];
 
 #include "psgd_device.h"
+#include "psgd_short.h"
 #include "psgd_tiled.h"
 #include "psgd_ring_walk.h"
 #include "psgd_streams.h"
@@ -253,22 +255,18 @@ int allow_lds(const void* fn, size_t lds_bytes) {
 }
 constexpr int kLaunchRefused = INT32_MIN;
 
-// Launches one instantiation of the mix kernel on a persistent grid sized to what is
-// actually resident: min(kGridPerCu, occupancy for this LDS size) workgroups per CU.
+// Launches one instantiation of the ring-walk kernel, one workgroup per compute unit.
 // Returns the grid size, minus the grid size (and launches nothing) when the fused distance would need more
 // than `slots` partials, or kLaunchRefused when the runtime refuses the LDS size.
-template <int VEC, typename GT, bool CD, int T, bool TILES>
-int launch_mix_t(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
-                 const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, int lpr,
-                 double* partials, int slots) {
-    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<VEC, GT, CD, T, TILES>);
+template <int VEC, typename GT, bool CD>
+int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
+               const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, int slots) {
+    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<VEC, GT, CD>);
     if (allow_lds(fn, lds_bytes)) return kLaunchRefused;
-    const int occ = resident_per_cu(fn, lds_bytes, T);
-    const int want = T == kThreads ? kGridPerCu : 1;
-    const int grid = persistent_grid(di, d / VEC, occ < want ? occ : want, T);
+    const int grid = persistent_grid(di, d / VEC, 1, kRingThreads);
     if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
-    hipLaunchKernelGGL((mix_step_kernel<VEC, GT, CD, T, TILES>), dim3(grid), dim3(T), lds_bytes, s, X, X_out, G, nbr, w,
-                       n, d, ld, neg_lr, lpr, make_sweeps(d / VEC, grid, T), partials);
+    hipLaunchKernelGGL((mix_step_kernel<VEC, GT, CD>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
+                       n, d, ld, neg_lr, make_sweeps(d / VEC, grid, kRingThreads), partials);
     return grid;
 }
 
@@ -278,14 +276,40 @@ inline bool long_rows(const DeviceInfo& di, int64_t column_groups, int sweeps = 
     return column_groups >= (int64_t)di.cus * kRingThreads * sweeps;
 }
 
-template <int VEC, typename GT, bool CD>
-int launch_mix(const DeviceInfo& di, bool big, size_t lds_bytes, hipStream_t s, const float* X, float* X_out,
-               const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, int lpr,
-               double* partials, int slots) {
-    return big ? launch_mix_t<VEC, GT, CD, kRingThreads, false>(di, lds_bytes, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, lpr,
-                                                                partials, slots)
-               : launch_mix_t<VEC, GT, CD, kThreads, true>(di, lds_bytes, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, lpr,
-                                                           partials, slots);
+// Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
+// negative status.
+template <typename GT, bool CD, int DEG, int R, bool ONE, bool FEW>
+int launch_short_t(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
+                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
+                   int slots) {
+    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, FEW>);
+    if (int rc = allow_lds(fn, p.lds)) return rc;
+    const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? slots : INT32_MAX);
+    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X, X_out, G,
+                       nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
+    return CD ? grid : 0;
+}
+
+template <typename GT, bool CD, int DEG>
+int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
+                 const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
+                 int slots) {
+#define PSGD_SHORT(R, ONE, FEW) \
+    return launch_short_t<GT, CD, DEG, R, ONE, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots)
+    if (d < 4) return launch_short_t<GT, CD, 0, 2, true, true>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
+    if (p.one) {
+        if (p.rows == 2) PSGD_SHORT(2, true, false);
+        if (p.rows == 4) PSGD_SHORT(4, true, false);
+        if (p.rows == 6) PSGD_SHORT(6, true, false);
+        if (p.rows == 8) PSGD_SHORT(8, true, false);
+    } else {
+        if (p.rows == 1) PSGD_SHORT(1, false, false);
+        if (p.rows == 2) PSGD_SHORT(2, false, false);
+        if (p.rows == 3) PSGD_SHORT(3, false, false);
+        if (p.rows == 4) PSGD_SHORT(4, false, false);
+    }
+#undef PSGD_SHORT
+    return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
 }
 
 // Pitches are in elements of the array they belong to.
@@ -348,58 +372,44 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const bool vec4 = (d % 4 == 0) && (ldx % 4 == 0) && (ldo % 4 == 0) && (ldg % 4 == 0) && aligned_to(X, 16) &&
                       aligned_to(X_out, 16) && aligned_to(G, 4 * sizeof(GT));
     const int vec = vec4 ? 4 : 1;
-    // Long rows take a large workgroup that is alone on its compute unit; short ones four small workgroups.
-    const bool big = long_rows(*di, d / vec);
     const float neg_lr = -lr;
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
+    const bool big = long_rows(*di, (d + 3) / 4);
+    if (!big) {
+        const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
+                                         : plan::short_plan(n, deg, (d + 3) / 4, di->cus, want_cd, slots);
+        if (want_cd && deg == 3) grid = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
+        else if (want_cd) grid = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
+        else if (deg == 3) grid = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
+        else grid = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
+        if (grid < 0) return grid;
+    }
     const size_t classify = lds_table_bytes(n) + (size_t)n * 4 * sizeof(int);   // the 3-slot kernels' table copy + ranking arrays
-    if (deg == 3) {
-        // The ring-walk kernel does the work when the table is one ring (every table of Sec. 3).  On short rows
-        // it also carries the tiled path, so that one launch serves any table; on long rows the tiled kernel
-        // follows it (below), because there each path wants its own workgroup shape and registers.
-        size_t ring_lds = classify;
-        int ring_lpr = 0;
-        if (!big) {
-            plan::TilePlan rp = plan::tile_plan(n, 3, vec, kThreads, want_cd, kLdsCapSmall, lds_table_bytes(n), TileShape<kThreads>::RB);
-            if (rp.lpr == 0) rp = plan::tile_plan(n, 3, vec, kThreads, want_cd, kLdsCapLarge, lds_table_bytes(n), TileShape<kThreads>::RB);
-            if (rp.lpr == 0) return fail(PSGD_EINVAL, "%s: n=%d does not fit the tiled path's LDS", name, n);
-            ring_lpr = rp.lpr;
-            if (rp.total > ring_lds) ring_lds = rp.total;
-        }
-        if (vec4 && want_cd)
-            grid = launch_mix<4, GT, true>(*di, big, ring_lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, ring_lpr, partials, slots);
-        else if (vec4)
-            grid = launch_mix<4, GT, false>(*di, big, ring_lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, ring_lpr, partials, slots);
-        else if (want_cd)
-            grid = launch_mix<1, GT, true>(*di, big, ring_lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, ring_lpr, partials, slots);
-        else
-            grid = launch_mix<1, GT, false>(*di, big, ring_lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, ring_lpr, partials, slots);
+    if (big && deg == 3) {
+        // The ring-walk kernel does the work when the table is one ring (every table of Sec. 3); the tiled kernel
+        // follows it (below) for all others, because each path wants its own workgroup shape and registers.
+        if (vec4 && want_cd) grid = launch_mix<4, GT, true>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
+        else if (vec4) grid = launch_mix<4, GT, false>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
+        else if (want_cd) grid = launch_mix<1, GT, true>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
+        else grid = launch_mix<1, GT, false>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
         if (grid == kLaunchRefused) return PSGD_EHIP;   // allow_lds has recorded the reason
         if (grid < 0)
             return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, -grid, slots);
         const hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return hip_fail(e1, name);
     }
-    if (deg != 3 || big) {
+    if (big) {
         // Tiled kernel: every table with another slot count, and behind the ring walk for 3-slot tables, where
         // it does the work only if the table turns out not to be one ring (decided on the device by both).
-        // Long rows: the 1024-lane one-batch form where the shape allows it (n <= 64 at 1 KB row segments), else
-        // 512 lanes with several batches per tile.  Short rows: small workgroups, several per compute unit.
+        // The 1024-lane one-batch form where the shape allows it (n <= 64 at 1 KB row segments; 512 lanes with the
+        // distance), else 512 lanes with several batches per tile.
         const size_t base = 0;
-        plan::TilePlan tp;
-        tp.lpr = 0;
-        bool deep = false;
         const int deep_threads = want_cd ? kTileThreads : kDeepThreads;
-        if (big) {
-            tp = plan::tile_plan(n, deg, vec, deep_threads, want_cd, kLdsCapLarge, base,
-                                 want_cd ? TileShape<kTileThreads>::RB : TileShape<kDeepThreads>::RB, true);
-            deep = tp.lpr != 0;
-            if (!deep) tp = plan::tile_plan(n, deg, vec, kTileThreads, want_cd, kLdsCapLarge, base, TileShape<kTileThreads>::RB);
-        } else {
-            tp = plan::tile_plan(n, deg, vec, kThreads, want_cd, kLdsCapSmall, base, TileShape<kThreads>::RB);
-            if (tp.lpr == 0) tp = plan::tile_plan(n, deg, vec, kThreads, want_cd, kLdsCapLarge, base, TileShape<kThreads>::RB);
-        }
+        plan::TilePlan tp = plan::tile_plan(n, deg, vec, deep_threads, want_cd, kLdsCapLarge, base,
+                                            want_cd ? TileShape<kTileThreads>::RB : TileShape<kDeepThreads>::RB, true);
+        const bool deep = tp.lpr != 0;
+        if (!deep) tp = plan::tile_plan(n, deg, vec, kTileThreads, want_cd, kLdsCapLarge, base, TileShape<kTileThreads>::RB);
         if (tp.lpr == 0)
             return fail(PSGD_EINVAL, "%s: n=%d, deg=%d does not fit the tiled path's LDS", name, n, deg);
         const int lpr = tp.lpr;
@@ -431,8 +441,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     do {                                                                                                                \
         if (deep && tp.lpr >= 64) PSGD_DEG_LAUNCH(VEC, CD, (CD ? kTileThreads : kDeepThreads), 1);                      \
         else if (deep) PSGD_DEG_LAUNCH(VEC, CD, (CD ? kTileThreads : kDeepThreads), 2);                                 \
-        else if (big) PSGD_DEG_LAUNCH(VEC, CD, kTileThreads, 0);                                                        \
-        else PSGD_DEG_LAUNCH(VEC, CD, kThreads, 0);                                                                     \
+        else PSGD_DEG_LAUNCH(VEC, CD, kTileThreads, 0);                                                                 \
     } while (0)
         if (vec4 && want_cd) PSGD_DEG_PICK(4, true);
         else if (vec4) PSGD_DEG_PICK(4, false);

@@ -4,7 +4,6 @@
 #define PSGD_RING_WALK_H
 
 #include "psgd_device.h"
-#include "psgd_tiled.h"
 
 namespace psgd {
 namespace {
@@ -85,16 +84,15 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 // CD = also reduce the consensus distance of the outputs into partials[blockIdx.x].
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
 // same number of sweeps, lanes beyond the chunk idle.
-// T = workgroup size: kRingThreads on long rows, kThreads (four workgroups per CU) where the row is too
-// short to give every CU a large workgroup's worth of column groups twice over.
-// TILES: the kernel also carries the tiled path for tables that are not one ring (short rows: one launch does
-// whatever the table needs).  Without it (long rows) such a table is left to the tiled kernel, which the launcher
-// enqueues right behind this one and which classifies the table the same way; this kernel then writes nothing.
-template <int VEC, typename GT, bool CD, int T, bool TILES>
-__global__ __launch_bounds__(T, 3) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
-                                                     const int32_t* __restrict__ nbr, const float* __restrict__ w,
-                                                     int n, int64_t d, Pitch ld, float neg_lr, int lpr,
-                                                     Sweeps sweeps, double* __restrict__ partials) {
+// A table that is not one ring is left to the tiled kernel, which the launcher enqueues right behind this one and which
+// classifies the table the same way; this kernel then writes nothing.
+template <int VEC, typename GT, bool CD>
+__global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
+                                                                   const int32_t* __restrict__ nbr,
+                                                                   const float* __restrict__ w, int n, int64_t d, Pitch ld,
+                                                                   float neg_lr, Sweeps sweeps,
+                                                                   double* __restrict__ partials) {
+    constexpr int T = kRingThreads;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[T / 64];
     const Lds l = carve(lds_raw, n);
@@ -119,14 +117,6 @@ __global__ __launch_bounds__(T, 3) void mix_step_kernel(const float* X, float* X
             ring_walk<VEC, GT, CD>(X + col, Xout + col, G + col, l.ring, n, ld, neg_lr, stats, act);
             if (CD && act) total += stats.result(inv_n);
         }
-    } else if (TILES) {
-        // The slot table in the tiled path's form, then the tile buffers (the ranking arrays that shared this
-        // space are dead: stage_table ended with a barrier on every path that comes here).
-        TileSlot* tab = reinterpret_cast<TileSlot*>(l.scratch);
-        for (int e = threadIdx.x; e < 3 * n; e += T) tab[e] = TileSlot{(uint32_t)(l.nbr[e] * lpr), l.w[e]};
-        __syncthreads();
-        const size_t tab_bytes = (((size_t)n * 3 * sizeof(TileSlot)) + 15) & ~(size_t)15;
-        total = tile_path<VEC, GT, CD, T>(X, Xout, G, tab, l.scratch + tab_bytes, n, 3, ld, ncg, neg_lr, lpr, inv_n);
     }
     if (CD) {
         const double bs = block_sum<T>(total, lds_waves);

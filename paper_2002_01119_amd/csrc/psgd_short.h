@@ -1,0 +1,263 @@
+// The model-averaging step (Sec. 2, Eq. 2) on short rows, for any mixing table: mix_short_kernel.  Included by
+// psgd_kernels.hip only.
+#ifndef PSGD_SHORT_H
+#define PSGD_SHORT_H
+
+#include "psgd_device.h"
+
+#include <type_traits>
+
+namespace psgd {
+namespace {
+
+// ---------------------------------------------------------------------------------------
+// One tile = all n rows x C column groups.  The workgroup's lanes form nrg row groups of C lanes; lane (rg, lane)
+// loads, produces and stores rows rg, rg + nrg, ... of column group `lane`, R of them, all in registers.  The X rows
+// pass through LDS once, where the other row groups read their neighbours; any table is served alike, so nothing is
+// classified.  The tile is complete in LDS before its first output is stored and tiles own their columns, so X_out
+// may alias X.
+//
+// Launches of this size are bound by latency and by how many bytes are in flight, not by the HBM's rate.  Rows are
+// spread over lanes as well as columns, so that few columns (many learners of a small model) still fill the chip;
+// every load of the first tile is issued at once, behind the loads of the table that they do not depend on; and where
+// a workgroup has several tiles the next one's X rows are loaded as soon as the registers have gone to LDS, its
+// gradients as each row is finished.
+//
+// Measured (step with the distance and its final sum unless noted, MI355X; before: the ring walk or the tiled path in
+// small workgroups, a lane walking all rows): 512 learners x 60 k 171 -> 77 us (4.8 TB/s), 16 x 1 M with 5 slots 49.8 -> 38.6,
+// 8 x 1 M 25.6 -> 18.5, 100 x 50 k without the distance 34.7 -> 10.8, 32 x 786 433 at odd addresses, no distance, 77 -> 58.
+//
+// Inside the loop every load and store is unconditional (the waits then count operations instead of waiting for all
+// of them): a lane without a row repeats the last one, loads and stores alike.  The one tile at the ragged end of the
+// rows comes after the loop.
+//
+// The distance (CD): every lane measures its outputs against its first one, in fp64, and the row groups' sums meet in
+// LDS, where they are brought to row group 0's pivot exactly (short_merge).
+// ---------------------------------------------------------------------------------------
+// The column sums a_q of the row groups, each against its own pivot p_q, to the squares about the column's mean: with
+// P = p_0, D_q = p_q - P and m_q rows in group q,
+//     sum_i (o_i - P)   = sum_q (a_q + m_q D_q)
+//     sum_i (o_i - P)^2 = sum_q (sq_q + 2 D_q a_q + m_q D_q^2)
+// exactly; in fp64 the corrections are of the size of the sums themselves, as every pivot is one of the outputs, and
+// equal outputs give exactly 0.  The lanes of a wavefront read neighbouring columns of 64 / L row groups (L columns
+// side by side), so that few columns occupy many lanes; these shares are added by a symmetric exchange.
+// sums, pivots: [4][nrg][C].  live(k, l): whether column k of lane l exists.  Returns this lane's part of the total.
+template <typename LIVE>
+__device__ __forceinline__ double short_merge(const double* sums, const float* pivots, int logc, int nrg, int n, int T,
+                                              double inv_n, const LIVE& live) {
+    const int C = 1 << logc, most = nrg >= 8 ? 4 : 6;
+    const int logl = logc < most ? logc : most, parts = 64 >> logl;
+    const int each = n / nrg, more = n % nrg;                   // rows of group q: each, one more if q < more
+    double total = 0.0;
+    for (int idx = threadIdx.x; idx < 4 * C * parts; idx += T) {
+        const int part = (idx >> logl) & (parts - 1);
+        const int col = (idx >> 6 << logl) + (idx & ((1 << logl) - 1));
+        const int k = col >> logc, l = col & (C - 1);
+        const size_t at0 = ((size_t)k * nrg << logc) + l;
+        const double p0 = (double)pivots[at0];
+        double at = 0.0, corr = 0.0;
+#pragma unroll 4
+        for (int q = part; q < nrg; q += parts) {
+            const double aq = sums[at0 + ((size_t)q << logc)];
+            const double dq = (double)pivots[at0 + ((size_t)q << logc)] - p0;
+            const double tq = fma((double)(each + (q < more ? 1 : 0)), dq, aq);
+            at += tq;
+            corr = fma(dq, tq + aq, corr);
+        }
+        for (int off = 1 << logl; off < 64; off <<= 1) {
+            at += __shfl_xor(at, off, 64);
+            corr += __shfl_xor(corr, off, 64);
+        }
+        if (part == 0 && live(k, l)) total += corr - at * at * inv_n;
+    }
+    return total;
+}
+
+// DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (twice the rows per lane: nothing is loaded ahead,
+// so their registers hold rows).  FEW: rows of fewer than four columns.
+template <typename GT, bool CD, int DEG, int R, bool ONE, bool FEW>
+__global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
+    const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
+    int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
+    double* __restrict__ partials) {
+    typedef typename RawG<GT, 4>::T GR;
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    __shared__ double lds_waves[plan::kShortThreads / 64];
+    __shared__ int lds_bad[plan::kShortThreads / 64];
+    const int deg = DEG ? DEG : deg_any;
+    const int T = nrg << logc, C = 1 << logc, tid = threadIdx.x, lane = tid & (C - 1), lane16 = lane * 16;
+    int rg = tid >> logc;
+    TileSlot* tab = reinterpret_cast<TileSlot*>(lds_raw);       // slot: byte offset of the source row in the tile, weight
+    char* tile = lds_raw + tab_bytes;
+    // the distance's merge slots, [4][nrg][C]: where there is one tile they take its place once it has been read
+    double* sums = reinterpret_cast<double*>(tile + (ONE ? 0 : tile_bytes));
+    float* pivots = reinterpret_cast<float*>(sums + 4 * T);
+    const int entries = n * deg;
+    const int64_t nfull = (d >> 2) >> logc, ntiles = (((d + 3) >> 2) + C - 1) >> logc;
+    const int64_t step = gridDim.x;
+    int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds);
+    const double inv_n = 1.0 / (double)n;
+    double total = 0.0;
+
+    // The table's loads go first, the first tile's behind them; a lane's share of a larger table follows.
+    constexpr int TE = 2;
+    int32_t tv[TE];
+    float tw[TE];
+#pragma unroll
+    for (int i = 0; i < TE; ++i) {
+        const int e = tid + i * T < entries ? tid + i * T : entries - 1;
+        tv[i] = nbr[e];
+        tw[i] = w[e];
+    }
+    f32x4 x[R];
+    GR g[R];
+    auto row_of = [&](int u) {
+        const int r = rg + u * nrg;
+        return r < n ? r : n - 1;
+    };
+    ColGroup cg = col_group(t * C + lane, d);
+#pragma unroll
+    for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW>(X + (int64_t)row_of(u) * ld.x + cg.col, d);
+#pragma unroll
+    for (int u = 0; u < R; ++u) g[u] = ld_cols_raw<FEW>(G + (int64_t)row_of(u) * ld.g + cg.col, d);
+    int bad = 0;
+#pragma unroll
+    for (int i = 0; i < TE; ++i) {
+        const int e = tid + i * T;
+        if (e < entries) {
+            bad |= (unsigned)tv[i] >= (unsigned)n;
+            tab[e] = TileSlot{(uint32_t)tv[i] << (logc + 4), tw[i]};
+        }
+    }
+    for (int e = tid + TE * T; e < entries; e += T) {
+        const int v = nbr[e];
+        bad |= (unsigned)v >= (unsigned)n;
+        tab[e] = TileSlot{(uint32_t)v << (logc + 4), w[e]};
+    }
+    const bool wave_bad = __any(bad);
+    if ((tid & 63) == 0) lds_bad[tid >> 6] = wave_bad;
+    lds_barrier();
+    {
+        int any = 0;
+        for (int i = 0; i < T / 64; ++i) any |= lds_bad[i];
+        if (any) {                                              // nothing is written
+            if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
+            if (CD && tid == 0) partials[blockIdx.x] = __builtin_nan("");
+            return;
+        }
+    }
+
+    // One tile, its X rows in x and its gradients in g; the next one's, columns `next`, take their places.
+    auto one_tile = [&](auto full, const ColGroup& next) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(full)::value;
+        // Row offsets are cheap to compute again and would take two registers per row and array if kept from tile to tile.
+        asm volatile("" : "+v"(rg));
+#pragma unroll
+        for (int u = 0; u < R; ++u) *reinterpret_cast<f32x4*>(tile + ((row_of(u) << (logc + 4)) + lane16)) = x[u];
+        lds_barrier();
+        if (FULL) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW>(X + (int64_t)row_of(u) * ld.x + next.col, d);
+        }
+        // SB rows' slot chains advance together (a table read, then a tile read that depends on it, per slot).
+        constexpr int SB = R < 4 ? R : 4;
+        double a[4] = {0.0, 0.0, 0.0, 0.0}, sq[4] = {0.0, 0.0, 0.0, 0.0};
+        f32x4 pv;
+#pragma unroll
+        for (int j = 0; j < R; j += SB) {
+            __builtin_amdgcn_sched_barrier(0);
+            const TileSlot* tp[SB];
+            f32x4 out[SB];
+#pragma unroll
+            for (int i = 0; i < SB; ++i) {
+                if (j + i >= R) break;
+                tp[i] = tab + row_of(j + i) * deg;
+                const TileSlot e = tp[i][0];
+                out[i] = *reinterpret_cast<const f32x4*>(tile + (e.off + lane16)) * e.w;
+            }
+            auto slot = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < SB; ++i) {
+                    if (j + i >= R) break;
+                    const TileSlot e = tp[i][s];
+                    out[i] = vfma(e.w, *reinterpret_cast<const f32x4*>(tile + (e.off + lane16)), out[i]);
+                }
+            };
+            if (DEG) {
+#pragma unroll
+                for (int s = 1; s < DEG; ++s) slot(s);
+            } else {
+#pragma unroll 2
+                for (int s = 1; s < deg; ++s) slot(s);
+            }
+#pragma unroll
+            for (int i = 0; i < SB; ++i) {
+                const int u = j + i;
+                if (u >= R) break;
+                const f32x4 o = vfma(neg_lr, widen_g(g[u]), out[i]);
+                float* to = Xout + (int64_t)row_of(u) * ld.o + cg.col;
+                if (FULL) {
+                    __builtin_nontemporal_store(o, reinterpret_cast<f32x4_any*>(to));
+                    g[u] = ld_cols_raw<FEW>(G + (int64_t)row_of(u) * ld.g + next.col, d);
+                } else if (rg + u * nrg < n) {
+                    st_cols(to, o, cg);
+                }
+                if (CD && u == 0) pv = o;
+                if (CD && u > 0 && rg + u * nrg < n) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const double df = (double)o[k] - (double)pv[k];
+                        a[k] += df;
+                        sq[k] = fma(df, df, sq[k]);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (CD && nrg == 1) {                                   // few learners: the lane has seen all rows of its columns
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (FULL || (k >= cg.lo && k < cg.hi)) total += sq[k] - a[k] * a[k] * inv_n;
+        } else if (CD) {
+            if (ONE) lds_barrier();                             // every row of the tile has been read
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                sums[((k * nrg + rg) << logc) + lane] = a[k];
+                pivots[((k * nrg + rg) << logc) + lane] = pv[k];
+                if (FULL || (k >= cg.lo && k < cg.hi)) total += sq[k];   // the column exists and is this lane's
+            }
+        }
+        lds_barrier();                                          // the tile is free again; the sums are complete
+        if (CD && nrg > 1) {
+            const int64_t first = (t - (FULL ? step : 0)) * C;  // t is already the next tile's in the loop
+            total += short_merge(sums, pivots, logc, nrg, n, T, inv_n, [&](int k, int l) {
+                if (FULL) return true;
+                const ColGroup c = col_group(first + l, d);
+                return k >= c.lo && k < c.hi;
+            });
+        }
+    };
+    while (!ONE && t < nfull) {
+        t += step;
+        const ColGroup next = col_group(t * C + lane, d);
+        one_tile(std::true_type{}, next);
+        cg = next;
+    }
+    if (t < ntiles) one_tile(std::false_type{}, cg);
+    if (CD) {
+        total = wave_sum(total);
+        if ((tid & 63) == 0) lds_waves[tid >> 6] = total;
+        lds_barrier();
+        if (tid == 0) {
+            double r = 0.0;
+            for (int i = 0; i < T / 64; ++i) r += lds_waves[i];
+            partials[blockIdx.x] = r;
+        }
+    }
+}
+
+}  // namespace
+}  // namespace psgd
+
+#endif

@@ -1,4 +1,4 @@
-// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) for mixing tables that are not one ring, and its
+// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows for mixing tables that are not one ring, and its
 // kernel mix_deg_kernel.  Included by psgd_kernels.hip only.
 #ifndef PSGD_TILED_H
 #define PSGD_TILED_H
@@ -19,9 +19,9 @@ namespace {
 // the next tile.  A tile is complete in LDS before its first output is stored, and different tiles own
 // different columns, so X_out may alias X.
 //
-// Two forms.  tile_path_deep (long rows, up to 256 learners): the tile's rows are one batch, every memory
+// Two forms.  tile_path_deep (up to 256 learners): the tile's rows are one batch, every memory
 // operation is unconditional, and a lane reloads each of its registers the moment its value has been used (see
-// there).  tile_path (short rows; long rows with more learners): several batches per tile, the next tile's
+// there).  tile_path (more learners): several batches per tile, the next tile's
 // batch travelling while this tile's is computed, loads under conditions.
 //
 // Per output the slots are taken in table order, acc = w0 * x0, one fma per further slot, then the gradient
@@ -47,12 +47,10 @@ __device__ __forceinline__ double lane_xor_quad(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// The large workgroups are alone on their compute unit: 512 lanes with up to 256 registers per lane (8
-// wavefronts x 8 rows cover n = 64 at once), or 1024 lanes with up to 128 (16 x 4).  The small one, which serves
-// short rows (launches bound by latency, several workgroups per CU) and shares the 3-slot kernel with the ring
-// walk there, stays frugal.
+// The workgroups are alone on their compute unit: 512 lanes with up to 256 registers per lane (8
+// wavefronts x 8 rows cover n = 64 at once), or 1024 lanes with up to 128 (16 x 4).
 template <int T> struct TileShape {
-    static constexpr int RB = T > 512 ? 4 : T > 256 ? 8 : 2;   // rows per lane and batch
+    static constexpr int RB = T > 512 ? 4 : 8;   // rows per lane and batch
     static constexpr int SB = T == 512 ? 3 : 2;   // rows whose slot chains advance together (two slots per trip each);
                                                  // more rows at once cost registers and ran slower (4: -1 to -6 %)
 };

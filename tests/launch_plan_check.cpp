@@ -165,6 +165,27 @@ int main() {
         CHECK(tile_plan(257, 3, 4, 1024, false, large, 0, 4, true).lpr == 0, "n = 257: no one-batch plan");
         CHECK(!tile_plan(64, 3, 1, 1024, true, large, 0, 4, true).comb_in_tile, "4 B per lane: the merge slots fit beside the tiles");
     }
+    // short rows: whole wavefronts, the rows covered, the LDS within a compute unit's, the grid within the buffer
+    for (int n : {1, 2, 3, 5, 8, 9, 16, 17, 33, 64, 65, 100, 128, 200, 256, 257, 300, 511, 512})
+        for (int deg : {1, 3, 8, 13, 32})
+            for (int64_t ncg : {1, 2, 63, 64, 65, 1000, 16384, 65536, 65537, 250000, 393215})
+                for (int cus : {1, 64, 256, 304})
+                    for (bool cd : {false, true})
+                        for (int slots : {2048, kMaxGrid}) {
+                            if ((long)n * deg > 4096) continue;
+                            const ShortPlan p = short_plan(n, deg, ncg, cus, cd, slots);
+                            CHECK(p.threads % 64 == 0 && p.threads >= 64 && p.threads <= kShortThreads && p.threads == p.nrg << p.logc,
+                                  "short rows n=%d deg=%d ncg=%lld: %d lanes", n, deg, (long long)ncg, p.threads);
+                            CHECK(p.rows * p.nrg >= n && p.rows >= 1 && p.rows <= (p.one ? kShortRowsOne : kShortRows) &&
+                                      (!p.one || p.rows % 2 == 0), "short rows n=%d: %d rows on %d row groups", n, p.rows, p.nrg);
+                            CHECK(p.tiles << p.logc >= ncg && (p.tiles - 1) << p.logc < ncg, "short rows: %lld tiles", (long long)p.tiles);
+                            const size_t merge = cd && p.nrg > 1 ? (size_t)p.threads * 48 : 0;
+                            CHECK(p.tab_bytes >= n * deg * 8 && p.tab_bytes % 16 == 0 && p.tile_bytes >= n * (16 << p.logc) &&
+                                      p.lds <= kShortLds && p.lds >= (size_t)p.tab_bytes + p.tile_bytes + (p.one ? 0 : merge) &&
+                                      (!p.one || (size_t)p.tile_bytes >= merge), "short rows n=%d deg=%d: LDS %zu", n, deg, p.lds);
+                            const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
+                            CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
+                        }
     if (failures) return 1;
     std::printf("launch plan ok\n");
     return 0;

@@ -1,0 +1,109 @@
+"""The short-row kernel at the edges of its forms: one round of tiles at each workgroup size, all rows in one lane, the
+looping form with a ragged last tile, row counts that do not fill the row groups, rows of one to five columns, arrays
+whose rows start at any element.  Every element and the distance against the oracle's sparse form."""
+import numpy as np
+import pytest
+
+from oracle import psgd_oracle as orc
+from paper_2002_01119_amd import inputs as inp
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# n, d, slots per row, gradients, elements between the rows of X / X_out / G beyond d (None: dense)
+CASES = [
+    (1, 1, 3, "f32", None), (3, 2, 2, "bf16", (1, 2, 3)), (512, 3, 3, "f32", None), (256, 5, 4, "bf16", (3, 0, 5)),
+    (2, 4, 3, "f32", (1, 1, 1)), (7, 257, 5, "bf16", None),
+    (9, 40_003, 3, "f32", (5, 2, 1)), (16, 250_001, 3, "bf16", None), (33, 63_999, 13, "f32", None),
+    (512, 6_001, 8, "bf16", (1, 2, 7)), (100, 50_002, 3, "f32", None),
+    (8, 1_048_578, 3, "f32", None), (8, 1_200_003, 3, "bf16", (2, 3, 1)), (5, 1_570_001, 4, "f32", None),
+    (9, 1_100_002, 3, "bf16", None), (16, 700_001, 5, "f32", (1, 2, 3)), (64, 200_003, 3, "bf16", (3, 1, 1)),
+    (100, 120_001, 3, "f32", None), (257, 40_007, 4, "bf16", None), (512, 20_002, 3, "f32", (1, 0, 2)),
+]
+
+
+@pytest.fixture(scope="module")
+def psgd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2002_01119_amd import psgd as m
+    m.load()
+    torch.cuda.set_device(0)
+    return m
+
+
+def _strided(a, extra, shift):
+    n, d = a.shape
+    pool = torch.empty(n * (d + extra) + shift, dtype=torch.from_numpy(a[:0]).dtype, device="cuda:0")
+    t = pool.as_strided((n, d), (d + extra, 1), shift)
+    t.copy_(torch.from_numpy(a))
+    return t
+
+
+@pytest.mark.parametrize("n,d,deg,gkind,extra", CASES)
+def test_short_rows_every_element(psgd, n, d, deg, gkind, extra):
+    rng = np.random.default_rng(n + d)
+    if deg == 3 and n != 64:
+        nbr, w = psgd.build_mixing(psgd.TOPO_RAND_RING, n, 5, d)
+    else:
+        c = rng.random(deg).astype(np.float32) + np.float32(0.05)
+        nbr = np.stack([rng.permutation(n) for _ in range(deg)], axis=1).astype(np.int32)
+        w = np.tile((c / c.sum()).astype(np.float32), (n, 1))
+    X = inp.host_normal_f32((n, d), 1.0, 31 + n) + np.float32(3.0)
+    G = inp.host_normal_f32((n, d), 0.5, 37 + n)
+    gmax = float(np.abs(G).max()) * 1.01
+    if gkind == "bf16":
+        G = inp.f32_to_bf16_bits(G)
+    lr = 0.2
+    want = orc.sparse_mix_step(X, G, nbr, w, lr, threads=4)
+    # one fp32 rounding per slot and one for the gradient term, each on a partial sum no larger than this
+    tol = (deg + 1) * 2.0 ** -24 * (float(np.abs(X).max()) + lr * gmax)
+    ex, eo, eg = extra or (0, 0, 0)
+    shift = 1 if extra else 0
+    Xd = _strided(X, ex, shift)
+    Gd = _strided(G.view(np.int16) if gkind == "bf16" else G, eg, 3 * shift)
+    nd, wd = torch.from_numpy(nbr).to("cuda:0"), torch.from_numpy(w).to("cuda:0")
+    results = []
+    for form in ("plain", "distance", "static", "in place"):
+        Y = _strided(np.zeros((n, d), np.float32), eo, 2 * shift) if form != "in place" else Xd
+        c = torch.full((1,), float("nan"), dtype=torch.float64, device="cuda:0")
+        if form == "static" and deg == 3:
+            psgd.mix_step_cd_static(Xd, Y, Gd, nd, wd, lr, c)
+        else:
+            psgd.mix_step(Xd, Y, Gd, nd, wd, lr, cdist_out=None if form == "plain" else c)
+        torch.cuda.synchronize()
+        got = Y.cpu().numpy()
+        assert np.abs(got - want).max() <= tol, form
+        if form != "plain":
+            ref = orc.sparse_consensus_dist(got.astype(np.float64), threads=4)
+            assert abs(c.item() - ref) <= 1e-9 * ref + 1e-300, form
+        results.append(got)
+    assert all(np.array_equal(r.view(np.uint32), results[0].view(np.uint32)) for r in results[1:])
+    assert psgd.device_status() == 0
+
+
+def test_short_rows_touch_nothing_beside_their_columns(psgd):
+    """A slice of wider arrays: the elements left and right of every written row stay as they are."""
+    n, wide, off, d = 12, 5_003, 501, 1_003
+    X = torch.from_numpy(inp.host_normal_f32((n, wide), 1.0, 5)).to("cuda:0")
+    G = torch.from_numpy(inp.host_normal_f32((n, wide), 1.0, 6)).to("cuda:0")
+    Y = torch.full((n, wide), 7.0, device="cuda:0")
+    nbr, w = psgd.build_mixing(psgd.TOPO_RING, n)
+    s = slice(off, off + d)
+    psgd.mix_step(X[:, s], Y[:, s], G[:, s], torch.from_numpy(nbr).to("cuda:0"), torch.from_numpy(w).to("cuda:0"), 0.5)
+    torch.cuda.synchronize()
+    assert bool((Y[:, :off] == 7).all()) and bool((Y[:, off + d:] == 7).all())
+    want = orc.sparse_mix_step(X[:, s].cpu().numpy(), G[:, s].cpu().numpy(), nbr, w, 0.5)
+    assert np.abs(Y[:, s].cpu().numpy() - want).max() <= 4 * 2.0 ** -24 * 10
+
+
+def test_short_rows_bad_table_writes_nothing(psgd):
+    for n, d in ((4, 100), (64, 200_000)):
+        X = torch.ones((n, d), device="cuda:0")
+        Y = torch.full((n, d), 5.0, device="cuda:0")
+        nbr, w = psgd.build_mixing(psgd.TOPO_RING, n)
+        nbr[n - 1, 2] = n
+        c = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+        psgd.mix_step(X, Y, X.clone(), torch.from_numpy(nbr).to("cuda:0"), torch.from_numpy(w).to("cuda:0"), 0.1, cdist_out=c)
+        assert psgd.device_status() == 1 and psgd.device_status() == 0
+        assert bool((Y == 5.0).all()) and bool(torch.isnan(c).all())
