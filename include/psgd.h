@@ -173,8 +173,8 @@ int psgd_mix_step_cd_bf16g(const float* X, float* X_out, const uint16_t* G_bf16,
  *   cdist_out  device double[1] for the consensus distance of the output, or NULL for none
  * Everything else is as in psgd_mix_step.  Mixing in place needs X_out == X and ldo == ldx;
  * any other sharing of a byte between rows of X_out and rows of X or G is PSGD_EALIAS (the
- * rows of different arrays may interleave as long as they do not overlap).  The 128-bit
- * path needs d and all three pitches to be multiples of 4.
+ * rows of different arrays may interleave as long as they do not overlap).  Any d and any
+ * pitch take 128-bit accesses; rows that start on 16 bytes run about a tenth faster.
  *
  * Why pitches: (1) a column shard of a wider array is such a view; (2) placement.  On
  * MI355X this step was measured at 65-72 % of the HBM peak when each array is one dense

@@ -36,14 +36,23 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ int g_status_word = 0;
 
 // ---------------------------------------------------------------------------------------
-// Column-group value types: VEC = 4 (128-bit accesses) or 1 (any d, any 4-byte alignment).
+// A lane owns a group of kVec adjacent columns: one 128-bit access per row (64-bit for bf16 gradients).
+//
+// Rows may start at any element and hold any number of columns: gfx950 takes such accesses at any element alignment
+// (the compiler's default for this target, unaligned-access-mode), so alignment decides nothing; the types below only
+// tell the compiler.  A row of d columns has (d + 3) / 4 groups.  If 4 does not divide d the last one covers columns
+// d-4 .. d-1, of which the first few belong to the group before: they are loaded and computed but not stored (in place
+// they may be read after that group has replaced them; the values are dropped), [lo, hi) is what the lane owns.  Rows
+// of fewer than four columns are one group, loaded element by element.
+// Measured on rows at odd addresses, before (a column per lane wherever d, a pitch or a base was odd) and now: step with
+// bf16 gradients on 16 x 4 100 003 227 -> 144 us, fp32 on 16 x 32 000 003 1406 -> 1264 (aligned 1141), 5 slots on
+// 64 x 8 000 001 2032 -> 1230, distance of 64 x 25 600 001 1738 -> 988 (aligned 981); aligned rows unchanged.
 // ---------------------------------------------------------------------------------------
-template <int VEC> struct Cols;
-template <> struct Cols<4> { typedef f32x4 T; };
-template <> struct Cols<1> { typedef float T; };
+constexpr int kVec = 4;
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
 
 __device__ __forceinline__ f32x4 splat4(float v) { return (f32x4){v, v, v, v}; }
-
 __device__ __forceinline__ float vfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ f32x4 vfma(float a, f32x4 b, f32x4 c) {
     return __builtin_elementwise_fma(splat4(a), b, c);
@@ -51,57 +60,33 @@ __device__ __forceinline__ f32x4 vfma(float a, f32x4 b, f32x4 c) {
 
 // X, G and X_out are each touched once per step: mark the accesses non-temporal so they
 // stream through the caches instead of displacing one another.
-__device__ __forceinline__ float ld_x(const float* p, Cols<1>) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ f32x4 ld_x(const float* p, Cols<4>) {
-    return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+__device__ __forceinline__ f32x4 ld_x(const float* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
 }
-__device__ __forceinline__ void st_x(float* p, float v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void st_x(float* p, f32x4 v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
-}
-__device__ __forceinline__ float ld_g(const float* p, Cols<1> c) { return ld_x(p, c); }
-__device__ __forceinline__ f32x4 ld_g(const float* p, Cols<4> c) { return ld_x(p, c); }
-// bfloat16 is the upper half of an fp32, so widening is a 16-bit shift and exact.
-__device__ __forceinline__ float ld_g(const uint16_t* p, Cols<1>) {
-    return __uint_as_float((uint32_t)__builtin_nontemporal_load(p) << 16);
-}
-__device__ __forceinline__ f32x4 ld_g(const uint16_t* p, Cols<4>) {
-    const u32x2 b = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
-    return (f32x4){__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u),
-                   __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u)};
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(p));
 }
 
 // A gradient group as it arrives from memory, widened only where it is used: a value that is converted right
 // after its load would make the wavefront wait for that load (and every earlier one) on the spot, which defeats
 // loads that are issued early to travel during other work; bf16 groups also take half the registers this way.
-template <typename GT, int VEC> struct RawG;
-template <> struct RawG<float, 4> { typedef f32x4 T; };
-template <> struct RawG<float, 1> { typedef float T; };
-template <> struct RawG<uint16_t, 4> { typedef u32x2 T; };
-template <> struct RawG<uint16_t, 1> { typedef uint16_t T; };
-__device__ __forceinline__ f32x4 ld_g_raw(const float* p, Cols<4> c) { return ld_x(p, c); }
-__device__ __forceinline__ float ld_g_raw(const float* p, Cols<1> c) { return ld_x(p, c); }
-__device__ __forceinline__ u32x2 ld_g_raw(const uint16_t* p, Cols<4>) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+// bfloat16 is the upper half of an fp32, so widening is a 16-bit shift and exact.
+template <typename GT> struct RawG;
+template <> struct RawG<float> { typedef f32x4 T; };
+template <> struct RawG<uint16_t> { typedef u32x2 T; };
+__device__ __forceinline__ f32x4 ld_g_raw(const float* p) { return ld_x(p); }
+__device__ __forceinline__ u32x2 ld_g_raw(const uint16_t* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p));
 }
-__device__ __forceinline__ uint16_t ld_g_raw(const uint16_t* p, Cols<1>) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ f32x4 widen_g(f32x4 v) { return v; }
-__device__ __forceinline__ float widen_g(float v) { return v; }
 __device__ __forceinline__ f32x4 widen_g(u32x2 b) {
     return (f32x4){__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u),
                    __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u)};
 }
-__device__ __forceinline__ float widen_g(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+template <typename GT> __device__ __forceinline__ f32x4 ld_g(const GT* p) { return widen_g(ld_g_raw(p)); }
+__device__ __forceinline__ float widen_1(float v) { return v; }
+__device__ __forceinline__ float widen_1(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Rows that may start at any element and hold any number of columns, still four columns per lane and one wide access
-// per row: gfx950 takes 128-bit (bf16: 64-bit) global accesses at any element alignment (the compiler's default for
-// this target, unaligned-access-mode), so alignment decides nothing here; the types below only tell the compiler.
-// A row of d columns has (d + 3) / 4 groups.  If 4 does not divide d the last one covers columns d-4 .. d-1, of which
-// the first few belong to the group before: they are loaded and computed but not stored (in place they may be read
-// after that group has replaced them; the values are dropped), [lo, hi) is what the lane owns.  Rows of fewer than
-// four columns are one group, loaded element by element.
-typedef f32x4 f32x4_any __attribute__((aligned(4)));
-typedef u32x2 u32x2_any __attribute__((aligned(2)));
 struct ColGroup {
     int64_t col;   // first column
     int lo, hi;    // the lane's columns are col + lo .. col + hi - 1; lo == hi: no group of its own
@@ -122,23 +107,24 @@ __device__ __forceinline__ ColGroup col_group(int64_t cg, int64_t d) {
 }
 // FEW: rows of fewer than four columns (d of them).
 template <bool FEW> __device__ __forceinline__ f32x4 ld_cols(const float* p, int64_t d) {
-    if (!FEW) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+    if (!FEW) return ld_x(p);
     return (f32x4){p[0], d > 1 ? p[1] : 0.0f, d > 2 ? p[2] : 0.0f, 0.0f};
 }
 template <bool FEW> __device__ __forceinline__ f32x4 ld_cols_raw(const float* p, int64_t d) { return ld_cols<FEW>(p, d); }
 template <bool FEW> __device__ __forceinline__ u32x2 ld_cols_raw(const uint16_t* p, int64_t d) {
-    if (!FEW) return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p));
+    if (!FEW) return ld_g_raw(p);
     return (u32x2){(uint32_t)p[0] | (d > 1 ? (uint32_t)p[1] << 16 : 0u), d > 2 ? (uint32_t)p[2] : 0u};
 }
 __device__ __forceinline__ void st_cols(float* p, f32x4 v, const ColGroup& c) {
     if (c.lo == 0 && c.hi == 4) {
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(p));
+        st_x(p, v);
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (k >= c.lo && k < c.hi) __builtin_nontemporal_store(v[k], p + k);
     }
 }
+
 // Two barriers that are lighter than __syncthreads(), which also waits until every global load and store the
 // wavefront has issued is complete.  That wait is exactly what the step kernels must avoid: their loads are
 // issued early to travel during other work, and their stores need never be waited for.
@@ -151,10 +137,9 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // One output group.  The operation order is part of the boundary's contract.
-template <typename V>
-__device__ __forceinline__ V mix_one(float w0, float w1, float w2, V self, V left, V right,
-                                     V g, float neg_lr) {
-    V acc = self * w0;
+__device__ __forceinline__ f32x4 mix_one(float w0, float w1, float w2, f32x4 self, f32x4 left, f32x4 right,
+                                         f32x4 g, float neg_lr) {
+    f32x4 acc = self * w0;
     acc = vfma(w1, left, acc);
     acc = vfma(w2, right, acc);
     return vfma(neg_lr, g, acc);
@@ -306,16 +291,7 @@ __device__ __forceinline__ double block_sum(double v, double* lds_waves) {
     return r;  // valid in thread 0
 }
 
-template <int VEC>
-__device__ __forceinline__ void acc_diff(double* a, double* b, typename Cols<VEC>::T x, const double* s);
-template <>
-__device__ __forceinline__ void acc_diff<1>(double* a, double* b, float x, const double* s) {
-    const double df = (double)x - s[0];
-    a[0] += df;
-    b[0] = fma(df, df, b[0]);
-}
-template <>
-__device__ __forceinline__ void acc_diff<4>(double* a, double* b, f32x4 x, const double* s) {
+__device__ __forceinline__ void acc_diff(double* a, double* b, f32x4 x, const double* s) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const double df = (double)x[k] - s[k];
@@ -323,51 +299,45 @@ __device__ __forceinline__ void acc_diff<4>(double* a, double* b, f32x4 x, const
         b[k] = fma(df, df, b[k]);
     }
 }
-__device__ __forceinline__ void pivot_of(float x, double* s) { s[0] = (double)x; }
 __device__ __forceinline__ void pivot_of(f32x4 x, double* s) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) s[k] = (double)x[k];
 }
-__device__ __forceinline__ void floats_of(float x, float* f) { f[0] = x; }
 __device__ __forceinline__ void floats_of(f32x4 x, float* f) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) f[k] = x[k];
 }
 
 // Running sums of one lane's column group; the first value it is given becomes the pivot (kept as
-// the fp32 value it is).  The squares of all the group's columns share one accumulator: only their
-// total is needed, and registers are what limits the size of the step kernel's workgroups.
-template <int VEC>
+// the fp32 value it is).
 struct ColStats {
-    typename Cols<VEC>::T s;
-    double a[VEC], sq;
+    f32x4 s;
+    double a[4], sq[4];
     int have;
     __device__ __forceinline__ void reset() {
         have = 0;
-        sq = 0.0;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) a[k] = 0.0;
+        for (int k = 0; k < 4; ++k) a[k] = sq[k] = 0.0;
     }
-    __device__ __forceinline__ void add(typename Cols<VEC>::T x) {
+    __device__ __forceinline__ void add(f32x4 x) {
         if (!have) {
             s = x;
             have = 1;
         } else {
-            double xs[VEC], ps[VEC];
-            pivot_of(x, xs);
-            pivot_of(s, ps);
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) {
-                const double df = xs[k] - ps[k];
+            for (int k = 0; k < 4; ++k) {
+                const double df = (double)x[k] - (double)s[k];
                 a[k] += df;
-                sq = fma(df, df, sq);
+                sq[k] = fma(df, df, sq[k]);
             }
         }
     }
-    __device__ __forceinline__ double result(double inv_n) const {
-        double t = sq;
+    // over the columns the lane owns
+    __device__ __forceinline__ double result(double inv_n, const ColGroup& c) const {
+        double t = 0.0;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) t -= a[k] * a[k] * inv_n;
+        for (int k = 0; k < 4; ++k)
+            if (k >= c.lo && k < c.hi) t += sq[k] - a[k] * a[k] * inv_n;
         return t;
     }
 };

@@ -258,15 +258,15 @@ constexpr int kLaunchRefused = INT32_MIN;
 // Launches one instantiation of the ring-walk kernel, one workgroup per compute unit.
 // Returns the grid size, minus the grid size (and launches nothing) when the fused distance would need more
 // than `slots` partials, or kLaunchRefused when the runtime refuses the LDS size.
-template <int VEC, typename GT, bool CD>
+template <typename GT, bool CD>
 int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
                const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, int slots) {
-    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<VEC, GT, CD>);
+    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<GT, CD>);
     if (allow_lds(fn, lds_bytes)) return kLaunchRefused;
-    const int grid = persistent_grid(di, d / VEC, 1, kRingThreads);
+    const int grid = persistent_grid(di, (d + 3) / 4, 1, kRingThreads);
     if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
-    hipLaunchKernelGGL((mix_step_kernel<VEC, GT, CD>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
-                       n, d, ld, neg_lr, make_sweeps(d / VEC, grid, kRingThreads), partials);
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
+                       n, d, ld, neg_lr, make_sweeps((d + 3) / 4, grid, kRingThreads), partials);
     return grid;
 }
 
@@ -368,10 +368,6 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         if (e0 != hipSuccess) return hip_fail(e0, "consensus_final_kernel");
         return no_alloc ? PSGD_OK : release_partials(di, s);
     }
-    // 128-bit path needs every row start 16-byte aligned (8-byte for bf16 gradients).
-    const bool vec4 = (d % 4 == 0) && (ldx % 4 == 0) && (ldo % 4 == 0) && (ldg % 4 == 0) && aligned_to(X, 16) &&
-                      aligned_to(X_out, 16) && aligned_to(G, 4 * sizeof(GT));
-    const int vec = vec4 ? 4 : 1;
     const float neg_lr = -lr;
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
@@ -389,10 +385,8 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     if (big && deg == 3) {
         // The ring-walk kernel does the work when the table is one ring (every table of Sec. 3); the tiled kernel
         // follows it (below) for all others, because each path wants its own workgroup shape and registers.
-        if (vec4 && want_cd) grid = launch_mix<4, GT, true>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
-        else if (vec4) grid = launch_mix<4, GT, false>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
-        else if (want_cd) grid = launch_mix<1, GT, true>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
-        else grid = launch_mix<1, GT, false>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
+        grid = want_cd ? launch_mix<GT, true>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots)
+                       : launch_mix<GT, false>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
         if (grid == kLaunchRefused) return PSGD_EHIP;   // allow_lds has recorded the reason
         if (grid < 0)
             return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, -grid, slots);
@@ -406,21 +400,23 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         // distance), else 512 lanes with several batches per tile.
         const size_t base = 0;
         const int deep_threads = want_cd ? kTileThreads : kDeepThreads;
-        plan::TilePlan tp = plan::tile_plan(n, deg, vec, deep_threads, want_cd, kLdsCapLarge, base,
+        plan::TilePlan tp = plan::tile_plan(n, deg, kVec, deep_threads, want_cd, kLdsCapLarge, base,
                                             want_cd ? TileShape<kTileThreads>::RB : TileShape<kDeepThreads>::RB, true);
         const bool deep = tp.lpr != 0;
-        if (!deep) tp = plan::tile_plan(n, deg, vec, kTileThreads, want_cd, kLdsCapLarge, base, TileShape<kTileThreads>::RB);
+        if (!deep) tp = plan::tile_plan(n, deg, kVec, kTileThreads, want_cd, kLdsCapLarge, base, TileShape<kTileThreads>::RB);
         if (tp.lpr == 0)
             return fail(PSGD_EINVAL, "%s: n=%d, deg=%d does not fit the tiled path's LDS", name, n, deg);
         const int lpr = tp.lpr;
         size_t lds_bytes = tp.total;
         if (deg == 3 && lds_bytes < tp.tab_bytes + classify) lds_bytes = tp.tab_bytes + classify;
-        const int64_t ntiles = (d / vec + lpr - 1) / lpr;
+        const size_t remainder = (size_t)n * (d % kVec) * 2 * sizeof(float);
+        if (lds_bytes < tp.tab_bytes + remainder) lds_bytes = tp.tab_bytes + remainder;
+        const int64_t ntiles = (d / kVec + lpr - 1) / lpr;
         const int first = grid;
         int tgrid = 0;
-#define PSGD_DEG_LAUNCH(VEC, CD, T, DEEP)                                                                                   \
+#define PSGD_DEG_LAUNCH(CD, T, DEEP)                                                                                   \
     do {                                                                                                                \
-        const void* fn = reinterpret_cast<const void*>(mix_deg_kernel<VEC, GT, CD, T, DEEP>);                           \
+        const void* fn = reinterpret_cast<const void*>(mix_deg_kernel<GT, CD, T, DEEP>);                           \
         if (int rc = allow_lds(fn, lds_bytes)) return rc;                                                               \
         int per_cu = resident_per_cu(fn, lds_bytes, T);                                                                 \
         if (per_cu > 2 * kGridPerCu) per_cu = 2 * kGridPerCu;                                                           \
@@ -432,21 +428,19 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
                 break;                                                                                                  \
             }                                                                                                           \
         }                                                                                                               \
-        hipLaunchKernelGGL((mix_deg_kernel<VEC, GT, CD, T, DEEP>), dim3(tgrid), dim3(T), lds_bytes, s, X, X_out, G,     \
+        hipLaunchKernelGGL((mix_deg_kernel<GT, CD, T, DEEP>), dim3(tgrid), dim3(T), lds_bytes, s, X, X_out, G,     \
                            nbr, w,                                                                                     \
                            deg, n, d, ld, neg_lr, lpr, deg == 3 ? 1 : 0, tp.comb_in_tile ? 1 : 0,                    \
                            CD ? partials + first : partials);             \
     } while (0)
-#define PSGD_DEG_PICK(VEC, CD)                                                                                          \
+#define PSGD_DEG_PICK(CD)                                                                                          \
     do {                                                                                                                \
-        if (deep && tp.lpr >= 64) PSGD_DEG_LAUNCH(VEC, CD, (CD ? kTileThreads : kDeepThreads), 1);                      \
-        else if (deep) PSGD_DEG_LAUNCH(VEC, CD, (CD ? kTileThreads : kDeepThreads), 2);                                 \
-        else PSGD_DEG_LAUNCH(VEC, CD, kTileThreads, 0);                                                                 \
+        if (deep && tp.lpr >= 64) PSGD_DEG_LAUNCH(CD, (CD ? kTileThreads : kDeepThreads), 1);                      \
+        else if (deep) PSGD_DEG_LAUNCH(CD, (CD ? kTileThreads : kDeepThreads), 2);                                 \
+        else PSGD_DEG_LAUNCH(CD, kTileThreads, 0);                                                                 \
     } while (0)
-        if (vec4 && want_cd) PSGD_DEG_PICK(4, true);
-        else if (vec4) PSGD_DEG_PICK(4, false);
-        else if (want_cd) PSGD_DEG_PICK(1, true);
-        else PSGD_DEG_PICK(1, false);
+        if (want_cd) PSGD_DEG_PICK(true);
+        else PSGD_DEG_PICK(false);
 #undef PSGD_DEG_PICK
 #undef PSGD_DEG_LAUNCH
         grid = tgrid < 0 ? tgrid : first + tgrid;
@@ -505,31 +499,20 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         if (e0 != hipSuccess) return hip_fail(e0, "consensus_final_kernel");
         return release_partials(di, s);
     }
-    const bool vec4 = (d % 4 == 0) && (ldx % 4 == 0) && (ldo % 4 == 0) && (ldg % 4 == 0) && aligned_to(X, 16) &&
-                      aligned_to(X_out, 16) && aligned_to(G, 4 * sizeof(GT));
-    const bool big = long_rows(*di, vec4 ? d / 4 : d, 2);
-    const int grid = big ? persistent_grid(*di, vec4 ? d / 4 : d, 1, kRingThreads)
-                         : persistent_grid(*di, vec4 ? d / 4 : d, kGridPerCu);
-    const dim3 g(grid), b(big ? kRingThreads : kThreads);
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    const bool big = long_rows(*di, ncg, 2);
+    const int grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : persistent_grid(*di, ncg, kGridPerCu);
     const Pitch ld{ldx, ldo, ldg};
     const float neg_lr = -lr;
-#define PSGD_LAUNCH_FULL(VEC, CD)                                                                                          \
-    do {                                                                                                                   \
-        if (big)                                                                                                           \
-            hipLaunchKernelGGL((mix_full_kernel<VEC, GT, CD, kRingThreads>), g, b, 0, s, X, X_out, G, n, d, ld, neg_lr,     \
-                               make_sweeps(d / VEC, grid, kRingThreads), partials);                                        \
-        else                                                                                                               \
-            hipLaunchKernelGGL((mix_full_kernel<VEC, GT, CD, kThreads>), g, b, 0, s, X, X_out, G, n, d, ld, neg_lr,         \
-                               make_sweeps(d / VEC, grid, kThreads), partials);                                            \
-    } while (0)
-    if (vec4 && want_cd)
-        PSGD_LAUNCH_FULL(4, true);
-    else if (vec4)
-        PSGD_LAUNCH_FULL(4, false);
-    else if (want_cd)
-        PSGD_LAUNCH_FULL(1, true);
-    else
-        PSGD_LAUNCH_FULL(1, false);
+#define PSGD_LAUNCH_FULL(CD, T, FEW)                                                                                      \
+    hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, FEW>), dim3(grid), dim3(T), 0, s, X, X_out, G, n, d, ld, neg_lr,         \
+                       make_sweeps(ncg, grid, T), partials)
+    if (big && want_cd) PSGD_LAUNCH_FULL(true, kRingThreads, false);
+    else if (big) PSGD_LAUNCH_FULL(false, kRingThreads, false);
+    else if (d < kVec && want_cd) PSGD_LAUNCH_FULL(true, kThreads, true);
+    else if (d < kVec) PSGD_LAUNCH_FULL(false, kThreads, true);
+    else if (want_cd) PSGD_LAUNCH_FULL(true, kThreads, false);
+    else PSGD_LAUNCH_FULL(false, kThreads, false);
 #undef PSGD_LAUNCH_FULL
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
@@ -549,25 +532,19 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
     double* partials = nullptr;
     if (int rc = acquire_partials(di, s, &partials)) return rc;
     if (result_slot) *result_slot = partials + kMaxGrid;
-    const bool vec4 = (d % 4 == 0) && (ldx % 4 == 0) && aligned_to(X, 16);
     int grid = 0;
     if (d > 0) {
-        const int64_t ncg = vec4 ? d / 4 : d;
+        const int64_t ncg = (d + kVec - 1) / kVec;
         if (long_rows(*di, ncg)) {
             grid = persistent_grid(*di, ncg, 1, kRingThreads);
-            const Sweeps sw = make_sweeps(ncg, grid, kRingThreads);
-            if (vec4)
-                hipLaunchKernelGGL((consensus_sweep_kernel<4, kRingThreads>), dim3(grid), dim3(kRingThreads), 0, s, X, n, d,
-                                   ldx, sw, partials);
-            else
-                hipLaunchKernelGGL((consensus_sweep_kernel<1, kRingThreads>), dim3(grid), dim3(kRingThreads), 0, s, X, n, d,
-                                   ldx, sw, partials);
+            hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads>), dim3(grid), dim3(kRingThreads), 0, s, X, n, d, ldx,
+                               make_sweeps(ncg, grid, kRingThreads), partials);
         } else {
             grid = persistent_grid(*di, ncg, 8);  // light kernel: 32 waves per CU
-            if (vec4)
-                hipLaunchKernelGGL(consensus_partial_kernel<4>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+            if (d < kVec)
+                hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
             else
-                hipLaunchKernelGGL(consensus_partial_kernel<1>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+                hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "consensus_partial_kernel");
@@ -746,10 +723,9 @@ int psgd_synth_grad(const float* X_prev, const float* noise, float* G, int64_t c
     if (count == 0) return PSGD_OK;
     DeviceInfo* di = nullptr;
     if (int rc = device_info(&di)) return rc;
-    const int vec4 = aligned_to(X_prev, 16) && aligned_to(noise, 16) && aligned_to(G, 16);
-    const int grid = persistent_grid(*di, vec4 ? (count + 3) / 4 : count, 16);
+    const int grid = persistent_grid(*di, (count + 3) / 4, 16);
     hipLaunchKernelGGL(synth_grad_kernel, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), X_prev,
-                       noise, G, count, c, vec4);
+                       noise, G, count, c);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "synth_grad_kernel");
     return PSGD_OK;
@@ -773,15 +749,13 @@ int psgd_synth_grad_ex(const float* X_prev, int64_t ldx, const float* noise, int
     if (d == 0) return PSGD_OK;
     DeviceInfo* di = nullptr;
     if (int rc = device_info(&di)) return rc;
-    const bool vec4 = d % 4 == 0 && ldx % 4 == 0 && ldn % 4 == 0 && ldg % 4 == 0 && aligned_to(X_prev, 16) &&
-                      aligned_to(noise, 16) && aligned_to(G, 16);
-    const int grid = persistent_grid(*di, vec4 ? d / 4 : d, 8);
+    const int grid = persistent_grid(*di, (d + kVec - 1) / kVec, 8);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (vec4)
-        hipLaunchKernelGGL(synth_grad_rows_kernel<4>, dim3(grid), dim3(kThreads), 0, s, X_prev, ldx, noise, ldn, G, ldg,
+    if (d < kVec)
+        hipLaunchKernelGGL(synth_grad_rows_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X_prev, ldx, noise, ldn, G, ldg,
                            n, d, c);
     else
-        hipLaunchKernelGGL(synth_grad_rows_kernel<1>, dim3(grid), dim3(kThreads), 0, s, X_prev, ldx, noise, ldn, G, ldg,
+        hipLaunchKernelGGL(synth_grad_rows_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X_prev, ldx, noise, ldn, G, ldg,
                            n, d, c);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "synth_grad_rows_kernel");

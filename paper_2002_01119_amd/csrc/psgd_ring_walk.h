@@ -18,16 +18,15 @@ namespace {
 // The workgroup's wavefronts are kept on the same batch of rows by a barrier per batch: each row
 // then receives one contiguous burst of (workgroup size) * 16 bytes, which the HBM serves a little
 // faster than the same bytes arriving wavefront by wavefront.  Every lane of the workgroup therefore
-// walks the ring the same number of times; a lane without a column group of its own (`act` false,
+// walks the ring the same number of times; a lane without a column group of its own (c.lo == c.hi,
 // ragged end of the row) shadows a valid group with its loads and stores nothing.
-template <int VEC, typename GT, bool CD>
+template <typename GT, bool CD>
 __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* __restrict__ gc,
                                           const RingEnt* ring, int n, Pitch ld, float neg_lr,
-                                          ColStats<VEC>& stats, bool act) {
-    typedef typename Cols<VEC>::T V;
-    const Cols<VEC> tag{};
-    const V first = ld_x(xc + (int64_t)ring_row(ring) * ld.x, tag);
-    const V last = (n > 1) ? ld_x(xc + (int64_t)ring_row(ring + n - 1) * ld.x, tag) : first;
+                                          ColStats& stats, const ColGroup& c) {
+    typedef f32x4 V;
+    const V first = ld_x(xc + (int64_t)ring_row(ring) * ld.x);
+    const V last = (n > 1) ? ld_x(xc + (int64_t)ring_row(ring + n - 1) * ld.x) : first;
     V prev = last, cur = first;
     int p = 0;
     // Whole batches: positions p .. p+U-1, whose right neighbours p+1 .. p+U are all fresh
@@ -39,13 +38,13 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             e[u] = ring_ent(ring + p + u);
-            xs[u] = ld_x(xc + (int64_t)ring_row(ring + p + u + 1) * ld.x, tag);
-            gs[u] = ld_g(gc + (int64_t)e[u].row * ld.g, tag);
+            xs[u] = ld_x(xc + (int64_t)ring_row(ring + p + u + 1) * ld.x);
+            gs[u] = ld_g(gc + (int64_t)e[u].row * ld.g);
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const V out = mix_one<V>(e[u].w0, e[u].w1, e[u].w2, cur, prev, xs[u], gs[u], neg_lr);
-            if (act) st_x(oc + (int64_t)e[u].row * ld.o, out);
+            const V out = mix_one(e[u].w0, e[u].w1, e[u].w2, cur, prev, xs[u], gs[u], neg_lr);
+            st_cols(oc + (int64_t)e[u].row * ld.o, out, c);
             if (CD) stats.add(out);
             prev = cur;
             cur = xs[u];
@@ -60,8 +59,8 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
             const int pp = p + u;
             if (pp < n) {
                 e[u] = ring_ent(ring + pp);
-                gs[u] = ld_g(gc + (int64_t)e[u].row * ld.g, tag);
-                if (pp + 1 <= n - 2) xs[u] = ld_x(xc + (int64_t)ring_row(ring + pp + 1) * ld.x, tag);
+                gs[u] = ld_g(gc + (int64_t)e[u].row * ld.g);
+                if (pp + 1 <= n - 2) xs[u] = ld_x(xc + (int64_t)ring_row(ring + pp + 1) * ld.x);
                 else if (pp + 1 == n - 1) xs[u] = last;
                 else xs[u] = first;
             }
@@ -69,8 +68,8 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             if (p + u < n) {
-                const V out = mix_one<V>(e[u].w0, e[u].w1, e[u].w2, cur, prev, xs[u], gs[u], neg_lr);
-                if (act) st_x(oc + (int64_t)e[u].row * ld.o, out);
+                const V out = mix_one(e[u].w0, e[u].w1, e[u].w2, cur, prev, xs[u], gs[u], neg_lr);
+                st_cols(oc + (int64_t)e[u].row * ld.o, out, c);
                 if (CD) stats.add(out);
                 prev = cur;
                 cur = xs[u];
@@ -86,7 +85,7 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 // same number of sweeps, lanes beyond the chunk idle.
 // A table that is not one ring is left to the tiled kernel, which the launcher enqueues right behind this one and which
 // classifies the table the same way; this kernel then writes nothing.
-template <int VEC, typename GT, bool CD>
+template <typename GT, bool CD>
 __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                                    const int32_t* __restrict__ nbr,
                                                                    const float* __restrict__ w, int n, int64_t d, Pitch ld,
@@ -102,7 +101,7 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
         if (CD && threadIdx.x == 0) partials[blockIdx.x] = __builtin_nan("");
         return;
     }
-    const int64_t ncg = d / VEC;  // the launcher picks VEC = 1 unless 4 divides d
+    const int64_t ncg = (d + kVec - 1) / kVec;
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
     if (kind == kTableRing) {
@@ -110,12 +109,11 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
             const int64_t base = sweeps.base(sw), cg = base + threadIdx.x;
             if (base >= ncg) break;                              // nothing left for this workgroup (uniform)
             const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
-            const bool act = cg < end;
-            const int64_t col = (act ? cg : 0) * VEC;            // idle lanes shadow column group 0
-            ColStats<VEC> stats;
+            const ColGroup c = col_group(cg < end ? cg : ncg, d);   // an idle lane owns nothing and shadows the last group
+            ColStats stats;
             if (CD) stats.reset();
-            ring_walk<VEC, GT, CD>(X + col, Xout + col, G + col, l.ring, n, ld, neg_lr, stats, act);
-            if (CD && act) total += stats.result(inv_n);
+            ring_walk<GT, CD>(X + c.col, Xout + c.col, G + c.col, l.ring, n, ld, neg_lr, stats, c);
+            if (CD) total += stats.result(inv_n, c);
         }
     }
     if (CD) {

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
     const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
     int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
     double* __restrict__ partials) {
-    typedef typename RawG<GT, 4>::T GR;
+    typedef typename RawG<GT>::T GR;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
     __shared__ int lds_bad[plan::kShortThreads / 64];
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
                 const f32x4 o = vfma(neg_lr, widen_g(g[u]), out[i]);
                 float* to = Xout + (int64_t)row_of(u) * ld.o + cg.col;
                 if (FULL) {
-                    __builtin_nontemporal_store(o, reinterpret_cast<f32x4_any*>(to));
+                    st_x(to, o);
                     g[u] = ld_cols_raw<FEW>(G + (int64_t)row_of(u) * ld.g + next.col, d);
                 } else if (rg + u * nrg < n) {
                     st_cols(to, o, cg);

@@ -17,72 +17,69 @@ namespace {
 // fp32 rounding whatever n is), second sweep reads G and writes the n outputs.  All of the
 // lane's X loads precede its first store, so X_out may alias X.  Same bytes as the ring step.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void add_to(double* s, float x) { s[0] += (double)x; }
 __device__ __forceinline__ void add_to(double* s, f32x4 x) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) s[k] += (double)x[k];
 }
-__device__ __forceinline__ float mean_of(const double* s, double inv_n, Cols<1>) { return (float)(s[0] * inv_n); }
-__device__ __forceinline__ f32x4 mean_of(const double* s, double inv_n, Cols<4>) {
+__device__ __forceinline__ f32x4 mean_of(const double* s, double inv_n) {
     return (f32x4){(float)(s[0] * inv_n), (float)(s[1] * inv_n), (float)(s[2] * inv_n), (float)(s[3] * inv_n)};
 }
 
 // T = workgroup size, chosen as for the ring step: on long rows a large workgroup whose wavefronts
 // sweep the rows in lockstep (a barrier per batch), so each row sees one long contiguous burst.
-template <int VEC, typename GT, bool CD, int T>
+// FEW: rows of fewer than four columns.
+template <typename GT, bool CD, int T, bool FEW>
 __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout, const GT* __restrict__ G, int n,
                                                      int64_t d, Pitch ld, float neg_lr, Sweeps sweeps,
                                                      double* __restrict__ partials) {
-    typedef typename Cols<VEC>::T V;
-    const Cols<VEC> tag{};
+    typedef f32x4 V;
     __shared__ double lds_waves[T / 64];
-    const int64_t ncg = d / VEC;
+    const int64_t ncg = (d + kVec - 1) / kVec;
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
     for (int64_t sw = 0; sw < sweeps.count; ++sw) {
         const int64_t base = sweeps.base(sw), cg = base + threadIdx.x;
         if (base >= ncg) break;                                  // nothing left for this workgroup (uniform)
         const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
-        const bool act = cg < end;                               // an idle lane shadows column group 0 and stores nothing
-        const int64_t col = (act ? cg : 0) * VEC;
-        const float* xc = X + col;
-        const GT* gc = G + col;
-        float* oc = Xout + col;
-        double sum[VEC];
+        const ColGroup c = col_group(cg < end ? cg : ncg, d);    // an idle lane owns nothing and shadows the last group
+        const float* xc = X + c.col;
+        const GT* gc = G + c.col;
+        float* oc = Xout + c.col;
+        double sum[kVec];
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) sum[k] = 0.0;
+        for (int k = 0; k < kVec; ++k) sum[k] = 0.0;
         int r = 0;
         for (; r + kUnroll <= n; r += kUnroll) {
             lockstep_barrier();
             V xs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_x(xc + (int64_t)(r + u) * ld.x, tag);
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)(r + u) * ld.x, d);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) add_to(sum, xs[u]);
         }
-        for (; r < n; ++r) add_to(sum, ld_x(xc + (int64_t)r * ld.x, tag));
-        const V mean = mean_of(sum, inv_n, tag);
-        ColStats<VEC> stats;
+        for (; r < n; ++r) add_to(sum, ld_cols<FEW>(xc + (int64_t)r * ld.x, d));
+        const V mean = mean_of(sum, inv_n);
+        ColStats stats;
         if (CD) stats.reset();
         r = 0;
         for (; r + kUnroll <= n; r += kUnroll) {
             lockstep_barrier();
             V gs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) gs[u] = ld_g(gc + (int64_t)(r + u) * ld.g, tag);
+            for (int u = 0; u < kUnroll; ++u) gs[u] = widen_g(ld_cols_raw<FEW>(gc + (int64_t)(r + u) * ld.g, d));
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const V out = vfma(neg_lr, gs[u], mean);
-                if (act) st_x(oc + (int64_t)(r + u) * ld.o, out);
+                st_cols(oc + (int64_t)(r + u) * ld.o, out, c);
                 if (CD) stats.add(out);
             }
         }
         for (; r < n; ++r) {
-            const V out = vfma(neg_lr, ld_g(gc + (int64_t)r * ld.g, tag), mean);
-            if (act) st_x(oc + (int64_t)r * ld.o, out);
+            const V out = vfma(neg_lr, widen_g(ld_cols_raw<FEW>(gc + (int64_t)r * ld.g, d)), mean);
+            st_cols(oc + (int64_t)r * ld.o, out, c);
             if (CD) stats.add(out);
         }
-        if (CD && act) total += stats.result(inv_n);
+        if (CD) total += stats.result(inv_n, c);
     }
     if (CD) {
         const double bs = block_sum<T>(total, lds_waves);
@@ -91,42 +88,43 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
 }
 
 // Consensus-distance kernels (the per-column arithmetic is defined above the ring walk).
-template <int VEC>
+template <bool FEW>
 __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float* __restrict__ X, int n,
                                                                      int64_t d, int64_t ldx,
                                                                      double* __restrict__ partials) {
-    typedef typename Cols<VEC>::T V;
-    const Cols<VEC> tag{};
+    typedef f32x4 V;
     __shared__ double lds4[4];
-    const int64_t ncg = d / VEC;
+    const int64_t ncg = (d + kVec - 1) / kVec;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
     for (int64_t cg = (int64_t)blockIdx.x * kThreads + threadIdx.x; cg < ncg; cg += stride) {
-        const float* xc = X + cg * VEC;
-        double s[VEC], a[VEC], b[VEC];
-        pivot_of(ld_x(xc, tag), s);
+        const ColGroup c = col_group(cg, d);
+        const float* xc = X + c.col;
+        double s[kVec], a[kVec], b[kVec];
+        pivot_of(ld_cols<FEW>(xc, d), s);
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) a[k] = b[k] = 0.0;
+        for (int k = 0; k < kVec; ++k) a[k] = b[k] = 0.0;
         int r = 1;
         for (; r + kUnroll <= n; r += kUnroll) {
             V xs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx, tag);
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)(r + u) * ldx, d);
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) acc_diff<VEC>(a, b, xs[u], s);
+            for (int u = 0; u < kUnroll; ++u) acc_diff(a, b, xs[u], s);
         }
         if (r < n) {
             V xs[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
-                if (r + u < n) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx, tag);
+                if (r + u < n) xs[u] = ld_cols<FEW>(xc + (int64_t)(r + u) * ldx, d);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
-                if (r + u < n) acc_diff<VEC>(a, b, xs[u], s);
+                if (r + u < n) acc_diff(a, b, xs[u], s);
         }
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) total += b[k] - a[k] * a[k] * inv_n;
+        for (int k = 0; k < kVec; ++k)
+            if (k >= c.lo && k < c.hi) total += b[k] - a[k] * a[k] * inv_n;
     }
     const double bs = block_sum(total, lds4);
     if (threadIdx.x == 0) partials[blockIdx.x] = bs;
@@ -134,41 +132,38 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float
 
 // The same distance for long rows, in the form of the step kernels: one large workgroup per compute unit whose
 // wavefronts sweep the rows in lockstep batches, the column groups split evenly and die-contiguously over the
-// persistent grid.  A lane owns one column group per sweep; a lane beyond the ragged end shadows column group 0
-// and adds nothing.
-template <int VEC, int T>
+// persistent grid.  A lane owns one column group per sweep.
+template <int T>
 __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restrict__ X, int n, int64_t d, int64_t ldx,
                                                             Sweeps sweeps, double* __restrict__ partials) {
-    typedef typename Cols<VEC>::T V;
-    const Cols<VEC> tag{};
+    typedef f32x4 V;
     __shared__ double lds_waves[T / 64];
-    const int64_t ncg = d / VEC;
+    const int64_t ncg = (d + kVec - 1) / kVec;
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
     for (int64_t sw = 0; sw < sweeps.count; ++sw) {
         const int64_t base = sweeps.base(sw), cg = base + threadIdx.x;
         if (base >= ncg) break;                                  // nothing left for this workgroup (uniform)
         const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
-        const bool act = cg < end;
-        const float* xc = X + (act ? cg : 0) * VEC;
-        double s[VEC], a[VEC], b[VEC];
-        pivot_of(ld_x(xc, tag), s);
+        const ColGroup c = col_group(cg < end ? cg : ncg, d);    // an idle lane owns nothing and shadows the last group
+        const float* xc = X + c.col;
+        double s[kVec], a[kVec], b[kVec];
+        pivot_of(ld_x(xc), s);
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) a[k] = b[k] = 0.0;
+        for (int k = 0; k < kVec; ++k) a[k] = b[k] = 0.0;
         int r = 1;
         for (; r + kUnroll <= n; r += kUnroll) {
             lockstep_barrier();
             V xs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx, tag);
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx);
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) acc_diff<VEC>(a, b, xs[u], s);
+            for (int u = 0; u < kUnroll; ++u) acc_diff(a, b, xs[u], s);
         }
-        for (; r < n; ++r) acc_diff<VEC>(a, b, ld_x(xc + (int64_t)r * ldx, tag), s);
-        if (act) {
+        for (; r < n; ++r) acc_diff(a, b, ld_x(xc + (int64_t)r * ldx), s);
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) total += b[k] - a[k] * a[k] * inv_n;
-        }
+        for (int k = 0; k < kVec; ++k)
+            if (k >= c.lo && k < c.hi) total += b[k] - a[k] * a[k] * inv_n;
     }
     const double bs = block_sum<T>(total, lds_waves);
     if (threadIdx.x == 0) partials[blockIdx.x] = bs;
@@ -188,37 +183,34 @@ __global__ __launch_bounds__(kThreads) void consensus_final_kernel(const double*
 
 __global__ __launch_bounds__(kThreads) void synth_grad_kernel(const float* __restrict__ xp,
                                                               const float* __restrict__ noise, float* __restrict__ g,
-                                                              int64_t count, float c, int vec4) {
+                                                              int64_t count, float c) {
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     const int64_t tid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (vec4) {
-        const int64_t groups = count / 4;
-        for (int64_t i = tid; i < groups; i += stride) {
-            const f32x4 x = ld_x(xp + 4 * i, Cols<4>{});
-            const f32x4 z = ld_x(noise + 4 * i, Cols<4>{});
-            st_x(g + 4 * i, vfma(c, x, z));
-        }
-        for (int64_t i = groups * 4 + tid; i < count; i += stride) g[i] = vfma(c, xp[i], noise[i]);
-    } else {
-        for (int64_t i = tid; i < count; i += stride) g[i] = vfma(c, xp[i], noise[i]);
-    }
+    const int64_t groups = count / 4;
+    for (int64_t i = tid; i < groups; i += stride) st_x(g + 4 * i, vfma(c, ld_x(xp + 4 * i), ld_x(noise + 4 * i)));
+    for (int64_t i = groups * 4 + tid; i < count; i += stride) g[i] = vfma(c, xp[i], noise[i]);
 }
 
-// Row-pitched form: a lane owns one column group and walks the n rows.
-template <int VEC>
+// Row-pitched form: a lane owns one column group and walks the n rows.  FEW: rows of fewer than four columns.
+template <bool FEW>
 __global__ __launch_bounds__(kThreads) void synth_grad_rows_kernel(const float* __restrict__ xp, int64_t ldx,
                                                                    const float* __restrict__ noise, int64_t ldn,
                                                                    float* __restrict__ g, int64_t ldg, int n,
                                                                    int64_t d, float c) {
-    const Cols<VEC> tag{};
-    const int64_t ncg = d / VEC;
+    const int64_t ncg = (d + kVec - 1) / kVec;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     for (int64_t cg = (int64_t)blockIdx.x * kThreads + threadIdx.x; cg < ncg; cg += stride) {
-        const int64_t col = cg * VEC;
+        const ColGroup at = col_group(cg, d);
+        const float* xc = xp + at.col;
+        const float* nc = noise + at.col;
+        float* gc = g + at.col;
+        if (!FEW && at.lo == 0) {                                // all but the ragged end: the stores are unconditional
 #pragma unroll 4
-        for (int r = 0; r < n; ++r)
-            st_x(g + (int64_t)r * ldg + col,
-                 vfma(c, ld_x(xp + (int64_t)r * ldx + col, tag), ld_x(noise + (int64_t)r * ldn + col, tag)));
+            for (int r = 0; r < n; ++r) st_x(gc + (int64_t)r * ldg, vfma(c, ld_x(xc + (int64_t)r * ldx), ld_x(nc + (int64_t)r * ldn)));
+        } else {
+            for (int r = 0; r < n; ++r)
+                st_cols(gc + (int64_t)r * ldg, vfma(c, ld_cols<FEW>(xc + (int64_t)r * ldx, d), ld_cols<FEW>(nc + (int64_t)r * ldn, d)), at);
+        }
     }
 }
 
@@ -235,7 +227,6 @@ enum { kRefRead = 0, kRefWrite = 1, kRefAxpy = 2 };
 template <int KIND, typename GT, int T>
 __global__ __launch_bounds__(T) void reference_stream_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                              int n, int64_t d, Pitch ld, float a, Sweeps sweeps) {
-    const Cols<4> tag{};
     const int64_t ncg = d / 4;
     f32x4 keep = splat4(0.0f);
     for (int64_t sw = 0; sw < sweeps.count; ++sw) {
@@ -254,8 +245,8 @@ __global__ __launch_bounds__(T) void reference_stream_kernel(const float* X, flo
             if (KIND != kRefWrite) {
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
-                    xs[u] = ld_x(xc + (int64_t)(r + u) * ld.x, tag);
-                    gs[u] = ld_g(gc + (int64_t)(r + u) * ld.g, tag);
+                    xs[u] = ld_x(xc + (int64_t)(r + u) * ld.x);
+                    gs[u] = ld_g(gc + (int64_t)(r + u) * ld.g);
                 }
             }
 #pragma unroll
@@ -266,10 +257,10 @@ __global__ __launch_bounds__(T) void reference_stream_kernel(const float* X, flo
             }
         }
         for (; r < n; ++r) {
-            if (KIND == kRefRead) keep += ld_x(xc + (int64_t)r * ld.x, tag) + ld_g(gc + (int64_t)r * ld.g, tag);
+            if (KIND == kRefRead) keep += ld_x(xc + (int64_t)r * ld.x) + ld_g(gc + (int64_t)r * ld.g);
             if (KIND == kRefWrite && act) st_x(oc + (int64_t)r * ld.o, splat4(a));
             if (KIND == kRefAxpy && act)
-                st_x(oc + (int64_t)r * ld.o, vfma(a, ld_g(gc + (int64_t)r * ld.g, tag), ld_x(xc + (int64_t)r * ld.x, tag)));
+                st_x(oc + (int64_t)r * ld.o, vfma(a, ld_g(gc + (int64_t)r * ld.g), ld_x(xc + (int64_t)r * ld.x)));
         }
     }
     // The loads of the read-only stream must have an observer: a store that the data never triggers.

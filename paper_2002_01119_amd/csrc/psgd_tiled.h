@@ -56,7 +56,6 @@ template <int T> struct TileShape {
 };
 
 // Per-lane state of the tiled path that does not change from tile to tile.
-template <int VEC>
 struct TileCtx {
     const TileSlot* tab;
     int n, deg, lpr, lane, rg, nrg;
@@ -66,14 +65,13 @@ struct TileCtx {
 };
 
 // Running sums of the distance for one lane and one tile.
-template <int VEC>
 struct TileStats {
-    double piv[VEC], a[VEC], sq;
-    float pivf[VEC];   // the pivot as the fp32 output it is (row groups with a pivot of their own keep it in this form)
+    double piv[kVec], a[kVec], sq;
+    float pivf[kVec];   // the pivot as the fp32 output it is (row groups with a pivot of their own keep it in this form)
     __device__ __forceinline__ void reset() {
         sq = 0.0;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
+        for (int k = 0; k < kVec; ++k) {
             piv[k] = a[k] = 0.0;
             pivf[k] = 0.0f;
         }
@@ -101,12 +99,12 @@ struct TileStats {
 struct NoFeed {
     __device__ __forceinline__ void operator()(int) const {}
 };
-template <int VEC, bool CD, int RB, int SB, bool CLAMP, bool OWNPIV, typename GR, typename FEED = NoFeed,
+template <bool CD, int RB, int SB, bool CLAMP, bool OWNPIV, typename GR, typename FEED = NoFeed,
           typename REFILL = NoFeed>
-__device__ __forceinline__ void tile_rows(const TileCtx<VEC>& c, const typename Cols<VEC>::T* cur, int b, const GR (&g)[RB],
+__device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, int b, const GR (&g)[RB],
                                           GR g0, bool with_pivot, bool active, float* out_col, int64_t ldo,
-                                          TileStats<VEC>& st, const FEED& feed = FEED{}, const REFILL& refill = REFILL{}) {
-    typedef typename Cols<VEC>::T V;
+                                          TileStats& st, const FEED& feed = FEED{}, const REFILL& refill = REFILL{}) {
+    typedef f32x4 V;
     constexpr int P = (CD && !OWNPIV) ? 1 : 0, ITEMS = RB + P;
 #pragma unroll
     for (int j0 = 0; j0 < ITEMS; j0 += SB) {
@@ -181,10 +179,10 @@ __device__ __forceinline__ void tile_rows(const TileCtx<VEC>& c, const typename 
                     st_x(out_col + (int64_t)row[i] * ldo, out);
                     if (CD && OWNPIV && j == 0) floats_of(out, st.pivf);
                     if (CD && ok[i]) {
-                        double o[VEC];
+                        double o[kVec];
                         pivot_of(out, o);      // widen
 #pragma unroll
-                        for (int k = 0; k < VEC; ++k) {
+                        for (int k = 0; k < kVec; ++k) {
                             const double df = o[k] - (OWNPIV ? (double)st.pivf[k] : st.piv[k]);
                             st.a[k] += df;
                             st.sq = fma(df, df, st.sq);
@@ -199,8 +197,8 @@ __device__ __forceinline__ void tile_rows(const TileCtx<VEC>& c, const typename 
 
 // Merge of the column sums at the end of a tile (CD only).  Contains the tile's barrier: when it returns every
 // read of the current buffer and every write of the other one is done.
-template <int VEC, bool CD, int T>
-__device__ __forceinline__ void tile_finish(const TileCtx<VEC>& c, double* comb, bool active, TileStats<VEC>& st,
+template <bool CD, int T>
+__device__ __forceinline__ void tile_finish(const TileCtx& c, double* comb, bool active, TileStats& st,
                                             double inv_n, double& total) {
     if (CD) {
         // first across the row groups that share a wavefront (lanes lpr apart hold the same columns; the exchange
@@ -208,12 +206,12 @@ __device__ __forceinline__ void tile_finish(const TileCtx<VEC>& c, double* comb,
         // (rows wider than a wavefront: a row group is whole wavefronts, one slot per row group)
         const int wl = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
+        for (int k = 0; k < kVec; ++k) {
             if (c.lpr <= 64) {
                 for (int off = c.lpr; off < 64; off <<= 1) st.a[k] += __shfl_xor(st.a[k], off, 64);
-                if (wl < c.lpr) comb[(size_t)(wave * c.lpr + wl) * VEC + k] = st.a[k];
+                if (wl < c.lpr) comb[(size_t)(wave * c.lpr + wl) * kVec + k] = st.a[k];
             } else {
-                comb[(size_t)(c.rg * c.lpr + c.lane) * VEC + k] = st.a[k];
+                comb[(size_t)(c.rg * c.lpr + c.lane) * kVec + k] = st.a[k];
             }
         }
         total += st.sq;
@@ -223,9 +221,9 @@ __device__ __forceinline__ void tile_finish(const TileCtx<VEC>& c, double* comb,
         if (active && c.rg == 0) {
             const int slots = c.lpr <= 64 ? T / 64 : c.nrg;
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) {
+            for (int k = 0; k < kVec; ++k) {
                 double at = 0.0;
-                for (int q = 0; q < slots; ++q) at += comb[(size_t)(q * c.lpr + c.lane) * VEC + k];
+                for (int q = 0; q < slots; ++q) at += comb[(size_t)(q * c.lpr + c.lane) * kVec + k];
                 total -= at * at * inv_n;
             }
         }
@@ -240,38 +238,38 @@ __device__ __forceinline__ void tile_finish(const TileCtx<VEC>& c, double* comb,
 // exactly; in fp64 the corrections are of the size of the sums themselves (every pivot is one of the outputs).
 // If all outputs of a column are equal every D_q is 0 and the distance comes out exactly 0.  One slot per row
 // group and column: a double for the sum and a float for the pivot.
-template <int VEC, int T>
-__device__ __forceinline__ void tile_finish_own(const TileCtx<VEC>& c, double* comb, float* combp, int live_cols,
-                                                TileStats<VEC>& st, double inv_n, double& total) {
+template <int T>
+__device__ __forceinline__ void tile_finish_own(const TileCtx& c, double* comb, float* combp, int live_cols,
+                                                TileStats& st, double inv_n, double& total) {
     // live_cols: the lanes of the tile that own a column group (all of them except in the ragged last tile)
-    // slot of row group q, column k of lane l: (q VEC + k) lpr + l, so that the lanes of a wavefront write
+    // slot of row group q, column k of lane l: (q kVec + k) lpr + l, so that the lanes of a wavefront write
     // neighbouring words (no bank conflicts); the merge below numbers the tile's columns in the same order
-    const int cols = c.lpr * VEC;
+    const int cols = c.lpr * kVec;
     const size_t mine = (size_t)c.rg * cols + c.lane;
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) {
+    for (int k = 0; k < kVec; ++k) {
         comb[mine + k * c.lpr] = st.a[k];
         combp[mine + k * c.lpr] = st.pivf[k];
     }
     total += st.sq;
     lds_barrier();
-    // The tile has lpr * VEC columns and nrg partial sums per column.  Where there are more lanes than columns
+    // The tile has lpr * kVec columns and nrg partial sums per column.  Where there are more lanes than columns
     // (1 KB row segments: four times as many) `parts` adjacent lanes share a column, each takes nrg / parts of its
     // row groups and a symmetric exchange adds the shares up, the same bits in every lane of the column.  (Left
     // to one lane per column the loop over the row groups is a chain of LDS round trips on a quarter of the
     // wavefronts while the others wait at the barrier below.)
-    // Nothing here branches on data: every lane reads VEC slots (clamped to slot 0 where it has fewer), all
+    // Nothing here branches on data: every lane reads kVec slots (clamped to slot 0 where it has fewer), all
     // reads are issued before the first is used, and a slot that does not count enters with weight 0.
-    const int parts = c.nrg >= VEC ? c.nrg / VEC : 1;        // a power of two; the lanes of a column sit side by side in one wavefront
-    const int each = c.nrg / parts;                          // row groups per lane: min(nrg, VEC)
+    const int parts = c.nrg >= kVec ? c.nrg / kVec : 1;        // a power of two; the lanes of a column sit side by side in one wavefront
+    const int each = c.nrg / parts;                          // row groups per lane: min(nrg, kVec)
     for (int idx = threadIdx.x; idx < cols * parts; idx += T) {
         const int col = idx / parts, part = idx % parts;
         const bool live = (col & (c.lpr - 1)) < live_cols;   // a column of a lane beyond the ragged end counts for nothing
-        double aq[VEC], md[VEC];
-        float pq[VEC];
+        double aq[kVec], md[kVec];
+        float pq[kVec];
         const float p0f = combp[col];                        // row group 0 owns row 0: its pivot is the common one
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
+        for (int k = 0; k < kVec; ++k) {
             const bool on = k < each;                        // uniform
             const int q = on ? part * each + k : 0;
             const size_t at_q = (size_t)q * cols + col;
@@ -282,7 +280,7 @@ __device__ __forceinline__ void tile_finish_own(const TileCtx<VEC>& c, double* c
         const double p0 = (double)p0f;
         double at = 0.0, corr = 0.0;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
+        for (int k = 0; k < kVec; ++k) {
             const double dq = (double)pq[k] - p0;
             const double tq = fma(md[k], dq, aq[k]);         // a row group without rows has a = 0 and weight 0: no share
             const double cq = dq * (tq + aq[k]);
@@ -306,14 +304,13 @@ __device__ __forceinline__ void tile_finish_own(const TileCtx<VEC>& c, double* c
     lds_barrier();                                     // the merge slots are free again
 }
 
-template <int VEC, typename GT, bool CD, int T>
+template <typename GT, bool CD, int T>
 __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ G, const TileSlot* tab, char* tiles,
                             int n, int deg, Pitch ld, int64_t ncg, float neg_lr, int lpr, double inv_n) {
-    typedef typename Cols<VEC>::T V;
-    typedef typename RawG<GT, VEC>::T GR;
-    const Cols<VEC> tag{};
+    typedef f32x4 V;
+    typedef typename RawG<GT>::T GR;
     constexpr int RB = TileShape<T>::RB, SB = TileShape<T>::SB;
-    TileCtx<VEC> c;
+    TileCtx c;
     c.tab = tab;
     c.n = n;
     c.deg = deg;
@@ -329,17 +326,17 @@ __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ 
     const size_t tile_bytes = (((size_t)n * lpr * sizeof(V)) + 15) & ~(size_t)15;
     V* cur = reinterpret_cast<V*>(tiles);
     V* nxt = reinterpret_cast<V*>(tiles + tile_bytes);
-    double* comb = reinterpret_cast<double*>(tiles + 2 * tile_bytes);   // [T / 64][lpr][VEC], CD only
+    double* comb = reinterpret_cast<double*>(tiles + 2 * tile_bytes);   // [T / 64][lpr][kVec], CD only
     const int64_t ntiles = (ncg + lpr - 1) / lpr;
     const int64_t step = gridDim.x;
     int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds);   // the first of tiles t, t + step, ...
     if (t >= ntiles) return 0.0;                             // uniform: the whole workgroup has nothing to do
     double total = 0.0;
-    TileStats<VEC> st;
+    TileStats st;
 
     // Loads of one batch of one tile: X rows into xs, gradient rows into g (nothing beyond the last tile or the
     // ragged end of the rows).
-    auto col_of = [&](int64_t tile) { return (tile * lpr + lane) * VEC; };
+    auto col_of = [&](int64_t tile) { return (tile * lpr + lane) * kVec; };
     auto live = [&](int64_t tile) { return tile < ntiles && tile * lpr + lane < ncg; };
     // `q` is the lane's row group: rg, or the same number held in a scalar register where it is known to be
     // uniform over the wavefront (row offsets and table addresses then cost no vector registers).
@@ -349,7 +346,7 @@ __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ 
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             const int r = q + (b * RB + u) * nrg;
-            if (on && r < n) xs[u] = ld_x(X + (int64_t)r * ld.x + col, tag);
+            if (on && r < n) xs[u] = ld_x(X + (int64_t)r * ld.x + col);
         }
     };
     auto load_g = [&](int q, int64_t tile, int b, GR (&g)[RB]) {
@@ -358,7 +355,7 @@ __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ 
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             const int r = q + (b * RB + u) * nrg;
-            if (on && r < n) g[u] = ld_g_raw(G + (int64_t)r * ld.g + col, tag);
+            if (on && r < n) g[u] = ld_g_raw(G + (int64_t)r * ld.g + col);
         }
     };
     auto stash = [&](int q, int64_t tile, int b, V* buf, const V (&xs)[RB]) {
@@ -381,7 +378,7 @@ __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ 
     // gradients one batch ahead.
     GR gcur[RB], g0 = {};
     load_g(rg, t, 0, gcur);
-    if (CD && live(t)) g0 = ld_g_raw(G + col_of(t), tag);
+    if (CD && live(t)) g0 = ld_g_raw(G + col_of(t));
     lds_barrier();
     for (;;) {
         const int64_t tn = t + step;
@@ -396,15 +393,15 @@ __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ 
                 load_g(rg, t, b + 1, gn);
             } else {
                 load_g(rg, tn, 0, gn);
-                if (CD && live(tn)) g0n = ld_g_raw(G + col_of(tn), tag);
+                if (CD && live(tn)) g0n = ld_g_raw(G + col_of(tn));
             }
-            tile_rows<VEC, CD, RB, SB, false, false>(c, cur, b, gcur, g0, b == 0, active, Xout + col_of(t), ld.o, st);
+            tile_rows<CD, RB, SB, false, false>(c, cur, b, gcur, g0, b == 0, active, Xout + col_of(t), ld.o, st);
             stash(rg, tn, b, nxt, xs);
 #pragma unroll
             for (int u = 0; u < RB; ++u) gcur[u] = gn[u];
         }
         g0 = g0n;
-        tile_finish<VEC, CD, T>(c, comb, active, st, inv_n, total);
+        tile_finish<CD, T>(c, comb, active, st, inv_n, total);
         if (tn >= ntiles) break;
         V* sw = cur;
         cur = nxt;
@@ -423,15 +420,14 @@ __device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ 
 // UQ: a row group is whole wavefronts (lpr >= 64), so its number is the same in every lane of a wavefront and is
 // kept in a scalar register: row offsets and table addresses then cost no vector registers.  Narrower rows
 // (n > 64 at 16 B per lane: two or four row groups share a wavefront) keep it per lane.
-template <int VEC, typename GT, bool CD, int T, bool UQ>
+template <typename GT, bool CD, int T, bool UQ>
 __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restrict__ G, const TileSlot* tab, char* tiles,
                                  int n, int deg, Pitch ld, int64_t ncg, float neg_lr, int lpr, double inv_n,
                                  bool comb_in_tile) {
-    typedef typename Cols<VEC>::T V;
-    typedef typename RawG<GT, VEC>::T GR;
-    const Cols<VEC> tag{};
+    typedef f32x4 V;
+    typedef typename RawG<GT>::T GR;
     constexpr int RB = TileShape<T>::RB, SB = TileShape<T>::SB;
-    TileCtx<VEC> c;
+    TileCtx c;
     c.tab = tab;
     c.n = n;
     c.deg = deg;
@@ -445,13 +441,13 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
     const size_t tile_bytes = (((size_t)n * lpr * sizeof(V)) + 15) & ~(size_t)15;
     V* cur = reinterpret_cast<V*>(tiles);
     V* nxt = reinterpret_cast<V*>(tiles + tile_bytes);
-    double* comb = reinterpret_cast<double*>(tiles + 2 * tile_bytes);   // [nrg][lpr][VEC] sums, then as many float pivots
+    double* comb = reinterpret_cast<double*>(tiles + 2 * tile_bytes);   // [nrg][lpr][kVec] sums, then as many float pivots
     const int64_t ntiles = (ncg + lpr - 1) / lpr;
     const int64_t step = gridDim.x;
     int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds);   // the first of tiles t, t + step, ...
     if (t >= ntiles) return 0.0;                             // uniform: the whole workgroup has nothing to do
     double total = 0.0;
-    TileStats<VEC> st;
+    TileStats st;
     // A tile is one batch of whole-wavefront rows (n <= 64 with 1 KB row segments, fewer learners with wider
     // ones).  A lane keeps ONE register per row for X and one for the gradients, each reloaded the moment
     // its value has been used, so every load has a whole tile's time to arrive:
@@ -480,15 +476,15 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             const int r = q + u * nrg;
-            if (r < n) cur[r * lpr + lane] = ld_x(X + (int64_t)r * ld.x + (t * lpr + lane) * VEC, tag);
+            if (r < n) cur[r * lpr + lane] = ld_x(X + (int64_t)r * ld.x + (t * lpr + lane) * kVec);
         }
     }
     {
-        const int64_t colx = cge_of(t + step) * VEC, colg = cge_of(t) * VEC;
+        const int64_t colx = cge_of(t + step) * kVec, colg = cge_of(t) * kVec;
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
-            x[u] = ld_x(X + (int64_t)row_of(u) * ld.x + colx, tag);
-            g[u] = ld_g_raw(G + (int64_t)row_of(u) * ld.g + colg, tag);
+            x[u] = ld_x(X + (int64_t)row_of(u) * ld.x + colx);
+            g[u] = ld_g_raw(G + (int64_t)row_of(u) * ld.g + colg);
         }
     }
     lds_barrier();
@@ -496,7 +492,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
     // are counted per place in the program, and a place that both the start and the loop reach waits for the
     // smaller count, the start's, where fewer operations have been issued since.
     auto one_tile = [&]() __attribute__((always_inline)) {
-        const int64_t colx = cge_of(t + 2 * step) * VEC, colg = cge_of(t + step) * VEC;
+        const int64_t colx = cge_of(t + 2 * step) * kVec, colg = cge_of(t + step) * kVec;
         // where tile t + step goes in the other buffer: the lane's own slot, the last valid lane's at the ragged
         // end (the same value twice), and beyond the last tile anywhere (nobody will read it) - never a branch
         const int lane_to = (int)(cge_of(t + step) - (t + step) * lpr);
@@ -509,7 +505,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
                 if (u < RB) {
                     const int r = row_of(u);
                     nxt[r * lpr + lane_n] = x[u];
-                    x[u] = ld_x(X + (int64_t)r * ld.x + colx, tag);
+                    x[u] = ld_x(X + (int64_t)r * ld.x + colx);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -519,7 +515,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
                 const int u = j0 + i;
-                if (u < RB) g[u] = ld_g_raw(G + (int64_t)row_of(u) * ld.g + colg, tag);
+                if (u < RB) g[u] = ld_g_raw(G + (int64_t)row_of(u) * ld.g + colg);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -527,7 +523,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
         const bool active = t * lpr + lane < ncg;
         c.tlane = (int)(cge - t * lpr);
         if (CD) st.reset();
-        tile_rows<VEC, CD, RB, SB, true, true>(c, cur, 0, g, GR{}, false, active, Xout + cge * VEC, ld.o, st, feed, refill);
+        tile_rows<CD, RB, SB, true, true>(c, cur, 0, g, GR{}, false, active, Xout + cge * kVec, ld.o, st, feed, refill);
         if (CD) {
             const int64_t left = ncg - t * lpr;                       // column groups of this tile (uniform)
             double* sums = comb;
@@ -535,7 +531,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
                 lds_barrier();                                        // every row of `cur` has been read
                 sums = reinterpret_cast<double*>(cur);
             }
-            tile_finish_own<VEC, T>(c, sums, reinterpret_cast<float*>(sums + (size_t)nrg * lpr * VEC),
+            tile_finish_own<T>(c, sums, reinterpret_cast<float*>(sums + (size_t)nrg * lpr * kVec),
                                     (int)(left < lpr ? left : lpr), st, inv_n, total);
         } else {
             lds_barrier();
@@ -551,6 +547,39 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
 }
 
 
+// The d mod 4 columns behind the last whole column group, one element per lane, by one workgroup: they pass through
+// LDS (`lds`: two floats per element, free when this is called) as a tile does.  Returns their part of the distance.
+template <typename GT, bool CD, int T>
+__device__ double tile_remainder(const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr,
+                                 const float* __restrict__ w, float* lds, int n, int deg, Pitch ld, int64_t d, float neg_lr,
+                                 double inv_n) {
+    const int rem = (int)(d & 3), count = n * rem;
+    const int64_t col = d - rem;
+    float* out = lds + count;
+    __syncthreads();                                             // the LDS is free
+    for (int e = threadIdx.x; e < count; e += T) lds[e] = X[(int64_t)(e / rem) * ld.x + col + e % rem];
+    __syncthreads();
+    for (int e = threadIdx.x; e < count; e += T) {
+        const int r = e / rem, c = e % rem;
+        float acc = lds[nbr[r * deg] * rem + c] * w[r * deg];
+        for (int s = 1; s < deg; ++s) acc = vfma(w[r * deg + s], lds[nbr[r * deg + s] * rem + c], acc);
+        acc = vfma(neg_lr, widen_1(G[(int64_t)r * ld.g + col + c]), acc);
+        Xout[(int64_t)r * ld.o + col + c] = acc;
+        out[e] = acc;
+    }
+    if (!CD) return 0.0;
+    __syncthreads();
+    double a = 0.0, sq = 0.0;
+    if ((int)threadIdx.x < rem) {
+        for (int r = 1; r < n; ++r) {
+            const double df = (double)out[r * rem + threadIdx.x] - (double)out[threadIdx.x];
+            a += df;
+            sq = fma(df, df, sq);
+        }
+    }
+    return sq - a * a * inv_n;
+}
+
 // Any table with `deg` slots per row (sparse doubly stochastic matrices beyond the ring: more neighbours, lazy
 // walks, products of several mixing rounds, and 3-slot tables that are not one ring).  Always the tiled path.
 // LDS: TileSlot tab[deg n] | two tile buffers | merge slots (plan::tile_plan).
@@ -561,7 +590,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
 //
 // DEEP: 0 = several batches per tile (tile_path); 1, 2 = the large workgroup's one-batch form (tile_path_deep)
 // with whole-wavefront rows (1) or narrower ones (2); the launcher has planned lpr for it.
-template <int VEC, typename GT, bool CD, int T, int DEEP>
+template <typename GT, bool CD, int T, int DEEP>
 __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                     const int32_t* __restrict__ nbr, const float* __restrict__ w,
                                                     int deg, int n, int64_t d, Pitch ld, float neg_lr, int lpr,
@@ -590,13 +619,16 @@ __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout,
         if (CD && threadIdx.x == 0) partials[blockIdx.x] = __builtin_nan("");
         return;
     }
+    const double inv_n = 1.0 / (double)n;
     double total;
     if (DEEP)
-        total = tile_path_deep<VEC, GT, CD, T, DEEP == 1>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / VEC, neg_lr,
-                                                          lpr, 1.0 / (double)n, comb_in_tile != 0);
+        total = tile_path_deep<GT, CD, T, DEEP == 1>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / kVec, neg_lr, lpr,
+                                                     inv_n, comb_in_tile != 0);
     else
-        total = tile_path<VEC, GT, CD, T>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / VEC, neg_lr, lpr,
-                                          1.0 / (double)n);
+        total = tile_path<GT, CD, T>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / kVec, neg_lr, lpr, inv_n);
+    if (d % kVec != 0 && blockIdx.x == 0)
+        total += tile_remainder<GT, CD, T>(X, Xout, G, nbr, w, reinterpret_cast<float*>(lds_raw + tab_bytes), n, deg, ld, d,
+                                           neg_lr, inv_n);
     if (CD) {
         const double bs = block_sum<T>(total, lds_waves);
         if (threadIdx.x == 0) partials[blockIdx.x] = bs;
