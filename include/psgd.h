@@ -115,9 +115,10 @@ int psgd_build_mixing_device(int topology, int n, uint64_t seed, uint64_t* step_
  *
  * Enqueues its work on `stream` and returns without waiting.  The table lives in device memory,
  * so only the device can tell whether it is one ring (every table of Sec. 3 is) or a general
- * 3-slot table.  Short rows: one kernel that serves any table.  Long rows (from about 1.5 M
- * columns): two kernels, the ring walk and behind it the tiled kernel, each shaped for its own
- * path; both classify the table and the one it does not belong to exits at once.
+ * 3-slot table.  Most shapes: one kernel that serves any table.  Long rows of many learners
+ * (64 learners: from about 2.4 M columns; 128 and more: from 0.6 M): two kernels, the ring walk
+ * and behind it the tiled kernel, each shaped for its own path; both classify the table and the
+ * one it does not belong to exits at once.
  * Errors: PSGD_EINVAL;
  * PSGD_EALIAS (X_out partially overlaps X, X_out overlaps G, or X_out == X with
  * delay_mode 1); PSGD_EALIGN (X, X_out, G not 4-byte aligned); PSGD_EHIP.  A table entry

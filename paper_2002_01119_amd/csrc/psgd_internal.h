@@ -53,9 +53,10 @@ PSGD_HOST_DEVICE inline int64_t die_contiguous_slot(int64_t b, int64_t grid, int
 
 // Even split of `ncg` column groups over a persistent grid: every workgroup makes `count` sweeps and takes
 // `chunk` <= threads consecutive groups in each; workgroup b's range in sweep sw starts at
-// (sw * grid + die_contiguous_slot(b)) * chunk.  With a fixed chunk of `threads` the last, partly filled sweep costs as much as a
-// full one (11 instead of 10.2 on rows of 2 M groups with 256 workgroups of 768 lanes); the kernels are bound
-// by bytes, so a sweep is as much faster as it is smaller.  The chunk stays a multiple of kChunkAlign.
+// (sw * grid + die_contiguous_slot(b)) * chunk.  With a fixed chunk of `threads` the last, partly filled sweep costs as
+// much as a full one (11 instead of 10.2 on rows of 2 M groups with 256 workgroups of 768 lanes; three instead of 2.03
+// on 400 000: ring step of 512 learners 2185 us, split evenly 1939); the kernels are bound by bytes, so a sweep is as
+// much faster as it is smaller.  The chunk stays a multiple of kChunkAlign.
 struct SweepPlan {
     int64_t count, chunk;
 };
@@ -63,14 +64,24 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads) {
     SweepPlan s;
     const int64_t per = (int64_t)grid * threads;
     s.count = (ncg + per - 1) / per;
-    if (s.count < 4) {   // a launch of one to three sweeps is bound by latency: full chunks, fewer of them
-        s.chunk = threads;
-        return s;
-    }
     const int64_t parts = s.count * grid;
-    s.chunk = (ncg + parts - 1) / parts;
+    s.chunk = parts > 0 ? (ncg + parts - 1) / parts : 1;
     s.chunk = (s.chunk + kChunkAlign - 1) / kChunkAlign * kChunkAlign;
     return s;
+}
+
+// Whether a 3-slot table on n rows of `ncg` column groups takes the ring walk (and the tiled kernel behind it) instead
+// of the short-row kernel, which serves any table at once.  The ring walk reads and writes 12 KB of a row at a time
+// whatever n is, but pays for classifying the table, for a second launch and for its sweeps; the short-row kernel's
+// row segments narrow as n grows (4096 / n lanes of 16 bytes).  In sweeps of one 768-lane workgroup per compute unit, us on
+// dense arrays with fp32 gradients and the distance, short-row kernel / ring walk:
+//   8 x 6.4 M 123 / 130, x 51.2 M 933 / 977;   16 x 6.4 M 241 / 246, x 12.8 M 477 / 473, x 51.2 M 1956 / 1891;
+//   64 x 1.6 M 246 / 250, x 3.2 M 489 / 486, x 25.6 M 3967 / 3834;   256 x 0.4 M 253 / 283, x 0.6 M 375 / 360,
+//   x 1.6 M 1054 / 970;   512 x 0.4 M 539 / 553, x 0.6 M 764 / 710.
+inline bool ring_rows(int n, int64_t ncg, int cus, int threads) {
+    if (n <= 8) return false;
+    const int64_t sweep = (int64_t)cus * threads;
+    return ncg >= (n < 48 ? 12 * sweep : n < 96 ? 3 * sweep : sweep * 3 / 4);
 }
 
 // LDS of the tiled path (tables that are not one ring): the slot table (8 bytes per slot), TWO tile buffers of

@@ -263,7 +263,7 @@ int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const floa
                const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, int slots) {
     const void* fn = reinterpret_cast<const void*>(mix_step_kernel<GT, CD>);
     if (allow_lds(fn, lds_bytes)) return kLaunchRefused;
-    const int grid = persistent_grid(di, (d + 3) / 4, 1, kRingThreads);
+    const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
     if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
     hipLaunchKernelGGL((mix_step_kernel<GT, CD>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
                        n, d, ld, neg_lr, make_sweeps((d + 3) / 4, grid, kRingThreads), partials);
@@ -371,10 +371,11 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const float neg_lr = -lr;
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
-    const bool big = long_rows(*di, (d + 3) / 4);
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    const bool big = deg == 3 ? plan::ring_rows(n, ncg, di->cus, kRingThreads) : long_rows(*di, ncg);
     if (!big) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
-                                         : plan::short_plan(n, deg, (d + 3) / 4, di->cus, want_cd, slots);
+                                         : plan::short_plan(n, deg, ncg, di->cus, want_cd, slots);
         if (want_cd && deg == 3) grid = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
         else if (want_cd) grid = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
         else if (deg == 3) grid = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);

@@ -1,4 +1,4 @@
-"""The short-row kernel at the edges of its forms: one round of tiles at each workgroup size, all rows in one lane, the
+"""The short-row kernel, and the ring walk where it takes over, at the edges of their forms: one round of tiles at each workgroup size, all rows in one lane, the
 looping form with a ragged last tile, row counts that do not fill the row groups, rows of one to five columns, arrays
 whose rows start at any element.  Every element and the distance against the oracle's sparse form."""
 import numpy as np
@@ -18,6 +18,9 @@ CASES = [
     (512, 6_001, 8, "bf16", (1, 2, 7)), (100, 50_002, 3, "f32", None),
     (8, 1_048_578, 3, "f32", None), (8, 1_200_003, 3, "bf16", (2, 3, 1)), (5, 1_570_001, 4, "f32", None),
     (9, 1_100_002, 3, "bf16", None), (16, 700_001, 5, "f32", (1, 2, 3)), (64, 200_003, 3, "bf16", (3, 1, 1)),
+    # either side of the line to the ring walk, whose last column group is ragged too; n = 64 is not a ring
+    (128, 589_821, 3, "f32", (1, 2, 3)), (128, 589_825, 3, "bf16", (3, 1, 2)), (200, 600_002, 3, "f32", None),
+    (64, 2_359_299, 3, "bf16", None),
     (100, 120_001, 3, "f32", None), (257, 40_007, 4, "bf16", None), (512, 20_002, 3, "f32", (1, 0, 2)),
 ]
 
