@@ -237,7 +237,7 @@ int psgd_mix_step_deg(const float* X, int64_t ldx, float* X_out, int64_t ldo,
  *
  * Arguments, pitches, gradient type, in-place rule, optional cdist_out, errors and
  * asynchrony are those of psgd_mix_step_ex.  Per element: the column sum is accumulated in
- * fp64 over rows 0..n-1, mean = (float)(sum / n), out = fma(-lr, g, mean).
+ * fp64, mean = (float)(sum / n), out = fma(-lr, g, mean).
  */
 int psgd_mix_full(const float* X, int64_t ldx, float* X_out, int64_t ldo,
                   const void* G, int64_t ldg, int g_is_bf16,

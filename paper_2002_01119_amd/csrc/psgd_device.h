@@ -115,6 +115,11 @@ template <bool FEW> __device__ __forceinline__ u32x2 ld_cols_raw(const uint16_t*
     if (!FEW) return ld_g_raw(p);
     return (u32x2){(uint32_t)p[0] | (d > 1 ? (uint32_t)p[1] << 16 : 0u), d > 2 ? (uint32_t)p[2] : 0u};
 }
+// The same for kernels that are built apart for rows that 4 divides (RAGGED false), where a group is whole or none.
+template <bool RAGGED> __device__ __forceinline__ ColGroup col_group_of(int64_t cg, int64_t ncg, int64_t d) {
+    if (RAGGED) return col_group(cg, d);
+    return cg < ncg ? ColGroup{cg * 4, 0, 4} : ColGroup{0, 4, 4};
+}
 __device__ __forceinline__ void st_cols(float* p, f32x4 v, const ColGroup& c) {
     if (c.lo == 0 && c.hi == 4) {
         st_x(p, v);
@@ -123,6 +128,11 @@ __device__ __forceinline__ void st_cols(float* p, f32x4 v, const ColGroup& c) {
         for (int k = 0; k < 4; ++k)
             if (k >= c.lo && k < c.hi) __builtin_nontemporal_store(v[k], p + k);
     }
+}
+
+template <bool RAGGED> __device__ __forceinline__ void st_cols_of(float* p, f32x4 v, const ColGroup& c) {
+    if (RAGGED) st_cols(p, v, c);
+    else if (c.lo == 0) st_x(p, v);
 }
 
 // Two barriers that are lighter than __syncthreads(), which also waits until every global load and store the
@@ -333,15 +343,98 @@ struct ColStats {
         }
     }
     // over the columns the lane owns
-    __device__ __forceinline__ double result(double inv_n, const ColGroup& c) const {
+    template <bool RAGGED> __device__ __forceinline__ double result(double inv_n, const ColGroup& c) const {
         double t = 0.0;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (k >= c.lo && k < c.hi) t += sq[k] - a[k] * a[k] * inv_n;
-        return t;
+            if (!RAGGED || (k >= c.lo && k < c.hi)) t += sq[k] - a[k] * a[k] * inv_n;
+        return RAGGED || c.lo == 0 ? t : 0.0;
     }
 };
 
+
+// ---------------------------------------------------------------------------------------
+// Tiles whose rows are spread over row groups: T = nrg * C lanes, C = 1 << logc column groups wide, lane (rg, lane) sees
+// rows rg, rg + nrg, ... of column group `lane`.  What follows combines the row groups' values per column through LDS
+// arrays laid out [4][nrg][C].
+// ---------------------------------------------------------------------------------------
+// Row `r` of n, or the last one for a lane without a row (which then repeats that row's loads).
+__device__ __forceinline__ int row_or_last(int r, int n) { return r < n ? r : n - 1; }
+
+// Calls f(k, l, first, step, reach) with every lane: column k of lane l is the lane's, which takes row groups first,
+// first + step, ...; the lanes that share a column differ in the bits reach, 2 reach, .. 32 of their number, and first = 0
+// in one of them.  The lanes of a wavefront read L neighbouring columns of 64 / L row groups, so that the few columns of
+// a tile with many rows still occupy many lanes.
+template <typename F>
+__device__ __forceinline__ void row_group_columns(int logc, int nrg, int T, const F& f) {
+    const int C = 1 << logc, most = nrg >= 8 ? 4 : 6;
+    const int logl = logc < most ? logc : most, parts = 64 >> logl;
+    for (int idx = threadIdx.x; idx < 4 * C * parts; idx += T) {   // whole wavefronts
+        const int col = (idx >> 6 << logl) + (idx & ((1 << logl) - 1));
+        f(col >> logc, col & (C - 1), (idx >> logl) & (parts - 1), parts, 1 << logl);
+    }
+}
+
+// The column sums a_q of the row groups, each against its own pivot p_q, to the squares about the column's mean: with
+// P = p_0, D_q = p_q - P and m_q rows in group q,
+//     sum_i (o_i - P)   = sum_q (a_q + m_q D_q)
+//     sum_i (o_i - P)^2 = sum_q (sq_q + 2 D_q a_q + m_q D_q^2)
+// exactly; in fp64 the corrections are of the size of the sums themselves, as every pivot is one of the values, and
+// equal values give exactly 0.  Returns this lane's part of what is to be added to the sum of all sq_q.
+// FULL: every column of the tile, which starts at column group `first`, exists.
+template <bool FULL>
+__device__ __forceinline__ double row_group_merge(const double* sums, const float* pivots, int logc, int nrg, int n, int T,
+                                                  double inv_n, int64_t first, int64_t d) {
+    const int each = n / nrg, more = n % nrg;                   // rows of group q: each, one more if q < more
+    double total = 0.0;
+    row_group_columns(logc, nrg, T, [&](int k, int l, int q0, int step, int reach) {
+        const int at0 = ((k * nrg) << logc) + l;
+        const double p0 = (double)pivots[at0];
+        double at = 0.0, corr = 0.0;
+#pragma unroll 4
+        for (int q = q0; q < nrg; q += step) {
+            const double aq = sums[at0 + (q << logc)];
+            const double dq = (double)pivots[at0 + (q << logc)] - p0;
+            const double tq = fma((double)(each + (q < more ? 1 : 0)), dq, aq);
+            at += tq;
+            corr = fma(dq, tq + aq, corr);
+        }
+        for (int off = reach; off < 64; off <<= 1) {
+            at += __shfl_xor(at, off, 64);
+            corr += __shfl_xor(corr, off, 64);
+        }
+        const ColGroup c = col_group(FULL ? 0 : first + l, d);
+        if (q0 == 0 && (FULL || (k >= c.lo && k < c.hi))) total += corr - at * at * inv_n;
+    });
+    return total;
+}
+
+// A tile's whole distance from every lane's sums against its pivot.  Contains a barrier; the LDS arrays must be free
+// when it is called and are being read when it returns.
+__device__ __forceinline__ double row_group_distance(double* sums, float* pivots, int logc, int nrg, int n, int T, int rg,
+                                                     int lane, double inv_n, const double (&a)[4], const double (&sq)[4],
+                                                     f32x4 pv, const ColGroup& c, int64_t first, int64_t d) {
+    double total = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        sums[((k * nrg + rg) << logc) + lane] = a[k];
+        pivots[((k * nrg + rg) << logc) + lane] = pv[k];
+        if (k >= c.lo && k < c.hi) total += sq[k];
+    }
+    lds_barrier();
+    return total + row_group_merge<false>(sums, pivots, logc, nrg, n, T, inv_n, first, d);
+}
+
+// block_sum for a workgroup of T lanes known at run time (whole wavefronts).
+__device__ __forceinline__ double block_sum_any(double v, double* lds_waves, int T) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) lds_waves[threadIdx.x >> 6] = v;
+    lds_barrier();
+    double r = 0.0;
+    if (threadIdx.x == 0)
+        for (int i = 0; i < T / 64; ++i) r += lds_waves[i];
+    return r;  // valid in thread 0
+}
 
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
 // same number of sweeps, lanes beyond the chunk idle.

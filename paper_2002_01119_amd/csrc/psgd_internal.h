@@ -178,6 +178,42 @@ inline int short_grid(const ShortPlan& p, int cus, int64_t most) {
     if (g > most) g = most;
     return (int)(g < 1 ? 1 : g);
 }
+// Tiles of global averaging and of the distance with rows spread over row groups of lanes: at most `rows` rows per lane,
+// the widest tile of at most `threads` lanes.  threads == 0: the columns alone fill the chip, a lane walks all rows.
+struct RowsPlan {
+    int threads, logc, nrg;
+    int64_t tiles;
+};
+inline RowsPlan rows_shape(int n, int64_t ncg, int threads, int rows) {
+    RowsPlan p;
+    for (p.logc = 10; p.logc >= 0; --p.logc) {
+        const int c = 1 << p.logc, whole = c < 64 ? 64 / c : 1;
+        p.nrg = ((n + rows - 1) / rows + whole - 1) / whole * whole;
+        p.threads = p.nrg * c;
+        p.tiles = (ncg + c - 1) >> p.logc;
+        if (p.threads <= threads) break;
+    }
+    return p;
+}
+// As for the short-row kernel, one round of at most one workgroup per compute unit where that holds everything (the
+// widest workgroup that occupies more than half of them); many learners beyond it take more rows per lane, up to where
+// the columns alone do as well.  us, lane per column group / rows spread: global averaging with the distance 512 x 6 k
+// 175 / 13.4, 64 x 100 k 28.8 / 19.5, 512 x 60 k 187 / 69, 128 x 200 k 61.6 / 60.8, 64 x 300 k 49.4 / 49.7; distance alone
+// 512 x 6 k 52 / 8.5, 64 x 100 k 11.4 / 9.2, 512 x 60 k 54 / 23, 128 x 200 k 20.2 / 22.3, 24 x 100 k 7.0 / 7.6.
+// `least`: the fewest learners, 9 for global averaging (two passes over the rows), 48 for the distance (one).
+inline RowsPlan rows_plan(int n, int64_t ncg, int cus, int most_threads, int rows, int least) {
+    if (ncg == 1) return rows_shape(n, ncg, 256, rows);          // also the only form for fewer than four columns
+    if (n >= least) {
+        for (int threads = most_threads; threads >= 256; threads /= 2) {
+            const RowsPlan p = rows_shape(n, ncg, threads, rows);
+            if (p.tiles > cus) break;
+            if (p.tiles > cus / 2 || threads == 256) return p;
+        }
+        if (n >= 128 && ncg < (int64_t)cus * 128) return rows_shape(n, ncg, 512, 32);
+    }
+    return RowsPlan{0, 0, 0, 0};
+}
+
 // Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
 //   - everything in one round of at most one workgroup per compute unit, eight rows per lane: the whole chip's loads
 //     are in flight at once.  8 learners x 1 M without the distance 15.7 us, looping over narrower tiles 18.9; 64 x 100 k

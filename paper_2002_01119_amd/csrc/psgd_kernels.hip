@@ -258,14 +258,14 @@ constexpr int kLaunchRefused = INT32_MIN;
 // Launches one instantiation of the ring-walk kernel, one workgroup per compute unit.
 // Returns the grid size, minus the grid size (and launches nothing) when the fused distance would need more
 // than `slots` partials, or kLaunchRefused when the runtime refuses the LDS size.
-template <typename GT, bool CD>
+template <typename GT, bool CD, bool RAGGED>
 int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
                const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, int slots) {
-    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<GT, CD>);
+    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED>);
     if (allow_lds(fn, lds_bytes)) return kLaunchRefused;
     const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
     if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
-    hipLaunchKernelGGL((mix_step_kernel<GT, CD>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
                        n, d, ld, neg_lr, make_sweeps((d + 3) / 4, grid, kRingThreads), partials);
     return grid;
 }
@@ -386,8 +386,10 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     if (big && deg == 3) {
         // The ring-walk kernel does the work when the table is one ring (every table of Sec. 3); the tiled kernel
         // follows it (below) for all others, because each path wants its own workgroup shape and registers.
-        grid = want_cd ? launch_mix<GT, true>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots)
-                       : launch_mix<GT, false>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots);
+#define PSGD_RING(CD, RAGGED) launch_mix<GT, CD, RAGGED>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots)
+        if (d % kVec) grid = want_cd ? PSGD_RING(true, true) : PSGD_RING(false, true);
+        else grid = want_cd ? PSGD_RING(true, false) : PSGD_RING(false, false);
+#undef PSGD_RING
         if (grid == kLaunchRefused) return PSGD_EHIP;   // allow_lds has recorded the reason
         if (grid < 0)
             return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, -grid, slots);
@@ -501,19 +503,39 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         return release_partials(di, s);
     }
     const int64_t ncg = (d + kVec - 1) / kVec;
-    const bool big = long_rows(*di, ncg, 2);
-    const int grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : persistent_grid(*di, ncg, kGridPerCu);
     const Pitch ld{ldx, ldo, ldg};
     const float neg_lr = -lr;
-#define PSGD_LAUNCH_FULL(CD, T, FEW)                                                                                      \
-    hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, FEW>), dim3(grid), dim3(T), 0, s, X, X_out, G, n, d, ld, neg_lr,         \
-                       make_sweeps(ncg, grid, T), partials)
-    if (big && want_cd) PSGD_LAUNCH_FULL(true, kRingThreads, false);
-    else if (big) PSGD_LAUNCH_FULL(false, kRingThreads, false);
-    else if (d < kVec && want_cd) PSGD_LAUNCH_FULL(true, kThreads, true);
-    else if (d < kVec) PSGD_LAUNCH_FULL(false, kThreads, true);
-    else if (want_cd) PSGD_LAUNCH_FULL(true, kThreads, false);
-    else PSGD_LAUNCH_FULL(false, kThreads, false);
+    const bool big = long_rows(*di, ncg, 2);
+    const plan::RowsPlan rp = plan::rows_plan(n, ncg, di->cus, plan::kShortThreads, kUnroll, kUnroll + 1);
+    const bool split = !big && rp.threads != 0;
+    int grid = 0;
+    if (split) {
+        grid = (int)(rp.tiles < kMaxGrid ? rp.tiles : kMaxGrid);
+        const size_t lds = (size_t)rp.threads * (want_cd ? 48 : 32) + (16 << rp.logc);
+#define PSGD_LAUNCH_ROWS(CD, FEW)                                                                                          \
+    hipLaunchKernelGGL((mix_full_rows_kernel<GT, CD, FEW>), dim3(grid), dim3(rp.threads), lds, s, X, X_out, G, n, d, ld,    \
+                       neg_lr, rp.logc, rp.nrg, partials)
+        if (d < kVec && want_cd) PSGD_LAUNCH_ROWS(true, true);
+        else if (d < kVec) PSGD_LAUNCH_ROWS(false, true);
+        else if (want_cd) PSGD_LAUNCH_ROWS(true, false);
+        else PSGD_LAUNCH_ROWS(false, false);
+#undef PSGD_LAUNCH_ROWS
+    } else {
+        grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : persistent_grid(*di, ncg, kGridPerCu);
+#define PSGD_LAUNCH_FULL(CD, T)                                                                                            \
+    do {                                                                                                                   \
+        if (d % kVec)                                                                                                      \
+            hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, true>), dim3(grid), dim3(T), 0, s, X, X_out, G, n, d, ld,        \
+                               neg_lr, make_sweeps(ncg, grid, T), partials);                                               \
+        else                                                                                                               \
+            hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, false>), dim3(grid), dim3(T), 0, s, X, X_out, G, n, d, ld,       \
+                               neg_lr, make_sweeps(ncg, grid, T), partials);                                               \
+    } while (0)
+        if (big && want_cd) PSGD_LAUNCH_FULL(true, kRingThreads);
+        else if (big) PSGD_LAUNCH_FULL(false, kRingThreads);
+        else if (want_cd) PSGD_LAUNCH_FULL(true, kThreads);
+        else PSGD_LAUNCH_FULL(false, kThreads);
+    }
 #undef PSGD_LAUNCH_FULL
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
@@ -541,11 +563,23 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
             hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads>), dim3(grid), dim3(kRingThreads), 0, s, X, n, d, ldx,
                                make_sweeps(ncg, grid, kRingThreads), partials);
         } else {
-            grid = persistent_grid(*di, ncg, 8);  // light kernel: 32 waves per CU
-            if (d < kVec)
-                hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
-            else
-                hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+            const plan::RowsPlan rp = plan::rows_plan(n, ncg, di->cus, 512, 2 * kUnroll, 48);
+            if (rp.threads != 0) {
+                grid = (int)(rp.tiles < kMaxGrid ? rp.tiles : kMaxGrid);
+                const size_t lds = (size_t)rp.threads * 48;
+                if (d < kVec)
+                    hipLaunchKernelGGL(consensus_rows_kernel<true>, dim3(grid), dim3(rp.threads), lds, s, X, n, d, ldx, rp.logc,
+                                       rp.nrg, partials);
+                else
+                    hipLaunchKernelGGL(consensus_rows_kernel<false>, dim3(grid), dim3(rp.threads), lds, s, X, n, d, ldx, rp.logc,
+                                       rp.nrg, partials);
+            } else {
+                grid = persistent_grid(*di, ncg, 8);  // light kernel: 32 waves per CU
+                if (d % kVec)
+                    hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+                else
+                    hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+            }
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "consensus_partial_kernel");

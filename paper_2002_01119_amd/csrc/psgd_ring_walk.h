@@ -20,7 +20,7 @@ namespace {
 // faster than the same bytes arriving wavefront by wavefront.  Every lane of the workgroup therefore
 // walks the ring the same number of times; a lane without a column group of its own (c.lo == c.hi,
 // ragged end of the row) shadows a valid group with its loads and stores nothing.
-template <typename GT, bool CD>
+template <typename GT, bool CD, bool RAGGED>
 __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* __restrict__ gc,
                                           const RingEnt* ring, int n, Pitch ld, float neg_lr,
                                           ColStats& stats, const ColGroup& c) {
@@ -44,7 +44,7 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const V out = mix_one(e[u].w0, e[u].w1, e[u].w2, cur, prev, xs[u], gs[u], neg_lr);
-            st_cols(oc + (int64_t)e[u].row * ld.o, out, c);
+            st_cols_of<RAGGED>(oc + (int64_t)e[u].row * ld.o, out, c);
             if (CD) stats.add(out);
             prev = cur;
             cur = xs[u];
@@ -69,7 +69,7 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
         for (int u = 0; u < kUnroll; ++u) {
             if (p + u < n) {
                 const V out = mix_one(e[u].w0, e[u].w1, e[u].w2, cur, prev, xs[u], gs[u], neg_lr);
-                st_cols(oc + (int64_t)e[u].row * ld.o, out, c);
+                st_cols_of<RAGGED>(oc + (int64_t)e[u].row * ld.o, out, c);
                 if (CD) stats.add(out);
                 prev = cur;
                 cur = xs[u];
@@ -85,7 +85,8 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 // same number of sweeps, lanes beyond the chunk idle.
 // A table that is not one ring is left to the tiled kernel, which the launcher enqueues right behind this one and which
 // classifies the table the same way; this kernel then writes nothing.
-template <typename GT, bool CD>
+// RAGGED: 4 does not divide d.
+template <typename GT, bool CD, bool RAGGED>
 __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                                    const int32_t* __restrict__ nbr,
                                                                    const float* __restrict__ w, int n, int64_t d, Pitch ld,
@@ -109,11 +110,11 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
             const int64_t base = sweeps.base(sw), cg = base + threadIdx.x;
             if (base >= ncg) break;                              // nothing left for this workgroup (uniform)
             const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
-            const ColGroup c = col_group(cg < end ? cg : ncg, d);   // an idle lane owns nothing and shadows the last group
+            const ColGroup c = col_group_of<RAGGED>(cg < end ? cg : ncg, ncg, d);   // an idle lane owns nothing and shadows another
             ColStats stats;
             if (CD) stats.reset();
-            ring_walk<GT, CD>(X + c.col, Xout + c.col, G + c.col, l.ring, n, ld, neg_lr, stats, c);
-            if (CD) total += stats.result(inv_n, c);
+            ring_walk<GT, CD, RAGGED>(X + c.col, Xout + c.col, G + c.col, l.ring, n, ld, neg_lr, stats, c);
+            if (CD) total += stats.result<RAGGED>(inv_n, c);
         }
     }
     if (CD) {

@@ -32,47 +32,8 @@ namespace {
 // rows comes after the loop.
 //
 // The distance (CD): every lane measures its outputs against its first one, in fp64, and the row groups' sums meet in
-// LDS, where they are brought to row group 0's pivot exactly (short_merge).
+// LDS, where they are brought to row group 0's pivot exactly (row_group_merge).
 // ---------------------------------------------------------------------------------------
-// The column sums a_q of the row groups, each against its own pivot p_q, to the squares about the column's mean: with
-// P = p_0, D_q = p_q - P and m_q rows in group q,
-//     sum_i (o_i - P)   = sum_q (a_q + m_q D_q)
-//     sum_i (o_i - P)^2 = sum_q (sq_q + 2 D_q a_q + m_q D_q^2)
-// exactly; in fp64 the corrections are of the size of the sums themselves, as every pivot is one of the outputs, and
-// equal outputs give exactly 0.  The lanes of a wavefront read neighbouring columns of 64 / L row groups (L columns
-// side by side), so that few columns occupy many lanes; these shares are added by a symmetric exchange.
-// sums, pivots: [4][nrg][C].  live(k, l): whether column k of lane l exists.  Returns this lane's part of the total.
-template <typename LIVE>
-__device__ __forceinline__ double short_merge(const double* sums, const float* pivots, int logc, int nrg, int n, int T,
-                                              double inv_n, const LIVE& live) {
-    const int C = 1 << logc, most = nrg >= 8 ? 4 : 6;
-    const int logl = logc < most ? logc : most, parts = 64 >> logl;
-    const int each = n / nrg, more = n % nrg;                   // rows of group q: each, one more if q < more
-    double total = 0.0;
-    for (int idx = threadIdx.x; idx < 4 * C * parts; idx += T) {
-        const int part = (idx >> logl) & (parts - 1);
-        const int col = (idx >> 6 << logl) + (idx & ((1 << logl) - 1));
-        const int k = col >> logc, l = col & (C - 1);
-        const size_t at0 = ((size_t)k * nrg << logc) + l;
-        const double p0 = (double)pivots[at0];
-        double at = 0.0, corr = 0.0;
-#pragma unroll 4
-        for (int q = part; q < nrg; q += parts) {
-            const double aq = sums[at0 + ((size_t)q << logc)];
-            const double dq = (double)pivots[at0 + ((size_t)q << logc)] - p0;
-            const double tq = fma((double)(each + (q < more ? 1 : 0)), dq, aq);
-            at += tq;
-            corr = fma(dq, tq + aq, corr);
-        }
-        for (int off = 1 << logl; off < 64; off <<= 1) {
-            at += __shfl_xor(at, off, 64);
-            corr += __shfl_xor(corr, off, 64);
-        }
-        if (part == 0 && live(k, l)) total += corr - at * at * inv_n;
-    }
-    return total;
-}
-
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (twice the rows per lane: nothing is loaded ahead,
 // so their registers hold rows).  FEW: rows of fewer than four columns.
 template <typename GT, bool CD, int DEG, int R, bool ONE, bool FEW>
@@ -229,14 +190,8 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
             }
         }
         lds_barrier();                                          // the tile is free again; the sums are complete
-        if (CD && nrg > 1) {
-            const int64_t first = (t - (FULL ? step : 0)) * C;  // t is already the next tile's in the loop
-            total += short_merge(sums, pivots, logc, nrg, n, T, inv_n, [&](int k, int l) {
-                if (FULL) return true;
-                const ColGroup c = col_group(first + l, d);
-                return k >= c.lo && k < c.hi;
-            });
-        }
+        if (CD && nrg > 1)                                      // t is already the next tile's in the loop
+            total += row_group_merge<FULL>(sums, pivots, logc, nrg, n, T, inv_n, (t - (FULL ? step : 0)) * C, d);
     };
     while (!ONE && t < nfull) {
         t += step;
@@ -246,14 +201,8 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
     }
     if (t < ntiles) one_tile(std::false_type{}, cg);
     if (CD) {
-        total = wave_sum(total);
-        if ((tid & 63) == 0) lds_waves[tid >> 6] = total;
-        lds_barrier();
-        if (tid == 0) {
-            double r = 0.0;
-            for (int i = 0; i < T / 64; ++i) r += lds_waves[i];
-            partials[blockIdx.x] = r;
-        }
+        const double bs = block_sum_any(total, lds_waves, T);
+        if (tid == 0) partials[blockIdx.x] = bs;
     }
 }
 

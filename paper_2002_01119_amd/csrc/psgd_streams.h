@@ -27,8 +27,8 @@ __device__ __forceinline__ f32x4 mean_of(const double* s, double inv_n) {
 
 // T = workgroup size, chosen as for the ring step: on long rows a large workgroup whose wavefronts
 // sweep the rows in lockstep (a barrier per batch), so each row sees one long contiguous burst.
-// FEW: rows of fewer than four columns.
-template <typename GT, bool CD, int T, bool FEW>
+// RAGGED: 4 does not divide d.
+template <typename GT, bool CD, int T, bool RAGGED>
 __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout, const GT* __restrict__ G, int n,
                                                      int64_t d, Pitch ld, float neg_lr, Sweeps sweeps,
                                                      double* __restrict__ partials) {
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
         const int64_t base = sweeps.base(sw), cg = base + threadIdx.x;
         if (base >= ncg) break;                                  // nothing left for this workgroup (uniform)
         const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
-        const ColGroup c = col_group(cg < end ? cg : ncg, d);    // an idle lane owns nothing and shadows the last group
+        const ColGroup c = col_group_of<RAGGED>(cg < end ? cg : ncg, ncg, d);   // an idle lane owns nothing and shadows another
         const float* xc = X + c.col;
         const GT* gc = G + c.col;
         float* oc = Xout + c.col;
@@ -53,11 +53,11 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
             lockstep_barrier();
             V xs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)(r + u) * ld.x, d);
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_x(xc + (int64_t)(r + u) * ld.x);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) add_to(sum, xs[u]);
         }
-        for (; r < n; ++r) add_to(sum, ld_cols<FEW>(xc + (int64_t)r * ld.x, d));
+        for (; r < n; ++r) add_to(sum, ld_x(xc + (int64_t)r * ld.x));
         const V mean = mean_of(sum, inv_n);
         ColStats stats;
         if (CD) stats.reset();
@@ -66,20 +66,20 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
             lockstep_barrier();
             V gs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) gs[u] = widen_g(ld_cols_raw<FEW>(gc + (int64_t)(r + u) * ld.g, d));
+            for (int u = 0; u < kUnroll; ++u) gs[u] = ld_g(gc + (int64_t)(r + u) * ld.g);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const V out = vfma(neg_lr, gs[u], mean);
-                st_cols(oc + (int64_t)(r + u) * ld.o, out, c);
+                st_cols_of<RAGGED>(oc + (int64_t)(r + u) * ld.o, out, c);
                 if (CD) stats.add(out);
             }
         }
         for (; r < n; ++r) {
-            const V out = vfma(neg_lr, widen_g(ld_cols_raw<FEW>(gc + (int64_t)r * ld.g, d)), mean);
-            st_cols(oc + (int64_t)r * ld.o, out, c);
+            const V out = vfma(neg_lr, ld_g(gc + (int64_t)r * ld.g), mean);
+            st_cols_of<RAGGED>(oc + (int64_t)r * ld.o, out, c);
             if (CD) stats.add(out);
         }
-        if (CD) total += stats.result(inv_n, c);
+        if (CD) total += stats.result<RAGGED>(inv_n, c);
     }
     if (CD) {
         const double bs = block_sum<T>(total, lds_waves);
@@ -87,8 +87,99 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
     }
 }
 
+// The same where the columns alone do not fill the chip: a tile is all n rows x C column groups on nrg row groups of C
+// lanes, as in the short-row kernel; a lane sums rows rg, rg + nrg, ... of its column group, the row groups' sums meet
+// in LDS and the mean comes back through it.  The first eight gradient rows travel beside the first X rows.  Every X
+// row of the tile has been read before its first output is stored, so X_out may alias X.
+// FEW: rows of fewer than four columns.
+template <typename GT, bool CD, bool FEW>
+__global__ __launch_bounds__(plan::kShortThreads, 4) void mix_full_rows_kernel(const float* X, float* Xout,
+                                                                               const GT* __restrict__ G, int n, int64_t d,
+                                                                               Pitch ld, float neg_lr, int logc, int nrg,
+                                                                               double* __restrict__ partials) {
+    typedef typename RawG<GT>::T GR;
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    __shared__ double lds_waves[plan::kShortThreads / 64];
+    const int T = nrg << logc, C = 1 << logc, tid = threadIdx.x, lane = tid & (C - 1);
+    int rg = tid >> logc;
+    double* sums = reinterpret_cast<double*>(lds_raw);             // [4][nrg][C]
+    float* means = reinterpret_cast<float*>(sums + 4 * T);         // [4][C]
+    float* pivots = means + 4 * C;                                 // [4][nrg][C], CD only
+    const double inv_n = 1.0 / (double)n;
+    const int64_t ntiles = (((d + 3) >> 2) + C - 1) >> logc;
+    double total = 0.0;
+    for (int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds); t < ntiles; t += gridDim.x) {
+        asm volatile("" : "+v"(rg));                             // row offsets are computed again, not kept in registers
+        const ColGroup c = col_group(t * C + lane, d);
+        const float* xc = X + c.col;
+        const GT* gc = G + c.col;
+        float* oc = Xout + c.col;
+        f32x4 xs[kUnroll];
+        GR gs[kUnroll];
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)row_or_last(rg + u * nrg, n) * ld.x, d);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) gs[u] = ld_cols_raw<FEW>(gc + (int64_t)row_or_last(rg + u * nrg, n) * ld.g, d);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            if (rg + u * nrg < n) add_to(sum, xs[u]);
+        for (int r = rg + kUnroll * nrg; r < n; r += kUnroll * nrg) {
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)row_or_last(r + u * nrg, n) * ld.x, d);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+                if (r + u * nrg < n) add_to(sum, xs[u]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sums[((k * nrg + rg) << logc) + lane] = sum[k];
+        lds_barrier();                                           // also: every X row of the tile has arrived
+        row_group_columns(logc, nrg, T, [&](int k, int l, int first, int step, int reach) {
+            double at = 0.0;
+#pragma unroll 4
+            for (int q = first; q < nrg; q += step) at += sums[((k * nrg + q) << logc) + l];
+            for (int off = reach; off < 64; off <<= 1) at += __shfl_xor(at, off, 64);
+            if (first == 0) means[(k << logc) + l] = (float)(at * inv_n);
+        });
+        lds_barrier();
+        const f32x4 mean = {means[lane], means[C + lane], means[2 * C + lane], means[3 * C + lane]};
+        asm volatile("" : "+v"(rg));
+        f32x4 pv;
+        double a[4] = {0.0, 0.0, 0.0, 0.0}, sq[4] = {0.0, 0.0, 0.0, 0.0};
+        auto put = [&](int r, GR g, bool first) __attribute__((always_inline)) {
+            const f32x4 out = vfma(neg_lr, widen_g(g), mean);
+            if (CD && first) pv = out;
+            if (r < n) {
+                st_cols(oc + (int64_t)r * ld.o, out, c);
+                if (CD && !first) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const double df = (double)out[k] - (double)pv[k];
+                        a[k] += df;
+                        sq[k] = fma(df, df, sq[k]);
+                    }
+                }
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) put(rg + u * nrg, gs[u], u == 0);
+        for (int r = rg + kUnroll * nrg; r < n; r += kUnroll * nrg) {
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) gs[u] = ld_cols_raw<FEW>(gc + (int64_t)row_or_last(r + u * nrg, n) * ld.g, d);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) put(r + u * nrg, gs[u], false);
+        }
+        if (CD) total += row_group_distance(sums, pivots, logc, nrg, n, T, rg, lane, inv_n, a, sq, pv, c, t * C, d);
+        lds_barrier();                                           // the merge slots are free again
+    }
+    if (CD) {
+        const double bs = block_sum_any(total, lds_waves, T);
+        if (tid == 0) partials[blockIdx.x] = bs;
+    }
+}
+
 // Consensus-distance kernels (the per-column arithmetic is defined above the ring walk).
-template <bool FEW>
+template <bool RAGGED>
 __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float* __restrict__ X, int n,
                                                                      int64_t d, int64_t ldx,
                                                                      double* __restrict__ partials) {
@@ -99,17 +190,17 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
     for (int64_t cg = (int64_t)blockIdx.x * kThreads + threadIdx.x; cg < ncg; cg += stride) {
-        const ColGroup c = col_group(cg, d);
+        const ColGroup c = col_group_of<RAGGED>(cg, ncg, d);
         const float* xc = X + c.col;
         double s[kVec], a[kVec], b[kVec];
-        pivot_of(ld_cols<FEW>(xc, d), s);
+        pivot_of(ld_x(xc), s);
 #pragma unroll
         for (int k = 0; k < kVec; ++k) a[k] = b[k] = 0.0;
         int r = 1;
         for (; r + kUnroll <= n; r += kUnroll) {
             V xs[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)(r + u) * ldx, d);
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) acc_diff(a, b, xs[u], s);
         }
@@ -117,17 +208,54 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float
             V xs[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
-                if (r + u < n) xs[u] = ld_cols<FEW>(xc + (int64_t)(r + u) * ldx, d);
+                if (r + u < n) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
                 if (r + u < n) acc_diff(a, b, xs[u], s);
         }
 #pragma unroll
         for (int k = 0; k < kVec; ++k)
-            if (k >= c.lo && k < c.hi) total += b[k] - a[k] * a[k] * inv_n;
+            if (!RAGGED || k >= c.lo) total += b[k] - a[k] * a[k] * inv_n;
     }
     const double bs = block_sum(total, lds4);
     if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+}
+
+// The same where the columns alone do not fill the chip: rows spread over row groups of lanes as in the short-row kernel.
+template <bool FEW>
+__global__ __launch_bounds__(plan::kShortThreads, 4) void consensus_rows_kernel(const float* __restrict__ X, int n, int64_t d,
+                                                                                int64_t ldx, int logc, int nrg,
+                                                                                double* __restrict__ partials) {
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    __shared__ double lds_waves[plan::kShortThreads / 64];
+    const int T = nrg << logc, C = 1 << logc, tid = threadIdx.x, lane = tid & (C - 1), rg = tid >> logc;
+    double* sums = reinterpret_cast<double*>(lds_raw);             // [4][nrg][C]
+    float* pivots = reinterpret_cast<float*>(sums + 4 * T);        // the same
+    const double inv_n = 1.0 / (double)n;
+    const int64_t ntiles = (((d + 3) >> 2) + C - 1) >> logc;
+    double total = 0.0;
+    for (int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds); t < ntiles; t += gridDim.x) {
+        const ColGroup c = col_group(t * C + lane, d);
+        const float* xc = X + c.col;
+        f32x4 pv;
+        double s[4], a[4] = {0.0, 0.0, 0.0, 0.0}, sq[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int r = rg; r == rg || r < n; r += kUnroll * nrg) {   // a row group without rows still has a pivot
+            f32x4 xs[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) xs[u] = ld_cols<FEW>(xc + (int64_t)row_or_last(r + u * nrg, n) * ldx, d);
+            if (r == rg) {
+                pv = xs[0];
+                pivot_of(pv, s);
+            }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+                if (r + u * nrg < n) acc_diff(a, sq, xs[u], s);
+        }
+        total += row_group_distance(sums, pivots, logc, nrg, n, T, rg, lane, inv_n, a, sq, pv, c, t * C, d);
+        lds_barrier();                                           // the merge slots are free again
+    }
+    const double bs = block_sum_any(total, lds_waves, T);
+    if (tid == 0) partials[blockIdx.x] = bs;
 }
 
 // The same distance for long rows, in the form of the step kernels: one large workgroup per compute unit whose

@@ -186,6 +186,21 @@ int main() {
                             const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
                             CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
                         }
+    // global averaging and the distance with rows spread over lanes
+    for (int n : {1, 2, 9, 16, 17, 33, 64, 128, 300, 512})
+        for (int64_t ncg : {1, 2, 63, 65, 1500, 15000, 32767, 32768, 250000})
+            for (int cus : {1, 256})
+                for (int rows : {8, 16}) {
+                    const RowsPlan p = rows == 8 ? rows_plan(n, ncg, cus, 1024, 8, 9) : rows_plan(n, ncg, cus, 512, 16, 48);
+                    if (p.threads == 0) {
+                        CHECK(ncg > 1, "one column group has no lane-per-column form");
+                        continue;
+                    }
+                    CHECK(p.threads % 64 == 0 && p.threads >= 64 && p.threads <= 1024 && p.threads == p.nrg << p.logc && p.nrg >= 1,
+                          "rows n=%d ncg=%lld: %d lanes", n, (long long)ncg, p.threads);
+                    CHECK(p.tiles << p.logc >= ncg && (p.tiles - 1) << p.logc < ncg, "rows: %lld tiles", (long long)p.tiles);
+                    CHECK(p.threads * 48 + (16 << p.logc) <= 65280, "rows: LDS");
+                }
     if (failures) return 1;
     std::printf("launch plan ok\n");
     return 0;

@@ -85,6 +85,36 @@ def test_short_rows_every_element(psgd, n, d, deg, gkind, extra):
     assert psgd.device_status() == 0
 
 
+@pytest.mark.parametrize("n,d,gkind,extra", [
+    (1, 1, "f32", None), (512, 2, "bf16", (1, 2, 3)), (70, 3, "f32", (1, 0, 2)), (9, 5, "bf16", None),
+    (512, 6_001, "f32", (1, 2, 3)), (64, 100_002, "bf16", None), (33, 70_001, "f32", (3, 1, 1)), (17, 10_003, "bf16", (1, 1, 1)),
+    (300, 60_003, "f32", None), (512, 131_071, "bf16", None), (130, 131_075, "f32", (1, 2, 3)), (16, 200_001, "f32", None)])
+def test_global_average_and_distance_with_rows_spread_over_lanes(psgd, n, d, gkind, extra):
+    """psgd_mix_full and the stand-alone distance where the columns alone do not fill the chip, either side of that line."""
+    X = inp.host_normal_f32((n, d), 1.0, 41 + n) + np.float32(100.0)
+    G = inp.host_normal_f32((n, d), 0.5, 43 + n)
+    if gkind == "bf16":
+        G = inp.f32_to_bf16_bits(G)
+    ex, eo, eg = extra or (0, 0, 0)
+    Xd, Gd = _strided(X, ex, 1 if extra else 0), _strided(G.view(np.int16) if gkind == "bf16" else G, eg, 0)
+    c = torch.full((3,), float("nan"), dtype=torch.float64, device="cuda:0")
+    Y, Z = (_strided(np.zeros((n, d), np.float32), eo, 0) for _ in range(2))
+    psgd.consensus_dist_async(Xd, c[0:1])
+    psgd.mix_full(Xd, Y, Gd, 0.2, cdist_out=c[1:2])
+    psgd.mix_full(Xd, Z, Gd, 0.2)
+    psgd.mix_full(Xd, Xd, Gd, 0.2, cdist_out=c[2:3])
+    torch.cuda.synchronize()
+    got = Y.cpu().numpy()
+    G64 = orc.bf16_bits_to_f64(G) if gkind == "bf16" else G.astype(np.float64)
+    want = X.astype(np.float64).mean(0, keepdims=True) - np.float64(np.float32(0.2)) * G64
+    # the mean is rounded to fp32 once, then one fp32 rounding of the sum with the gradient term
+    assert np.abs(got - want).max() <= 2 * 2.0 ** -24 * (np.abs(want).max() + 1)
+    assert torch.equal(Z, Y) and torch.equal(Xd, Y)
+    for k, a in ((0, X), (1, got), (2, got)):
+        ref = orc.sparse_consensus_dist(a.astype(np.float64), threads=4)
+        assert abs(c[k].item() - ref) <= 1e-9 * ref + 1e-300, k
+
+
 def test_short_rows_touch_nothing_beside_their_columns(psgd):
     """A slice of wider arrays: the elements left and right of every written row stay as they are."""
     n, wide, off, d = 12, 5_003, 501, 1_003
