@@ -59,12 +59,15 @@ __device__ __forceinline__ f32x4 vfma(float a, f32x4 b, f32x4 c) {
 }
 
 // X, G and X_out are each touched once per step: mark the accesses non-temporal so they
-// stream through the caches instead of displacing one another.
-__device__ __forceinline__ f32x4 ld_x(const float* p) {
+// stream through the caches instead of displacing one another.  CACHED: without the hint, for launches where a line is
+// wanted again soon, by the neighbouring tile or by the next call (plan::cached_accesses).
+template <bool CACHED = false> __device__ __forceinline__ f32x4 ld_x(const float* p) {
+    if (CACHED) return *reinterpret_cast<const f32x4_any*>(p);
     return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
 }
-__device__ __forceinline__ void st_x(float* p, f32x4 v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(p));
+template <bool CACHED = false> __device__ __forceinline__ void st_x(float* p, f32x4 v) {
+    if (CACHED) *reinterpret_cast<f32x4_any*>(p) = v;
+    else __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(p));
 }
 
 // A gradient group as it arrives from memory, widened only where it is used: a value that is converted right
@@ -74,8 +77,9 @@ __device__ __forceinline__ void st_x(float* p, f32x4 v) {
 template <typename GT> struct RawG;
 template <> struct RawG<float> { typedef f32x4 T; };
 template <> struct RawG<uint16_t> { typedef u32x2 T; };
-__device__ __forceinline__ f32x4 ld_g_raw(const float* p) { return ld_x(p); }
-__device__ __forceinline__ u32x2 ld_g_raw(const uint16_t* p) {
+template <bool CACHED = false> __device__ __forceinline__ f32x4 ld_g_raw(const float* p) { return ld_x<CACHED>(p); }
+template <bool CACHED = false> __device__ __forceinline__ u32x2 ld_g_raw(const uint16_t* p) {
+    if (CACHED) return *reinterpret_cast<const u32x2_any*>(p);
     return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any*>(p));
 }
 __device__ __forceinline__ f32x4 widen_g(f32x4 v) { return v; }
@@ -106,13 +110,15 @@ __device__ __forceinline__ ColGroup col_group(int64_t cg, int64_t d) {
     return c;
 }
 // FEW: rows of fewer than four columns (d of them).
-template <bool FEW> __device__ __forceinline__ f32x4 ld_cols(const float* p, int64_t d) {
-    if (!FEW) return ld_x(p);
+template <bool FEW, bool CACHED = false> __device__ __forceinline__ f32x4 ld_cols(const float* p, int64_t d) {
+    if (!FEW) return ld_x<CACHED>(p);
     return (f32x4){p[0], d > 1 ? p[1] : 0.0f, d > 2 ? p[2] : 0.0f, 0.0f};
 }
-template <bool FEW> __device__ __forceinline__ f32x4 ld_cols_raw(const float* p, int64_t d) { return ld_cols<FEW>(p, d); }
-template <bool FEW> __device__ __forceinline__ u32x2 ld_cols_raw(const uint16_t* p, int64_t d) {
-    if (!FEW) return ld_g_raw(p);
+template <bool FEW, bool CACHED = false> __device__ __forceinline__ f32x4 ld_cols_raw(const float* p, int64_t d) {
+    return ld_cols<FEW, CACHED>(p, d);
+}
+template <bool FEW, bool CACHED = false> __device__ __forceinline__ u32x2 ld_cols_raw(const uint16_t* p, int64_t d) {
+    if (!FEW) return ld_g_raw<CACHED>(p);
     return (u32x2){(uint32_t)p[0] | (d > 1 ? (uint32_t)p[1] << 16 : 0u), d > 2 ? (uint32_t)p[2] : 0u};
 }
 // The same for kernels that are built apart for rows that 4 divides (RAGGED false), where a group is whole or none.
@@ -120,9 +126,9 @@ template <bool RAGGED> __device__ __forceinline__ ColGroup col_group_of(int64_t 
     if (RAGGED) return col_group(cg, d);
     return cg < ncg ? ColGroup{cg * 4, 0, 4} : ColGroup{0, 4, 4};
 }
-__device__ __forceinline__ void st_cols(float* p, f32x4 v, const ColGroup& c) {
+template <bool CACHED = false> __device__ __forceinline__ void st_cols(float* p, f32x4 v, const ColGroup& c) {
     if (c.lo == 0 && c.hi == 4) {
-        st_x(p, v);
+        st_x<CACHED>(p, v);
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k)

@@ -71,17 +71,19 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads) {
 }
 
 // Whether a 3-slot table on n rows of `ncg` column groups takes the ring walk (and the tiled kernel behind it) instead
-// of the short-row kernel, which serves any table at once.  The ring walk reads and writes 12 KB of a row at a time
-// whatever n is, but pays for classifying the table, for a second launch and for its sweeps; the short-row kernel's
-// row segments narrow as n grows (4096 / n lanes of 16 bytes).  In sweeps of one 768-lane workgroup per compute unit, us on
-// dense arrays with fp32 gradients and the distance, short-row kernel / ring walk:
-//   8 x 6.4 M 123 / 130, x 51.2 M 933 / 977;   16 x 6.4 M 241 / 246, x 12.8 M 477 / 473, x 51.2 M 1956 / 1891;
-//   64 x 1.6 M 246 / 250, x 3.2 M 489 / 486, x 25.6 M 3967 / 3834;   256 x 0.4 M 253 / 283, x 0.6 M 375 / 360,
-//   x 1.6 M 1054 / 970;   512 x 0.4 M 539 / 553, x 0.6 M 764 / 710.
+// of the short-row kernel, which serves any table at once.  The ring walk reads and writes up to 12 KB of a row at a
+// time whatever n is, but pays for classifying the table and for a second launch, and walks all rows one batch after
+// the other, which takes 0.4 us a row however few columns there are; the short-row kernel's row segments narrow as n
+// grows (4096 / n lanes of 16 bytes).  In sweeps of one 768-lane workgroup per compute unit; us on dense arrays with fp32
+// gradients, short-row kernel / ring walk:
+//   8 x 51.2 M 933 / 977;   16 x 2.5 M (3.2 sweeps) 90 / 96, x 7.5 M (9.5) 261 / 262, x 51.2 M 1956 / 1891;
+//   32 x 1.2 M (1.5) 100 / 93, x 2.4 M 169 / 170, x 25.6 M 1910 / 1906;   64 x 0.6 M (0.8) 94 / 95, x 1 M (1.3) 143 / 145,
+//   x 1.9 M (2.4) 285 / 262;   120 x 333 k (0.4) 105 / 101, x 1 M (1.3) 281 / 260;   200 x 200 k (0.25) 97 / 114, x 600 k (0.8)
+//   277 / 262;   512 x 78 k (0.1) 97 / 222, x 234 k (0.3) 333 / 261.  Rows that do not start on lines: the same line.
 inline bool ring_rows(int n, int64_t ncg, int cus, int threads) {
     if (n <= 8) return false;
     const int64_t sweep = (int64_t)cus * threads;
-    return ncg >= (n < 48 ? 12 * sweep : n < 96 ? 3 * sweep : sweep * 3 / 4);
+    return ncg * 4 >= (n < 29 ? 32 * sweep : n < 48 ? 6 * sweep : n < 96 ? 5 * sweep : n < 256 ? 8 * sweep / 5 : sweep);
 }
 
 // LDS of the tiled path (tables that are not one ring): the slot table (8 bytes per slot), TWO tile buffers of
@@ -168,8 +170,22 @@ inline ShortPlan short_widest(int n, int deg, int64_t ncg, bool cd, bool one, in
     }
     return p;
 }
-// Workgroups of the looping form: one per tile up to what is resident together (128 registers per lane: 1024 lanes per
-// compute unit), at most `most`.
+// Which accesses of the short-row kernel go without the non-temporal hint.  `bytes`: X, G and X_out together;
+// `on_lines`: every row of X and X_out starts on a 128-byte line.  (us, with the hint / without.)
+//   - Loads where all arrays together take up to half of the 256 MB last-level cache and a workgroup has several tiles:
+//     120 x 66 656 28.4 / 23.2, 24 x 333 312 23.1 / 20.5, 120 x 66 669 29.8 / 24.2 (stores too: 28.4); not beyond (192 MB, 16 x 1 M:
+//     35.2 / 36.2), nor with one tile each (64 x 100 k with bf16 gradients 11.2 / 11.6).
+//   - Loads and stores where rows are off the lines: neighbouring tiles share a line at every row's end, and a hinted line
+//     travels twice.  Up to 128 column groups wide: 512 x 78 125 166 / 117, 200 x 200 013 131 / 110, 64 x 1 874 989 325 / 301,
+//     24 x 5 000 013 287 / 280; wider tiles lose (16 x 2 500 013 94 / 97), as do rows on lines (512 x 78 112 97 / 103); one tile each, up
+//     to 16 wide: 512 x 15 629 30.2 / 25.7 (128 wide, 64 x 125 005: 22.9 / 23.6).
+enum { kCachedLoads = 1, kCachedStores = 2 };
+inline int cached_accesses(const ShortPlan& p, int64_t bytes, bool on_lines) {
+    if (!p.one && bytes <= (int64_t)128 << 20) return kCachedLoads;
+    return !on_lines && p.logc <= (p.one ? 4 : 7) ? kCachedLoads | kCachedStores : 0;
+}
+// Workgroups of the looping form: one per tile up to what is resident together (128 registers per lane at four rows:
+// 1024 lanes per compute unit), at most `most`.
 inline int short_grid(const ShortPlan& p, int cus, int64_t most) {
     int64_t per_cu = kShortThreads / p.threads;
     if (per_cu > (int64_t)(kShortLds / p.lds)) per_cu = kShortLds / p.lds;
@@ -234,7 +250,15 @@ inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, int64
         const ShortPlan p = short_widest(n, deg, ncg, cd, true, 256, kShortRowsOne);
         if (!cd || p.tiles <= slots) return p;
     }
-    return short_widest(n, deg, ncg, cd, false, kShortThreads, kShortRows);
+    // A lane without a row of its own repeats the last one, loads and stores alike: fewer rows per lane where that leaves
+    // fewer such places, unless the tile then narrows below a wavefront's 64 column groups (13 x 3.9 M, 16 places at four
+    // rows, 14 at two: 131 and 119 us; 200 x 250 k, 208 at four, 204 at three on half the width: 131 and 143).
+    ShortPlan best = short_widest(n, deg, ncg, cd, false, kShortThreads, kShortRows);
+    for (int rows = kShortRows - 1; rows >= 2; --rows) {
+        const ShortPlan p = short_widest(n, deg, ncg, cd, false, kShortThreads, rows);
+        if (p.nrg * p.rows < best.nrg * best.rows && (p.logc >= 6 || p.logc == best.logc)) best = p;
+    }
+    return best;
 }
 
 }  // namespace plan

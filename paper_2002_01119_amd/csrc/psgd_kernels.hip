@@ -278,15 +278,15 @@ inline bool long_rows(const DeviceInfo& di, int64_t column_groups, int sweeps = 
 
 // Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
 // negative status.
-template <typename GT, bool CD, int DEG, int R, bool ONE, bool FEW>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
 int launch_short_t(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
                    const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
                    int slots) {
-    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, FEW>);
+    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>);
     if (int rc = allow_lds(fn, p.lds)) return rc;
     const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? slots : INT32_MAX);
-    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X, X_out, G,
-                       nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
+    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X, X_out,
+                       G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
     return CD ? grid : 0;
 }
 
@@ -294,20 +294,38 @@ template <typename GT, bool CD, int DEG>
 int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
                  const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
                  int slots) {
-#define PSGD_SHORT(R, ONE, FEW) \
-    return launch_short_t<GT, CD, DEG, R, ONE, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots)
-    if (d < 4) return launch_short_t<GT, CD, 0, 2, true, true>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots);
+    const bool on_lines = aligned_to(X, 128) && aligned_to(X_out, 128) && ld.x % 32 == 0 && ld.o % 32 == 0;
+    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), on_lines);
+    constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
+#define PSGD_SHORT(DEG, R, ONE, CACHED, FEW)                                                                              \
+    return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots)
+#define PSGD_SHORT_ONE(R)                                                                                                 \
+    case R:                                                                                                               \
+        if (cached) PSGD_SHORT(DEG, R, true, kBoth, false);                                                               \
+        PSGD_SHORT(DEG, R, true, 0, false)
+#define PSGD_SHORT_LOOP(R)                                                                                                \
+    case R:                                                                                                               \
+        if (cached == kBoth) PSGD_SHORT(DEG, R, false, kBoth, false);                                                     \
+        if (cached) PSGD_SHORT(DEG, R, false, plan::kCachedLoads, false);                                                 \
+        PSGD_SHORT(DEG, R, false, 0, false)
+    if (d < kVec) PSGD_SHORT(0, 2, true, 0, true);
     if (p.one) {
-        if (p.rows == 2) PSGD_SHORT(2, true, false);
-        if (p.rows == 4) PSGD_SHORT(4, true, false);
-        if (p.rows == 6) PSGD_SHORT(6, true, false);
-        if (p.rows == 8) PSGD_SHORT(8, true, false);
+        switch (p.rows) {
+            PSGD_SHORT_ONE(2);
+            PSGD_SHORT_ONE(4);
+            PSGD_SHORT_ONE(6);
+            PSGD_SHORT_ONE(8);
+        }
     } else {
-        if (p.rows == 1) PSGD_SHORT(1, false, false);
-        if (p.rows == 2) PSGD_SHORT(2, false, false);
-        if (p.rows == 3) PSGD_SHORT(3, false, false);
-        if (p.rows == 4) PSGD_SHORT(4, false, false);
+        switch (p.rows) {
+            PSGD_SHORT_LOOP(1);
+            PSGD_SHORT_LOOP(2);
+            PSGD_SHORT_LOOP(3);
+            PSGD_SHORT_LOOP(4);
+        }
     }
+#undef PSGD_SHORT_LOOP
+#undef PSGD_SHORT_ONE
 #undef PSGD_SHORT
     return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
 }

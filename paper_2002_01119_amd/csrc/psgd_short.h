@@ -35,8 +35,9 @@ namespace {
 // LDS, where they are brought to row group 0's pivot exactly (row_group_merge).
 // ---------------------------------------------------------------------------------------
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (twice the rows per lane: nothing is loaded ahead,
-// so their registers hold rows).  FEW: rows of fewer than four columns.
-template <typename GT, bool CD, int DEG, int R, bool ONE, bool FEW>
+// so their registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
+// FEW: rows of fewer than four columns.
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
 __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
     const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
     int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
@@ -77,10 +78,11 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
         return r < n ? r : n - 1;
     };
     ColGroup cg = col_group(t * C + lane, d);
+    constexpr bool CL = (CACHED & plan::kCachedLoads) != 0, CS = (CACHED & plan::kCachedStores) != 0;
 #pragma unroll
-    for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW>(X + (int64_t)row_of(u) * ld.x + cg.col, d);
+    for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW, CL>(X + (int64_t)row_of(u) * ld.x + cg.col, d);
 #pragma unroll
-    for (int u = 0; u < R; ++u) g[u] = ld_cols_raw<FEW>(G + (int64_t)row_of(u) * ld.g + cg.col, d);
+    for (int u = 0; u < R; ++u) g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + cg.col, d);
     int bad = 0;
 #pragma unroll
     for (int i = 0; i < TE; ++i) {
@@ -119,7 +121,7 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
         if (FULL) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW>(X + (int64_t)row_of(u) * ld.x + next.col, d);
+            for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW, CL>(X + (int64_t)row_of(u) * ld.x + next.col, d);
         }
         // SB rows' slot chains advance together (a table read, then a tile read that depends on it, per slot).
         constexpr int SB = R < 4 ? R : 4;
@@ -159,10 +161,10 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
                 const f32x4 o = vfma(neg_lr, widen_g(g[u]), out[i]);
                 float* to = Xout + (int64_t)row_of(u) * ld.o + cg.col;
                 if (FULL) {
-                    st_x(to, o);
-                    g[u] = ld_cols_raw<FEW>(G + (int64_t)row_of(u) * ld.g + next.col, d);
+                    st_x<CS>(to, o);
+                    g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + next.col, d);
                 } else if (rg + u * nrg < n) {
-                    st_cols(to, o, cg);
+                    st_cols<CS>(to, o, cg);
                 }
                 if (CD && u == 0) pv = o;
                 if (CD && u > 0 && rg + u * nrg < n) {
