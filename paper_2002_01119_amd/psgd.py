@@ -119,24 +119,30 @@ def _check(rc):
 
 
 def _stream_handle(stream):
-    """hipStream_t of a torch stream (None = torch's current stream)."""
+    """hipStream_t of a torch stream (None = torch's current stream on the current GPU)."""
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # 0.1 us; building the Stream object takes 2.5
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _on_current_device(*tensors):
     """Every pointer handed to the library must be device memory of the CURRENT device: a host
     pointer or another GPU's would be dereferenced by a kernel."""
     import torch
-    if not torch.cuda.is_available():
-        raise ValueError("no GPU visible: the library works on device memory only")
-    cur = torch.cuda.current_device()
+    cur = -1
     for t in tensors:
         if t is None:
             continue
-        if not isinstance(t, torch.Tensor) or not t.is_cuda or t.device.index != cur:
+        if not isinstance(t, torch.Tensor) or not t.is_cuda:
+            raise ValueError("expected tensors on the current GPU" if torch.cuda.is_available() else
+                             "no GPU visible: the library works on device memory only")
+        if cur < 0:
+            cur = torch.cuda.current_device()
+        if t.get_device() != cur:
             raise ValueError("expected tensors on the current GPU (cuda:%d)" % cur)
 
 
@@ -148,10 +154,11 @@ def _rows_cols(t):
 
 def _rows_cols_pitch(t):
     """(n, d, pitch in elements) of a 2-D tensor whose rows are contiguous (stride(1) == 1)."""
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or (shape[1] > 1 and stride[1] != 1):
         raise ValueError("expected an [n, d] tensor with unit stride along d")
-    n, d = int(t.shape[0]), int(t.shape[1])
-    return n, d, (int(t.stride(0)) if n > 1 else d)
+    n, d = shape
+    return n, d, (stride[0] if n > 1 else d)
 
 
 def build_mixing(topology, n, seed=0, step=0):

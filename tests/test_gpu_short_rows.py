@@ -140,3 +140,24 @@ def test_short_rows_bad_table_writes_nothing(psgd):
         psgd.mix_step(X, Y, X.clone(), torch.from_numpy(nbr).to("cuda:0"), torch.from_numpy(w).to("cuda:0"), 0.1, cdist_out=c)
         assert psgd.device_status() == 1 and psgd.device_status() == 0
         assert bool((Y == 5.0).all()) and bool(torch.isnan(c).all())
+
+
+def test_consensus_dist_from_several_threads(psgd):
+    """The synchronous distance returns its own array's value, whichever thread asks and whatever other calls run."""
+    import threading
+    arrays = [torch.from_numpy(inp.host_normal_f32((n, d), s, 60 + n)).to("cuda:0") for n, d, s in ((8, 5000, 1.0), (64, 3001, 2.0), (17, 40_000, 3.0))]
+    want = [orc.consensus_dist(a.cpu().numpy()) for a in arrays]
+    got = [[] for _ in arrays]
+
+    def ask(k):
+        torch.cuda.set_device(0)
+        for _ in range(20):
+            got[k].append(psgd.consensus_dist(arrays[k]))
+
+    threads = [threading.Thread(target=ask, args=(k,)) for k in range(len(arrays))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    for k, w in enumerate(want):
+        assert len(got[k]) == 20 and max(abs(v - w) for v in got[k]) <= 1e-9 * w
