@@ -277,6 +277,11 @@ inline bool long_rows(const DeviceInfo& di, int64_t column_groups, int sweeps = 
     return column_groups >= (int64_t)di.cus * kRingThreads * sweeps;
 }
 
+// Every row of X and X_out starts on a 128-byte line.
+inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) {
+    return aligned_to(X, 128) && aligned_to(X_out, 128) && ld.x % 32 == 0 && ld.o % 32 == 0;
+}
+
 // Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
 // negative status.
 template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
@@ -295,8 +300,7 @@ template <typename GT, bool CD, int DEG>
 int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
                  const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
                  int slots) {
-    const bool on_lines = aligned_to(X, 128) && aligned_to(X_out, 128) && ld.x % 32 == 0 && ld.o % 32 == 0;
-    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), on_lines);
+    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld));
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
 #define PSGD_SHORT(DEG, R, ONE, CACHED, FEW)                                                                              \
     return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials, slots)
@@ -391,7 +395,12 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
     const int64_t ncg = (d + kVec - 1) / kVec;
-    const bool big = deg == 3 ? plan::ring_rows(n, ncg, di->cus, kRingThreads) : long_rows(*di, ncg);
+    // Tables of other slot counts: on long rows the tiled kernel is as good or a little better while its row segments are
+    // wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5 slots 76.6 / 76.0),
+    // else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001 838 / 1322, 300 x 1.6 M
+    // 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).
+    const bool big = deg == 3 ? plan::ring_rows(n, ncg, di->cus, kRingThreads)
+                              : long_rows(*di, ncg) && n > 8 && n <= 128 && rows_on_lines(X, X_out, ld);
     if (!big) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
                                          : plan::short_plan(n, deg, ncg, di->cus, want_cd, slots);
