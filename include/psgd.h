@@ -141,12 +141,12 @@ int psgd_mix_step_bf16g(const float* X, float* X_out, const uint16_t* G_bf16,
 /*
  * psgd_mix_step_cd / psgd_mix_step_cd_bf16g - the same fused step (Sec. 2, Eq. 2) that also
  * returns the consensus distance of its own output, sum_i || x_out_i - mean(x_out) ||^2 (the
- * quantity Sec. 3 bounds), without reading X_out back: the lane that produces all n rows of
- * a column group keeps their running sums.  X_out is bit-identical to psgd_mix_step's.
+ * quantity Sec. 3 bounds), without reading X_out back: the lanes that produce the rows of
+ * a column group keep their running sums.  X_out is bit-identical to psgd_mix_step's.
  *
  *   cdist_out  device, double[1], 8-byte aligned, written by work enqueued on `stream`; it
  *              must not overlap X, X_out or G.  NaN if the table held an out-of-range entry.
- * The per-column sums are taken against the column's first output in fp64 and the
+ * The per-column sums are taken against one of the column's outputs in fp64 and the
  * per-workgroup partials are combined in a fixed order (bit-reproducible; it agrees with
  * psgd_consensus_dist of X_out to rounding, about 1e-13 relative, not bit for bit).
  * Uses the same per-device buffer of partial sums as psgd_consensus_dist_async (allocated by
@@ -197,9 +197,9 @@ int psgd_mix_step_ex(const float* X, int64_t ldx, float* X_out, int64_t ldo,
  * is part of the library's device image, one copy per GPU, held until the process ends.  The
  * call makes no hipMalloc / hipFree and creates no event or stream.
  *
- * Limit: a launch uses one partial per persistent workgroup of its two kernels (the ring walk:
- * at most 4 per compute unit, 1024 on MI355X; the tiled kernel behind it takes what is left).
- * If the ring walk alone would need PSGD_STATIC_SLOTS or more the call fails with PSGD_EINVAL
+ * Limit: a launch uses one partial per workgroup.  Most shapes loop over their tiles within the
+ * array; the ring walk takes one workgroup per compute unit and the tiled kernel behind it what is
+ * left.  If the ring walk alone would need PSGD_STATIC_SLOTS or more the call fails with PSGD_EINVAL
  * and launches nothing.  n, d and the pitches are limited as in psgd_mix_step_ex.
  * Every call on a GPU uses that GPU's one array, which keeps the previous call's partials (each
  * launch overwrites the slots it reads, so nothing needs clearing).  Calls that overlap in time
@@ -218,8 +218,8 @@ int psgd_mix_step_cd_static(const float* X, int64_t ldx, float* X_out, int64_t l
  * learner, lazy walks, or the product of several mixing rounds collapsed into one matrix (the
  * remedy of the prior work the paper cites in Sec. 7).  1 <= deg <= PSGD_MAX_DEG and
  * n * deg <= PSGD_MAX_TABLE.  Per element: acc = w0 * x0; acc = fma(w_s, x_s, acc) for
- * s = 1..deg-1 in table order; out = fma(-lr, g, acc).  deg = 3 is psgd_mix_step_ex (ring
- * tables then take the register walk); other degrees always stage [n x columns] tiles in
+ * s = 1..deg-1 in table order; out = fma(-lr, g, acc).  deg = 3 is psgd_mix_step_ex (long
+ * ring tables then take the register walk); other degrees always stage [n x columns] tiles in
  * LDS.  Everything else (pitches, gradient type, in-place rule, cdist_out gathered in the same
  * pass, errors) is as in psgd_mix_step_ex.
  */
@@ -249,7 +249,7 @@ int psgd_mix_full(const float* X, int64_t ldx, float* X_out, int64_t ldo,
  *
  *   X  device, float [n * d] row-major, read.
  * Synchronous: waits for all work on the device, runs, waits again, returns the value.
- * Differences are taken against row 0 and accumulated in fp64; partial sums are combined
+ * Differences are taken against one of the rows and accumulated in fp64; partial sums are combined
  * in a fixed order, so the result is bit-reproducible.  Returns NaN on error (see
  * psgd_last_error()).  d = 0 or n = 1 gives 0.
  */

@@ -240,7 +240,7 @@ int allow_lds(const void* fn, size_t lds_bytes) {
         int device;
     };
     static std::mutex mu;
-    static Entry done[128];
+    static Entry done[512];
     static int used = 0;
     int device = 0;
     hipError_t e = hipGetDevice(&device);
@@ -251,7 +251,7 @@ int allow_lds(const void* fn, size_t lds_bytes) {
     // the most this library ever asks for (the kernels' few hundred bytes of static LDS come on top of it)
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCapLarge);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)");
-    if (used < 128) done[used++] = Entry{fn, device};
+    if (used < 512) done[used++] = Entry{fn, device};
     return PSGD_OK;
 }
 constexpr int kLaunchRefused = INT32_MIN;

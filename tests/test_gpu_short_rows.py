@@ -161,3 +161,44 @@ def test_consensus_dist_from_several_threads(psgd):
         t.join(60)
     for k, w in enumerate(want):
         assert len(got[k]) == 20 and max(abs(v - w) for v in got[k]) <= 1e-9 * w
+
+
+_FIRST_CALL = """
+import torch
+from paper_2002_01119_amd import psgd
+torch.cuda.set_device(0)
+X = torch.randn(8, 1_000_000, device="cuda:0")
+G = torch.randn(8, 1_000_000, device="cuda:0")
+Y, Z, U = (torch.empty_like(X) for _ in range(3))
+c = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+nbr, w = (torch.from_numpy(a).to("cuda:0") for a in psgd.build_mixing(psgd.TOPO_RAND_RING, 8, 1, 2))
+torch.cuda.synchronize()
+g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+with torch.cuda.graph(g, stream=s):                     # the first call of the process, with more than 64 KB of LDS
+    psgd.mix_step(X, Y, G, nbr, w, 0.1)
+    psgd.mix_step_cd_static(Y, Z, G, nbr, w, 0.1, c)
+    psgd.mix_full(Z, U, G, 0.1)
+got = []
+for _ in range(3):
+    for t in (Y, Z, U):
+        t.fill_(float("nan"))
+    g.replay()
+    torch.cuda.synchronize()
+    got.append([t.clone() for t in (Y, Z, U, c)])
+psgd.mix_step(X, Y, G, nbr, w, 0.1)
+psgd.mix_step_cd_static(Y, Z, G, nbr, w, 0.1, c)
+psgd.mix_full(Z, U, G, 0.1)
+torch.cuda.synchronize()
+assert all(torch.equal(a, b) for r in got for a, b in zip(r, (Y, Z, U, c))) and psgd.device_status() == 0
+print("captured first calls match")
+"""
+
+
+def test_first_calls_of_a_process_under_capture(psgd):
+    """Nothing these calls do once per process or kernel is forbidden while a stream is being captured."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _FIRST_CALL], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "match" in r.stdout, r.stderr[-2000:]
