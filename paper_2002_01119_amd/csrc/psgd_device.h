@@ -325,15 +325,18 @@ __device__ __forceinline__ void floats_of(f32x4 x, float* f) {
 }
 
 // Running sums of one lane's column group; the first value it is given becomes the pivot (kept as
-// the fp32 value it is).
+// the fp32 value it is).  Unless the group may be owned in part (RAGGED) the squares of its columns share one
+// accumulator: only their total is needed, and registers decide how many wavefronts of a kernel on another stream
+// find room beside the step (delay-by-one pair of 128 x 8 M: 4.96 ms, with four accumulators 4.99).
+template <bool RAGGED>
 struct ColStats {
     f32x4 s;
-    double a[4], sq[4];
+    double a[4], sq[RAGGED ? 4 : 1];
     int have;
     __device__ __forceinline__ void reset() {
         have = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) a[k] = sq[k] = 0.0;
+        for (int k = 0; k < 4; ++k) a[k] = sq[RAGGED ? k : 0] = 0.0;
     }
     __device__ __forceinline__ void add(f32x4 x) {
         if (!have) {
@@ -344,20 +347,19 @@ struct ColStats {
             for (int k = 0; k < 4; ++k) {
                 const double df = (double)x[k] - (double)s[k];
                 a[k] += df;
-                sq[k] = fma(df, df, sq[k]);
+                sq[RAGGED ? k : 0] = fma(df, df, sq[RAGGED ? k : 0]);
             }
         }
     }
     // over the columns the lane owns
-    template <bool RAGGED> __device__ __forceinline__ double result(double inv_n, const ColGroup& c) const {
-        double t = 0.0;
+    __device__ __forceinline__ double result(double inv_n, const ColGroup& c) const {
+        double t = RAGGED ? 0.0 : sq[0];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (!RAGGED || (k >= c.lo && k < c.hi)) t += sq[k] - a[k] * a[k] * inv_n;
+            if (!RAGGED || (k >= c.lo && k < c.hi)) t += (RAGGED ? sq[RAGGED ? k : 0] : 0.0) - a[k] * a[k] * inv_n;
         return RAGGED || c.lo == 0 ? t : 0.0;
     }
 };
-
 
 // ---------------------------------------------------------------------------------------
 // Tiles whose rows are spread over row groups: T = nrg * C lanes, C = 1 << logc column groups wide, lane (rg, lane) sees

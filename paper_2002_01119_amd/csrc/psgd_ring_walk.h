@@ -23,7 +23,7 @@ namespace {
 template <typename GT, bool CD, bool RAGGED>
 __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* __restrict__ gc,
                                           const RingEnt* ring, int n, Pitch ld, float neg_lr,
-                                          ColStats& stats, const ColGroup& c) {
+                                          ColStats<RAGGED>& stats, const ColGroup& c) {
     typedef f32x4 V;
     const V first = ld_x(xc + (int64_t)ring_row(ring) * ld.x);
     const V last = (n > 1) ? ld_x(xc + (int64_t)ring_row(ring + n - 1) * ld.x) : first;
@@ -111,10 +111,10 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
             if (base >= ncg) break;                              // nothing left for this workgroup (uniform)
             const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
             const ColGroup c = col_group_of<RAGGED>(cg < end ? cg : ncg, ncg, d);   // an idle lane owns nothing and shadows another
-            ColStats stats;
+            ColStats<RAGGED> stats;
             if (CD) stats.reset();
             ring_walk<GT, CD, RAGGED>(X + c.col, Xout + c.col, G + c.col, l.ring, n, ld, neg_lr, stats, c);
-            if (CD) total += stats.result<RAGGED>(inv_n, c);
+            if (CD) total += stats.result(inv_n, c);
         }
     }
     if (CD) {

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
         }
         for (; r < n; ++r) add_to(sum, ld_x(xc + (int64_t)r * ld.x));
         const V mean = mean_of(sum, inv_n);
-        ColStats stats;
+        ColStats<RAGGED> stats;
         if (CD) stats.reset();
         r = 0;
         for (; r + kUnroll <= n; r += kUnroll) {
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
             st_cols_of<RAGGED>(oc + (int64_t)r * ld.o, out, c);
             if (CD) stats.add(out);
         }
-        if (CD) total += stats.result<RAGGED>(inv_n, c);
+        if (CD) total += stats.result(inv_n, c);
     }
     if (CD) {
         const double bs = block_sum<T>(total, lds_waves);
