@@ -137,6 +137,9 @@ constexpr int kShortThreads = 1024;      // most lanes of its workgroups
 constexpr int kShortRows = 4;            // most rows per lane where the next tile's rows are loaded ahead,
 constexpr int kShortRowsOne = 8;         // and where a workgroup has one tile: what 128 registers hold in flight
 constexpr size_t kShortLds = 160 * 1024 - 2048;
+// A launch counts its lanes in 32 bits: one row of 2^34 columns at a tile per workgroup would be more than that (and would
+// still fit the device).  Beyond these tiles the looping form, whose grid does not grow with the row.
+constexpr int64_t kShortMostTiles = (int64_t)1 << 22;   // times up to 256 lanes
 struct ShortPlan {
     bool one;                            // a tile per workgroup
     int threads, rows, logc, nrg;
@@ -236,7 +239,7 @@ inline RowsPlan rows_plan(int n, int64_t ncg, int cus, int most_threads, int row
 //     17.9 against 21.2.  The widest workgroup that still occupies more than half of the compute units: 16 x 250 k at
 //     512 lanes (245 tiles) 12.4, at 1024 (123 tiles) 15.2;
 //   - up to 8 learners beyond that: a lane holds all rows of its columns, nothing is exchanged and small independent
-//     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2;
+//     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2; up to kShortMostTiles of them;
 //   - all else: 1024 lanes, four rows each, the next tile's loads ahead: 512 x 60 k 77.6 us, at 512 lanes 107;
 //     64 x 1 M with bf16 gradients 126 against 130.
 // `slots`: with the distance, the most workgroups.
@@ -248,7 +251,7 @@ inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, int64
     }
     if (n <= kShortRowsOne) {
         const ShortPlan p = short_widest(n, deg, ncg, cd, true, 256, kShortRowsOne);
-        if (!cd || p.tiles <= slots) return p;
+        if (p.tiles <= (cd ? slots : kShortMostTiles)) return p;
     }
     // A lane without a row of its own repeats the last one, loads and stores alike: fewer rows per lane where that leaves
     // fewer such places, unless the tile then narrows below a wavefront's 64 column groups (13 x 3.9 M, 16 places at four

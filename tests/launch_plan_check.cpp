@@ -186,6 +186,15 @@ int main() {
                             const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
                             CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
                         }
+    // a launch holds fewer than 2^32 lanes, also on the longest rows that fit a device (one learner of 18e9 columns and more)
+    for (int n : {1, 2, 3, 8, 9, 64})
+        for (int64_t ncg : {(int64_t)1 << 22, (int64_t)1 << 30, ((int64_t)1 << 32) + 3, (int64_t)4500000001, (int64_t)1 << 34})
+            for (bool cd : {false, true}) {
+                const ShortPlan p = short_plan(n, 3, ncg, 256, cd, kMaxGrid);
+                const int64_t grid = p.one ? p.tiles : short_grid(p, 256, cd ? kMaxGrid : INT32_MAX);
+                CHECK(grid >= 1 && grid * p.threads < (int64_t)1 << 32, "short rows n=%d ncg=%lld: %lld workgroups of %d lanes", n,
+                      (long long)ncg, (long long)grid, p.threads);
+            }
     // global averaging and the distance with rows spread over lanes
     for (int n : {1, 2, 9, 16, 17, 33, 64, 128, 300, 512})
         for (int64_t ncg : {1, 2, 63, 65, 1500, 15000, 32767, 32768, 250000})
