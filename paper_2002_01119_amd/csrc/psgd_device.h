@@ -223,9 +223,9 @@ enum TableKind { kTableBad = 0, kTableRing = 1, kTableGeneral = 2 };
 // bijection, and following it from learner 0 visits all n learners.  The last property is
 // decided by parallel list ranking (pointer doubling) toward learner 0's left neighbour;
 // the resulting distances are the ring positions, used to fill `ring` in walk order.
-template <int T>
-__device__ int stage_table(const int32_t* __restrict__ nbr, const float* __restrict__ w, int n,
-                           const Lds& l) {
+// T: lanes of the workgroup.
+__device__ __forceinline__ int stage_table(const int32_t* __restrict__ nbr, const float* __restrict__ w, int n, const Lds& l,
+                                           int T) {
     const int tid = threadIdx.x;
     int ok = 1;
     for (int e = tid; e < 3 * n; e += T) {

@@ -70,6 +70,15 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads) {
     return s;
 }
 
+// Lanes of the ring walk's workgroups: all of `threads`, but no wavefront without columns where the row takes one sweep.
+// Such a wavefront walks the ring with the others, shadowing a column group: its loads and the barriers it takes part in
+// cost more than it hides, and beside another stream's kernel its registers are missing there (us, with / without: with the
+// distance 256 x 235 k 157 / 137, 512 x 234 k 310 / 267, 128 x 354 k 111 / 105; delay-by-one pair of 200 x 400 k 404 / 371).  Two
+// sweeps and more: all lanes (128 x 1.02 M 289 / 294).
+inline int ring_threads(const SweepPlan& s, int threads) {
+    return s.count > 1 ? threads : (int)((s.chunk + 63) / 64 * 64);
+}
+
 // Whether a 3-slot table on n rows of `ncg` column groups takes the ring walk (and the tiled kernel behind it) instead
 // of the short-row kernel, which serves any table at once.  The ring walk reads and writes up to 12 KB of a row at a
 // time whatever n is, but pays for classifying the table and for a second launch, and walks all rows one batch after

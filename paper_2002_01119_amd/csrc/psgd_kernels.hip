@@ -266,8 +266,9 @@ int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const floa
     if (allow_lds(fn, lds_bytes)) return kLaunchRefused;
     const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
     if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
-    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED>), dim3(grid), dim3(kRingThreads), lds_bytes, s, X, X_out, G, nbr, w,
-                       n, d, ld, neg_lr, make_sweeps((d + 3) / 4, grid, kRingThreads), partials);
+    const plan::SweepPlan sp = plan::sweep_plan((d + 3) / 4, grid, kRingThreads);
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED>), dim3(grid), dim3(plan::ring_threads(sp, kRingThreads)), lds_bytes, s, X,
+                       X_out, G, nbr, w, n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk}, partials);
     return grid;
 }
 

@@ -92,11 +92,11 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
                                                                    const float* __restrict__ w, int n, int64_t d, Pitch ld,
                                                                    float neg_lr, Sweeps sweeps,
                                                                    double* __restrict__ partials) {
-    constexpr int T = kRingThreads;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    __shared__ double lds_waves[T / 64];
+    __shared__ double lds_waves[kRingThreads / 64];
+    const int T = blockDim.x;
     const Lds l = carve(lds_raw, n);
-    const int kind = stage_table<T>(nbr, w, n, l);
+    const int kind = stage_table(nbr, w, n, l, T);
     if (kind == kTableBad) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&g_status_word, 1);
         if (CD && threadIdx.x == 0) partials[blockIdx.x] = __builtin_nan("");
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
         }
     }
     if (CD) {
-        const double bs = block_sum<T>(total, lds_waves);
+        const double bs = block_sum_any(total, lds_waves, T);
         if (threadIdx.x == 0) partials[blockIdx.x] = bs;
     }
 }

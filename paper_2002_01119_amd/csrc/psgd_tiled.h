@@ -600,7 +600,7 @@ __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout,
     const size_t tab_bytes = (((size_t)n * deg * sizeof(TileSlot)) + 15) & ~(size_t)15;
     if (skip_rings) {
         // the tile area is free until the first tile is loaded: classify there
-        const int kind = stage_table<T>(nbr, w, n, carve(lds_raw + tab_bytes, n));
+        const int kind = stage_table(nbr, w, n, carve(lds_raw + tab_bytes, n), T);
         if (kind != kTableGeneral) {
             // one ring: the other kernel's work.  Invalid: it has raised the flag; the distance is NaN.
             if (CD && threadIdx.x == 0) partials[blockIdx.x] = kind == kTableRing ? 0.0 : __builtin_nan("");

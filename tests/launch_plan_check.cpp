@@ -82,6 +82,14 @@ int main() {
     const SweepPlan w4 = sweep_plan(2000000, 256, 768);
     CHECK(w4.count == 11 && w4.chunk == 720, "workload 4 plan %lld x %lld", (long long)w4.count, (long long)w4.chunk);
 
+    // the ring walk's workgroups: every column group has a lane, and no wavefront of a single sweep is without one
+    for (int64_t ncg : {(int64_t)1, (int64_t)49152, (int64_t)52500, (int64_t)88474, (int64_t)196608, (int64_t)196609, (int64_t)25000000}) {
+        const SweepPlan p = sweep_plan(ncg, 256, 768);
+        const int t = ring_threads(p, 768);
+        CHECK(t % 64 == 0 && t <= 768 && t >= p.chunk && (p.count > 1 ? t == 768 : t < p.chunk + 64), "ring walk: %d lanes for chunks of %lld",
+              t, (long long)p.chunk);
+    }
+
     // grids never exceed the partials buffer, however many compute units a device reports
     for (int cus : {1, 64, 256, 304, 512, 513, 1024, 100000})
         for (int per_cu : {1, 4, 8}) {
