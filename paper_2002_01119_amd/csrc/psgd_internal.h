@@ -149,6 +149,9 @@ constexpr size_t kShortLds = 160 * 1024 - 2048;
 // A launch counts its lanes in 32 bits: one row of 2^34 columns at a tile per workgroup would be more than that (and would
 // still fit the device).  Beyond these tiles the looping form, whose grid does not grow with the row.
 constexpr int64_t kShortMostTiles = (int64_t)1 << 22;   // times up to 256 lanes
+// With the distance, a workgroup has one partial sum: no more workgroups than the smallest buffer of them holds, whichever
+// buffer the call uses, so that the form and with it the order of the sums do not depend on the entry point.
+constexpr int64_t kShortSlots = 2048;
 struct ShortPlan {
     bool one;                            // a tile per workgroup
     int threads, rows, logc, nrg;
@@ -248,19 +251,21 @@ inline RowsPlan rows_plan(int n, int64_t ncg, int cus, int most_threads, int row
 //     17.9 against 21.2.  The widest workgroup that still occupies more than half of the compute units: 16 x 250 k at
 //     512 lanes (245 tiles) 12.4, at 1024 (123 tiles) 15.2;
 //   - up to 8 learners beyond that: a lane holds all rows of its columns, nothing is exchanged and small independent
-//     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2; up to kShortMostTiles of them;
+//     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2; up to kShortMostTiles of them, with the distance
+//     kShortSlots, of twice the lanes from five learners on (5 x 4 M 47, looping 54; 7 x 4 M 64 / 72; 2 x 2.5 M 15.8 / 14.4);
 //   - all else: 1024 lanes, four rows each, the next tile's loads ahead: 512 x 60 k 77.6 us, at 512 lanes 107;
 //     64 x 1 M with bf16 gradients 126 against 130.
-// `slots`: with the distance, the most workgroups.
-inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, int64_t slots) {
+inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd) {
     for (int threads = kShortThreads; threads >= 256; threads /= 2) {
         const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, kShortRowsOne);
         if (p.threads > threads || p.tiles > cus) break;
         if (p.tiles > cus / 2 || threads == 256) return p;
     }
     if (n <= kShortRowsOne) {
-        const ShortPlan p = short_widest(n, deg, ncg, cd, true, 256, kShortRowsOne);
-        if (p.tiles <= (cd ? slots : kShortMostTiles)) return p;
+        for (int threads = 256; threads <= (cd && n > 4 ? 512 : 256); threads *= 2) {
+            const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, kShortRowsOne);
+            if (p.tiles <= (cd ? kShortSlots : kShortMostTiles)) return p;
+        }
     }
     // A lane without a row of its own repeats the last one, loads and stores alike: fewer rows per lane where that leaves
     // fewer such places, unless the tile then narrows below a wavefront's 64 column groups (13 x 3.9 M, 16 places at four

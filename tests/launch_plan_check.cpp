@@ -178,28 +178,28 @@ int main() {
         for (int deg : {1, 3, 8, 13, 32})
             for (int64_t ncg : {1, 2, 63, 64, 65, 1000, 16384, 65536, 65537, 250000, 393215})
                 for (int cus : {1, 64, 256, 304})
-                    for (bool cd : {false, true})
-                        for (int slots : {2048, kMaxGrid}) {
-                            if ((long)n * deg > 4096) continue;
-                            const ShortPlan p = short_plan(n, deg, ncg, cus, cd, slots);
-                            CHECK(p.threads % 64 == 0 && p.threads >= 64 && p.threads <= kShortThreads && p.threads == p.nrg << p.logc,
-                                  "short rows n=%d deg=%d ncg=%lld: %d lanes", n, deg, (long long)ncg, p.threads);
-                            CHECK(p.rows * p.nrg >= n && p.rows >= 1 && p.rows <= (p.one ? kShortRowsOne : kShortRows) &&
-                                      (!p.one || p.rows % 2 == 0), "short rows n=%d: %d rows on %d row groups", n, p.rows, p.nrg);
-                            CHECK(p.tiles << p.logc >= ncg && (p.tiles - 1) << p.logc < ncg, "short rows: %lld tiles", (long long)p.tiles);
-                            const size_t merge = cd && p.nrg > 1 ? (size_t)p.threads * 48 : 0;
-                            CHECK(p.tab_bytes >= n * deg * 8 && p.tab_bytes % 16 == 0 && p.tile_bytes >= n * (16 << p.logc) &&
-                                      p.lds <= kShortLds && p.lds >= (size_t)p.tab_bytes + p.tile_bytes + (p.one ? 0 : merge) &&
-                                      (!p.one || (size_t)p.tile_bytes >= merge), "short rows n=%d deg=%d: LDS %zu", n, deg, p.lds);
-                            const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
-                            CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
-                        }
+                    for (bool cd : {false, true}) {
+                        if ((long)n * deg > 4096) continue;
+                        const int64_t slots = kShortSlots;
+                        const ShortPlan p = short_plan(n, deg, ncg, cus, cd);
+                        CHECK(p.threads % 64 == 0 && p.threads >= 64 && p.threads <= kShortThreads && p.threads == p.nrg << p.logc,
+                              "short rows n=%d deg=%d ncg=%lld: %d lanes", n, deg, (long long)ncg, p.threads);
+                        CHECK(p.rows * p.nrg >= n && p.rows >= 1 && p.rows <= (p.one ? kShortRowsOne : kShortRows) &&
+                                  (!p.one || p.rows % 2 == 0), "short rows n=%d: %d rows on %d row groups", n, p.rows, p.nrg);
+                        CHECK(p.tiles << p.logc >= ncg && (p.tiles - 1) << p.logc < ncg, "short rows: %lld tiles", (long long)p.tiles);
+                        const size_t merge = cd && p.nrg > 1 ? (size_t)p.threads * 48 : 0;
+                        CHECK(p.tab_bytes >= n * deg * 8 && p.tab_bytes % 16 == 0 && p.tile_bytes >= n * (16 << p.logc) &&
+                                  p.lds <= kShortLds && p.lds >= (size_t)p.tab_bytes + p.tile_bytes + (p.one ? 0 : merge) &&
+                                  (!p.one || (size_t)p.tile_bytes >= merge), "short rows n=%d deg=%d: LDS %zu", n, deg, p.lds);
+                        const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
+                        CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
+                    }
     // a launch holds fewer than 2^32 lanes, also on the longest rows that fit a device (one learner of 18e9 columns and more)
     for (int n : {1, 2, 3, 8, 9, 64})
         for (int64_t ncg : {(int64_t)1 << 22, (int64_t)1 << 30, ((int64_t)1 << 32) + 3, (int64_t)4500000001, (int64_t)1 << 34})
             for (bool cd : {false, true}) {
-                const ShortPlan p = short_plan(n, 3, ncg, 256, cd, kMaxGrid);
-                const int64_t grid = p.one ? p.tiles : short_grid(p, 256, cd ? kMaxGrid : INT32_MAX);
+                const ShortPlan p = short_plan(n, 3, ncg, 256, cd);
+                const int64_t grid = p.one ? p.tiles : short_grid(p, 256, cd ? kShortSlots : INT32_MAX);
                 CHECK(grid >= 1 && grid * p.threads < (int64_t)1 << 32, "short rows n=%d ncg=%lld: %lld workgroups of %d lanes", n,
                       (long long)ncg, (long long)grid, p.threads);
             }

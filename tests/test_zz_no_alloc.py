@@ -84,6 +84,13 @@ def test_static_entry_point_twice_second_call_smaller(lib):
     _case(lib, 8, 300_000, "f32", orc.TOPO_RAND_RING, 7, pitched=False)
 
 
+@pytest.mark.parametrize("n,d", [(8, 3_000_001), (5, 2_097_160), (7, 4_194_304), (2, 2_500_000)])
+def test_static_entry_point_few_learners_of_long_rows(lib, n, d):
+    """Up to eight learners, where a tile per workgroup is more tiles than the static array has slots (2048 tiles of 1024
+    columns): the entry point with the larger buffer takes the same form."""
+    _case(lib, n, d, "f32", orc.TOPO_RAND_RING, 8 + n, pitched=False)
+
+
 def test_static_entry_point_argument_checks_and_empty_input(lib):
     from paper_2002_01119_amd import psgd as m
     dev = "cuda:0"
