@@ -58,6 +58,7 @@ struct DeviceInfo {
     bool partials_used = false;
     double* static_partials = nullptr;  // device address of ::scratch on this GPU (psgd_mix_step_cd_static)
     double* host_result = nullptr;      // pinned host memory, hipHostMalloc'ed on first use (psgd_consensus_dist)
+    std::mutex host_result_mutex;       // held from the launch until the word has been read
 };
 constexpr int kMaxDevices = 64;
 DeviceInfo g_dev[kMaxDevices];
@@ -754,12 +755,11 @@ double psgd_consensus_dist(const float* X, int n, int64_t d) {
     if (d == 0 || n == 1) return 0.0;
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) { hip_fail(e, "hipDeviceSynchronize"); return NAN; }
-    // The final sum goes straight to pinned host memory, one word per device, one call at a time: a copy of eight bytes
+    // The final sum goes straight to pinned host memory, one word and one call at a time per device: a copy of eight bytes
     // after the kernels cost more host time than both launches (27 us a call on a small array, now 16).
-    static std::mutex mu;
-    std::lock_guard<std::mutex> lock(mu);
     DeviceInfo* di = nullptr;
     if (device_info(&di) != PSGD_OK) return NAN;
+    std::lock_guard<std::mutex> lock(di->host_result_mutex);
     if (!di->host_result) {
         e = hipHostMalloc(reinterpret_cast<void**>(&di->host_result), sizeof(double), hipHostMallocDefault);
         if (e != hipSuccess) {

@@ -286,3 +286,35 @@ def test_launch_arithmetic_covers_every_column_group_once_and_clamps_grids(tmp_p
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "launch plan ok" in r.stdout
+
+
+_TWO_DEVICES = """
+import ctypes, sys, threading
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+lib.psgd_consensus_dist.restype = ctypes.c_double
+lib.psgd_consensus_dist.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int64]
+def ask(device):
+    stub.stub_device(device)
+    lib.psgd_consensus_dist(4096, 4, 1000)                # no kernel reads the address
+stub.stub_expect(2)
+threads = [threading.Thread(target=ask, args=(k,)) for k in range(2)]
+[t.start() for t in threads]
+[t.join() for t in threads]
+print("waits that met:", stub.stub_met())
+"""
+
+
+def test_synchronous_distance_does_not_serialise_devices(tmp_path):
+    """Two threads asking for the distance on two GPUs wait for them at the same time (runtime calls replaced on the CPU)."""
+    import shutil
+    import subprocess
+    import sys
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    stub = str(tmp_path / "libhipstub.so")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(ROOT, "tests", "hip_host_stub.cpp"), "-o", stub],
+                   check=True)
+    r = subprocess.run([sys.executable, "-c", _TWO_DEVICES, stub, psgd._LIB_PATH], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "waits that met: 2" in r.stdout, r.stdout + r.stderr
