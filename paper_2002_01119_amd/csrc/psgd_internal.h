@@ -245,24 +245,58 @@ inline RowsPlan rows_plan(int n, int64_t ncg, int cus, int most_threads, int row
     return RowsPlan{0, 0, 0, 0};
 }
 
+// Most lanes per compute unit, over the whole launch, at which two rows per lane are the better form (short_plan): 384
+// where a row has few slots, or few and the distance's merge, more the wider the table; fewer where row segments are a
+// line or less.  us, eight rows per lane / two, on the far side of the lines: 25 x 38 k 8.2 / 9.4, 30 x 68 k with 5 slots
+// 11.0 / 13.9 (both with the distance), 85 x 21.7 k with 5 slots and none 7.6 / 8.8 (128-byte segments).
+inline int two_rows_lanes(int n, int deg, bool cd, int logc) {
+    if (cd && n < 5) return 256;
+    int most = deg <= 3 || (cd && deg < 8) ? 384 : 960;
+    if (!cd && deg > 3) {
+        if (deg < 8) most = logc > 4 ? 1024 : logc == 4 ? 640 : 512;
+        else most = logc <= 3 ? 1024 : deg < 16 ? 1280 : 1536;
+    }
+    if (logc < 3 && most > 512) most = 512;
+    return cd && n < 8 && most > 768 ? 768 : most;
+}
 // Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
+//   - few columns: two rows per lane, on as few lanes as leave a row segment of a 128-byte line.  A lane reads its rows'
+//     slots from LDS one after the other; with eight rows each on a few workgroups that chain is the launch.  Eight rows /
+//     two, without the distance: 8 x 20 k with 5 slots 5.1 / 3.8, with 32 12.6 / 4.4; 64 x 20 k with 13 8.3 / 4.9; ring of 8 x 61 k
+//     with it 7.1 / 6.1;
+//   - wide tables on rows that start on 16 bytes (`quads`), where LDS reads are the bound: two rows per lane, a tile per
+//     workgroup of 512 lanes.  Without the distance, bf16 gradients: 8 x 700 k with 13 slots 15.7 / 12.1, 16 x 1.4 M with 32
+//     71 / 49; fp32 32 x 410 k with 32 54 / 34; with it 8 x 700 k with 32 29.5 / 23.9.  On other rows it loses (20 x 941 559 with 20 slots
+//     55 / 64), as with fewer slots (45 x 1.2 M with 16 119 / 138);
 //   - everything in one round of at most one workgroup per compute unit, eight rows per lane: the whole chip's loads
 //     are in flight at once.  8 learners x 1 M without the distance 15.7 us, looping over narrower tiles 18.9; 64 x 100 k
 //     17.9 against 21.2.  The widest workgroup that still occupies more than half of the compute units: 16 x 250 k at
 //     512 lanes (245 tiles) 12.4, at 1024 (123 tiles) 15.2;
 //   - up to 8 learners beyond that: a lane holds all rows of its columns, nothing is exchanged and small independent
 //     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2; up to kShortMostTiles of them, with the distance
-//     kShortSlots, of twice the lanes from five learners on (5 x 4 M 47, looping 54; 7 x 4 M 64 / 72; 2 x 2.5 M 15.8 / 14.4);
+//     kShortSlots, of twice the lanes from five learners on (5 x 4 M 47, looping 54; 7 x 4 M 64 / 72; 2 x 2.5 M 15.8 / 14.4; wide
+//     tables loop);
 //   - all else: 1024 lanes, four rows each, the next tile's loads ahead: 512 x 60 k 77.6 us, at 512 lanes 107;
 //     64 x 1 M with bf16 gradients 126 against 130.
-inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd) {
+inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, bool quads) {
+    if (n > 2 && (!cd || n > 5 || deg >= (n > 4 ? 4 : 9))) {
+        for (int threads = 256; threads <= kShortThreads; threads *= 2) {
+            const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, 2);
+            if (p.threads > threads || (p.logc < 3 && threads < kShortThreads)) continue;
+            if (p.tiles * p.threads <= (int64_t)cus * two_rows_lanes(n, deg, cd, p.logc) && (!cd || p.tiles <= kShortSlots)) return p;
+        }
+    }
+    if (quads && n > 4 && (cd ? n <= 8 && deg >= 20 : n <= 8 ? deg >= 7 : n <= 16 ? deg >= 16 : n <= 48 && deg >= 24)) {
+        const ShortPlan p = short_widest(n, deg, ncg, cd, true, 512, 2);
+        if (p.tiles <= (cd ? kShortSlots : kShortMostTiles)) return p;
+    }
     for (int threads = kShortThreads; threads >= 256; threads /= 2) {
         const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, kShortRowsOne);
         if (p.threads > threads || p.tiles > cus) break;
         if (p.tiles > cus / 2 || threads == 256) return p;
     }
     if (n <= kShortRowsOne) {
-        for (int threads = 256; threads <= (cd && n > 4 ? 512 : 256); threads *= 2) {
+        for (int threads = 256; threads <= (cd && n > 4 && deg < 16 ? 512 : 256); threads *= 2) {
             const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, kShortRowsOne);
             if (p.tiles <= (cd ? kShortSlots : kShortMostTiles)) return p;
         }

@@ -279,10 +279,11 @@ inline bool long_rows(const DeviceInfo& di, int64_t column_groups, int sweeps = 
     return column_groups >= (int64_t)di.cus * kRingThreads * sweeps;
 }
 
-// Every row of X and X_out starts on a 128-byte line.
-inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) {
-    return aligned_to(X, 128) && aligned_to(X_out, 128) && ld.x % 32 == 0 && ld.o % 32 == 0;
+// Every row of X and X_out starts on `bytes` (a power of two): a 128-byte line, or a lane's 16 bytes.
+inline bool rows_start_on(int bytes, const float* X, const float* X_out, const Pitch& ld) {
+    return aligned_to(X, bytes) && aligned_to(X_out, bytes) && ld.x % (bytes / 4) == 0 && ld.o % (bytes / 4) == 0;
 }
+inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) { return rows_start_on(128, X, X_out, ld); }
 
 // Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
 // negative status.
@@ -400,11 +401,12 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5 slots 76.6 / 76.0),
     // else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001 838 / 1322, 300 x 1.6 M
     // 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).
+    const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
     const bool big = deg == 3 ? plan::ring_rows(n, ncg, di->cus, kRingThreads)
                               : long_rows(*di, ncg) && n > 8 && n <= 128 && rows_on_lines(X, X_out, ld);
     if (!big) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
-                                         : plan::short_plan(n, deg, ncg, di->cus, want_cd);
+                                         : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
         if (want_cd && deg == 3) grid = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
         else if (want_cd) grid = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
         else if (deg == 3) grid = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);

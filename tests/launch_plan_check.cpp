@@ -178,10 +178,11 @@ int main() {
         for (int deg : {1, 3, 8, 13, 32})
             for (int64_t ncg : {1, 2, 63, 64, 65, 1000, 16384, 65536, 65537, 250000, 393215})
                 for (int cus : {1, 64, 256, 304})
-                    for (bool cd : {false, true}) {
+                    for (int form = 0; form < 4; ++form) {
                         if ((long)n * deg > 4096) continue;
+                        const bool cd = form & 1, quads = form & 2;
                         const int64_t slots = kShortSlots;
-                        const ShortPlan p = short_plan(n, deg, ncg, cus, cd);
+                        const ShortPlan p = short_plan(n, deg, ncg, cus, cd, quads);
                         CHECK(p.threads % 64 == 0 && p.threads >= 64 && p.threads <= kShortThreads && p.threads == p.nrg << p.logc,
                               "short rows n=%d deg=%d ncg=%lld: %d lanes", n, deg, (long long)ncg, p.threads);
                         CHECK(p.rows * p.nrg >= n && p.rows >= 1 && p.rows <= (p.one ? kShortRowsOne : kShortRows) &&
@@ -194,11 +195,23 @@ int main() {
                         const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
                         CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
                     }
+    // few columns: two rows per lane, so that a table's slot chain is short and the workgroups are many; wide tables the same
+    // on longer rows; row segments stay a 128-byte line wide where the workgroup has room for it
+    for (int n : {3, 8, 16, 40, 64, 105, 200})
+        for (int deg : {5, 13, 20}) {
+            const ShortPlan p = short_plan(n, deg, 250, 256, false, true);
+            CHECK(p.one && p.rows == 2 && (p.logc >= 3 || n > 128), "n=%d deg=%d on few columns: %d rows per lane, 2^%d groups wide", n,
+                  deg, p.rows, p.logc);
+        }
+    CHECK(short_plan(8, 3, 15000, 256, true, true).rows == 2 && short_plan(8, 3, 40000, 256, true, true).rows == 8, "8 learners: two rows up to 24 576 column groups");
+    CHECK(short_plan(8, 13, 175000, 256, false, true).rows == 2 && short_plan(8, 13, 175000, 256, false, false).rows == 8, "wide tables on 16 bytes");
+    CHECK(short_plan(4, 13, 700000, 256, false, true).rows == 4 && short_plan(64, 20, 300000, 256, false, true).rows == 4, "wide tables, other counts");
+
     // a launch holds fewer than 2^32 lanes, also on the longest rows that fit a device (one learner of 18e9 columns and more)
     for (int n : {1, 2, 3, 8, 9, 64})
         for (int64_t ncg : {(int64_t)1 << 22, (int64_t)1 << 30, ((int64_t)1 << 32) + 3, (int64_t)4500000001, (int64_t)1 << 34})
             for (bool cd : {false, true}) {
-                const ShortPlan p = short_plan(n, 3, ncg, 256, cd);
+                const ShortPlan p = short_plan(n, 3, ncg, 256, cd, true);
                 const int64_t grid = p.one ? p.tiles : short_grid(p, 256, cd ? kShortSlots : INT32_MAX);
                 CHECK(grid >= 1 && grid * p.threads < (int64_t)1 << 32, "short rows n=%d ncg=%lld: %lld workgroups of %d lanes", n,
                       (long long)ncg, (long long)grid, p.threads);

@@ -22,6 +22,13 @@ CASES = [
     (128, 589_821, 3, "f32", (1, 2, 3)), (128, 589_825, 3, "bf16", (3, 1, 2)), (200, 600_002, 3, "f32", None),
     (64, 2_359_299, 3, "bf16", None),
     (100, 120_001, 3, "f32", None), (257, 40_007, 4, "bf16", None), (512, 20_002, 3, "f32", (1, 0, 2)),
+    # two rows per lane: few columns, narrow and wide tables, either side of its lines
+    (3, 1_001, 13, "f32", None), (4, 30_004, 9, "bf16", None), (6, 2_050, 3, "bf16", (1, 2, 3)), (8, 40_000, 32, "f32", None),
+    (64, 5_001, 13, "bf16", None), (200, 2_050, 9, "f32", (3, 1, 1)), (400, 1_030, 5, "bf16", None), (18, 40_004, 3, "f32", None),
+    (18, 60_004, 3, "f32", None), (30, 45_000, 5, "bf16", None), (30, 90_001, 5, "f32", None), (64, 90_000, 16, "bf16", None),
+    # wide tables, a tile per workgroup where rows start on 16 bytes
+    (8, 700_004, 13, "bf16", None), (8, 700_003, 13, "f32", None), (5, 900_004, 24, "f32", (4, 8, 4)), (16, 600_000, 24, "f32", None),
+    (40, 300_004, 32, "bf16", None),
 ]
 
 
