@@ -276,6 +276,8 @@ inline int two_rows_lanes(int n, int deg, bool cd, int logc) {
 //     workgroups hide each other's latency: 8 x 1.5 M 30.3, looping 32.2; up to kShortMostTiles of them, with the distance
 //     kShortSlots, of twice the lanes from five learners on (5 x 4 M 47, looping 54; 7 x 4 M 64 / 72; 2 x 2.5 M 15.8 / 14.4; wide
 //     tables loop);
+//   - five to eight learners of longer rows, with the distance: looping, two rows per lane (5 x 30 M with bf16 gradients 307
+//     on three rows, 289 on two; 7 x 8 M 135 / 124);
 //   - all else: 1024 lanes, four rows each, the next tile's loads ahead: 512 x 60 k 77.6 us, at 512 lanes 107;
 //     64 x 1 M with bf16 gradients 126 against 130.
 inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, bool quads) {
@@ -300,14 +302,17 @@ inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, bool 
             const ShortPlan p = short_widest(n, deg, ncg, cd, true, threads, kShortRowsOne);
             if (p.tiles <= (cd ? kShortSlots : kShortMostTiles)) return p;
         }
+        if (n > 4) return short_widest(n, deg, ncg, cd, false, kShortThreads, 2);
     }
     // A lane without a row of its own repeats the last one, loads and stores alike: fewer rows per lane where that leaves
     // fewer such places, unless the tile then narrows below a wavefront's 64 column groups (13 x 3.9 M, 16 places at four
-    // rows, 14 at two: 131 and 119 us; 200 x 250 k, 208 at four, 204 at three on half the width: 131 and 143).
+    // rows, 14 at two: 131 and 119 us; 200 x 250 k, 208 at four, 204 at three on half the width: 131 and 143), or from 128 with
+    // the distance and 20 to 28 learners (28 places, 26 on half the width: 26 x 2 M 126 / 134, with 13 slots 131 / 156).
     ShortPlan best = short_widest(n, deg, ncg, cd, false, kShortThreads, kShortRows);
     for (int rows = kShortRows - 1; rows >= 2; --rows) {
         const ShortPlan p = short_widest(n, deg, ncg, cd, false, kShortThreads, rows);
-        if (p.nrg * p.rows < best.nrg * best.rows && (p.logc >= 6 || p.logc == best.logc)) best = p;
+        if (p.nrg * p.rows < best.nrg * best.rows && (p.logc == best.logc || (p.logc >= 6 && (!cd || n < 20 || n > 28))))
+            best = p;
     }
     return best;
 }

@@ -206,6 +206,10 @@ int main() {
     CHECK(short_plan(8, 3, 15000, 256, true, true).rows == 2 && short_plan(8, 3, 40000, 256, true, true).rows == 8, "8 learners: two rows up to 24 576 column groups");
     CHECK(short_plan(8, 13, 175000, 256, false, true).rows == 2 && short_plan(8, 13, 175000, 256, false, false).rows == 8, "wide tables on 16 bytes");
     CHECK(short_plan(4, 13, 700000, 256, false, true).rows == 4 && short_plan(64, 20, 300000, 256, false, true).rows == 4, "wide tables, other counts");
+    // five to eight learners of long rows with the distance loop on two rows; 26 learners keep the wide tile with it
+    for (int n : {5, 6, 7, 8})
+        CHECK(short_plan(n, 3, 7500000, 256, true, true).rows == 2 && !short_plan(n, 3, 7500000, 256, true, true).one, "n=%d loops on two rows", n);
+    CHECK(short_plan(26, 5, 500000, 256, true, true).logc == 7 && short_plan(26, 5, 500000, 256, false, true).logc == 6, "26 learners");
 
     // a launch holds fewer than 2^32 lanes, also on the longest rows that fit a device (one learner of 18e9 columns and more)
     for (int n : {1, 2, 3, 8, 9, 64})

@@ -29,6 +29,8 @@ CASES = [
     # wide tables, a tile per workgroup where rows start on 16 bytes
     (8, 700_004, 13, "bf16", None), (8, 700_003, 13, "f32", None), (5, 900_004, 24, "f32", (4, 8, 4)), (16, 600_000, 24, "f32", None),
     (40, 300_004, 32, "bf16", None),
+    # five to eight learners looping, and 22 learners on the wider tile
+    (5, 4_194_440, 3, "f32", None), (7, 2_300_001, 20, "bf16", None), (22, 600_002, 7, "f32", None),
 ]
 
 
