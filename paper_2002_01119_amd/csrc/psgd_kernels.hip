@@ -400,10 +400,13 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // Tables of other slot counts: on long rows the tiled kernel is as good or a little better while its row segments are
     // wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5 slots 76.6 / 76.0),
     // else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001 838 / 1322, 300 x 1.6 M
-    // 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).
+    // 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).  Tables of 16 slots and more, bound by LDS reads,
+    // on 9 to 64 learners also where rows start on 16 bytes only (64 x 3 200 004 with 32 slots 674 / 599, 16 x 12 000 004 601 / 559), not on
+    // shorter rows (9 x 2.3 M with bf16 gradients 80 / 112).
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
     const bool big = deg == 3 ? plan::ring_rows(n, ncg, di->cus, kRingThreads)
-                              : long_rows(*di, ncg) && n > 8 && n <= 128 && rows_on_lines(X, X_out, ld);
+                              : long_rows(*di, ncg) && n > 8 &&
+                                    ((n <= 128 && rows_on_lines(X, X_out, ld)) || (n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
     if (!big) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
                                          : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);

@@ -1019,12 +1019,13 @@ def test_tiled_kernel_long_rows_many_learners(psgd, n, kind, gkind):
     assert psgd.device_status() == 0
 
 
-@pytest.mark.parametrize("n,deg,gkind", [(64, 32, "f32"), (64, 32, "bf16"), (128, 32, "bf16")])
-def test_tiled_kernel_long_rows_widest_tables(psgd, n, deg, gkind):
-    """32 slots per row on long rows: the slot table takes 16 KB (32 KB for 128 learners) of LDS, so the merge
-    slots of the distance no longer fit beside the two tile buffers and live in the buffer that has just been
-    consumed (n = 64), or the rows get narrower (n = 128).  Every element and the distance against the oracle."""
-    d = 1_580_004
+@pytest.mark.parametrize("n,deg,gkind,d", [(64, 32, "f32", 1_580_064), (64, 32, "bf16", 1_580_064), (128, 32, "bf16", 1_580_064),
+                                           (9, 20, "f32", 3_145_732)])
+def test_tiled_kernel_long_rows_widest_tables(psgd, n, deg, gkind, d):
+    """32 slots per row on long rows that start on 128-byte lines: the slot table takes 16 KB (32 KB for 128
+    learners) of LDS, so the merge slots of the distance no longer fit beside the two tile buffers and live in the
+    buffer that has just been consumed (n = 64), or the rows get narrower (n = 128).  From 16 slots on the kernel also
+    takes longer rows that only start on 16 bytes (n = 9).  Every element and the distance against the oracle."""
     rng = np.random.default_rng(n + deg)
     nbr, w = _perm_sum_table(n, deg, rng)
     X = inp.host_normal_f32((n, d), 1.0, 740 + n)

@@ -31,6 +31,8 @@ CASES = [
     (40, 300_004, 32, "bf16", None),
     # five to eight learners looping, and 22 learners on the wider tile
     (5, 4_194_440, 3, "f32", None), (7, 2_300_001, 20, "bf16", None), (22, 600_002, 7, "f32", None),
+    # long rows of other tables that do not start on lines
+    (64, 1_600_004, 13, "bf16", None), (200, 1_580_004, 5, "f32", None),
 ]
 
 
