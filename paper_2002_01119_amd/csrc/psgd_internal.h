@@ -227,22 +227,40 @@ inline RowsPlan rows_shape(int n, int64_t ncg, int threads, int rows) {
     return p;
 }
 // As for the short-row kernel, one round of at most one workgroup per compute unit where that holds everything (the
-// widest workgroup that occupies more than half of them); many learners beyond it take more rows per lane, up to where
-// the columns alone do as well.  us, lane per column group / rows spread: global averaging with the distance 512 x 6 k
-// 175 / 13.4, 64 x 100 k 28.8 / 19.5, 512 x 60 k 187 / 69, 128 x 200 k 61.6 / 60.8, 64 x 300 k 49.4 / 49.7; distance alone
-// 512 x 6 k 52 / 8.5, 64 x 100 k 11.4 / 9.2, 512 x 60 k 54 / 23, 128 x 200 k 20.2 / 22.3, 24 x 100 k 7.0 / 7.6.
-// `least`: the fewest learners, 9 for global averaging (two passes over the rows), 48 for the distance (one).
-inline RowsPlan rows_plan(int n, int64_t ncg, int cus, int most_threads, int rows, int least) {
-    if (ncg == 1) return rows_shape(n, ncg, 256, rows);          // also the only form for fewer than four columns
+// widest workgroup that occupies more than half of them), on eight rows per lane, or up to `most_rows`; many learners
+// beyond it take more rows per lane, up to where the columns alone do as well.  us, lane per column group / rows spread:
+// global averaging with the distance 512 x 6 k 175 / 13.4, 64 x 100 k 28.8 / 19.5, 512 x 60 k 187 / 69, 82 x 90 k 38 / 22, 128 x 200 k
+// 61.6 / 60.8, 64 x 300 k 49.4 / 49.7; distance alone 512 x 6 k 52 / 8.5, 64 x 100 k 11.4 / 9.2, 512 x 60 k 54 / 23, 127 x 90 k 18 / 12,
+// 128 x 200 k 20.2 / 22.3.
+// `least`: the fewest learners.
+inline RowsPlan rows_plan(int n, int64_t ncg, int cus, int most_threads, int most_rows, int least) {
+    if (ncg == 1) return rows_shape(n, ncg, 256, 8);             // also the only form for fewer than four columns
     if (n >= least) {
-        for (int threads = most_threads; threads >= 256; threads /= 2) {
-            const RowsPlan p = rows_shape(n, ncg, threads, rows);
-            if (p.tiles > cus) break;
-            if (p.tiles > cus / 2 || threads == 256) return p;
+        for (int rows = 8; rows <= most_rows; rows *= 2) {
+            for (int threads = most_threads; threads >= 256; threads /= 2) {
+                const RowsPlan p = rows_shape(n, ncg, threads, rows);
+                if (p.tiles > cus) break;
+                if (p.tiles > cus / 2 || threads == 256) return p;
+            }
         }
-        if (n >= 128 && ncg < (int64_t)cus * 128) return rows_shape(n, ncg, 512, 32);
+        if (n > 64 && ncg < (int64_t)cus * 128)
+            return most_threads > 512 && n < 128 ? rows_shape(n, ncg, most_threads, 16) : rows_shape(n, ncg, 512, 32);
     }
     return RowsPlan{0, 0, 0, 0};
+}
+// Global averaging passes twice over the rows: from 17 learners on, a lane walking all of them is behind on few columns, from
+// 10 on at 4000 columns and more (us, lane / spread: 12 x 50 k 9.2 / 8.5, with bf16 gradients and no distance 5.3 / 4.7; 12 x 1000 6.5 / 7.7; 9 x
+// 200 k 9.1 / 10.2), ragged rows earlier (13 x 1599 5.2 / 4.4); with the distance and whole column groups not for ten (10 x 164 k
+// 7.0 / 9.0), for 16, whole batches of eight, from 160 000 (16 x 50 k 8.4 / 8.9, 16 x 200 k 11.3 / 11.0).
+inline RowsPlan full_rows_plan(int n, int64_t d, int cus, bool cd) {
+    const int64_t ncg = (d + 3) / 4;
+    const int64_t from = d % 4 ? 230 : cd && n == 16 ? 40000 : cd && n == 10 ? INT64_MAX : 1000;
+    return rows_plan(n, ncg, cus, kShortThreads, 8, ncg < from ? 17 : 10);
+}
+// The distance passes once: from 48 learners on, from 30 where rows are ragged and not the shortest (42 x 50 001 8.3 / 6.3; 36 x
+// 20 k 5.9 / 6.0; 33 x 566 4.9 / 5.7).
+inline RowsPlan distance_rows_plan(int n, int64_t d, int cus) {
+    return rows_plan(n, (d + 3) / 4, cus, 512, 16, d % 4 && d >= 4000 ? 30 : 48);
 }
 
 // Most lanes per compute unit, over the whole launch, at which two rows per lane are the better form (short_plan): 384

@@ -540,7 +540,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const Pitch ld{ldx, ldo, ldg};
     const float neg_lr = -lr;
     const bool big = long_rows(*di, ncg, 2);
-    const plan::RowsPlan rp = plan::rows_plan(n, ncg, di->cus, plan::kShortThreads, kUnroll, kUnroll + 1);
+    const plan::RowsPlan rp = plan::full_rows_plan(n, d, di->cus, want_cd);
     const bool split = !big && rp.threads != 0;
     int grid = 0;
     if (split) {
@@ -595,7 +595,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
             hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads>), dim3(grid), dim3(kRingThreads), 0, s, X, n, d, ldx,
                                make_sweeps(ncg, grid, kRingThreads), partials);
         } else {
-            const plan::RowsPlan rp = plan::rows_plan(n, ncg, di->cus, 512, 2 * kUnroll, 48);
+            const plan::RowsPlan rp = plan::distance_rows_plan(n, d, di->cus);
             if (rp.threads != 0) {
                 grid = (int)(rp.tiles < kMaxGrid ? rp.tiles : kMaxGrid);
                 const size_t lds = (size_t)rp.threads * 48;

@@ -221,11 +221,12 @@ int main() {
                       (long long)ncg, (long long)grid, p.threads);
             }
     // global averaging and the distance with rows spread over lanes
-    for (int n : {1, 2, 9, 16, 17, 33, 64, 128, 300, 512})
-        for (int64_t ncg : {1, 2, 63, 65, 1500, 15000, 32767, 32768, 250000})
+    for (int n : {1, 2, 9, 10, 14, 16, 17, 30, 33, 48, 64, 65, 82, 127, 128, 300, 512})
+        for (int64_t d : {1, 4, 5, 8, 252, 257, 260, 3999, 4000, 6000, 60000, 131068, 131069, 131072, 1000000})
             for (int cus : {1, 256})
-                for (int rows : {8, 16}) {
-                    const RowsPlan p = rows == 8 ? rows_plan(n, ncg, cus, 1024, 8, 9) : rows_plan(n, ncg, cus, 512, 16, 48);
+                for (int form = 0; form < 3; ++form) {
+                    const int64_t ncg = (d + 3) / 4;
+                    const RowsPlan p = form == 2 ? distance_rows_plan(n, d, cus) : full_rows_plan(n, d, cus, form);
                     if (p.threads == 0) {
                         CHECK(ncg > 1, "one column group has no lane-per-column form");
                         continue;
@@ -235,6 +236,13 @@ int main() {
                     CHECK(p.tiles << p.logc >= ncg && (p.tiles - 1) << p.logc < ncg, "rows: %lld tiles", (long long)p.tiles);
                     CHECK(p.threads * 48 + (16 << p.logc) <= 65280, "rows: LDS");
                 }
+    CHECK(full_rows_plan(9, 200000, 256, false).threads == 0 && full_rows_plan(16, 20000, 256, true).threads == 0 &&
+              full_rows_plan(16, 20000, 256, false).threads != 0 && full_rows_plan(16, 20001, 256, true).threads != 0 &&
+              full_rows_plan(12, 20000, 256, true).threads != 0 && full_rows_plan(12, 3000, 256, false).threads == 0 &&
+              full_rows_plan(17, 3000, 256, true).threads != 0, "global averaging: where rows are spread over lanes");
+    CHECK(full_rows_plan(82, 89641, 256, true).threads != 0 && full_rows_plan(82, 131072, 256, true).threads == 0 &&
+              distance_rows_plan(82, 89641, 256).threads != 0 && distance_rows_plan(42, 50001, 256).threads != 0 &&
+              distance_rows_plan(42, 50000, 256).threads == 0, "65 learners and more; ragged rows");
     if (failures) return 1;
     std::printf("launch plan ok\n");
     return 0;

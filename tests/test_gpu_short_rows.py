@@ -99,7 +99,12 @@ def test_short_rows_every_element(psgd, n, d, deg, gkind, extra):
 @pytest.mark.parametrize("n,d,gkind,extra", [
     (1, 1, "f32", None), (512, 2, "bf16", (1, 2, 3)), (70, 3, "f32", (1, 0, 2)), (9, 5, "bf16", None),
     (512, 6_001, "f32", (1, 2, 3)), (64, 100_002, "bf16", None), (33, 70_001, "f32", (3, 1, 1)), (17, 10_003, "bf16", (1, 1, 1)),
-    (300, 60_003, "f32", None), (512, 131_071, "bf16", None), (130, 131_075, "f32", (1, 2, 3)), (16, 200_001, "f32", None)])
+    (300, 60_003, "f32", None), (512, 131_071, "bf16", None), (130, 131_075, "f32", (1, 2, 3)), (16, 200_001, "f32", None),
+    (10, 4_100, "bf16", None), (14, 925, "f32", None), (16, 50_000, "f32", None), (82, 89_641, "bf16", (1, 0, 2)), (127, 100_000, "f32", None),
+    (31, 4_003, "f32", None), (42, 50_001, "f32", (1, 2, 3)), (72, 120_001, "f32", None),
+    # one and more sweeps of large workgroups, rows that do not fill the last batch, ragged and whole
+    (3, 1_100_002, "f32", None), (1, 1_600_001, "f32", None), (2, 1_600_000, "f32", None), (7, 1_700_003, "bf16", (1, 2, 3)),
+    (14, 1_572_868, "f32", None)])
 def test_global_average_and_distance_with_rows_spread_over_lanes(psgd, n, d, gkind, extra):
     """psgd_mix_full and the stand-alone distance where the columns alone do not fill the chip, either side of that line."""
     X = inp.host_normal_f32((n, d), 1.0, 41 + n) + np.float32(100.0)
