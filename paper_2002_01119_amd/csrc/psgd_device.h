@@ -292,9 +292,10 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Sum over the workgroup (T threads); the per-wavefront sums are added in a fixed order.
+// Sum over the workgroup (T threads, or the first `lanes` of them: whole wavefronts); the per-wavefront sums are read at
+// once and added in a fixed order.
 template <int T = kThreads>
-__device__ __forceinline__ double block_sum(double v, double* lds_waves) {
+__device__ __forceinline__ double block_sum(double v, double* lds_waves, int lanes = T) {
     v = wave_sum(v);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane == 0) lds_waves[wave] = v;
@@ -302,7 +303,8 @@ __device__ __forceinline__ double block_sum(double v, double* lds_waves) {
     double r = 0.0;
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int i = 0; i < T / 64; i += 2) r += lds_waves[i] + lds_waves[i + 1];
+        for (int i = 0; i < T / 64; i += 2)
+            r += (64 * i < lanes ? lds_waves[i] : 0.0) + (64 * (i + 1) < lanes ? lds_waves[i + 1] : 0.0);
     }
     return r;  // valid in thread 0
 }

@@ -279,6 +279,9 @@ inline bool long_rows(const DeviceInfo& di, int64_t column_groups, int sweeps = 
     return column_groups >= (int64_t)di.cus * kRingThreads * sweeps;
 }
 
+// Lanes of a workgroup that takes `sw.chunk` column groups at a time, without a wavefront that has none.
+inline int sweep_threads(const Sweeps& sw) { return ((int)sw.chunk + 63) / 64 * 64; }
+
 // Every row of X and X_out starts on `bytes` (a power of two): a 128-byte line, or a lane's 16 bytes.
 inline bool rows_start_on(int bytes, const float* X, const float* X_out, const Pitch& ld) {
     return aligned_to(X, bytes) && aligned_to(X_out, bytes) && ld.x % (bytes / 4) == 0 && ld.o % (bytes / 4) == 0;
@@ -558,12 +561,13 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : persistent_grid(*di, ncg, kGridPerCu);
 #define PSGD_LAUNCH_FULL(CD, T)                                                                                            \
     do {                                                                                                                   \
+        const Sweeps sw = make_sweeps(ncg, grid, T);                                                                       \
         if (d % kVec)                                                                                                      \
-            hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, true>), dim3(grid), dim3(T), 0, s, X, X_out, G, n, d, ld,        \
-                               neg_lr, make_sweeps(ncg, grid, T), partials);                                               \
+            hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, true>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, X_out, G,  \
+                               n, d, ld, neg_lr, sw, partials);                                                            \
         else                                                                                                               \
-            hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, false>), dim3(grid), dim3(T), 0, s, X, X_out, G, n, d, ld,       \
-                               neg_lr, make_sweeps(ncg, grid, T), partials);                                               \
+            hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, false>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, X_out, G, \
+                               n, d, ld, neg_lr, sw, partials);                                                            \
     } while (0)
         if (big && want_cd) PSGD_LAUNCH_FULL(true, kRingThreads);
         else if (big) PSGD_LAUNCH_FULL(false, kRingThreads);
@@ -592,8 +596,13 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
         const int64_t ncg = (d + kVec - 1) / kVec;
         if (long_rows(*di, ncg)) {
             grid = persistent_grid(*di, ncg, 1, kRingThreads);
-            hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads>), dim3(grid), dim3(kRingThreads), 0, s, X, n, d, ldx,
-                               make_sweeps(ncg, grid, kRingThreads), partials);
+            const Sweeps sw = make_sweeps(ncg, grid, kRingThreads);
+            if (d % kVec)
+                hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads, true>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d,
+                                   ldx, sw, partials);
+            else
+                hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads, false>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d,
+                                   ldx, sw, partials);
         } else {
             const plan::RowsPlan rp = plan::distance_rows_plan(n, d, di->cus);
             if (rp.threads != 0) {

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* 
         }
     }
     if (CD) {
-        const double bs = block_sum_any(total, lds_waves, T);
+        const double bs = block_sum<kRingThreads>(total, lds_waves, T);
         if (threadIdx.x == 0) partials[blockIdx.x] = bs;
     }
 }

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
         if (CD) total += stats.result(inv_n, c);
     }
     if (CD) {
-        const double bs = block_sum<T>(total, lds_waves);
+        const double bs = block_sum<T>(total, lds_waves, blockDim.x);
         if (threadIdx.x == 0) partials[blockIdx.x] = bs;
     }
 }
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(plan::kShortThreads, 4) void consensus_rows_kernel(
 // The same distance for long rows, in the form of the step kernels: one large workgroup per compute unit whose
 // wavefronts sweep the rows in lockstep batches, the column groups split evenly and die-contiguously over the
 // persistent grid.  A lane owns one column group per sweep.
-template <int T>
+template <int T, bool RAGGED>
 __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restrict__ X, int n, int64_t d, int64_t ldx,
                                                             Sweeps sweeps, double* __restrict__ partials) {
     typedef f32x4 V;
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restr
         const int64_t base = sweeps.base(sw), cg = base + threadIdx.x;
         if (base >= ncg) break;                                  // nothing left for this workgroup (uniform)
         const int64_t end = base + sweeps.chunk < ncg ? base + sweeps.chunk : ncg;   // uniform
-        const ColGroup c = col_group(cg < end ? cg : ncg, d);    // an idle lane owns nothing and shadows the last group
+        const ColGroup c = col_group_of<RAGGED>(cg < end ? cg : ncg, ncg, d);   // an idle lane owns nothing and shadows another
         const float* xc = X + c.col;
         double s[kVec], a[kVec], b[kVec];
         pivot_of(ld_x(xc), s);
@@ -288,12 +288,20 @@ __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restr
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) acc_diff(a, b, xs[u], s);
         }
-        for (; r < n; ++r) acc_diff(a, b, ld_x(xc + (int64_t)r * ldx), s);
+        if (r < n) {
+            V xs[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll - 1; ++u)
+                if (r + u < n) xs[u] = ld_x(xc + (int64_t)(r + u) * ldx);
+#pragma unroll
+            for (int u = 0; u < kUnroll - 1; ++u)
+                if (r + u < n) acc_diff(a, b, xs[u], s);
+        }
 #pragma unroll
         for (int k = 0; k < kVec; ++k)
-            if (k >= c.lo && k < c.hi) total += b[k] - a[k] * a[k] * inv_n;
+            if (RAGGED ? k >= c.lo && k < c.hi : c.lo == 0) total += b[k] - a[k] * a[k] * inv_n;
     }
-    const double bs = block_sum<T>(total, lds_waves);
+    const double bs = block_sum<T>(total, lds_waves, blockDim.x);
     if (threadIdx.x == 0) partials[blockIdx.x] = bs;
 }
 
