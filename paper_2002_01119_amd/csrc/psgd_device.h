@@ -456,8 +456,8 @@ struct Sweeps {
     }
 };
 // Computed by the launcher (the device would pay two 64-bit divisions per lane for it).
-inline Sweeps make_sweeps(int64_t ncg, int grid, int threads) {
-    const plan::SweepPlan p = plan::sweep_plan(ncg, grid, threads);
+inline Sweeps make_sweeps(int64_t ncg, int grid, int threads, bool even = true) {
+    const plan::SweepPlan p = plan::sweep_plan(ncg, grid, threads, even);
     return Sweeps{p.count, p.chunk};
 }
 

@@ -561,7 +561,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : persistent_grid(*di, ncg, kGridPerCu);
 #define PSGD_LAUNCH_FULL(CD, T)                                                                                            \
     do {                                                                                                                   \
-        const Sweeps sw = make_sweeps(ncg, grid, T);                                                                       \
+        const Sweeps sw = make_sweeps(ncg, grid, T, n > 8);                                                                \
         if (d % kVec)                                                                                                      \
             hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, true>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, X_out, G,  \
                                n, d, ld, neg_lr, sw, partials);                                                            \

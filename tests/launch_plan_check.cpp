@@ -21,8 +21,8 @@ static int failures = 0;
         }                                      \
     } while (0)
 
-static void check_cover(int64_t ncg, int grid, int threads) {
-    const SweepPlan p = sweep_plan(ncg, grid, threads);
+static void check_cover(int64_t ncg, int grid, int threads, bool even = true) {
+    const SweepPlan p = sweep_plan(ncg, grid, threads, even);
     CHECK(p.chunk >= 1 && p.chunk <= threads, "ncg=%lld grid=%d: chunk %lld", (long long)ncg, grid, (long long)p.chunk);
     CHECK(p.count < 4 || p.chunk % kChunkAlign == 0, "ncg=%lld grid=%d: chunk %lld unaligned", (long long)ncg, grid,
           (long long)p.chunk);
@@ -59,7 +59,10 @@ int main() {
     const int threads[] = {256, 768};
     for (int64_t ncg : rows)
         for (int g : grids)
-            for (int t : threads) check_cover(ncg, g, t);
+            for (int t : threads) {
+                check_cover(ncg, g, t);
+                check_cover(ncg, g, t, false);
+            }
     // the die-contiguous mapping permutes the ranges of a sweep among the workgroups: a bijection, and the
     // workgroups of one die (b, b + 8, ...) take neighbouring ranges
     for (int grid : {1, 7, 8, 16, 255, 256, 304, 1024}) {
@@ -82,6 +85,7 @@ int main() {
     const SweepPlan w4 = sweep_plan(2000000, 256, 768);
     CHECK(w4.count == 11 && w4.chunk == 720, "workload 4 plan %lld x %lld", (long long)w4.count, (long long)w4.chunk);
 
+    CHECK(sweep_plan(275000, 1024, 256, false).chunk == 256 && sweep_plan(275000, 1024, 256).chunk == 144, "full chunks where sweeps are short");
     // the ring walk's workgroups: every column group has a lane, and no wavefront of a single sweep is without one
     for (int64_t ncg : {(int64_t)1, (int64_t)49152, (int64_t)52500, (int64_t)88474, (int64_t)196608, (int64_t)196609, (int64_t)25000000}) {
         const SweepPlan p = sweep_plan(ncg, 256, 768);
