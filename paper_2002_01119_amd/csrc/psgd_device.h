@@ -19,10 +19,9 @@ namespace {
 constexpr int kThreads = 256;        // 4 wavefronts of 64 lanes
 constexpr int kRingThreads = 768;    // workgroup of the step kernels on long rows (12 wavefronts in lockstep, one per CU;
                                      // 1024 lanes would leave the fused distance too few registers)
-constexpr int kDeepThreads = 1024;   // workgroup of the tiled path on long rows, one-batch form: 16 wavefronts, four per
-                                     // SIMD, which is what keeps the slot loop's LDS round trips and arithmetic hidden
-constexpr int kTileThreads = 512;    // the same for shapes the one-batch form does not take (more than 64 learners at
-                                     // 16 B per lane): 8 wavefronts with up to 256 registers, several batches per tile
+constexpr int kDeepThreads = 1024;   // workgroup of the tiled path: 16 wavefronts, four per SIMD, which is what keeps the slot
+                                     // loop's LDS round trips and arithmetic hidden
+constexpr int kTileThreads = 512;    // the same with the distance: 8 wavefronts with up to 256 registers
 constexpr int kUnroll = 8;           // rows whose loads are in flight together per lane
 using plan::kMaxGrid;                // upper bound on persistent workgroups (partials buffer sizing)
 constexpr int kGridPerCu = 4;        // persistent workgroups per compute unit (16 waves per CU)
@@ -193,6 +192,8 @@ struct Lds {
 __host__ __device__ inline size_t lds_table_bytes(int n) {
     return (((size_t)n * (sizeof(RingEnt) + 3 * (sizeof(int) + sizeof(float)))) + 15) & ~(size_t)15;
 }
+// with the ranking arrays
+__host__ __device__ inline size_t lds_classify_bytes(int n) { return lds_table_bytes(n) + (size_t)n * 4 * sizeof(int); }
 __device__ __forceinline__ Lds carve(char* base, int n) {
     Lds l;
     l.ring = reinterpret_cast<RingEnt*>(base);

@@ -102,41 +102,32 @@ inline bool ring_rows(int n, int64_t ncg, int cus, int threads) {
     return ncg * 4 >= (n < 29 ? 32 * sweep : n < 48 ? 6 * sweep : n < 96 ? 5 * sweep : n < 256 ? 8 * sweep / 5 : sweep);
 }
 
-// LDS of the tiled path (tables that are not one ring): the slot table (8 bytes per slot), TWO tile buffers of
-// n rows x lpr lanes x vec floats (the next tile is staged while the current one is read), and, when the
-// consensus distance is gathered in the same pass, the merge slots of the column sums: one double per column
-// and per wavefront (lpr <= 64: row groups inside a wavefront merge by shuffles) or per row group (lpr > 64),
-// plus a float per slot where row groups are whole wavefronts (lpr >= 64: each keeps its own pivot).
-// `lpr`, the lanes that share a row, is the largest power of two <= threads for which all of it, plus `base`
-// bytes the kernel keeps for itself, fits `cap`; rows wider than a wavefront (lpr > 64) are only taken while a
-// lane still gets at most `rows_per_batch` rows, which is what few learners need to keep enough bytes in flight
-// (n = 16: 256 lanes per row, 8 rows per lane).  lpr = 0 if not even one lane per row fits.
-constexpr int kOneBatchMinLpr = 16;
+// LDS of the tiled path (long rows on lines, tables that are not one ring): the slot table (8 bytes per slot), TWO tile
+// buffers of n rows x lpr lanes x 16 bytes (the next tile is staged while the current one is read), and, when the
+// consensus distance is gathered in the same pass, the merge slots of the column sums: a double and a float (the row
+// group's own pivot) per column and row group.  They go into the buffer that has just been read (one more barrier per tile)
+// when they do not fit beside the two tiles.
+// `lpr`, the lanes that share a row, is the largest power of two <= threads for which all of it fits `cap` and every row
+// of a tile is in one batch, at most rows_per_batch rows per lane; at least 16 (256-byte row segments; also what keeps the
+// lanes that share a column in the merge inside one wavefront).  lpr = 0 if there is none.
+constexpr int kTileMinLpr = 16;
 struct TilePlan {
     int lpr;
-    bool comb_in_tile;   // one-batch form only: the merge slots of the distance live in the tile buffer just consumed
+    bool comb_in_tile;
     size_t tab_bytes, tile_bytes, comb_bytes, total;
 };
-// one_batch: plan for the large workgroup's one-batch form, which needs every row of a tile in one batch (at most
-// rows_per_batch rows per lane) and at least 16 lanes per row (256-byte row segments at 16 B per lane; also what
-// keeps the lanes that share a column in the merge of the distance inside one wavefront); it may put the merge
-// slots into the buffer it has finished reading (one more barrier per tile) when they do not fit beside the two
-// tiles.
-inline TilePlan tile_plan(int n, int deg, int vec, int threads, bool cd, size_t cap, size_t base, int rows_per_batch,
-                          bool one_batch = false) {
+inline TilePlan tile_plan(int n, int deg, int threads, bool cd, size_t cap, int rows_per_batch) {
     TilePlan p;
     p.comb_in_tile = false;
     p.tab_bytes = (((size_t)n * deg * 8) + 15) & ~(size_t)15;
-    for (p.lpr = threads; p.lpr >= (one_batch ? kOneBatchMinLpr : 1); p.lpr >>= 1) {
+    for (p.lpr = threads; p.lpr >= kTileMinLpr; p.lpr >>= 1) {
         const int nrg = threads / p.lpr;
-        const int rows = (n + nrg - 1) / nrg;
-        if ((one_batch || p.lpr > 64) && rows > rows_per_batch) continue;
-        const int slots = (one_batch || p.lpr > 64) ? nrg : threads / 64;   // one per row group, or per wavefront where row groups share one
-        p.tile_bytes = (((size_t)n * p.lpr * vec * 4) + 15) & ~(size_t)15;
-        p.comb_bytes = cd ? (size_t)slots * p.lpr * vec * (one_batch ? 12 : 8) : 0;   // one-batch form: + a float per slot, the row group's own pivot
-        p.total = base + p.tab_bytes + 2 * p.tile_bytes + p.comb_bytes;
+        if ((n + nrg - 1) / nrg > rows_per_batch) continue;
+        p.tile_bytes = (size_t)n * p.lpr * 16;
+        p.comb_bytes = cd ? (size_t)nrg * p.lpr * 48 : 0;
+        p.total = p.tab_bytes + 2 * p.tile_bytes + p.comb_bytes;
         if (p.total <= cap) return p;
-        if (one_batch && cd && p.comb_bytes <= p.tile_bytes && p.total - p.comb_bytes <= cap) {
+        if (cd && p.comb_bytes <= p.tile_bytes && p.total - p.comb_bytes <= cap) {
             p.comb_in_tile = true;
             p.total -= p.comb_bytes;
             return p;
@@ -201,10 +192,13 @@ inline ShortPlan short_widest(int n, int deg, int64_t ncg, bool cd, bool one, in
 //     travels twice.  Up to 128 column groups wide: 512 x 78 125 166 / 117, 200 x 200 013 131 / 110, 64 x 1 874 989 325 / 301,
 //     24 x 5 000 013 287 / 280; wider tiles lose (16 x 2 500 013 94 / 97), as do rows on lines (512 x 78 112 97 / 103); one tile each, up
 //     to 16 wide: 512 x 15 629 30.2 / 25.7 (128 wide, 64 x 125 005: 22.9 / 23.6).
+//   - Loads where bf16 gradients come in segments of half a line (8 column groups): neighbouring tiles share that line too.
+//     512 x 800 k without the distance 979 / 887, 300 x 800 k 570 / 502, with it 512 x 200 k 237 / 208.
 enum { kCachedLoads = 1, kCachedStores = 2 };
-inline int cached_accesses(const ShortPlan& p, int64_t bytes, bool on_lines) {
+inline int cached_accesses(const ShortPlan& p, int64_t bytes, bool on_lines, bool bf16) {
     if (!p.one && bytes <= (int64_t)128 << 20) return kCachedLoads;
-    return !on_lines && p.logc <= (p.one ? 4 : 7) ? kCachedLoads | kCachedStores : 0;
+    if (!on_lines && p.logc <= (p.one ? 4 : 7)) return kCachedLoads | kCachedStores;
+    return bf16 && !p.one && p.logc <= 3 ? kCachedLoads : 0;
 }
 // Workgroups of the looping form: one per tile up to what is resident together (128 registers per lane at four rows:
 // 1024 lanes per compute unit), at most `most`.

@@ -290,14 +290,17 @@ inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) {
 
 // Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
 // negative status.
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool SKIP_RINGS = false>
 int launch_short_t(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
-                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
-    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>);
-    if (int rc = allow_lds(fn, p.lds)) return rc;
-    const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? plan::kShortSlots : INT32_MAX);
-    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X, X_out,
-                       G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
+                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
+                   int64_t slots = plan::kShortSlots) {
+    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW, SKIP_RINGS>);
+    size_t lds = p.lds;
+    if (SKIP_RINGS && lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
+    if (int rc = allow_lds(fn, lds)) return rc;
+    const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? slots : INT32_MAX);
+    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW, SKIP_RINGS>), dim3(grid), dim3(p.threads), lds, s, X,
+                       X_out, G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
     return CD ? grid : 0;
 }
 
@@ -305,7 +308,8 @@ template <typename GT, bool CD, int DEG>
 int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
                  const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
     static_assert(plan::kShortSlots <= PSGD_STATIC_SLOTS && plan::kShortSlots <= kMaxGrid, "one partial per workgroup");
-    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld));
+    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
+                                             sizeof(GT) == 2);
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
 #define PSGD_SHORT(DEG, R, ONE, CACHED, FEW)                                                                              \
     return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials)
@@ -336,6 +340,36 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
     }
 #undef PSGD_SHORT_LOOP
 #undef PSGD_SHORT_ONE
+#undef PSGD_SHORT
+    return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
+}
+
+// The same kernel behind the ring walk, for 3-slot tables that are not one ring: rows long enough to loop and far too large
+// for the last-level cache.  `partials` and `slots`: what the ring walk has left.
+template <typename GT, bool CD>
+int launch_short_behind_ring(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out,
+                             const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr,
+                             double* partials, int64_t slots) {
+    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
+                                             sizeof(GT) == 2);
+    constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
+#define PSGD_SHORT(R, CACHED)                                                                                             \
+    return launch_short_t<GT, CD, 3, R, false, CACHED, false, true>(di, p, s, X, X_out, G, nbr, w, 3, n, d, ld, neg_lr,    \
+                                                                    partials, slots)
+#define PSGD_SHORT_BEHIND(R)                                                                                              \
+    case R:                                                                                                               \
+        if (R == 2 || cached == kBoth) PSGD_SHORT(R, kBoth);                                                              \
+        if constexpr (R != 2 && sizeof(GT) == 2)                                                                          \
+            if (cached) PSGD_SHORT(R, plan::kCachedLoads);                                                                \
+        if constexpr (R != 2) PSGD_SHORT(R, 0)
+    if (!p.one) {
+        switch (p.rows) {
+            PSGD_SHORT_BEHIND(2);
+            PSGD_SHORT_BEHIND(3);
+            PSGD_SHORT_BEHIND(4);
+        }
+    }
+#undef PSGD_SHORT_BEHIND
 #undef PSGD_SHORT
     return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
 }
@@ -381,11 +415,10 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // use, shared by every call on the device, streams serialised), or the static array of the entry point
     // that may not allocate (no serialisation: that would need an event).
     double* partials = nullptr;
-    int slots = kMaxGrid;
+    constexpr int slots = (int)plan::kShortSlots;
     if (want_cd) {
         if (no_alloc) {
             if (int rc = static_partials(di, &partials)) return rc;
-            slots = PSGD_STATIC_SLOTS;
         } else if (int rc = acquire_partials(di, s, &partials)) {
             return rc;
         }
@@ -400,93 +433,83 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
     const int64_t ncg = (d + kVec - 1) / kVec;
-    // Tables of other slot counts: on long rows the tiled kernel is as good or a little better while its row segments are
-    // wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5 slots 76.6 / 76.0),
-    // else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001 838 / 1322, 300 x 1.6 M
-    // 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).  Tables of 16 slots and more, bound by LDS reads,
-    // on 9 to 64 learners also where rows start on 16 bytes only (64 x 3 200 004 with 32 slots 674 / 599, 16 x 12 000 004 601 / 559), not on
-    // shorter rows (9 x 2.3 M with bf16 gradients 80 / 112).
+    // 3-slot tables: from plan::ring_rows on the ring-walk kernel does the work when the table is one ring (every table of
+    // Sec. 3); the kernel for any other table follows it, because each path wants its own workgroup shape and registers.
+    // That kernel, and the one for tables of other slot counts: on long rows the tiled kernel is as good or a little better while
+    // its row segments are wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5
+    // slots 76.6 / 76.0), else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001
+    // 838 / 1322, 300 x 1.6 M 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).  Tables of 16 slots and more, bound by LDS
+    // reads, on 9 to 64 learners also where rows start on 16 bytes only (64 x 3 200 004 with 32 slots 674 / 599, 16 x 12 000 004 601 /
+    // 559), not on shorter rows (9 x 2.3 M with bf16 gradients 80 / 112).  3-slot tables behind the ring walk: 200 x 1 000 001 513 / 738,
+    // 512 x 400 001 556 / 1084, 128 x 1 600 004 495 / 579, 24 x 6 400 004 365 / 390; on lines 64 x 2 M 297 / 297, 128 x 1.6 M 497 / 497.  29 to 32 learners, whose
+    // short-row tile is 128 column groups wide, are ahead on the tiled kernel off the lines too (32 x 1 400 004 124 / 116, 32 x 3 000 016
+    // with 13 slots 236 / 220).
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
-    const bool big = deg == 3 ? plan::ring_rows(n, ncg, di->cus, kRingThreads)
-                              : long_rows(*di, ncg) && n > 8 &&
-                                    ((n <= 128 && rows_on_lines(X, X_out, ld)) || (n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
-    if (!big) {
-        const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
-                                         : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
-        if (want_cd && deg == 3) grid = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else if (want_cd) grid = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else if (deg == 3) grid = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else grid = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        if (grid < 0) return grid;
-    }
-    const size_t classify = lds_table_bytes(n) + (size_t)n * 4 * sizeof(int);   // the 3-slot kernels' table copy + ranking arrays
-    if (big && deg == 3) {
-        // The ring-walk kernel does the work when the table is one ring (every table of Sec. 3); the tiled kernel
-        // follows it (below) for all others, because each path wants its own workgroup shape and registers.
-#define PSGD_RING(CD, RAGGED) launch_mix<GT, CD, RAGGED>(*di, classify, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots)
+    const bool wide = n > 8 && n <= 128 && (rows_on_lines(X, X_out, ld) || (n > 28 && n <= 32));
+    const bool ring = deg == 3 && plan::ring_rows(n, ncg, di->cus, kRingThreads);
+    const bool tiled = deg == 3 ? ring && wide
+                                : long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
+    if (ring) {
+#define PSGD_RING(CD, RAGGED)                                                                                             \
+    launch_mix<GT, CD, RAGGED>(*di, lds_classify_bytes(n), s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots - 1)
         if (d % kVec) grid = want_cd ? PSGD_RING(true, true) : PSGD_RING(false, true);
         else grid = want_cd ? PSGD_RING(true, false) : PSGD_RING(false, false);
 #undef PSGD_RING
         if (grid == kLaunchRefused) return PSGD_EHIP;   // allow_lds has recorded the reason
-        if (grid < 0)
-            return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, -grid, slots);
+        if (grid < 0)                                   // one more for the kernel behind it
+            return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, 1 - grid, slots);
         const hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return hip_fail(e1, name);
     }
-    if (big) {
-        // Tiled kernel: every table with another slot count, and behind the ring walk for 3-slot tables, where
-        // it does the work only if the table turns out not to be one ring (decided on the device by both).
-        // The 1024-lane one-batch form where the shape allows it (n <= 64 at 1 KB row segments; 512 lanes with the
-        // distance), else 512 lanes with several batches per tile.
-        const size_t base = 0;
-        const int deep_threads = want_cd ? kTileThreads : kDeepThreads;
-        plan::TilePlan tp = plan::tile_plan(n, deg, kVec, deep_threads, want_cd, kLdsCapLarge, base,
-                                            want_cd ? TileShape<kTileThreads>::RB : TileShape<kDeepThreads>::RB, true);
-        const bool deep = tp.lpr != 0;
-        if (!deep) tp = plan::tile_plan(n, deg, kVec, kTileThreads, want_cd, kLdsCapLarge, base, TileShape<kTileThreads>::RB);
+    const int first = want_cd ? grid : 0;
+    if (!tiled) {
+        const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
+                                         : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
+        int more = 0;
+        if (ring && want_cd)
+            more = launch_short_behind_ring<GT, true>(*di, sp, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials + first,
+                                                      slots - first);
+        else if (ring) more = launch_short_behind_ring<GT, false>(*di, sp, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, nullptr, 0);
+        else if (want_cd && deg == 3) more = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        else if (want_cd) more = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        else if (deg == 3) more = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        else more = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        if (more < 0) return more;
+        grid = first + more;
+    } else {
+        // 1024 lanes without the distance, 512 with it.
+        const int threads = want_cd ? kTileThreads : kDeepThreads;
+        const plan::TilePlan tp = plan::tile_plan(n, deg, threads, want_cd, kLdsCapLarge,
+                                                  want_cd ? TileShape<kTileThreads>::RB : TileShape<kDeepThreads>::RB);
         if (tp.lpr == 0)
             return fail(PSGD_EINVAL, "%s: n=%d, deg=%d does not fit the tiled path's LDS", name, n, deg);
-        const int lpr = tp.lpr;
         size_t lds_bytes = tp.total;
-        if (deg == 3 && lds_bytes < tp.tab_bytes + classify) lds_bytes = tp.tab_bytes + classify;
+        if (ring && lds_bytes < tp.tab_bytes + lds_classify_bytes(n)) lds_bytes = tp.tab_bytes + lds_classify_bytes(n);
         const size_t remainder = (size_t)n * (d % kVec) * 2 * sizeof(float);
         if (lds_bytes < tp.tab_bytes + remainder) lds_bytes = tp.tab_bytes + remainder;
-        const int64_t ntiles = (d / kVec + lpr - 1) / lpr;
-        const int first = grid;
+        const int64_t ntiles = (d / kVec + tp.lpr - 1) / tp.lpr;
         int tgrid = 0;
-#define PSGD_DEG_LAUNCH(CD, T, DEEP)                                                                                   \
-    do {                                                                                                                \
-        const void* fn = reinterpret_cast<const void*>(mix_deg_kernel<GT, CD, T, DEEP>);                           \
-        if (int rc = allow_lds(fn, lds_bytes)) return rc;                                                               \
-        int per_cu = resident_per_cu(fn, lds_bytes, T);                                                                 \
-        if (per_cu > 2 * kGridPerCu) per_cu = 2 * kGridPerCu;                                                           \
-        tgrid = deg_grid(ntiles, di->cus, per_cu);                                                                      \
-        if (CD && first + tgrid > slots) {   /* one partial per workgroup: a smaller persistent grid still covers */    \
-            tgrid = slots - first;           /* every tile                                                        */    \
-            if (tgrid < 1) {                                                                                            \
-                tgrid = -(first + 1);                                                                                   \
-                break;                                                                                                  \
-            }                                                                                                           \
-        }                                                                                                               \
-        hipLaunchKernelGGL((mix_deg_kernel<GT, CD, T, DEEP>), dim3(tgrid), dim3(T), lds_bytes, s, X, X_out, G,     \
-                           nbr, w,                                                                                     \
-                           deg, n, d, ld, neg_lr, lpr, deg == 3 ? 1 : 0, tp.comb_in_tile ? 1 : 0,                    \
-                           CD ? partials + first : partials);             \
+#define PSGD_DEG_LAUNCH(CD, UQ)                                                                                           \
+    do {                                                                                                                  \
+        constexpr int T = CD ? kTileThreads : kDeepThreads;                                                               \
+        const void* fn = reinterpret_cast<const void*>(mix_deg_kernel<GT, CD, T, UQ>);                                    \
+        if (int rc = allow_lds(fn, lds_bytes)) return rc;                                                                 \
+        int per_cu = resident_per_cu(fn, lds_bytes, T);                                                                   \
+        if (per_cu > 2 * kGridPerCu) per_cu = 2 * kGridPerCu;                                                             \
+        tgrid = deg_grid(ntiles, di->cus, per_cu);                                                                        \
+        /* one partial per workgroup: a smaller persistent grid still covers every tile */                                \
+        if (CD && tgrid > slots - first) tgrid = slots - first;                                                           \
+        hipLaunchKernelGGL((mix_deg_kernel<GT, CD, T, UQ>), dim3(tgrid), dim3(T), lds_bytes, s, X, X_out, G, nbr, w, deg, \
+                           n, d, ld, neg_lr, tp.lpr, ring ? 1 : 0, tp.comb_in_tile ? 1 : 0,                               \
+                           CD ? partials + first : partials);                                                            \
     } while (0)
-#define PSGD_DEG_PICK(CD)                                                                                          \
-    do {                                                                                                                \
-        if (deep && tp.lpr >= 64) PSGD_DEG_LAUNCH(CD, (CD ? kTileThreads : kDeepThreads), 1);                      \
-        else if (deep) PSGD_DEG_LAUNCH(CD, (CD ? kTileThreads : kDeepThreads), 2);                                 \
-        else PSGD_DEG_LAUNCH(CD, kTileThreads, 0);                                                                 \
-    } while (0)
-        if (want_cd) PSGD_DEG_PICK(true);
-        else PSGD_DEG_PICK(false);
-#undef PSGD_DEG_PICK
+        if (want_cd && tp.lpr >= 64) PSGD_DEG_LAUNCH(true, true);
+        else if (want_cd) PSGD_DEG_LAUNCH(true, false);
+        else if (tp.lpr >= 64) PSGD_DEG_LAUNCH(false, true);
+        else PSGD_DEG_LAUNCH(false, false);
 #undef PSGD_DEG_LAUNCH
-        grid = tgrid < 0 ? tgrid : first + tgrid;
+        grid = first + tgrid;
     }
-    if (grid < 0)
-        return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, -grid, slots);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
     if (want_cd) {

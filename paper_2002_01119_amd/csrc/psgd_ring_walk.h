@@ -82,9 +82,9 @@ __device__ __forceinline__ void ring_walk(const float* xc, float* oc, const GT* 
 
 // CD = also reduce the consensus distance of the outputs into partials[blockIdx.x].
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
-// same number of sweeps, lanes beyond the chunk idle.
-// A table that is not one ring is left to the tiled kernel, which the launcher enqueues right behind this one and which
-// classifies the table the same way; this kernel then writes nothing.
+// same number of sweeps, lanes beyond the chunk idle; the launch has no more wavefronts than one sweep needs (plan::ring_threads).
+// A table that is not one ring is left to the kernel that the launcher enqueues right behind this one (tiled, or the short-row
+// kernel) and that classifies the table the same way; this kernel then writes nothing.
 // RAGGED: 4 does not divide d.
 template <typename GT, bool CD, bool RAGGED>
 __global__ __launch_bounds__(kRingThreads, 3) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,

@@ -36,8 +36,9 @@ namespace {
 // ---------------------------------------------------------------------------------------
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (twice the rows per lane: nothing is loaded ahead,
 // so their registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
-// FEW: rows of fewer than four columns.
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+// FEW: rows of fewer than four columns.  SKIP_RINGS: enqueued behind the ring walk, which leaves tables that are not one ring to this
+// kernel; both classify the table with the same code, and the one it does not belong to writes nothing (and contributes 0 to the distance).
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool SKIP_RINGS = false>
 __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
     const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
     int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
@@ -61,6 +62,13 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
 
+    if (SKIP_RINGS) {
+        const int kind = stage_table(nbr, w, n, carve(lds_raw, n), T);
+        if (kind != kTableGeneral) {                            // out of range: the ring walk has raised the flag
+            if (CD && tid == 0) partials[blockIdx.x] = kind == kTableRing ? 0.0 : __builtin_nan("");
+            return;
+        }
+    }
     // The table's loads go first, the first tile's behind them; a lane's share of a larger table follows.
     constexpr int TE = 2;
     int32_t tv[TE];

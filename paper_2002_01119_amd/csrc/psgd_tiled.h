@@ -1,5 +1,5 @@
-// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows for mixing tables that are not one ring, and its
-// kernel mix_deg_kernel.  Included by psgd_kernels.hip only.
+// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows that start on lines, for mixing tables that are
+// not one ring, and its kernel mix_deg_kernel.  Included by psgd_kernels.hip only.
 #ifndef PSGD_TILED_H
 #define PSGD_TILED_H
 
@@ -19,10 +19,8 @@ namespace {
 // the next tile.  A tile is complete in LDS before its first output is stored, and different tiles own
 // different columns, so X_out may alias X.
 //
-// Two forms.  tile_path_deep (up to 256 learners): the tile's rows are one batch, every memory
-// operation is unconditional, and a lane reloads each of its registers the moment its value has been used (see
-// there).  tile_path (more learners): several batches per tile, the next tile's
-// batch travelling while this tile's is computed, loads under conditions.
+// The tile's rows are one batch, every memory operation is unconditional, and a lane reloads each of its registers
+// the moment its value has been used (tile_path).
 //
 // Per output the slots are taken in table order, acc = w0 * x0, one fma per further slot, then the gradient
 // term (for 3 slots exactly mix_one's order).  The slot loop is the latency-critical part (a table read, then
@@ -30,12 +28,8 @@ namespace {
 // independent chains hide each other's LDS round trips.
 //
 // With CD the distance of the outputs is gathered in the same pass.  The rows of one column group are spread
-// over the row groups.  tile_path: all of them measure against ONE pivot, the output of row 0, which every row
-// group computes for itself (bit-identical: same tile, same table, same gradient bits); the squares then add up
-// lane by lane and only the plain sums need merging per column: across the row groups that share a wavefront by
-// shuffles, across wavefronts through one LDS slot each, summed in fixed order (tile_finish).  tile_path_deep:
-// every row group measures against its own first output and the merge brings the sums to row group 0's pivot
-// exactly (tile_finish_own).
+// over the row groups; every row group measures against its own first output and the merge brings the sums to row
+// group 0's pivot exactly (tile_finish).
 // ---------------------------------------------------------------------------------------
 // The value of the lane whose number differs in bit 0 (CTRL 0xB1: quad order 1,0,3,2) or bit 1 (0x4E: 2,3,0,1),
 // moved inside the vector unit (no LDS round trip).  All four lanes of a quad must be active.
@@ -66,48 +60,36 @@ struct TileCtx {
 
 // Running sums of the distance for one lane and one tile.
 struct TileStats {
-    double piv[kVec], a[kVec], sq;
-    float pivf[kVec];   // the pivot as the fp32 output it is (row groups with a pivot of their own keep it in this form)
+    double a[kVec], sq;
+    float pivot[kVec];   // the pivot as the fp32 output it is
     __device__ __forceinline__ void reset() {
         sq = 0.0;
 #pragma unroll
         for (int k = 0; k < kVec; ++k) {
-            piv[k] = a[k] = 0.0;
-            pivf[k] = 0.0f;
+            a[k] = 0.0;
+            pivot[k] = 0.0f;
         }
     }
 };
 
-// Rows rg + (b RB + u) nrg, u < RB, of the tile in `cur`: mix, subtract the gradient, store, gather.  With CD and
-// `with_pivot` the list starts with one more item, row 0 of the lane's columns with its gradient g0: its output is
-// the pivot the distance sums are taken against (computed, not stored; it rides along with the first rows so that
-// its chain of LDS reads costs no latency of its own).
+// Rows rg + u nrg, u < RB, of the tile in `cur`: mix, subtract the gradient, store, gather.
 //
-// CLAMP: nothing here is conditional except the arithmetic of the distance.  A lane without a row (or without a
+// Nothing here is conditional except the arithmetic of the distance.  A lane without a row (or without a
 // column group: the caller then points it at the last valid one) repeats the work of the lane that owns the
 // clamped row and column and stores the same bits to the same place.  This is what lets loads that were issued
 // early stay in flight: the compiler counts outstanding memory operations to wait for exactly the ones it
 // needs, and a load or store that may or may not have been issued makes that count unknown, upon which it
 // waits for all of them.
 //
-// OWNPIV (with CLAMP and CD): no extra item; the lane's first own output is its pivot, and the merge at the end
-// of the tile brings the row groups' sums to one common pivot (tile_finish_own).
-//
 // `feed(j0)` runs in front of every group of SB rows and `refill(j0)` behind it (its gradients have been used,
 // its outputs stored): the caller's places for the loads of the next tiles, so that they enter the memory
 // pipeline a few at a time between the rows' arithmetic instead of in one burst.
-struct NoFeed {
-    __device__ __forceinline__ void operator()(int) const {}
-};
-template <bool CD, int RB, int SB, bool CLAMP, bool OWNPIV, typename GR, typename FEED = NoFeed,
-          typename REFILL = NoFeed>
-__device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, int b, const GR (&g)[RB],
-                                          GR g0, bool with_pivot, bool active, float* out_col, int64_t ldo,
-                                          TileStats& st, const FEED& feed = FEED{}, const REFILL& refill = REFILL{}) {
+template <bool CD, int RB, int SB, typename GR, typename FEED, typename REFILL>
+__device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, const GR (&g)[RB], bool active, float* out_col,
+                                          int64_t ldo, TileStats& st, const FEED& feed, const REFILL& refill) {
     typedef f32x4 V;
-    constexpr int P = (CD && !OWNPIV) ? 1 : 0, ITEMS = RB + P;
 #pragma unroll
-    for (int j0 = 0; j0 < ITEMS; j0 += SB) {
+    for (int j0 = 0; j0 < RB; j0 += SB) {
         feed(j0);
         const TileSlot* tp[SB];
         bool ok[SB];
@@ -115,16 +97,10 @@ __device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, in
         V acc[SB];
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
-            const int j = j0 + i;
-            const bool piv = P && j == 0;
-            row[i] = piv ? 0 : c.rg + (b * RB + (j - P)) * c.nrg;
-            ok[i] = j < ITEMS && active && (piv ? with_pivot : row[i] < c.n);
-            if (CLAMP) {
-                if (row[i] > c.n - 1) row[i] = c.n - 1;
-                tp[i] = c.tab + row[i] * c.deg;
-            } else {
-                tp[i] = c.tab + (ok[i] ? row[i] : 0) * c.deg;     // an idle item follows row 0 and stores nothing
-            }
+            row[i] = c.rg + (j0 + i) * c.nrg;
+            ok[i] = active && row[i] < c.n;
+            if (row[i] > c.n - 1) row[i] = c.n - 1;
+            tp[i] = c.tab + row[i] * c.deg;
         }
         {
             TileSlot e[SB];
@@ -155,7 +131,7 @@ __device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, in
             }
         };
         int s = 1;
-        if (RB == 4 || (CLAMP && CD && sizeof(GR) > 8)) {
+        if (RB == 4 || (CD && sizeof(GR) > 8)) {
 #pragma unroll 1
             for (; s + 1 < c.deg; s += 2) trip(s);
         } else {
@@ -171,22 +147,18 @@ __device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, in
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
             const int j = j0 + i;
-            if (P && j == 0) {
-                if (CLAMP || ok[i]) pivot_of(vfma(c.neg_lr, widen_g(g0), acc[i]), st.piv);
-            } else if (j < ITEMS) {
-                if (CLAMP || ok[i]) {
-                    const V out = vfma(c.neg_lr, widen_g(g[j - P < 0 ? 0 : j - P]), acc[i]);
-                    st_x(out_col + (int64_t)row[i] * ldo, out);
-                    if (CD && OWNPIV && j == 0) floats_of(out, st.pivf);
-                    if (CD && ok[i]) {
-                        double o[kVec];
-                        pivot_of(out, o);      // widen
+            if (j < RB) {
+                const V out = vfma(c.neg_lr, widen_g(g[j]), acc[i]);
+                st_x(out_col + (int64_t)row[i] * ldo, out);
+                if (CD && j == 0) floats_of(out, st.pivot);
+                if (CD && ok[i]) {
+                    double o[kVec];
+                    pivot_of(out, o);      // widen
 #pragma unroll
-                        for (int k = 0; k < kVec; ++k) {
-                            const double df = o[k] - (OWNPIV ? (double)st.pivf[k] : st.piv[k]);
-                            st.a[k] += df;
-                            st.sq = fma(df, df, st.sq);
-                        }
+                    for (int k = 0; k < kVec; ++k) {
+                        const double df = o[k] - (double)st.pivot[k];
+                        st.a[k] += df;
+                        st.sq = fma(df, df, st.sq);
                     }
                 }
             }
@@ -195,52 +167,17 @@ __device__ __forceinline__ void tile_rows(const TileCtx& c, const f32x4* cur, in
     }
 }
 
-// Merge of the column sums at the end of a tile (CD only).  Contains the tile's barrier: when it returns every
-// read of the current buffer and every write of the other one is done.
-template <bool CD, int T>
-__device__ __forceinline__ void tile_finish(const TileCtx& c, double* comb, bool active, TileStats& st,
-                                            double inv_n, double& total) {
-    if (CD) {
-        // first across the row groups that share a wavefront (lanes lpr apart hold the same columns; the exchange
-        // is symmetric, so all of them end with the same bits), then one slot per wavefront in LDS
-        // (rows wider than a wavefront: a row group is whole wavefronts, one slot per row group)
-        const int wl = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int k = 0; k < kVec; ++k) {
-            if (c.lpr <= 64) {
-                for (int off = c.lpr; off < 64; off <<= 1) st.a[k] += __shfl_xor(st.a[k], off, 64);
-                if (wl < c.lpr) comb[(size_t)(wave * c.lpr + wl) * kVec + k] = st.a[k];
-            } else {
-                comb[(size_t)(c.rg * c.lpr + c.lane) * kVec + k] = st.a[k];
-            }
-        }
-        total += st.sq;
-    }
-    lds_barrier();
-    if (CD) {
-        if (active && c.rg == 0) {
-            const int slots = c.lpr <= 64 ? T / 64 : c.nrg;
-#pragma unroll
-            for (int k = 0; k < kVec; ++k) {
-                double at = 0.0;
-                for (int q = 0; q < slots; ++q) at += comb[(size_t)(q * c.lpr + c.lane) * kVec + k];
-                total -= at * at * inv_n;
-            }
-        }
-        lds_barrier();                                 // the merge slots are free again
-    }
-}
-
-// The same for row groups that each measured against their own pivot p_q (their first output): with P = p_0,
-// D_q = p_q - P and m_q rows in group q,
+// Merge of the column sums at the end of a tile (CD only), brought from each row group's own pivot p_q (its first
+// output) to a common one: with P = p_0, D_q = p_q - P and m_q rows in group q,
 //     sum_i (o_i - P)   = sum_q (a_q + m_q D_q)
 //     sum_i (o_i - P)^2 = sum_q (sq_q + 2 D_q a_q + m_q D_q^2)
 // exactly; in fp64 the corrections are of the size of the sums themselves (every pivot is one of the outputs).
 // If all outputs of a column are equal every D_q is 0 and the distance comes out exactly 0.  One slot per row
-// group and column: a double for the sum and a float for the pivot.
+// group and column: a double for the sum and a float for the pivot.  Contains the tile's barriers: when it returns every
+// read of the current buffer and every write of the other one is done.
 template <int T>
-__device__ __forceinline__ void tile_finish_own(const TileCtx& c, double* comb, float* combp, int live_cols,
-                                                TileStats& st, double inv_n, double& total) {
+__device__ __forceinline__ void tile_finish(const TileCtx& c, double* comb, float* combp, int live_cols,
+                                            TileStats& st, double inv_n, double& total) {
     // live_cols: the lanes of the tile that own a column group (all of them except in the ragged last tile)
     // slot of row group q, column k of lane l: (q kVec + k) lpr + l, so that the lanes of a wavefront write
     // neighbouring words (no bank conflicts); the merge below numbers the tile's columns in the same order
@@ -249,7 +186,7 @@ __device__ __forceinline__ void tile_finish_own(const TileCtx& c, double* comb, 
 #pragma unroll
     for (int k = 0; k < kVec; ++k) {
         comb[mine + k * c.lpr] = st.a[k];
-        combp[mine + k * c.lpr] = st.pivf[k];
+        combp[mine + k * c.lpr] = st.pivot[k];
     }
     total += st.sq;
     lds_barrier();
@@ -304,126 +241,18 @@ __device__ __forceinline__ void tile_finish_own(const TileCtx& c, double* comb, 
     lds_barrier();                                     // the merge slots are free again
 }
 
-template <typename GT, bool CD, int T>
-__device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ G, const TileSlot* tab, char* tiles,
-                            int n, int deg, Pitch ld, int64_t ncg, float neg_lr, int lpr, double inv_n) {
-    typedef f32x4 V;
-    typedef typename RawG<GT>::T GR;
-    constexpr int RB = TileShape<T>::RB, SB = TileShape<T>::SB;
-    TileCtx c;
-    c.tab = tab;
-    c.n = n;
-    c.deg = deg;
-    c.lpr = lpr;
-    c.lane = c.tlane = threadIdx.x % lpr;
-    c.rg = threadIdx.x / lpr;
-    c.nrg = T / lpr;
-    c.rows_each = n / c.nrg;
-    c.rows_more = n % c.nrg;
-    c.neg_lr = neg_lr;
-    const int lane = c.lane, rg = c.rg, nrg = c.nrg;
-    const int nb = ((n + nrg - 1) / nrg + RB - 1) / RB;      // batches per tile: the same for every lane
-    const size_t tile_bytes = (((size_t)n * lpr * sizeof(V)) + 15) & ~(size_t)15;
-    V* cur = reinterpret_cast<V*>(tiles);
-    V* nxt = reinterpret_cast<V*>(tiles + tile_bytes);
-    double* comb = reinterpret_cast<double*>(tiles + 2 * tile_bytes);   // [T / 64][lpr][kVec], CD only
-    const int64_t ntiles = (ncg + lpr - 1) / lpr;
-    const int64_t step = gridDim.x;
-    int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds);   // the first of tiles t, t + step, ...
-    if (t >= ntiles) return 0.0;                             // uniform: the whole workgroup has nothing to do
-    double total = 0.0;
-    TileStats st;
-
-    // Loads of one batch of one tile: X rows into xs, gradient rows into g (nothing beyond the last tile or the
-    // ragged end of the rows).
-    auto col_of = [&](int64_t tile) { return (tile * lpr + lane) * kVec; };
-    auto live = [&](int64_t tile) { return tile < ntiles && tile * lpr + lane < ncg; };
-    // `q` is the lane's row group: rg, or the same number held in a scalar register where it is known to be
-    // uniform over the wavefront (row offsets and table addresses then cost no vector registers).
-    auto load_x = [&](int q, int64_t tile, int b, V (&xs)[RB]) {
-        const bool on = live(tile);
-        const int64_t col = col_of(tile);
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            const int r = q + (b * RB + u) * nrg;
-            if (on && r < n) xs[u] = ld_x(X + (int64_t)r * ld.x + col);
-        }
-    };
-    auto load_g = [&](int q, int64_t tile, int b, GR (&g)[RB]) {
-        const bool on = live(tile);
-        const int64_t col = col_of(tile);
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            const int r = q + (b * RB + u) * nrg;
-            if (on && r < n) g[u] = ld_g_raw(G + (int64_t)r * ld.g + col);
-        }
-    };
-    auto stash = [&](int q, int64_t tile, int b, V* buf, const V (&xs)[RB]) {
-        const bool on = live(tile);
-#pragma unroll
-        for (int u = 0; u < RB; ++u) {
-            const int r = q + (b * RB + u) * nrg;
-            if (on && r < n) buf[r * lpr + lane] = xs[u];
-        }
-    };
-
-    // First tile: straight into `cur`.
-    for (int b = 0; b < nb; ++b) {
-        V xs[RB];
-        load_x(rg, t, b, xs);
-        stash(rg, t, b, cur, xs);
-    }
-
-    // Several batches per tile: batch b of the next tile travels while batch b of this one is computed, the
-    // gradients one batch ahead.
-    GR gcur[RB], g0 = {};
-    load_g(rg, t, 0, gcur);
-    if (CD && live(t)) g0 = ld_g_raw(G + col_of(t));
-    lds_barrier();
-    for (;;) {
-        const int64_t tn = t + step;
-        const bool active = live(t);
-        GR g0n = {};
-        if (CD) st.reset();
-        for (int b = 0; b < nb; ++b) {
-            V xs[RB];
-            GR gn[RB];
-            load_x(rg, tn, b, xs);
-            if (b + 1 < nb) {
-                load_g(rg, t, b + 1, gn);
-            } else {
-                load_g(rg, tn, 0, gn);
-                if (CD && live(tn)) g0n = ld_g_raw(G + col_of(tn));
-            }
-            tile_rows<CD, RB, SB, false, false>(c, cur, b, gcur, g0, b == 0, active, Xout + col_of(t), ld.o, st);
-            stash(rg, tn, b, nxt, xs);
-#pragma unroll
-            for (int u = 0; u < RB; ++u) gcur[u] = gn[u];
-        }
-        g0 = g0n;
-        tile_finish<CD, T>(c, comb, active, st, inv_n, total);
-        if (tn >= ntiles) break;
-        V* sw = cur;
-        cur = nxt;
-        nxt = sw;
-        t = tn;
-    }
-    return total;
-}
-
 // The tiled path of the large workgroup (1024 lanes without the distance, 512 with it; alone on its compute
 // unit) for tables whose tile is ONE batch of rows: at most TileShape<T>::RB rows per lane (n = 64 with 1 KB row
 // segments, fewer learners with wider ones, up to 256 learners with narrower ones).  The launcher picks the
-// shape (plan::tile_plan, one-batch form).
+// shape (plan::tile_plan).
 // With `comb_in_tile` the merge slots of the distance are the tile buffer that has just been consumed.
 //
 // UQ: a row group is whole wavefronts (lpr >= 64), so its number is the same in every lane of a wavefront and is
 // kept in a scalar register: row offsets and table addresses then cost no vector registers.  Narrower rows
 // (n > 64 at 16 B per lane: two or four row groups share a wavefront) keep it per lane.
 template <typename GT, bool CD, int T, bool UQ>
-__device__ double tile_path_deep(const float* X, float* Xout, const GT* __restrict__ G, const TileSlot* tab, char* tiles,
-                                 int n, int deg, Pitch ld, int64_t ncg, float neg_lr, int lpr, double inv_n,
-                                 bool comb_in_tile) {
+__device__ double tile_path(const float* X, float* Xout, const GT* __restrict__ G, const TileSlot* tab, char* tiles, int n,
+                            int deg, Pitch ld, int64_t ncg, float neg_lr, int lpr, double inv_n, bool comb_in_tile) {
     typedef f32x4 V;
     typedef typename RawG<GT>::T GR;
     constexpr int RB = TileShape<T>::RB, SB = TileShape<T>::SB;
@@ -523,7 +352,7 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
         const bool active = t * lpr + lane < ncg;
         c.tlane = (int)(cge - t * lpr);
         if (CD) st.reset();
-        tile_rows<CD, RB, SB, true, true>(c, cur, 0, g, GR{}, false, active, Xout + cge * kVec, ld.o, st, feed, refill);
+        tile_rows<CD, RB, SB>(c, cur, g, active, Xout + cge * kVec, ld.o, st, feed, refill);
         if (CD) {
             const int64_t left = ncg - t * lpr;                       // column groups of this tile (uniform)
             double* sums = comb;
@@ -531,8 +360,8 @@ __device__ double tile_path_deep(const float* X, float* Xout, const GT* __restri
                 lds_barrier();                                        // every row of `cur` has been read
                 sums = reinterpret_cast<double*>(cur);
             }
-            tile_finish_own<T>(c, sums, reinterpret_cast<float*>(sums + (size_t)nrg * lpr * kVec),
-                                    (int)(left < lpr ? left : lpr), st, inv_n, total);
+            tile_finish<T>(c, sums, reinterpret_cast<float*>(sums + (size_t)nrg * lpr * kVec),
+                           (int)(left < lpr ? left : lpr), st, inv_n, total);
         } else {
             lds_barrier();
         }
@@ -581,16 +410,15 @@ __device__ double tile_remainder(const float* X, float* Xout, const GT* __restri
 }
 
 // Any table with `deg` slots per row (sparse doubly stochastic matrices beyond the ring: more neighbours, lazy
-// walks, products of several mixing rounds, and 3-slot tables that are not one ring).  Always the tiled path.
+// walks, products of several mixing rounds, and 3-slot tables that are not one ring).
 // LDS: TileSlot tab[deg n] | two tile buffers | merge slots (plan::tile_plan).
 //
 // skip_rings (3-slot tables only): the launcher enqueues this kernel behind the ring-walk kernel because only
 // the device can tell which of the two a table needs; both classify it with the same code, and the one it does
 // not belong to writes nothing (and contributes 0 to the distance).
 //
-// DEEP: 0 = several batches per tile (tile_path); 1, 2 = the large workgroup's one-batch form (tile_path_deep)
-// with whole-wavefront rows (1) or narrower ones (2); the launcher has planned lpr for it.
-template <typename GT, bool CD, int T, int DEEP>
+// UQ: a row group is whole wavefronts (lpr >= 64).
+template <typename GT, bool CD, int T, bool UQ>
 __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                     const int32_t* __restrict__ nbr, const float* __restrict__ w,
                                                     int deg, int n, int64_t d, Pitch ld, float neg_lr, int lpr,
@@ -620,12 +448,8 @@ __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout,
         return;
     }
     const double inv_n = 1.0 / (double)n;
-    double total;
-    if (DEEP)
-        total = tile_path_deep<GT, CD, T, DEEP == 1>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / kVec, neg_lr, lpr,
-                                                     inv_n, comb_in_tile != 0);
-    else
-        total = tile_path<GT, CD, T>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / kVec, neg_lr, lpr, inv_n);
+    double total = tile_path<GT, CD, T, UQ>(X, Xout, G, tab, lds_raw + tab_bytes, n, deg, ld, d / kVec, neg_lr, lpr, inv_n,
+                                            comb_in_tile != 0);
     if (d % kVec != 0 && blockIdx.x == 0)
         total += tile_remainder<GT, CD, T>(X, Xout, G, nbr, w, reinterpret_cast<float*>(lds_raw + tab_bytes), n, deg, ld, d,
                                            neg_lr, inv_n);

@@ -109,74 +109,57 @@ int main() {
     CHECK(persistent_grid(256, 25000000, 1, 768) == 256, "workload 5 grid");
     CHECK(persistent_grid(256, 1000, 4, 256) == 4, "short rows take one workgroup per 256 items");
     CHECK(deg_grid(1 << 30, 1024, 8) == kMaxGrid, "deg_grid clamp");
-    // LDS plan of the tiled path: the widest power-of-two lane count whose slot table, two tile buffers and merge
-    // slots fit the cap; workload shapes get full 1 KB row segments (wider for few learners), and nothing ever
-    // exceeds the cap
-    const size_t large = 160 * 1024 - 1024, small_cap = 40 * 1024 - 256;
-    for (int n : {1, 2, 8, 16, 64, 65, 128, 300, 512})
-        for (int deg : {1, 3, 5, 8, 13, 32}) {
-            if ((long)n * deg > 4096) continue;
-            for (int vec : {1, 4})
-                for (int threads : {256, 512})
-                    for (bool cd : {false, true})
-                        for (size_t cap : {small_cap, large}) {
-                            const int rpb = threads > 256 ? 8 : 4;
-                            const TilePlan p = tile_plan(n, deg, vec, threads, cd, cap, 0, rpb);
-                            if (p.lpr == 0) {
-                                CHECK(cap == small_cap, "n=%d deg=%d vec=%d does not fit the large cap", n, deg, vec);
-                                continue;
-                            }
-                            CHECK(p.lpr >= 1 && p.lpr <= threads && (p.lpr & (p.lpr - 1)) == 0, "lpr %d", p.lpr);
-                            const int nrg = threads / p.lpr;
-                            CHECK(p.lpr <= 64 || (n + nrg - 1) / nrg <= rpb, "n=%d: %d lanes per row leave %d rows per lane", n,
-                                  p.lpr, (n + nrg - 1) / nrg);
-                            CHECK(p.total <= cap, "n=%d deg=%d: %zu bytes over the cap %zu", n, deg, p.total, cap);
-                            CHECK(p.tab_bytes >= (size_t)n * deg * 8 && p.tab_bytes % 16 == 0, "slot table size");
-                            CHECK(p.tile_bytes >= (size_t)n * p.lpr * vec * 4 && p.tile_bytes % 16 == 0, "tile size");
-                            const size_t slots = p.lpr <= 64 ? threads / 64 : nrg;
-                            CHECK(p.comb_bytes == (cd ? slots * p.lpr * vec * 8 : 0), "merge slots");
-                            CHECK(p.total == p.tab_bytes + 2 * p.tile_bytes + p.comb_bytes && !p.comb_in_tile, "total");
-                        }
-        }
-    CHECK(tile_plan(128, 3, 4, 512, true, large, 0, 8).lpr == 32, "n = 128: 512-byte row segments");
-    CHECK(tile_plan(70, 3, 4, 512, true, large, 0, 8).lpr == 64, "n = 70, several batches per tile: 1 KB row segments");
-    CHECK(tile_plan(75, 3, 4, 512, true, large, 0, 8).lpr == 32, "n = 75 with the distance: 512-byte row segments");
-    // one-batch form of the 1024-lane workgroup: whole-wavefront rows, at most 4 rows per lane, the merge slots
-    // (48 KB at 16 B per lane) inside the consumed tile buffer when they do not fit beside the two tiles
+    // LDS plan of the tiled path: the widest power-of-two lane count whose slot table, two tile buffers and merge slots
+    // fit, every row of a tile in one batch; the merge slots (48 KB at 1024 lanes) inside the consumed tile buffer when they
+    // do not fit beside the two tiles.  Every table of the learners it serves (9 to 128) has a plan.
+    const size_t large = 160 * 1024 - 1024;
     for (int n : {1, 2, 3, 5, 8, 9, 16, 20, 32, 48, 64, 65, 70, 128, 200, 256, 257, 512})
         for (int deg : {1, 3, 5, 13, 32})
-            for (int vec : {1, 4})
-                for (int threads : {512, 1024})
-                    for (bool cd : {false, true}) {
-                        if ((long)n * deg > 4096) continue;
-                        const int rpb = threads == 1024 ? 4 : 8;
-                        const TilePlan p = tile_plan(n, deg, vec, threads, cd, large, 0, rpb, true);
-                        if (p.lpr == 0) {
-                            CHECK(n > 256 || (long)n * deg * 8 > 24 * 1024, "n=%d deg=%d vec=%d cd=%d has no one-batch plan", n, deg, vec, (int)cd);
-                            continue;
-                        }
-                        const int nrg = threads / p.lpr;
-                        CHECK(p.lpr >= 16 && (p.lpr & (p.lpr - 1)) == 0 && (n + nrg - 1) / nrg <= rpb, "one-batch shape: lpr %d", p.lpr);
-                        CHECK(nrg <= 64, "n=%d: %d row groups, the lanes of a column would not fit a wavefront", n, nrg);
-                        CHECK(p.comb_bytes == (cd ? (size_t)nrg * p.lpr * vec * 12 : 0), "one-batch merge slots");
-                        CHECK(p.total == p.tab_bytes + 2 * p.tile_bytes + (p.comb_in_tile ? 0 : p.comb_bytes) && p.total <= large,
-                              "one-batch total");
-                        CHECK(!p.comb_in_tile || (cd && p.comb_bytes <= p.tile_bytes), "merge slots inside a tile buffer must fit it");
+            for (int threads : {512, 1024})
+                for (bool cd : {false, true}) {
+                    if ((long)n * deg > 4096) continue;
+                    const int rpb = threads == 1024 ? 4 : 8;
+                    const TilePlan p = tile_plan(n, deg, threads, cd, large, rpb);
+                    if (p.lpr == 0) {
+                        CHECK(n > 128, "n=%d deg=%d cd=%d has no tile", n, deg, (int)cd);
+                        continue;
                     }
+                    const int nrg = threads / p.lpr;
+                    CHECK(p.lpr >= 16 && (p.lpr & (p.lpr - 1)) == 0 && (n + nrg - 1) / nrg <= rpb, "tile shape: lpr %d", p.lpr);
+                    CHECK(nrg <= 64, "n=%d: %d row groups, the lanes of a column would not fit a wavefront", n, nrg);
+                    CHECK(p.tab_bytes >= (size_t)n * deg * 8 && p.tab_bytes % 16 == 0, "slot table size");
+                    CHECK(p.tile_bytes >= (size_t)n * p.lpr * 16 && p.tile_bytes % 16 == 0, "tile size");
+                    CHECK(p.comb_bytes == (cd ? (size_t)nrg * p.lpr * 48 : 0), "merge slots");
+                    CHECK(p.total == p.tab_bytes + 2 * p.tile_bytes + (p.comb_in_tile ? 0 : p.comb_bytes) && p.total <= large, "total");
+                    CHECK(!p.comb_in_tile || (cd && p.comb_bytes <= p.tile_bytes), "merge slots inside a tile buffer must fit it");
+                }
     {
-        const TilePlan p = tile_plan(64, 13, 4, 1024, true, large, 0, 4, true);
+        const TilePlan p = tile_plan(64, 13, 1024, true, large, 4);
         CHECK(p.lpr == 64 && p.comb_in_tile, "n = 64, 13 slots, distance: 1 KB row segments, merge slots in the tile");
-        CHECK(tile_plan(64, 3, 4, 1024, false, large, 0, 4, true).lpr == 64, "n = 64 without the distance");
-        CHECK(tile_plan(64, 13, 4, 512, true, large, 0, 8, true).lpr == 64 && !tile_plan(64, 13, 4, 512, true, large, 0, 8, true).comb_in_tile,
+        CHECK(tile_plan(64, 3, 1024, false, large, 4).lpr == 64, "n = 64 without the distance");
+        CHECK(tile_plan(64, 13, 512, true, large, 8).lpr == 64 && !tile_plan(64, 13, 512, true, large, 8).comb_in_tile,
               "n = 64 with the distance at 512 lanes: merge slots beside the tiles");
-        CHECK(tile_plan(16, 3, 4, 1024, true, large, 0, 4, true).lpr == 256, "n = 16: 4 KB row segments, 4 rows per lane");
-        CHECK(tile_plan(8, 3, 4, 1024, true, large, 0, 4, true).lpr == 512, "n = 8: 8 KB row segments");
-        CHECK(tile_plan(128, 3, 4, 1024, false, large, 0, 4, true).lpr == 32, "n = 128: 512-byte row segments, 32 row groups of 4 rows");
-        CHECK(tile_plan(128, 3, 4, 512, true, large, 0, 8, true).lpr == 32, "n = 128 with the distance: 16 row groups of 8 rows");
-        CHECK(tile_plan(256, 3, 4, 1024, false, large, 0, 4, true).lpr == 16, "n = 256: 256-byte row segments");
-        CHECK(tile_plan(257, 3, 4, 1024, false, large, 0, 4, true).lpr == 0, "n = 257: no one-batch plan");
-        CHECK(!tile_plan(64, 3, 1, 1024, true, large, 0, 4, true).comb_in_tile, "4 B per lane: the merge slots fit beside the tiles");
+        CHECK(tile_plan(64, 32, 512, true, large, 8).lpr == 64 && tile_plan(64, 32, 512, true, large, 8).comb_in_tile,
+              "n = 64, 32 slots, distance: merge slots in the tile");
+        CHECK(tile_plan(16, 3, 1024, true, large, 4).lpr == 256, "n = 16: 4 KB row segments, 4 rows per lane");
+        CHECK(tile_plan(8, 3, 1024, true, large, 4).lpr == 512, "n = 8: 8 KB row segments");
+        CHECK(tile_plan(128, 3, 1024, false, large, 4).lpr == 32, "n = 128: 512-byte row segments, 32 row groups of 4 rows");
+        CHECK(tile_plan(128, 3, 512, true, large, 8).lpr == 32, "n = 128 with the distance: 16 row groups of 8 rows");
+        CHECK(tile_plan(256, 3, 1024, false, large, 4).lpr == 16, "n = 256: 256-byte row segments");
+        CHECK(tile_plan(257, 3, 1024, false, large, 4).lpr == 0, "n = 257: no plan");
     }
+    // where the ring walk runs: the lines of each band of learners (in column groups, 256 compute units of 768 lanes), and what
+    // the short-row kernel behind it is built for there
+    const struct { int lo, hi; int64_t line; } bands[] = {{9, 28, 1572864}, {29, 47, 294912}, {48, 95, 245760}, {96, 255, 78643}, {256, 512, 49152}};
+    for (const auto& b : bands)
+        for (int n : {b.lo, (b.lo + b.hi) / 2, b.hi})
+            for (int64_t ncg : {b.line - 1, b.line, b.line * 3 + 1}) {
+                CHECK(ring_rows(n, ncg, 256, 768) == (ncg >= b.line), "ring walk: n=%d, %lld column groups", n, (long long)ncg);
+                const ShortPlan p = short_plan(n, 3, ncg, 256, n & 1, true);
+                CHECK(ncg < b.line || (!p.one && p.rows >= 2 && p.rows <= 4 && short_grid(p, 256, kShortSlots - 256) >= 1),
+                      "n=%d, %lld column groups: %d rows per lane behind the ring walk", n, (long long)ncg, p.rows);
+            }
+    for (int n : {1, 8}) CHECK(!ring_rows(n, (int64_t)1 << 32, 256, 768), "no ring walk for %d learners", n);
     // short rows: whole wavefronts, the rows covered, the LDS within a compute unit's, the grid within the buffer
     for (int n : {1, 2, 3, 5, 8, 9, 16, 17, 33, 64, 65, 100, 128, 200, 256, 257, 300, 511, 512})
         for (int deg : {1, 3, 8, 13, 32})

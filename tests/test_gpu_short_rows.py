@@ -1,5 +1,5 @@
-"""The short-row kernel, and the ring walk where it takes over, at the edges of their forms: one round of tiles at each workgroup size, all rows in one lane, the
-looping form with a ragged last tile, row counts that do not fill the row groups, rows of one to five columns, arrays
+"""The short-row kernel, and the ring walk where it takes over, at the edges of their forms: one round of tiles at each workgroup
+size, two rows per lane, all rows in one lane, the looping form with a ragged last tile, row counts that do not fill the row groups, rows of one to five columns, arrays
 whose rows start at any element.  Every element and the distance against the oracle's sparse form."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ from paper_2002_01119_amd import inputs as inp
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-# n, d, slots per row, gradients, elements between the rows of X / X_out / G beyond d (None: dense)
+# n, d, slots per row (-3: not one ring), gradients, elements between the rows of X / X_out / G beyond d (None: dense)
 CASES = [
     (1, 1, 3, "f32", None), (3, 2, 2, "bf16", (1, 2, 3)), (512, 3, 3, "f32", None), (256, 5, 4, "bf16", (3, 0, 5)),
     (2, 4, 3, "f32", (1, 1, 1)), (7, 257, 5, "bf16", None),
@@ -18,9 +18,17 @@ CASES = [
     (512, 6_001, 8, "bf16", (1, 2, 7)), (100, 50_002, 3, "f32", None),
     (8, 1_048_578, 3, "f32", None), (8, 1_200_003, 3, "bf16", (2, 3, 1)), (5, 1_570_001, 4, "f32", None),
     (9, 1_100_002, 3, "bf16", None), (16, 700_001, 5, "f32", (1, 2, 3)), (64, 200_003, 3, "bf16", (3, 1, 1)),
-    # either side of the line to the ring walk, whose last column group is ragged too; n = 64 is not a ring
+    # the ring walk, whose last column group is ragged too, in one sweep; n = 64 is not a ring: the short-row kernel behind it
     (128, 589_821, 3, "f32", (1, 2, 3)), (128, 589_825, 3, "bf16", (3, 1, 2)), (200, 600_002, 3, "f32", None),
     (64, 2_359_299, 3, "bf16", None),
+    # either side of the line to the ring walk, in each band of learners
+    (9, 6_291_452, 3, "bf16", None), (9, 6_291_453, 3, "bf16", None), (32, 1_179_644, 3, "f32", None), (32, 1_179_645, 3, "bf16", None),
+    (64, 983_036, -3, "bf16", None), (64, 983_037, -3, "f32", (1, 2, 3)), (128, 314_568, 3, "bf16", (3, 1, 2)),
+    (128, 314_569, 3, "f32", (1, 2, 3)), (256, 196_604, 3, "f32", None), (256, 196_605, 3, "bf16", None),
+    # 3-slot tables that are not one ring above it (-3): on lines the tiled kernel, its ragged end apart; else the short-row kernel
+    (33, 1_200_000, -3, "f32", None), (33, 1_200_002, -3, "bf16", (30, 62, 0)), (30, 1_200_003, -3, "f32", None),
+    (10, 6_300_003, -3, "bf16", None), (13, 6_300_001, -3, "f32", None), (100, 400_004, -3, "bf16", None), (136, 330_016, -3, "f32", None),
+    (200, 320_001, -3, "bf16", (1, 2, 3)), (257, 200_003, -3, "f32", None), (300, 200_032, -3, "bf16", None), (301, 200_032, -3, "f32", None),
     (100, 120_001, 3, "f32", None), (257, 40_007, 4, "bf16", None), (512, 20_002, 3, "f32", (1, 0, 2)),
     # two rows per lane: few columns, narrow and wide tables, either side of its lines
     (3, 1_001, 13, "f32", None), (4, 30_004, 9, "bf16", None), (6, 2_050, 3, "bf16", (1, 2, 3)), (8, 40_000, 32, "f32", None),
@@ -57,7 +65,8 @@ def _strided(a, extra, shift):
 @pytest.mark.parametrize("n,d,deg,gkind,extra", CASES)
 def test_short_rows_every_element(psgd, n, d, deg, gkind, extra):
     rng = np.random.default_rng(n + d)
-    if deg == 3 and n != 64:
+    ring, deg = deg == 3 and n != 64, abs(deg)
+    if ring:
         nbr, w = psgd.build_mixing(psgd.TOPO_RAND_RING, n, 5, d)
     else:
         c = rng.random(deg).astype(np.float32) + np.float32(0.05)
