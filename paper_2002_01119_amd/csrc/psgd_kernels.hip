@@ -313,14 +313,19 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
 #define PSGD_SHORT(DEG, R, ONE, CACHED, FEW)                                                                              \
     return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials)
+    // Only what the plan asks for is built: four rows and one tile are three or four learners on wide tiles, one row and
+    // several tiles a single learner; without a variant the accesses keep their hints.
 #define PSGD_SHORT_ONE(R)                                                                                                 \
     case R:                                                                                                               \
-        if (cached) PSGD_SHORT(DEG, R, true, kBoth, false);                                                               \
+        if constexpr (R != 4)                                                                                             \
+            if (cached) PSGD_SHORT(DEG, R, true, kBoth, false);                                                           \
         PSGD_SHORT(DEG, R, true, 0, false)
 #define PSGD_SHORT_LOOP(R)                                                                                                \
     case R:                                                                                                               \
-        if (cached == kBoth) PSGD_SHORT(DEG, R, false, kBoth, false);                                                     \
-        if (cached) PSGD_SHORT(DEG, R, false, plan::kCachedLoads, false);                                                 \
+        if constexpr (R != 1)                                                                                             \
+            if (cached == kBoth) PSGD_SHORT(DEG, R, false, kBoth, false);                                                 \
+        if constexpr (R != 1 || CD)                                                                                       \
+            if (cached == plan::kCachedLoads) PSGD_SHORT(DEG, R, false, plan::kCachedLoads, false);                       \
         PSGD_SHORT(DEG, R, false, 0, false)
     if (d < kVec) PSGD_SHORT(0, 2, true, 0, true);
     if (p.one) {
