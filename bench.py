@@ -150,7 +150,7 @@ def main():
                          "side, weight 1/K each) through psgd_mix_step_deg, the general sparse-table kernel")
     ap.add_argument("--two-rings", action="store_true",
                     help="3-slot table that is NOT one ring (two disjoint rings over the even and the odd learners): "
-                         "takes the tiled fallback of the step kernel")
+                         "takes the step's kernel for tables that are not one ring")
     ap.add_argument("--device-tables", action="store_true",
                     help="build each iteration's table on the device (psgd_build_mixing_device) instead of on the "
                          "host followed by an upload")
@@ -522,7 +522,7 @@ def main():
         "config": {
             "workload": wl.name, "n": n, "d": d, "g_dtype": wl.g_dtype,
             "topology": ("full (T_u)" if args.global_average else
-                         "two disjoint rings (tiled fallback)" if args.two_rings else
+                         "two disjoint rings (kernel for any table)" if args.two_rings else
                          {0: "ring", 1: "rand_ring"}[wl.topology]),
             "table_degree": deg, "tables_built_on": "device" if args.device_tables else "host",
             "lr": wl.lr,
@@ -532,8 +532,8 @@ def main():
             "hbm_layout": layout_report,
         },
         "roofline": {
-            "kernel": ("mix_full_kernel" if args.global_average else "mix_deg_kernel" if deg > 3
-                       else "mix_step_kernel (tiled path)" if args.two_rings else "mix_step_kernel")
+            "kernel": ("mix_full_kernel" if args.global_average else "mix_deg_kernel or mix_short_kernel"
+                       if deg > 3 or args.two_rings else "mix_step_kernel")
                       + (" (with fused consensus statistics)" if fused else ""),
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,

@@ -129,7 +129,8 @@ def _general_table(n, rng, weights=(0.5, 0.3, 0.2)):
 
 @pytest.mark.parametrize("n,d", [(4, 9), (6, 2048), (16, 4 * 3000), (64, 1025), (128, 8192 + 4), (300, 516)])
 @pytest.mark.parametrize("gkind", ["f32", "bf16"])
-def test_general_tables_use_the_tiled_path(psgd, n, d, gkind):
+def test_general_tables(psgd, n, d, gkind):
+    """Doubly stochastic 3-slot tables that are not one ring, on short rows (the short-row kernel)."""
     rng = np.random.default_rng(n * 7 + d)
     nbr, w = _general_table(n, rng)
     T = orc.densify(nbr, w)
@@ -203,7 +204,7 @@ def test_binding_reports_alias_errors(psgd):
     torch.cuda.synchronize()
 
 
-def test_misaligned_views_take_the_scalar_path(psgd):
+def test_misaligned_views(psgd):
     """Buffers that are only 4-byte aligned (and 2-byte for bf16) must still be right."""
     n, d = 8, 1001
     X = inp.host_normal_f32((n, d), 1.0, 61)
@@ -367,12 +368,13 @@ def test_degree_k_tables(psgd, n, d, deg, gkind):
     assert np.array_equal(run_step(psgd, X, G, nbr, w, 0.2).view(np.uint32), got.view(np.uint32))
 
 
-@pytest.mark.parametrize("n,deg", [(16, 3), (16, 5), (64, 9), (300, 4)])
-def test_tiled_distance_far_from_origin(psgd, n, deg):
-    """Replicas that agree to 1e-4 but sit at O(1) and move by a common 1000 per step: the tiled
-    path measures against the output of row 0, so the large common shift must cancel exactly
-    (a pivot taken from the inputs would leave only ~4 of the distance's digits)."""
-    d = 4100
+@pytest.mark.parametrize("n,deg,d", [(16, 3, 4100), (16, 5, 4100), (64, 9, 4100), (300, 4, 4100), (16, 3, 1_600_032),
+                                     (16, 5, 1_600_032), (64, 9, 1_600_032)])
+def test_distance_far_from_origin(psgd, n, deg, d):
+    """Replicas that agree to 1e-4 but sit at O(1) and move by a common 1000 per step: the distance is measured
+    against an output of the same column, so the large common shift must cancel exactly (a pivot taken from the
+    inputs would leave only ~4 of the distance's digits).  The short-row kernel on the short rows; on the long ones
+    (on 128-byte lines) the tiled kernel for more than three slots."""
     rng = np.random.default_rng(n + deg)
     nbr, w = _general_table(n, rng) if deg == 3 else _perm_sum_table(n, deg, rng)
     X = (np.tile(inp.host_normal_f32((1, d), 1.0, 1), (n, 1)) + inp.host_normal_f32((n, d), 1e-4, 2)).astype(np.float32)
@@ -675,11 +677,12 @@ def test_steps_captured_in_a_hip_graph_replay_exactly(psgd):
         assert abs(psgd.consensus_dist(out) - c_eager[-1].item()) <= 1e-9 * c_eager[-1].item()
 
 
-def test_long_row_kernels_captured_in_a_hip_graph_replay_exactly(psgd):
-    """The same on rows long enough for the large workgroups: the ring walk (with the tiled kernel enqueued
-    behind it), a 5-slot table through the tiled kernel (more than 64 KB of LDS) and global averaging, every
-    one with the fused distance, captured once after an eager pass and replayed between eager work."""
-    n, d = 16, 1_600_004
+@pytest.mark.parametrize("n,d", [(16, 1_600_004), (40, 1_600_032), (40, 1_200_003)])
+def test_long_row_kernels_captured_in_a_hip_graph_replay_exactly(psgd, n, d):
+    """The same on rows long enough for the large workgroups: the ring walk with the kernel for any other table enqueued
+    behind it (d on 128-byte lines: the tiled one, else the short-row one), a 5-slot table through the same kernel
+    (tiled: more than 64 KB of LDS) and global averaging, every one with the fused distance, captured once after an
+    eager pass and replayed between eager work.  n = 16 takes one pass per table only."""
     rng = np.random.default_rng(5)
     X0 = dev(inp.host_normal_f32((n, d), 1.0, 23))
     G = dev(inp.host_normal_f32((n, d), 0.1, 24))
@@ -808,11 +811,12 @@ def test_binding_checks_dtypes_and_devices(psgd):
 
 
 @pytest.mark.parametrize("kind", ["ring", "general3", "deg5", "full"])
-@pytest.mark.parametrize("n,d", [(4, 8_000_004), (4, 6_000_001), (16, 2_000_004), (16, 1_500_001)])
+@pytest.mark.parametrize("n,d", [(4, 8_000_004), (4, 6_000_001), (16, 2_000_004), (16, 1_500_001), (40, 2_000_032),
+                                  (40, 1_500_001)])
 def test_many_sweeps_per_workgroup(psgd, kind, n, d):
-    """Rows long enough that every persistent workgroup strides over many column groups /
-    tiles (the small shapes finish in one), with a ragged last tile; every element is compared.
-    n = 16 takes the tiled kernel's variant without per-row guards, n = 4 the guarded one."""
+    """Rows long enough that the workgroups of the short-row kernel and of global averaging stride over many
+    tiles / column groups (the small shapes finish in one), with a ragged last tile; n = 40 takes the ring walk and,
+    on its lines, the tiled kernel.  Every element is compared."""
     lr = 0.1
     rng = np.random.default_rng(d % 1000 + len(kind))
     X = inp.host_normal_f32((n, d), 1.0, 61)
@@ -864,8 +868,10 @@ def test_global_average_large_workgroups_every_element(psgd, gkind):
     assert torch.equal(Xd, Yd)
 
 
-def test_status_flag_is_sticky_until_cleared_and_long_rows_refuse_bad_tables(psgd):
-    n, d = 4, 2_000_000                      # long rows: the large-workgroup variant of the step kernel
+@pytest.mark.parametrize("n,d", [(4, 2_000_000), (64, 1_000_064), (33, 1_200_003)])
+def test_status_flag_is_sticky_until_cleared_and_long_rows_refuse_bad_tables(psgd, n, d):
+    """Four learners take the short-row kernel, 64 and 33 the ring walk with the tiled and the short-row kernel behind
+    it: a bad table is written off by one of the two, and only once."""
     nbr, w = psgd.build_mixing(psgd.TOPO_RING, n)
     bad = nbr.copy()
     bad[1, 2] = -1
@@ -946,7 +952,7 @@ def test_reference_streams_do_what_they_say(psgd, n, d, gkind):
         psgd.reference_stream(psgd.REF_AXPY, Xd, Xd, Gd)          # output over an input
 
 
-# ------------------------------------------------------------------------- tiled kernel on long rows
+# ------------------------------------------------------------------------- general tables on long rows
 def _two_rings_table(n):
     """The even and the odd learners on two disjoint rings: 3 slots, locally consistent, not ONE ring."""
     idx = np.arange(n)
@@ -965,16 +971,23 @@ _LONG_ROW_CASES = (
        (70, 1_600_004, "two_rings", "f32"), (70, 1_600_004, "deg13", "bf16"),
        (16, 1_900_004, "two_rings", "bf16"), (16, 1_900_004, "deg5", "f32"),
        (5, 2_000_004, "deg5", "f32"), (5, 2_000_004, "deg13", "bf16"),
-       (48, 1_600_003, "two_rings", "f32"), (48, 1_600_003, "deg5", "bf16")])
+       (48, 1_600_003, "two_rings", "f32"), (48, 1_600_003, "deg5", "bf16")]
+    # rows on 128-byte lines: the tiled kernel (behind the ring walk for the two rings)
+    + [(64, 1_600_032, k, g) for k in ("two_rings", "deg5", "deg13") for g in ("f32", "bf16")]
+    + [(128, 1_600_032, "two_rings", "bf16"), (128, 1_600_032, "deg5", "f32"), (128, 1_600_032, "deg13", "bf16"),
+       (33, 1_700_032, "deg5", "f32"), (33, 1_700_032, "deg13", "bf16"), (30, 1_600_003, "two_rings", "bf16"),
+       (70, 1_600_032, "two_rings", "f32"), (70, 1_600_032, "deg13", "bf16"),
+       (10, 6_300_032, "two_rings", "bf16"), (16, 1_900_032, "deg5", "f32")])
 
 
 @pytest.mark.parametrize("n,d,kind,gkind", _LONG_ROW_CASES)
-def test_tiled_kernel_long_rows_every_element(psgd, n, d, kind, gkind):
-    """Rows long enough for the large-workgroup tiled kernels: the 1024-lane one-batch form for n <= 64 (merge
-    slots of the distance inside the consumed tile buffer at 16 B per lane; wider rows for n = 16, 8, 5; an odd
-    row count per row group for n = 33, 48), the 512-lane form with several batches per tile for n = 70 and
-    n = 128; d not a multiple of 4 takes one column per lane.  Every element and the fused distance against
-    the oracle, out of place and in place, ragged last tile included."""
+def test_general_tables_long_rows_every_element(psgd, n, d, kind, gkind):
+    """Long rows and tables that are not one ring.  On 128-byte lines (and for n = 29 to 32) the tiled kernel: merge
+    slots of the distance inside the consumed tile buffer at 16 B per lane; wider rows for n = 16 and 10; an odd row
+    count per row group for n = 33; narrower rows for n = 70 and n = 128; 16-byte accesses on the lines and, for n = 30
+    off them, one column per lane at the ragged end.  Off the lines and for n <= 8 the short-row kernel over many
+    tiles, behind the ring walk for 3 slots from its line on.  Every element and the fused distance against the
+    oracle, out of place and in place, ragged last tile included."""
     rng = np.random.default_rng(n + d % 1000)
     if kind == "two_rings":
         if n % 2:
@@ -999,9 +1012,9 @@ def test_tiled_kernel_long_rows_every_element(psgd, n, d, kind, gkind):
 
 
 @pytest.mark.parametrize("n,kind,gkind", [(200, "deg5", "bf16"), (256, "two_rings", "f32")])
-def test_tiled_kernel_long_rows_many_learners(psgd, n, kind, gkind):
-    """More than 128 learners on long rows: 256-byte row segments (16 lanes per row), four row groups per
-    wavefront, in the one-batch form; every element and the fused distance against the oracle."""
+def test_general_tables_long_rows_many_learners(psgd, n, kind, gkind):
+    """More than 128 learners on long rows: the short-row kernel over many tiles, behind the ring walk for the two
+    rings; every element and the fused distance against the oracle."""
     d = 1_580_004
     rng = np.random.default_rng(n)
     nbr, w = _two_rings_table(n) if kind == "two_rings" else _perm_sum_table(n, 5, rng)
@@ -1045,11 +1058,12 @@ def test_tiled_kernel_long_rows_widest_tables(psgd, n, deg, gkind, d):
 
 
 @pytest.mark.parametrize("n", [16, 64, 128])
-def test_tiled_kernel_long_rows_distance_corner_cases(psgd, n):
-    """The row groups of the large tiled kernel each measure against their own pivot and the merge brings
-    them to a common one: replicas far from the origin and close together must still give the distance to
-    1e-6, and identical outputs must give exactly 0."""
-    d = 1_600_004
+@pytest.mark.parametrize("d", [1_600_004, 1_600_032])
+def test_general_tables_long_rows_distance_corner_cases(psgd, n, d):
+    """The row groups of a tile each measure against their own pivot and the merge brings them to a common one:
+    replicas far from the origin and close together must still give the distance to 1e-6, and identical outputs must
+    give exactly 0.  Rows off the 128-byte lines and n = 16 take the short-row kernel, 64 and 128 learners on the
+    lines the tiled one."""
     nbr, w = _two_rings_table(n)
     base = inp.host_normal_f32((1, d), 100.0, 3)
     X = (np.tile(base, (n, 1)) + inp.host_normal_f32((n, d), 1e-3, 4)).astype(np.float32)

@@ -400,8 +400,8 @@ def test_cfg5_dense_layout_full_size(psgd):
 
 def test_rows_longer_than_2_31_elements(psgd):
     """Column indices beyond 2^31 (d = 2^31 + 1028, n = 2; the workloads only exercise row offsets
-    beyond 2^32): ring walk, tiled path, global average and the distance, on sampled columns that
-    include both ends of the row."""
+    beyond 2^32): a ring and a table that is none (both the short-row kernel for two learners), global
+    average and the distance, on sampled columns that include both ends of the row."""
     n, d, lr = 2, 2 ** 31 + 1028, 0.25
     X = inp.device_normal_f32((n, d), 1.0, 71)
     Y = torch.empty_like(X)
@@ -422,7 +422,7 @@ def test_rows_longer_than_2_31_elements(psgd):
     del diff
     torch.cuda.synchronize()
     assert abs(c[0].item() - want_c) <= 1e-9 * want_c
-    gen = np.array([[0, 1, 1], [1, 0, 0]], dtype=np.int32)                # not a ring by the slot rule: tiled path
+    gen = np.array([[0, 1, 1], [1, 0, 0]], dtype=np.int32)                # not a ring by the slot rule
     wg = np.array([[0.5, 0.25, 0.25], [0.5, 0.3, 0.2]], dtype=np.float32)
     psgd.mix_step(X, Y, G, dev(gen), dev(wg), lr, cdist_out=c[1:2])
     assert_close(pull(Y, cols_t), orc.mix_step(Xo, Go, orc.densify(gen, wg), lr))
@@ -431,5 +431,31 @@ def test_rows_longer_than_2_31_elements(psgd):
     torch.cuda.synchronize()
     chk = psgd.consensus_dist(Y)
     assert abs(c[2].item() - chk) <= 1e-9 * chk and psgd.device_status() == 0
+    del X, Y, G
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d", [2 ** 31 + 1088, 2 ** 31 + 1027])
+def test_rows_longer_than_2_31_elements_ring_walk_and_the_kernel_behind_it(psgd, d):
+    """The same for the kernels of long rows, which take nine learners: the ring walk, and for two rings the kernel
+    behind it (rows on 128-byte lines: the tiled one; ragged rows: the short-row one), on sampled columns; the fused
+    distance against the pass of its own (both add a column's n squares in fp32: at most (n + 2) 2^-24 relative)."""
+    n, lr = 9, 0.25
+    X = inp.device_normal_f32((n, d), 1.0, 74)
+    Y = torch.empty_like(X)
+    G = inp.device_normal_bf16((n, d), 0.5, 75)
+    cols = inp.sample_columns(d, SAMPLE, seed=76)
+    assert cols.max() == d - 1 and (cols > 2 ** 31).sum() >= 8
+    cols_t = torch.from_numpy(cols).to("cuda:0")
+    Xo, Go = pull(X, cols_t), pull(G, cols_t)
+    c = torch.zeros(2, dtype=torch.float64, device="cuda:0")
+    ring = psgd.build_mixing(psgd.TOPO_RAND_RING, n, 5, 0)
+    nxt = np.array([1, 2, 3, 0, 5, 6, 7, 8, 4])                           # a ring of four and a ring of five
+    two = (np.stack([np.arange(n), np.argsort(nxt), nxt], axis=1).astype(np.int32), ring[1])
+    for k, (nbr, w) in enumerate((ring, two)):
+        psgd.mix_step(X, Y, G, dev(nbr), dev(w), lr, cdist_out=c[k:k + 1])
+        assert_close(pull(Y, cols_t), orc.mix_step(Xo, Go, orc.densify(nbr, w), lr))
+        chk = psgd.consensus_dist(Y)
+        assert abs(c[k].item() - chk) <= REL * chk and psgd.device_status() == 0
     del X, Y, G
     torch.cuda.empty_cache()

@@ -76,12 +76,19 @@ def _case(lib, n, d, gkind, topo, seed, pitched):
 
 
 def test_static_entry_point_twice_second_call_smaller(lib):
-    # long rows: 768-lane workgroups, many sweeps, one workgroup per CU -> about 256 partials
+    # long rows of few learners: the short-row kernel with many tiles per launch
     _case(lib, 16, 1_600_004, "bf16", orc.TOPO_RAND_RING, 5, pitched=True)
-    # then a small ragged one: 256-lane workgroups, a handful of partials, scalar columns (d odd)
+    # then a small ragged one: a handful of partials, scalar columns (d odd)
     _case(lib, 5, 1001, "f32", orc.TOPO_RING, 6, pitched=False)
-    # and a mid-sized one whose grid is the largest the kernel uses (4 workgroups per CU)
+    # a mid-sized one with a tile per workgroup
     _case(lib, 8, 300_000, "f32", orc.TOPO_RAND_RING, 7, pitched=False)
+
+
+@pytest.mark.parametrize("n,d,gkind", [(64, 1_000_064, "bf16"), (33, 1_200_003, "f32"), (200, 400_004, "bf16")])
+def test_static_entry_point_behind_the_ring_walk(lib, n, d, gkind):
+    """From the ring walk's line on two kernels share the array: the ring walk, and behind it the tiled kernel (64
+    learners, rows on 128-byte lines) or the short-row kernel."""
+    _case(lib, n, d, gkind, orc.TOPO_RAND_RING, n, pitched=False)
 
 
 @pytest.mark.parametrize("n,d", [(8, 3_000_001), (5, 2_097_160), (7, 4_194_304), (2, 2_500_000)])
