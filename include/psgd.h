@@ -115,10 +115,10 @@ int psgd_build_mixing_device(int topology, int n, uint64_t seed, uint64_t* step_
  *
  * Enqueues its work on `stream` and returns without waiting.  The table lives in device memory,
  * so only the device can tell whether it is one ring (every table of Sec. 3 is) or a general
- * 3-slot table.  Most shapes: one kernel that serves any table.  Long rows of many learners
- * (64 learners: from about 2.4 M columns; 128 and more: from 0.6 M): two kernels, the ring walk
- * and behind it the tiled kernel, each shaped for its own path; both classify the table and the
- * one it does not belong to exits at once.
+ * 3-slot table.  Most shapes: one kernel that serves any table.  Long rows of nine and more
+ * learners (9 to 28 learners: from about 6.3 M columns; up to 47: 1.2 M; up to 95: 1 M; up to 255:
+ * 0.31 M; above: 0.2 M): two kernels, the ring walk and behind it one for any other table (LDS tiles);
+ * both classify the table and the one it does not belong to exits at once (4 to 7 us).
  * Errors: PSGD_EINVAL;
  * PSGD_EALIAS (X_out partially overlaps X, X_out overlaps G, or X_out == X with
  * delay_mode 1); PSGD_EALIGN (X, X_out, G not 4-byte aligned); PSGD_EHIP.  A table entry
@@ -175,7 +175,7 @@ int psgd_mix_step_cd_bf16g(const float* X, float* X_out, const uint16_t* G_bf16,
  * Everything else is as in psgd_mix_step.  Mixing in place needs X_out == X and ldo == ldx;
  * any other sharing of a byte between rows of X_out and rows of X or G is PSGD_EALIAS (the
  * rows of different arrays may interleave as long as they do not overlap).  Any d and any
- * pitch take 128-bit accesses; rows that start on 16 bytes run about a tenth faster.
+ * pitch take 128-bit accesses; rows that start on 128-byte lines run a few percent faster.
  *
  * Why pitches: (1) a column shard of a wider array is such a view; (2) placement.  On
  * MI355X this step was measured at 65-72 % of the HBM peak when each array is one dense
@@ -198,8 +198,7 @@ int psgd_mix_step_ex(const float* X, int64_t ldx, float* X_out, int64_t ldo,
  * call makes no hipMalloc / hipFree and creates no event or stream.
  *
  * Limit: a launch uses one partial per workgroup.  Most shapes loop over their tiles within the
- * array; the ring walk takes one workgroup per compute unit and the tiled kernel behind it what is
- * left.  If the ring walk alone would need PSGD_STATIC_SLOTS or more the call fails with PSGD_EINVAL
+ * array; the ring walk takes one workgroup per compute unit and the kernel behind it what is left.  If the ring walk alone would need PSGD_STATIC_SLOTS or more the call fails with PSGD_EINVAL
  * and launches nothing.  n, d and the pitches are limited as in psgd_mix_step_ex.
  * Every call on a GPU uses that GPU's one array, which keeps the previous call's partials (each
  * launch overwrites the slots it reads, so nothing needs clearing).  Calls that overlap in time
@@ -219,8 +218,8 @@ int psgd_mix_step_cd_static(const float* X, int64_t ldx, float* X_out, int64_t l
  * remedy of the prior work the paper cites in Sec. 7).  1 <= deg <= PSGD_MAX_DEG and
  * n * deg <= PSGD_MAX_TABLE.  Per element: acc = w0 * x0; acc = fma(w_s, x_s, acc) for
  * s = 1..deg-1 in table order; out = fma(-lr, g, acc).  deg = 3 is psgd_mix_step_ex (long
- * ring tables then take the register walk); other degrees always stage [n x columns] tiles in
- * LDS.  Everything else (pitches, gradient type, in-place rule, cdist_out gathered in the same
+ * ring tables then take the register walk); tables of other degrees are served from
+ * [n x columns] tiles in LDS.  Everything else (pitches, gradient type, in-place rule, cdist_out gathered in the same
  * pass, errors) is as in psgd_mix_step_ex.
  */
 int psgd_mix_step_deg(const float* X, int64_t ldx, float* X_out, int64_t ldo,

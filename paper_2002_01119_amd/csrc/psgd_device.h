@@ -19,7 +19,7 @@ namespace {
 constexpr int kThreads = 256;        // 4 wavefronts of 64 lanes
 constexpr int kRingThreads = 768;    // workgroup of the step kernels on long rows (12 wavefronts in lockstep, one per CU;
                                      // 1024 lanes would leave the fused distance too few registers)
-constexpr int kDeepThreads = 1024;   // workgroup of the tiled path: 16 wavefronts, four per SIMD, which is what keeps the slot
+constexpr int kDeepThreads = 1024;   // workgroup of the tiled kernel: 16 wavefronts, four per SIMD, which is what keeps the slot
                                      // loop's LDS round trips and arithmetic hidden
 constexpr int kTileThreads = 512;    // the same with the distance: 8 wavefronts with up to 256 registers
 constexpr int kUnroll = 8;           // rows whose loads are in flight together per lane
@@ -173,7 +173,7 @@ struct __attribute__((aligned(16))) RingEnt {
     float w0, w1, w2;
 };
 
-// One slot of a table row as the tiled path keeps it in LDS: where the source row starts inside the tile
+// One slot of a table row as the tiled and the short-row kernel keep it in LDS: where the source row starts inside the tile
 // (nbr * lanes-per-row, in column groups) and its weight.
 struct __attribute__((aligned(8))) TileSlot {
     uint32_t off;
@@ -329,8 +329,9 @@ __device__ __forceinline__ void floats_of(f32x4 x, float* f) {
 
 // Running sums of one lane's column group; the first value it is given becomes the pivot (kept as
 // the fp32 value it is).  Unless the group may be owned in part (RAGGED) the squares of its columns share one
-// accumulator: only their total is needed, and registers decide how many wavefronts of a kernel on another stream
-// find room beside the step (delay-by-one pair of 128 x 8 M: 4.96 ms, with four accumulators 4.99).
+// accumulator: only their total is needed, and three fp64 accumulators less are six registers less in the ring walk
+// (142 against 148), of which a kernel on another stream may find the room; the time of a delay-by-one pair does not
+// tell the two apart (128 x 8 M: 4.96 and 4.99 ms, where runs differ by more).
 template <bool RAGGED>
 struct ColStats {
     f32x4 s;

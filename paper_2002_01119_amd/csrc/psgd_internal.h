@@ -86,7 +86,7 @@ inline int ring_threads(const SweepPlan& s, int threads) {
     return s.count > 1 ? threads : (int)((s.chunk + 63) / 64 * 64);
 }
 
-// Whether a 3-slot table on n rows of `ncg` column groups takes the ring walk (and the tiled kernel behind it) instead
+// Whether a 3-slot table on n rows of `ncg` column groups takes the ring walk (and a kernel for any other table behind it) instead
 // of the short-row kernel, which serves any table at once.  The ring walk reads and writes up to 12 KB of a row at a
 // time whatever n is, but pays for classifying the table and for a second launch, and walks all rows one batch after
 // the other, which takes 0.4 us a row however few columns there are; the short-row kernel's row segments narrow as n
@@ -102,7 +102,7 @@ inline bool ring_rows(int n, int64_t ncg, int cus, int threads) {
     return ncg * 4 >= (n < 29 ? 32 * sweep : n < 48 ? 6 * sweep : n < 96 ? 5 * sweep : n < 256 ? 8 * sweep / 5 : sweep);
 }
 
-// LDS of the tiled path (long rows on lines, tables that are not one ring): the slot table (8 bytes per slot), TWO tile
+// LDS of the tiled kernel (long rows, tables that are not one ring): the slot table (8 bytes per slot), TWO tile
 // buffers of n rows x lpr lanes x 16 bytes (the next tile is staged while the current one is read), and, when the
 // consensus distance is gathered in the same pass, the merge slots of the column sums: a double and a float (the row
 // group's own pivot) per column and row group.  They go into the buffer that has just been read (one more barrier per tile)

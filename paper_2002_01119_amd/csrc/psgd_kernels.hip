@@ -1,9 +1,10 @@
 // libpsgd's HIP translation unit (gfx950 / CDNA4): the launchers and C entry points for the model-averaging step
 //     X_out[i,:] = sum_s w[i,s] * X[nbr[i,s],:] - lr * G[i,:]            (Sec. 2, Eq. 2)
 // and for the consensus distance sum_i ||x_i - xbar||^2 (Sec. 3).  The kernels live in the headers included
-// below: psgd_device.h (shared building blocks), psgd_short.h (short rows, any table), psgd_ring_walk.h (long rows, ring
-// tables, registers only), psgd_tiled.h (long rows, any other table, LDS tiles), psgd_streams.h (global averaging, distance, gradient producer, reference streams,
-// table builder).
+// below: psgd_device.h (shared building blocks), psgd_short.h (any table: short rows, few or many learners, rows off
+// the lines), psgd_ring_walk.h (long rows of nine and more learners, ring tables, registers only), psgd_tiled.h (long rows
+// of 9 to 128 learners, any other table, LDS tiles), psgd_streams.h (global averaging, distance, gradient producer,
+// reference streams, table builder).
 //
 // The step is bound by HBM traffic (about 7 flops against 10-12 bytes per element), so the
 // design goal is to touch every X, G and X_out byte exactly once:
@@ -13,14 +14,13 @@
 //     the ring in position order holding three consecutive rows in registers, so each
 //     neighbour read is a register move, not a memory access, and the update may run in
 //     place because a row is only written after its old value is in registers;
-//   * any other table goes through [n x columns] tiles in LDS (a neighbour read is an LDS read), double
-//     buffered, with the next tiles travelling from HBM through registers while the current one is
-//     computed; a tile is complete in LDS before its first output is stored, so this path too may
-//     run in place.
-// Short rows, where a launch is bound by latency, take one kernel of their own for every table (psgd_short.h).
+//   * any other table goes through [n x columns] tiles in LDS (a neighbour read is an LDS read), with the
+//     next tiles travelling from HBM through registers while the current one is computed; a tile is
+//     complete in LDS before its first output is stored, so this path too may run in place.
+// Short rows, where a launch is bound by latency, take tiles for every table (psgd_short.h).
 // Tables live in device memory and are validated and, on long rows, classified (one ring or not) by the kernels.
 // Workgroups are persistent, so table staging is paid once per launch.  On long rows the workgroups are
-// large (768 lanes for the ring walk, 512 or 1024 for the tiled path), one per compute unit; the ring walk's
+// large (768 lanes for the ring walk, 512 or 1024 for the tiled kernel), one per compute unit; the ring walk's
 // wavefronts sweep the rows in lockstep, a barrier per batch of rows: the HBM then sees one 12 KB burst
 // per row instead of twelve separate 1 KB requests, which is worth 1-3 % of the peak for kernels that
 // write.
@@ -487,7 +487,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         const plan::TilePlan tp = plan::tile_plan(n, deg, threads, want_cd, kLdsCapLarge,
                                                   want_cd ? TileShape<kTileThreads>::RB : TileShape<kDeepThreads>::RB);
         if (tp.lpr == 0)
-            return fail(PSGD_EINVAL, "%s: n=%d, deg=%d does not fit the tiled path's LDS", name, n, deg);
+            return fail(PSGD_EINVAL, "%s: n=%d, deg=%d does not fit the tiled kernel's LDS", name, n, deg);
         size_t lds_bytes = tp.total;
         if (ring && lds_bytes < tp.tab_bytes + lds_classify_bytes(n)) lds_bytes = tp.tab_bytes + lds_classify_bytes(n);
         const size_t remainder = (size_t)n * (d % kVec) * 2 * sizeof(float);

@@ -23,7 +23,7 @@ namespace {
 // a workgroup has several tiles the next one's X rows are loaded as soon as the registers have gone to LDS, its
 // gradients as each row is finished.
 //
-// Measured (step with the distance and its final sum unless noted, MI355X; before: the ring walk or the tiled path in
+// Measured (step with the distance and its final sum unless noted, MI355X; before: the ring walk or the tiled kernel in
 // small workgroups, a lane walking all rows): 512 learners x 60 k 171 -> 77 us (4.8 TB/s), 16 x 1 M with 5 slots 49.8 -> 38.6,
 // 8 x 1 M 25.6 -> 18.5, 100 x 50 k without the distance 34.7 -> 10.8, 32 x 786 433 at odd addresses, no distance, 77 -> 58.
 //
@@ -34,8 +34,8 @@ namespace {
 // The distance (CD): every lane measures its outputs against its first one, in fp64, and the row groups' sums meet in
 // LDS, where they are brought to row group 0's pivot exactly (row_group_merge).
 // ---------------------------------------------------------------------------------------
-// DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (twice the rows per lane: nothing is loaded ahead,
-// so their registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
+// DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (two or up to eight rows per lane: nothing is
+// loaded ahead, so those registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
 // FEW: rows of fewer than four columns.  SKIP_RINGS: enqueued behind the ring walk, which leaves tables that are not one ring to this
 // kernel; both classify the table with the same code, and the one it does not belong to writes nothing (and contributes 0 to the distance).
 template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool SKIP_RINGS = false>

@@ -1,5 +1,5 @@
-// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows that start on lines, for mixing tables that are
-// not one ring, and its kernel mix_deg_kernel.  Included by psgd_kernels.hip only.
+// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows of 9 to 128 learners, for mixing tables that are
+// not one ring, and its kernel mix_deg_kernel (rows on lines, with two exceptions: see the rule in mix_step_impl).  Included by psgd_kernels.hip only.
 #ifndef PSGD_TILED_H
 #define PSGD_TILED_H
 
