@@ -533,7 +533,7 @@ def main():
         },
         "roofline": {
             "kernel": ("mix_full_kernel" if args.global_average else "mix_deg_kernel or mix_short_kernel"
-                       if deg > 3 or args.two_rings else "mix_step_kernel")
+                       if deg > 3 or args.two_rings else "mix_short_kernel" if n <= 8 else "mix_step_kernel")
                       + (" (with fused consensus statistics)" if fused else ""),
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
