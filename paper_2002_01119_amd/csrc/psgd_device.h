@@ -17,8 +17,7 @@ namespace psgd {
 namespace {
 
 constexpr int kThreads = 256;        // 4 wavefronts of 64 lanes
-constexpr int kRingThreads = 768;    // workgroup of the step kernels on long rows (12 wavefronts in lockstep, one per CU;
-                                     // 1024 lanes would leave the fused distance too few registers)
+constexpr int kRingThreads = 768;    // workgroup of the streaming kernels on long rows (12 wavefronts in lockstep, one per CU)
 constexpr int kDeepThreads = 1024;   // workgroup of the tiled kernel: 16 wavefronts, four per SIMD, which is what keeps the slot
                                      // loop's LDS round trips and arithmetic hidden
 constexpr int kTileThreads = 512;    // the same with the distance: 8 wavefronts with up to 256 registers
@@ -31,6 +30,7 @@ constexpr size_t kLdsCapLarge = 160 * 1024 - 1024;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ int g_status_word = 0;
 

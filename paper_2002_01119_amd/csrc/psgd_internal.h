@@ -2,6 +2,7 @@
 #ifndef PSGD_INTERNAL_H
 #define PSGD_INTERNAL_H
 
+#include <cstddef>
 #include <cstdint>
 
 namespace psgd {
@@ -77,11 +78,26 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads, bool even = true
     return s;
 }
 
-// Lanes of the ring walk's workgroups: all of `threads`, but no wavefront without columns where the row takes one sweep.
-// Such a wavefront walks the ring with the others, shadowing a column group: its loads and the barriers it takes part in
-// cost more than it hides, and beside another stream's kernel its registers are missing there (us, with / without: with the
-// distance 256 x 235 k 157 / 137, 512 x 234 k 310 / 267, 128 x 354 k 111 / 105; delay-by-one pair of 200 x 400 k 404 / 371).  Two
-// sweeps and more: all lanes (128 x 1.02 M 289 / 294).
+// The ring walk: most lanes that have columns (one more wavefront keeps the pace), words to keep it with (launches under way at a
+// time that do not share one), and how often a wavefront asks before it walks on by itself (about 30 us).
+constexpr int kRingLanes = 960;
+constexpr int kPaceSlots = 64;
+constexpr int kPaceSpins = 400;
+// Rows on their way per lane, most lanes of the workgroup with them (all, pacing wavefront included), and how far ahead of the mean
+// a workgroup may be, in quarter rows.  The narrower the chunk, the more rows: about 900 lanes times rows keep the memory busy, and
+// what is beyond that costs more in order than it gains (us; one row each 64 x 1.2 M 154, two 153; 128 x 500 k 138 / 129; two / four
+// 130 x 200 k with a distance 79 / 68, 256 x 280 k with bf16 gradients 154 / 135; four / eight 512 x 205 k 242 / 235, 256 x 210 k bf16
+// 112 / 105).  Lead: one row 1.25 / 1.5 / 1.75 / 2 rows 64 x 25.6 M 3134 / 3136 / 3186 / 3289; four rows of lead or none
+// for a depth of one: 3500 / 3800.
+inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 8; }
+constexpr int ring_most_threads(int depth) { return depth <= 2 ? kRingLanes + 64 : depth == 4 ? 448 : 320; }
+inline int pace_lead(int depth) { return depth == 1 ? 6 : 5 * depth; }
+// More than half of a compute unit's LDS: the workgroups then take a compute unit each.  Two on one fall behind the others, which wait.
+constexpr size_t kRingLds = 82 * 1024;
+
+// Lanes that a plan's workgroups need: all of `threads`, but no wavefront without columns where the row takes one sweep.  The ring
+// walk asks for one sweep's worth whatever their number: a wavefront without columns shadows another's loads (paced, 256 x 1 M with
+// bf16 gradients in two sweeps of 496 lanes: 532 us on 960 lanes, 429 on 512).
 inline int ring_threads(const SweepPlan& s, int threads) {
     return s.count > 1 ? threads : (int)((s.chunk + 63) / 64 * 64);
 }

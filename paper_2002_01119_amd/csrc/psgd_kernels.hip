@@ -19,13 +19,13 @@
 //     complete in LDS before its first output is stored, so this path too may run in place.
 // Short rows, where a launch is bound by latency, take tiles for every table (psgd_short.h).
 // Tables live in device memory and are validated and, on long rows, classified (one ring or not) by the kernels.
-// Workgroups are persistent, so table staging is paid once per launch.  On long rows the workgroups are
-// large (768 lanes for the ring walk, 512 or 1024 for the tiled kernel), one per compute unit; the ring walk's
-// wavefronts sweep the rows in lockstep, a barrier per batch of rows: the HBM then sees one 12 KB burst
-// per row instead of twelve separate 1 KB requests, which is worth 1-3 % of the peak for kernels that
-// write.
+// Workgroups are persistent, so table staging is paid once per launch.  On long rows there is one large workgroup per compute
+// unit (up to 1024 lanes for the ring walk, 512 or 1024 for the tiled kernel, 768 for the kernels in psgd_streams.h).  What the
+// HBM delivers then depends on the order the chip visits the rows in: the ring walk keeps the workgroups of a die on the same
+// row (psgd_ring_walk.h), which is worth 15-20 % on plain dense arrays.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -260,17 +260,33 @@ constexpr int kLaunchRefused = INT32_MIN;
 // Launches one instantiation of the ring-walk kernel, one workgroup per compute unit.
 // Returns the grid size, minus the grid size (and launches nothing) when the fused distance would need more
 // than `slots` partials, or kLaunchRefused when the runtime refuses the LDS size.
+std::atomic<unsigned> g_ring_launches{0};   // each takes the next of the pace words
+template <typename GT, bool CD, bool RAGGED, int D>
+int launch_mix_t(const plan::SweepPlan& sp, int grid, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
+                 const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+    if (lds_bytes < plan::kRingLds) lds_bytes = plan::kRingLds;
+    if (allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D>), lds_bytes)) return kLaunchRefused;
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D>), dim3(grid), dim3(plan::ring_threads({1, sp.chunk}, plan::kRingLanes) + 64), lds_bytes,
+                       s, X, X_out, G, nbr, w, n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk},
+                       (int)(g_ring_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots), plan::pace_lead(D), partials);
+    return grid;
+}
 template <typename GT, bool CD, bool RAGGED>
 int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
                const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, int slots) {
-    const void* fn = reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED>);
-    if (allow_lds(fn, lds_bytes)) return kLaunchRefused;
     const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
     if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
-    const plan::SweepPlan sp = plan::sweep_plan((d + 3) / 4, grid, kRingThreads);
-    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED>), dim3(grid), dim3(plan::ring_threads(sp, kRingThreads)), lds_bytes, s, X,
-                       X_out, G, nbr, w, n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk}, partials);
-    return grid;
+    const plan::SweepPlan sp = plan::sweep_plan((d + 3) / 4, grid, plan::kRingLanes);
+#define PSGD_RING_DEPTH(D)                                                                                                \
+    case D: return launch_mix_t<GT, CD, RAGGED, D>(sp, grid, lds_bytes, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials)
+    switch (plan::ring_depth(sp, n)) {
+        PSGD_RING_DEPTH(1);
+        PSGD_RING_DEPTH(2);
+        PSGD_RING_DEPTH(4);
+        PSGD_RING_DEPTH(8);
+    }
+#undef PSGD_RING_DEPTH
+    return kLaunchRefused;
 }
 
 // Long rows take the large lockstep workgroup: at least `sweeps` column groups per lane of one such

@@ -94,6 +94,19 @@ int main() {
               t, (long long)p.chunk);
     }
 
+    // the ring walk at every length of row: its workgroups are no larger than the depth's kernel is built for, and no load is issued
+    // further ahead than the end of the next sweep
+    for (int cus : {1, 64, 256, 304})
+        for (int64_t ncg = 1; ncg < (int64_t)1 << 34; ncg += ncg / 7 + 16)
+            for (int n : {9, 10, 15, 16, 17, 64, 512}) {
+                const SweepPlan p = sweep_plan(ncg, cus, kRingLanes);
+                const int depth = ring_depth(p, n), t = ring_threads({1, p.chunk}, kRingLanes) + 64;
+                CHECK(t <= ring_most_threads(depth) && t - 64 >= p.chunk && t % 64 == 0, "ring walk: %d lanes, depth %d, chunk %lld", t, depth,
+                      (long long)p.chunk);
+                CHECK((depth == 1 || depth == 2 || depth == 4 || depth == 8) && n - 1 + 2 + depth < 2 * n, "ring walk: depth %d, n %d", depth, n);
+                CHECK(pace_lead(depth) >= 4 * depth && kPaceSpins > 0, "ring walk: a lead that the loads on their way need");
+            }
+
     // grids never exceed the partials buffer, however many compute units a device reports
     for (int cus : {1, 64, 256, 304, 512, 513, 1024, 100000})
         for (int per_cu : {1, 4, 8}) {
