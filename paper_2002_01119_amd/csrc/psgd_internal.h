@@ -83,14 +83,13 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads, bool even = true
 constexpr int kRingLanes = 960;
 constexpr int kPaceSlots = 64;
 constexpr int kPaceSpins = 400;
-// Rows on their way per lane, most lanes of the workgroup with them (all, pacing wavefront included), and how far ahead of the mean
-// a workgroup may be, in quarter rows.  The narrower the chunk, the more rows: about 900 lanes times rows keep the memory busy, and
+// Rows on their way per lane, and how far ahead of the mean a workgroup may be, in quarter rows.  The narrower the chunk, the more rows: about 900 lanes times rows keep the memory busy, and
 // what is beyond that costs more in order than it gains (us; one row each 64 x 1.2 M 154, two 153; 128 x 500 k 138 / 129; two / four
 // 130 x 200 k with a distance 79 / 68, 256 x 280 k with bf16 gradients 154 / 135; four / eight 512 x 205 k 242 / 235, 256 x 210 k bf16
 // 112 / 105).  Lead: one row 1.25 / 1.5 / 1.75 / 2 rows 64 x 25.6 M 3134 / 3136 / 3186 / 3289; four rows of lead or none
 // for a depth of one: 3500 / 3800.
-inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 8; }
-constexpr int ring_most_threads(int depth) { return depth <= 2 ? kRingLanes + 64 : depth == 4 ? 448 : 320; }
+inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 6; }
+constexpr int kRingThreadsMost = kRingLanes + 64;   // of the workgroup
 inline int pace_lead(int depth) { return depth == 1 ? 6 : 5 * depth; }
 // More than half of a compute unit's LDS: the workgroups then take a compute unit each.  Two on one fall behind the others, which wait.
 constexpr size_t kRingLds = 82 * 1024;
@@ -102,20 +101,24 @@ inline int ring_threads(const SweepPlan& s, int threads) {
     return s.count > 1 ? threads : (int)((s.chunk + 63) / 64 * 64);
 }
 
-// Whether a 3-slot table on n rows of `ncg` column groups takes the ring walk (and a kernel for any other table behind it) instead
-// of the short-row kernel, which serves any table at once.  The ring walk reads and writes up to 12 KB of a row at a
-// time whatever n is, but pays for classifying the table and for a second launch, and walks all rows one batch after
-// the other, which takes 0.4 us a row however few columns there are; the short-row kernel's row segments narrow as n
-// grows (4096 / n lanes of 16 bytes).  In sweeps of one 768-lane workgroup per compute unit; us on dense arrays with fp32
-// gradients, short-row kernel / ring walk:
-//   8 x 51.2 M 933 / 977;   16 x 2.5 M (3.2 sweeps) 90 / 96, x 7.5 M (9.5) 261 / 262, x 51.2 M 1956 / 1891;
-//   32 x 1.2 M (1.5) 100 / 93, x 2.4 M 169 / 170, x 25.6 M 1910 / 1906;   64 x 0.6 M (0.8) 94 / 95, x 1 M (1.3) 143 / 145,
-//   x 1.9 M (2.4) 285 / 262;   120 x 333 k (0.4) 105 / 101, x 1 M (1.3) 281 / 260;   200 x 200 k (0.25) 97 / 114, x 600 k (0.8)
-//   277 / 262;   512 x 78 k (0.1) 97 / 222, x 234 k (0.3) 333 / 261.  Rows that do not start on lines: the same line.
+// Whether a 3-slot table on n rows of `ncg` column groups takes mix_step_kernel (the ring walk, tiles for any other table) instead
+// of the short-row kernel, by the lines of the ring walk without pacing; paced it is ahead from ring_rows_paced on.  In sweeps of
+// one 768-lane workgroup per compute unit.
 inline bool ring_rows(int n, int64_t ncg, int cus, int threads) {
     if (n <= 8) return false;
     const int64_t sweep = (int64_t)cus * threads;
     return ncg * 4 >= (n < 29 ? 32 * sweep : n < 48 ? 6 * sweep : n < 96 ? 5 * sweep : n < 256 ? 8 * sweep / 5 : sweep);
+}
+
+// The same with the workgroups of a die in step, in column groups per compute unit.  The walk takes 0.45 us a row and sweep however
+// few columns there are, and stages and classifies the table first; the short-row kernel reads and writes all rows of a tile at once,
+// which holds its rate to 5.0-5.3 TB/s once the arrays do not fit the last-level cache.  us, short-row kernel / ring walk, fp32 with the
+// distance: 9 x 2.5 M 52.5 / 51 (bf16 gradients 43 / 45), 12 x 1.5 M 42.6 / 44.7, 16 x 1.5 M 56.0 / 56.1, x 2.9 M 106 / 95, 24 x 0.66 M 37.5 / 39.2, x 0.82 M 48.1 / 46.8,
+// 32 x 0.51 M 41.3 / 41.2, x 0.82 M 66 / 59, 64 x 0.33 M 51 / 54, x 0.41 M 64 / 60, x 0.66 M 97 / 88, 128 x 0.26 M 78 / 75 (bf16 gradients, no
+// distance, 0.19 M 53 / 66, 0.33 M 93 / 86), 200 x 0.26 M 135 / 113.
+inline bool ring_rows_paced(int n, int64_t ncg, int cus) {
+    const int64_t from = n < 12 ? 3600 : n < 16 ? 2500 : n < 24 ? 1600 : n < 32 ? 800 : n < 48 ? 560 : n < 96 ? 400 : n < 200 ? 330 : 230;
+    return n > 8 && ncg >= from * cus;
 }
 
 // LDS of the tiled kernel (long rows, tables that are not one ring): the slot table (8 bytes per slot), TWO tile
@@ -294,6 +297,20 @@ inline int two_rows_lanes(int n, int deg, bool cd, int logc) {
     if (logc < 3 && most > 512) most = 512;
     return cd && n < 8 && most > 768 ? 768 : most;
 }
+// The looping form: 1024 lanes, up to four rows each.
+inline ShortPlan short_loop_plan(int n, int deg, int64_t ncg, bool cd) {
+    // A lane without a row of its own repeats the last one, loads and stores alike: fewer rows per lane where that leaves
+    // fewer such places, unless the tile then narrows below a wavefront's 64 column groups (13 x 3.9 M, 16 places at four
+    // rows, 14 at two: 131 and 119 us; 200 x 250 k, 208 at four, 204 at three on half the width: 131 and 143), or from 128 with
+    // the distance and 20 to 28 learners (28 places, 26 on half the width: 26 x 2 M 126 / 134, with 13 slots 131 / 156).
+    ShortPlan best = short_widest(n, deg, ncg, cd, false, kShortThreads, kShortRows);
+    for (int rows = kShortRows - 1; rows >= 2; --rows) {
+        const ShortPlan p = short_widest(n, deg, ncg, cd, false, kShortThreads, rows);
+        if (p.nrg * p.rows < best.nrg * best.rows && (p.logc == best.logc || (p.logc >= 6 && (!cd || n < 20 || n > 28))))
+            best = p;
+    }
+    return best;
+}
 // Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
 //   - few columns: two rows per lane, on as few lanes as leave a row segment of a 128-byte line.  A lane reads its rows'
 //     slots from LDS one after the other; with eight rows each on a few workgroups that chain is the launch.  Eight rows /
@@ -339,17 +356,7 @@ inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, bool 
         }
         if (n > 4) return short_widest(n, deg, ncg, cd, false, kShortThreads, 2);
     }
-    // A lane without a row of its own repeats the last one, loads and stores alike: fewer rows per lane where that leaves
-    // fewer such places, unless the tile then narrows below a wavefront's 64 column groups (13 x 3.9 M, 16 places at four
-    // rows, 14 at two: 131 and 119 us; 200 x 250 k, 208 at four, 204 at three on half the width: 131 and 143), or from 128 with
-    // the distance and 20 to 28 learners (28 places, 26 on half the width: 26 x 2 M 126 / 134, with 13 slots 131 / 156).
-    ShortPlan best = short_widest(n, deg, ncg, cd, false, kShortThreads, kShortRows);
-    for (int rows = kShortRows - 1; rows >= 2; --rows) {
-        const ShortPlan p = short_widest(n, deg, ncg, cd, false, kShortThreads, rows);
-        if (p.nrg * p.rows < best.nrg * best.rows && (p.logc == best.logc || (p.logc >= 6 && (!cd || n < 20 || n > 28))))
-            best = p;
-    }
-    return best;
+    return short_loop_plan(n, deg, ncg, cd);
 }
 
 }  // namespace plan

@@ -255,39 +255,6 @@ int allow_lds(const void* fn, size_t lds_bytes) {
     if (used < 512) done[used++] = Entry{fn, device};
     return PSGD_OK;
 }
-constexpr int kLaunchRefused = INT32_MIN;
-
-// Launches one instantiation of the ring-walk kernel, one workgroup per compute unit.
-// Returns the grid size, minus the grid size (and launches nothing) when the fused distance would need more
-// than `slots` partials, or kLaunchRefused when the runtime refuses the LDS size.
-std::atomic<unsigned> g_ring_launches{0};   // each takes the next of the pace words
-template <typename GT, bool CD, bool RAGGED, int D>
-int launch_mix_t(const plan::SweepPlan& sp, int grid, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
-                 const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
-    if (lds_bytes < plan::kRingLds) lds_bytes = plan::kRingLds;
-    if (allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D>), lds_bytes)) return kLaunchRefused;
-    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D>), dim3(grid), dim3(plan::ring_threads({1, sp.chunk}, plan::kRingLanes) + 64), lds_bytes,
-                       s, X, X_out, G, nbr, w, n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk},
-                       (int)(g_ring_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots), plan::pace_lead(D), partials);
-    return grid;
-}
-template <typename GT, bool CD, bool RAGGED>
-int launch_mix(const DeviceInfo& di, size_t lds_bytes, hipStream_t s, const float* X, float* X_out, const GT* G,
-               const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, int slots) {
-    const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
-    if (CD && grid > slots) return -grid;   // one partial per workgroup must fit the caller's buffer: nothing is launched
-    const plan::SweepPlan sp = plan::sweep_plan((d + 3) / 4, grid, plan::kRingLanes);
-#define PSGD_RING_DEPTH(D)                                                                                                \
-    case D: return launch_mix_t<GT, CD, RAGGED, D>(sp, grid, lds_bytes, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials)
-    switch (plan::ring_depth(sp, n)) {
-        PSGD_RING_DEPTH(1);
-        PSGD_RING_DEPTH(2);
-        PSGD_RING_DEPTH(4);
-        PSGD_RING_DEPTH(8);
-    }
-#undef PSGD_RING_DEPTH
-    return kLaunchRefused;
-}
 
 // Long rows take the large lockstep workgroup: at least `sweeps` column groups per lane of one such
 // workgroup per CU.
@@ -306,16 +273,13 @@ inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) {
 
 // Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
 // negative status.
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool SKIP_RINGS = false>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
 int launch_short_t(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
-                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
-                   int64_t slots = plan::kShortSlots) {
-    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW, SKIP_RINGS>);
-    size_t lds = p.lds;
-    if (SKIP_RINGS && lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
-    if (int rc = allow_lds(fn, lds)) return rc;
-    const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? slots : INT32_MAX);
-    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW, SKIP_RINGS>), dim3(grid), dim3(p.threads), lds, s, X,
+                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>);
+    if (int rc = allow_lds(fn, p.lds)) return rc;
+    const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? plan::kShortSlots : INT32_MAX);
+    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X,
                        X_out, G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
     return CD ? grid : 0;
 }
@@ -365,34 +329,45 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
     return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
 }
 
-// The same kernel behind the ring walk, for 3-slot tables that are not one ring: rows long enough to loop and far too large
-// for the last-level cache.  `partials` and `slots`: what the ring walk has left.
+// Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.  Returns the number of workgroups (partial
+// sums with the distance) or a negative status.
+std::atomic<unsigned> g_ring_launches{0};   // each takes the next of the pace words
+template <typename GT, bool CD, bool RAGGED, int D>
+int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp, int cached, hipStream_t s, const float* X, float* X_out,
+                  const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+    size_t lds = tp.lds > plan::kRingLds ? tp.lds : plan::kRingLds;
+    if (lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
+    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D>), lds)) return rc;
+    const int lanes = plan::ring_threads({1, sp.chunk}, plan::kRingLanes);
+    const int threads = lanes + 64 > tp.threads ? lanes + 64 : tp.threads;
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
+                       Sweeps{sp.count, sp.chunk}, lanes,
+                       (int)(g_ring_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots), plan::pace_lead(D),
+                       Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, partials);
+    return grid;
+}
 template <typename GT, bool CD>
-int launch_short_behind_ring(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out,
-                             const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr,
-                             double* partials, int64_t slots) {
-    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
+int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const float* X, float* X_out, const GT* G, const int32_t* nbr,
+                const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
+    if (CD && grid > plan::kShortSlots)                       // one partial per workgroup must fit the smallest buffer
+        return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, grid, (int)plan::kShortSlots);
+    const plan::SweepPlan sp = plan::sweep_plan(ncg, grid, plan::kRingLanes);
+    const plan::ShortPlan tp = plan::short_loop_plan(n, 3, ncg, CD);
+    const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
-    constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
-#define PSGD_SHORT(R, CACHED)                                                                                             \
-    return launch_short_t<GT, CD, 3, R, false, CACHED, false, true>(di, p, s, X, X_out, G, nbr, w, 3, n, d, ld, neg_lr,    \
-                                                                    partials, slots)
-#define PSGD_SHORT_BEHIND(R)                                                                                              \
-    case R:                                                                                                               \
-        if (R == 2 || cached == kBoth) PSGD_SHORT(R, kBoth);                                                              \
-        if constexpr (R != 2 && sizeof(GT) == 2)                                                                          \
-            if (cached) PSGD_SHORT(R, plan::kCachedLoads);                                                                \
-        if constexpr (R != 2) PSGD_SHORT(R, 0)
-    if (!p.one) {
-        switch (p.rows) {
-            PSGD_SHORT_BEHIND(2);
-            PSGD_SHORT_BEHIND(3);
-            PSGD_SHORT_BEHIND(4);
-        }
+#define PSGD_RING(RAGGED, D) launch_ring_t<GT, CD, RAGGED, D>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials)
+    // With one or two rows on their way the ragged form costs nothing (64 x 25.6 M 3137 / 3129 us); with more, a lane's own work shows
+    // (512 x 205 k with six: 246, ragged 265).
+    switch (plan::ring_depth(sp, n)) {
+        case 1: return PSGD_RING(true, 1);
+        case 2: return PSGD_RING(true, 2);
+        case 4: return d % kVec ? PSGD_RING(true, 4) : PSGD_RING(false, 4);
+        case 6: return d % kVec ? PSGD_RING(true, 6) : PSGD_RING(false, 6);
     }
-#undef PSGD_SHORT_BEHIND
-#undef PSGD_SHORT
-    return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
+#undef PSGD_RING
+    return fail(PSGD_EINVAL, "%s: no ring walk of this depth", name);
 }
 
 // Pitches are in elements of the array they belong to.
@@ -436,7 +411,6 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // use, shared by every call on the device, streams serialised), or the static array of the entry point
     // that may not allocate (no serialisation: that would need an event).
     double* partials = nullptr;
-    constexpr int slots = (int)plan::kShortSlots;
     if (want_cd) {
         if (no_alloc) {
             if (int rc = static_partials(di, &partials)) return rc;
@@ -454,49 +428,32 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
     const int64_t ncg = (d + kVec - 1) / kVec;
-    // 3-slot tables: from plan::ring_rows on the ring-walk kernel does the work when the table is one ring (every table of
-    // Sec. 3); the kernel for any other table follows it, because each path wants its own workgroup shape and registers.
-    // That kernel, and the one for tables of other slot counts: on long rows the tiled kernel is as good or a little better while
+    // 3-slot tables: from plan::ring_rows_paced on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
+    // through tiles; below it the short-row kernel.
+    // Tables of other slot counts: on long rows the tiled kernel is as good or a little better while
     // its row segments are wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5
     // slots 76.6 / 76.0), else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001
     // 838 / 1322, 300 x 1.6 M 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).  Tables of 16 slots and more, bound by LDS
     // reads, on 9 to 64 learners also where rows start on 16 bytes only (64 x 3 200 004 with 32 slots 674 / 599, 16 x 12 000 004 601 /
-    // 559), not on shorter rows (9 x 2.3 M with bf16 gradients 80 / 112).  3-slot tables behind the ring walk: 200 x 1 000 001 513 / 738,
-    // 512 x 400 001 556 / 1084, 128 x 1 600 004 495 / 579, 24 x 6 400 004 365 / 390; on lines 64 x 2 M 297 / 297, 128 x 1.6 M 497 / 497.  29 to 32 learners, whose
-    // short-row tile is 128 column groups wide, are ahead on the tiled kernel off the lines too (32 x 1 400 004 124 / 116, 32 x 3 000 016
+    // 559), not on shorter rows (9 x 2.3 M with bf16 gradients 80 / 112).  29 to 32 learners, whose
+    // short-row tile is 128 column groups wide, are ahead on the tiled kernel off the lines too (32 x 3 000 016
     // with 13 slots 236 / 220).
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
     const bool wide = n > 8 && n <= 128 && (rows_on_lines(X, X_out, ld) || (n > 28 && n <= 32));
-    const bool ring = deg == 3 && plan::ring_rows(n, ncg, di->cus, kRingThreads);
-    const bool tiled = deg == 3 ? ring && wide
-                                : long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
+    const bool ring = deg == 3 && (plan::ring_rows_paced(n, ncg, di->cus) || plan::ring_rows(n, ncg, di->cus, kRingThreads));
+    const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
     if (ring) {
-#define PSGD_RING(CD, RAGGED)                                                                                             \
-    launch_mix<GT, CD, RAGGED>(*di, lds_classify_bytes(n), s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, slots - 1)
-        if (d % kVec) grid = want_cd ? PSGD_RING(true, true) : PSGD_RING(false, true);
-        else grid = want_cd ? PSGD_RING(true, false) : PSGD_RING(false, false);
-#undef PSGD_RING
-        if (grid == kLaunchRefused) return PSGD_EHIP;   // allow_lds has recorded the reason
-        if (grid < 0)                                   // one more for the kernel behind it
-            return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, 1 - grid, slots);
-        const hipError_t e1 = hipGetLastError();
-        if (e1 != hipSuccess) return hip_fail(e1, name);
-    }
-    const int first = want_cd ? grid : 0;
-    if (!tiled) {
+        grid = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials)
+                       : launch_ring<GT, false>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials);
+        if (grid < 0) return grid;
+    } else if (!tiled) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
                                          : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
-        int more = 0;
-        if (ring && want_cd)
-            more = launch_short_behind_ring<GT, true>(*di, sp, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials + first,
-                                                      slots - first);
-        else if (ring) more = launch_short_behind_ring<GT, false>(*di, sp, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, nullptr, 0);
-        else if (want_cd && deg == 3) more = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else if (want_cd) more = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else if (deg == 3) more = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else more = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        if (more < 0) return more;
-        grid = first + more;
+        if (want_cd && deg == 3) grid = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        else if (want_cd) grid = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        else if (deg == 3) grid = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        else grid = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
+        if (grid < 0) return grid;
     } else {
         // 1024 lanes without the distance, 512 with it.
         const int threads = want_cd ? kTileThreads : kDeepThreads;
@@ -505,11 +462,9 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         if (tp.lpr == 0)
             return fail(PSGD_EINVAL, "%s: n=%d, deg=%d does not fit the tiled kernel's LDS", name, n, deg);
         size_t lds_bytes = tp.total;
-        if (ring && lds_bytes < tp.tab_bytes + lds_classify_bytes(n)) lds_bytes = tp.tab_bytes + lds_classify_bytes(n);
         const size_t remainder = (size_t)n * (d % kVec) * 2 * sizeof(float);
         if (lds_bytes < tp.tab_bytes + remainder) lds_bytes = tp.tab_bytes + remainder;
         const int64_t ntiles = (d / kVec + tp.lpr - 1) / tp.lpr;
-        int tgrid = 0;
 #define PSGD_DEG_LAUNCH(CD, UQ)                                                                                           \
     do {                                                                                                                  \
         constexpr int T = CD ? kTileThreads : kDeepThreads;                                                               \
@@ -517,19 +472,17 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         if (int rc = allow_lds(fn, lds_bytes)) return rc;                                                                 \
         int per_cu = resident_per_cu(fn, lds_bytes, T);                                                                   \
         if (per_cu > 2 * kGridPerCu) per_cu = 2 * kGridPerCu;                                                             \
-        tgrid = deg_grid(ntiles, di->cus, per_cu);                                                                        \
+        grid = deg_grid(ntiles, di->cus, per_cu);                                                                         \
         /* one partial per workgroup: a smaller persistent grid still covers every tile */                                \
-        if (CD && tgrid > slots - first) tgrid = slots - first;                                                           \
-        hipLaunchKernelGGL((mix_deg_kernel<GT, CD, T, UQ>), dim3(tgrid), dim3(T), lds_bytes, s, X, X_out, G, nbr, w, deg, \
-                           n, d, ld, neg_lr, tp.lpr, ring ? 1 : 0, tp.comb_in_tile ? 1 : 0,                               \
-                           CD ? partials + first : partials);                                                            \
+        if (CD && grid > (int)plan::kShortSlots) grid = (int)plan::kShortSlots;                                           \
+        hipLaunchKernelGGL((mix_deg_kernel<GT, CD, T, UQ>), dim3(grid), dim3(T), lds_bytes, s, X, X_out, G, nbr, w, deg,  \
+                           n, d, ld, neg_lr, tp.lpr, tp.comb_in_tile ? 1 : 0, partials);                                  \
     } while (0)
         if (want_cd && tp.lpr >= 64) PSGD_DEG_LAUNCH(true, true);
         else if (want_cd) PSGD_DEG_LAUNCH(true, false);
         else if (tp.lpr >= 64) PSGD_DEG_LAUNCH(false, true);
         else PSGD_DEG_LAUNCH(false, false);
 #undef PSGD_DEG_LAUNCH
-        grid = first + tgrid;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);

@@ -4,6 +4,7 @@
 #define PSGD_RING_WALK_H
 
 #include "psgd_device.h"
+#include "psgd_short.h"
 
 namespace psgd {
 namespace {
@@ -235,41 +236,70 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
 }
 
 
+// The step on long rows for any 3-slot table, one launch.  The workgroups stage and classify the table alike; one ring is walked, any
+// other table goes through tiles (short_tiles; Tiles: how), an invalid one raises the flag and nothing is written.  A
+// kernel of its own behind this one for the other tables, which for a ring classified the table once more and ended, took 4.5 to 7 us
+// of every launch.
 // CD = also reduce the consensus distance of the outputs into partials[blockIdx.x].
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
-// same number of sweeps, lanes beyond the chunk idle; the launch has no more wavefronts than one sweep needs (plan::ring_threads).
-// A table that is not one ring is left to the kernel that the launcher enqueues right behind this one (tiled, or the short-row
-// kernel) and that classifies the table the same way; this kernel then writes nothing.
-// RAGGED: 4 does not divide d.
+// same number of sweeps; the wavefronts that neither a sweep nor the tiles need are not launched.
+// RAGGED: 4 may not divide d.  D: rows on their way per lane.
+struct Tiles {
+    int rows, cached, logc, nrg, tab_bytes, tile_bytes;
+};
 template <typename GT, bool CD, bool RAGGED, int D>
-__global__ __launch_bounds__(plan::ring_most_threads(D)) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
+__global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                                          const int32_t* __restrict__ nbr,
                                                                          const float* __restrict__ w, int n, int64_t d, Pitch ld,
-                                                                         float neg_lr, Sweeps sweeps, int slot, int lead,
-                                                                         double* __restrict__ partials) {
+                                                                         float neg_lr, Sweeps sweeps, int lanes, int slot, int lead,
+                                                                         Tiles tiles, double* __restrict__ partials) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[(plan::kRingLanes + 64) / 64];
+    __shared__ int lds_bad[(plan::kRingLanes + 64) / 64];
     __shared__ Pace pace;
-    const int T = blockDim.x;
+    const int tid = threadIdx.x;
     const Lds l = carve(lds_raw, n);
-    if (threadIdx.x == 0) pace = Pace{0, lead};
-    const int kind = stage_table(nbr, w, n, l, T);               // contains barriers
+    if (tid == 0) pace = Pace{0, lead};
+    const int kind = stage_table(nbr, w, n, l, blockDim.x);      // contains barriers
     if (kind == kTableBad) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&g_status_word, 1);
-        if (CD && threadIdx.x == 0) partials[blockIdx.x] = __builtin_nan("");
+        if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
+        if (CD && tid == 0) partials[blockIdx.x] = __builtin_nan("");
         return;
     }
+    if (kind == kTableGeneral) {
+        if (tid >= tiles.nrg << tiles.logc) return;              // whole wavefronts
+        lds_barrier();                                           // the staged table has been read
+#define PSGD_TILES(R, CACHED)                                                                                              \
+    short_tiles<GT, CD, 3, R, false, CACHED, false>(X, Xout, G, nbr, w, 3, n, d, ld, neg_lr, tiles.logc, tiles.nrg,        \
+                                                    tiles.tab_bytes, tiles.tile_bytes, partials,                          \
+                                                    ShortLds{lds_raw, lds_waves, lds_bad})
+        constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
+        if (tiles.rows <= 2) {
+            if (tiles.cached == kBoth) PSGD_TILES(2, kBoth);
+            else PSGD_TILES(2, 0);
+        } else if (tiles.rows == 3) {
+            if (tiles.cached == kBoth) PSGD_TILES(3, kBoth);
+            else PSGD_TILES(3, 0);
+        } else {
+            if (tiles.cached == kBoth) PSGD_TILES(4, kBoth);
+            else if (sizeof(GT) == 2 && tiles.cached) PSGD_TILES(4, plan::kCachedLoads);
+            else PSGD_TILES(4, 0);
+        }
+#undef PSGD_TILES
+        return;
+    }
+    if (tid >= lanes + 64) return;                               // whole wavefronts
     const int64_t ncg = (d + kVec - 1) / kVec;
     double total = 0.0;
-    int64_t my_sweeps = kind == kTableRing ? sweeps.count : 0;
+    int64_t my_sweeps = sweeps.count;
     while (my_sweeps > 0 && sweeps.base(my_sweeps - 1) >= ncg) --my_sweeps;   // uniform
     if (my_sweeps > 0) {
-        if ((int)threadIdx.x >= T - 64) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
+        if (tid >= lanes) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
         else total = ring_walk<GT, CD, RAGGED, D>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n);
     }
     if (CD) {
-        const double bs = block_sum_any(total, lds_waves, T);
-        if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+        const double bs = block_sum_any(total, lds_waves, lanes + 64);
+        if (tid == 0) partials[blockIdx.x] = bs;
     }
 }
 

@@ -36,17 +36,21 @@ namespace {
 // ---------------------------------------------------------------------------------------
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (two or up to eight rows per lane: nothing is
 // loaded ahead, so those registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
-// FEW: rows of fewer than four columns.  SKIP_RINGS: enqueued behind the ring walk, which leaves tables that are not one ring to this
-// kernel; both classify the table with the same code, and the one it does not belong to writes nothing (and contributes 0 to the distance).
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool SKIP_RINGS = false>
-__global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
-    const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
-    int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
-    double* __restrict__ partials) {
+// FEW: rows of fewer than four columns.  Run by nrg << logc lanes of the workgroup, the others having ended.
+struct ShortLds {
+    char* dynamic;                           // plan::ShortPlan::lds bytes
+    double* waves;                           // one per wavefront
+    int* bad;                                // the same
+};
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+__device__ __forceinline__ void short_tiles(const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr,
+                                            const float* __restrict__ w, int deg_any, int n, int64_t d, Pitch ld, float neg_lr,
+                                            int logc, int nrg, int tab_bytes, int tile_bytes, double* __restrict__ partials,
+                                            const ShortLds& lds) {
     typedef typename RawG<GT>::T GR;
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    __shared__ double lds_waves[plan::kShortThreads / 64];
-    __shared__ int lds_bad[plan::kShortThreads / 64];
+    char* lds_raw = lds.dynamic;
+    double* lds_waves = lds.waves;
+    int* lds_bad = lds.bad;
     const int deg = DEG ? DEG : deg_any;
     const int T = nrg << logc, C = 1 << logc, tid = threadIdx.x, lane = tid & (C - 1), lane16 = lane * 16;
     int rg = tid >> logc;
@@ -62,13 +66,6 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
 
-    if (SKIP_RINGS) {
-        const int kind = stage_table(nbr, w, n, carve(lds_raw, n), T);
-        if (kind != kTableGeneral) {                            // out of range: the ring walk has raised the flag
-            if (CD && tid == 0) partials[blockIdx.x] = kind == kTableRing ? 0.0 : __builtin_nan("");
-            return;
-        }
-    }
     // The table's loads go first, the first tile's behind them; a lane's share of a larger table follows.
     constexpr int TE = 2;
     int32_t tv[TE];
@@ -214,6 +211,18 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
         const double bs = block_sum_any(total, lds_waves, T);
         if (tid == 0) partials[blockIdx.x] = bs;
     }
+}
+
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+__global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
+    const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
+    int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
+    double* __restrict__ partials) {
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    __shared__ double lds_waves[plan::kShortThreads / 64];
+    __shared__ int lds_bad[plan::kShortThreads / 64];
+    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW>(X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes, tile_bytes,
+                                                  partials, ShortLds{lds_raw, lds_waves, lds_bad});
 }
 
 }  // namespace

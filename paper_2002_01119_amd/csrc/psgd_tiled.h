@@ -413,28 +413,15 @@ __device__ double tile_remainder(const float* X, float* Xout, const GT* __restri
 // walks, products of several mixing rounds, and 3-slot tables that are not one ring).
 // LDS: TileSlot tab[deg n] | two tile buffers | merge slots (plan::tile_plan).
 //
-// skip_rings (3-slot tables only): the launcher enqueues this kernel behind the ring-walk kernel because only
-// the device can tell which of the two a table needs; both classify it with the same code, and the one it does
-// not belong to writes nothing (and contributes 0 to the distance).
-//
 // UQ: a row group is whole wavefronts (lpr >= 64).
 template <typename GT, bool CD, int T, bool UQ>
 __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                     const int32_t* __restrict__ nbr, const float* __restrict__ w,
                                                     int deg, int n, int64_t d, Pitch ld, float neg_lr, int lpr,
-                                                    int skip_rings, int comb_in_tile, double* __restrict__ partials) {
+                                                    int comb_in_tile, double* __restrict__ partials) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[T / 64];
     const size_t tab_bytes = (((size_t)n * deg * sizeof(TileSlot)) + 15) & ~(size_t)15;
-    if (skip_rings) {
-        // the tile area is free until the first tile is loaded: classify there
-        const int kind = stage_table(nbr, w, n, carve(lds_raw + tab_bytes, n), T);
-        if (kind != kTableGeneral) {
-            // one ring: the other kernel's work.  Invalid: it has raised the flag; the distance is NaN.
-            if (CD && threadIdx.x == 0) partials[blockIdx.x] = kind == kTableRing ? 0.0 : __builtin_nan("");
-            return;
-        }
-    }
     TileSlot* tab = reinterpret_cast<TileSlot*>(lds_raw);
     int ok = 1;
     for (int e = threadIdx.x; e < deg * n; e += T) {

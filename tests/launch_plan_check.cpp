@@ -101,9 +101,9 @@ int main() {
             for (int n : {9, 10, 15, 16, 17, 64, 512}) {
                 const SweepPlan p = sweep_plan(ncg, cus, kRingLanes);
                 const int depth = ring_depth(p, n), t = ring_threads({1, p.chunk}, kRingLanes) + 64;
-                CHECK(t <= ring_most_threads(depth) && t - 64 >= p.chunk && t % 64 == 0, "ring walk: %d lanes, depth %d, chunk %lld", t, depth,
+                CHECK(t <= kRingThreadsMost && t - 64 >= p.chunk && t % 64 == 0, "ring walk: %d lanes, depth %d, chunk %lld", t, depth,
                       (long long)p.chunk);
-                CHECK((depth == 1 || depth == 2 || depth == 4 || depth == 8) && n - 1 + 2 + depth < 2 * n, "ring walk: depth %d, n %d", depth, n);
+                CHECK((depth == 1 || depth == 2 || depth == 4 || depth == 6) && n - 1 + 2 + depth < 2 * n, "ring walk: depth %d, n %d", depth, n);
                 CHECK(pace_lead(depth) >= 4 * depth && kPaceSpins > 0, "ring walk: a lead that the loads on their way need");
             }
 

@@ -59,6 +59,39 @@ def test_ring_walk_every_element(psgd, n, d, gkind):
     assert psgd.device_status() == 0
 
 
+# tables that are not one ring on rows as long: two, three and four rows per lane, rows on and off 128-byte lines
+@pytest.mark.parametrize("n,d,gkind", [
+    (10, 3_700_003, "f32"), (13, 2_600_000, "bf16"), (16, 1_700_032, "f32"), (17, 1_700_001, "bf16"), (33, 600_001, "f32"),
+    (64, 420_032, "bf16"), (100, 350_002, "f32"), (300, 240_032, "bf16"), (301, 240_001, "bf16"), (512, 240_032, "f32")])
+def test_other_tables_on_the_same_rows(psgd, n, d, gkind):
+    X, G, nbr, w, tol = _inputs(psgd, n, d, gkind, 83 + n)
+    rng = np.random.default_rng(n)
+    c = rng.random(3).astype(np.float32) + np.float32(0.05)
+    nbr = np.stack([rng.permutation(n) for _ in range(3)], axis=1).astype(np.int32)
+    w = np.tile((c / c.sum()).astype(np.float32), (n, 1))
+    want = orc.sparse_mix_step(X, G, nbr, w, 0.2, threads=4)
+    Xd = torch.from_numpy(X).to("cuda:0")
+    Gd = torch.from_numpy(G.view(np.int16) if gkind == "bf16" else G).to("cuda:0")
+    nd, wd = torch.from_numpy(nbr).to("cuda:0"), torch.from_numpy(w).to("cuda:0")
+    for form in ("plain", "distance", "in place"):
+        Y = torch.full_like(Xd, float("nan")) if form != "in place" else Xd
+        c = torch.full((1,), float("nan"), dtype=torch.float64, device="cuda:0") if form != "plain" else None
+        psgd.mix_step(Xd, Y, Gd, nd, wd, 0.2, cdist_out=c)
+        torch.cuda.synchronize()
+        got = Y.cpu().numpy()
+        assert np.abs(got - want).max() <= tol, form
+        if c is not None:
+            ref = orc.sparse_consensus_dist(got.astype(np.float64), threads=4)
+            assert abs(c.item() - ref) <= 1e-9 * ref, form
+    bad = nbr.copy()
+    bad[n - 1, 2] = n
+    before = Xd.clone()
+    c = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    psgd.mix_step(Xd, Xd, Gd, torch.from_numpy(bad).to("cuda:0"), wd, 0.2, cdist_out=c)
+    torch.cuda.synchronize()
+    assert torch.equal(Xd, before) and torch.isnan(c).all() and psgd.device_status() == 1
+
+
 def test_launches_that_overlap_and_share_pace_words(psgd):
     """Three streams with 100 launches each, so that launches under way at once share words; the bits are those of a launch alone."""
     n, d = 64, 1_000_004
