@@ -277,6 +277,18 @@ int psgd_synth_grad(const float* X_prev, const float* noise, float* G,
 /* psgd_synth_grad_ex - the same for [n, d] arrays whose rows are ld* (>= d) elements apart. */
 int psgd_synth_grad_ex(const float* X_prev, int64_t ldx, const float* noise, int64_t ldn,
                        float* G, int64_t ldg, int n, int64_t d, float c, void* stream);
+/*
+ * psgd_mix_step_d1d - one iteration of the delay-by-one schedule (Sec. 4, Eq. 14) in one pass: the step
+ *     X_out[i,:] = sum_s w[i,s] * X[nbr[i,s],:] - lr * G[i,:]
+ * of psgd_mix_step_deg (fp32 gradients, delay_mode 1, `deg` slots, optional distance) and the producer of the next
+ * gradients, G_next = fma(c, X, noise) as psgd_synth_grad_ex computes it, from the same rows of X.  Same values as the
+ * two calls one after the other.  Row pitches in elements.  No output may overlap another array (PSGD_EALIAS).  The next
+ * gradients are written whatever the table holds, the step only if it is valid.
+ */
+int psgd_mix_step_d1d(const float* X, int64_t ldx, float* X_out, int64_t ldo, const float* G, int64_t ldg,
+                      const int32_t* nbr, const float* w, int deg, int n, int64_t d, float lr,
+                      const float* noise, int64_t ldn, float* G_next, int64_t ldgn, float c,
+                      double* cdist_out, void* stream);
 
 /*
  * psgd_reference_stream - measurement support, not a step of the method: the memory traffic of

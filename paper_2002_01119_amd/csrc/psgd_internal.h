@@ -90,7 +90,11 @@ constexpr int kPaceSpins = 400;
 // for a depth of one: 3500 / 3800.
 inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 6; }
 constexpr int kRingThreadsMost = kRingLanes + 64;   // of the workgroup
-inline int pace_lead(int depth) { return depth == 1 ? 6 : 5 * depth; }
+// With the producer of the next gradients in the walk five arrays are on their way, not three: fewer rows, less lead (pairs, us: one row
+// of lead 5, 6 and 7 quarters 128 x 8 M 3414 / 3494 / 3674; one row or two of depth 128 x 520 k 223 / 235, two or four 113 x 328 k 134 / 171,
+// 421 x 301 k 445 / 576).
+inline int ring_depth_produce(const SweepPlan& s) { return s.chunk >= 450 ? 1 : 2; }
+inline int pace_lead(int depth, bool produce = false) { return depth == 1 ? (produce ? 5 : 6) : 5 * depth; }
 // More than half of a compute unit's LDS: the workgroups then take a compute unit each.  Two on one fall behind the others, which wait.
 constexpr size_t kRingLds = 82 * 1024;
 

@@ -332,23 +332,24 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
 // Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.  Returns the number of workgroups (partial
 // sums with the distance) or a negative status.
 std::atomic<unsigned> g_ring_launches{0};   // each takes the next of the pace words
-template <typename GT, bool CD, bool RAGGED, int D>
+template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp, int cached, hipStream_t s, const float* X, float* X_out,
-                  const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+                  const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
+                  const Produce& prod) {
     size_t lds = tp.lds > plan::kRingLds ? tp.lds : plan::kRingLds;
     if (lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
-    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D>), lds)) return rc;
+    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D, PROD>), lds)) return rc;
     const int lanes = plan::ring_threads({1, sp.chunk}, plan::kRingLanes);
     const int threads = lanes + 64 > tp.threads ? lanes + 64 : tp.threads;
-    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D, PROD>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
                        Sweeps{sp.count, sp.chunk}, lanes,
-                       (int)(g_ring_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots), plan::pace_lead(D),
-                       Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, partials);
+                       (int)(g_ring_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots), plan::pace_lead(D, PROD),
+                       Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, prod, partials);
     return grid;
 }
 template <typename GT, bool CD>
 int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const float* X, float* X_out, const GT* G, const int32_t* nbr,
-                const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+                const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, const Produce* prod) {
     const int64_t ncg = (d + kVec - 1) / kVec;
     const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
     if (CD && grid > plan::kShortSlots)                       // one partial per workgroup must fit the smallest buffer
@@ -357,24 +358,50 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
     const plan::ShortPlan tp = plan::short_loop_plan(n, 3, ncg, CD);
     const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
-#define PSGD_RING(RAGGED, D) launch_ring_t<GT, CD, RAGGED, D>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials)
+#define PSGD_RING(RAGGED, D, PROD)                                                                                         \
+    launch_ring_t<GT, CD, RAGGED, D, PROD>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials,      \
+                                           prod ? *prod : Produce{})
+    const int depth = plan::ring_depth(sp, n);
     // With one or two rows on their way the ragged form costs nothing (64 x 25.6 M 3137 / 3129 us); with more, a lane's own work shows
     // (512 x 205 k with six: 246, ragged 265).
-    switch (plan::ring_depth(sp, n)) {
-        case 1: return PSGD_RING(true, 1);
-        case 2: return PSGD_RING(true, 2);
-        case 4: return d % kVec ? PSGD_RING(true, 4) : PSGD_RING(false, 4);
-        case 6: return d % kVec ? PSGD_RING(true, 6) : PSGD_RING(false, 6);
+    if constexpr (sizeof(GT) == 4) {
+        if (prod) {
+            return plan::ring_depth_produce(sp) == 1 ? PSGD_RING(true, 1, true) : PSGD_RING(true, 2, true);
+        }
+    }
+    switch (depth) {
+        case 1: return PSGD_RING(true, 1, false);
+        case 2: return PSGD_RING(true, 2, false);
+        case 4: return d % kVec ? PSGD_RING(true, 4, false) : PSGD_RING(false, 4, false);
+        case 6: return d % kVec ? PSGD_RING(true, 6, false) : PSGD_RING(false, 6, false);
     }
 #undef PSGD_RING
     return fail(PSGD_EINVAL, "%s: no ring walk of this depth", name);
+}
+
+// Enqueues G = c X_prev + noise on n rows of d columns, in dispatch order, one 128-bit access per lane and array: what is in flight
+// stays a narrow window that moves through the arrays, which the HBM serves at 6.4 TB/s; lanes that walk the rows, or 4096 persistent
+// workgroups that stride over the array, reach 4.9-5.4 (128 x 8 M dense 2460 -> 1930 us).  A launch counts its lanes in 32 bits: beyond
+// kShortMostTiles workgroups a row they stride.
+int enqueue_producer(const char* name, const float* xp, int64_t ldx, const float* noise, int64_t ldn, float* g, int64_t ldg, int n,
+                     int64_t d, float c, hipStream_t s) {
+    if (n > 1 && ldx == d && ldn == d && ldg == d) {           // dense: one row
+        d *= n;
+        n = 1;
+    }
+    const int64_t need = ((d + kVec - 1) / kVec + kThreads - 1) / kThreads;
+    const dim3 grid((unsigned)(need < plan::kShortMostTiles ? need : plan::kShortMostTiles), (unsigned)n);
+    if (d < kVec) hipLaunchKernelGGL(synth_grad_kernel<true>, grid, dim3(kThreads), 0, s, xp, ldx, noise, ldn, g, ldg, d, c);
+    else hipLaunchKernelGGL(synth_grad_kernel<false>, grid, dim3(kThreads), 0, s, xp, ldx, noise, ldn, g, ldg, d, c);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? PSGD_OK : hip_fail(e, name);
 }
 
 // Pitches are in elements of the array they belong to.
 template <typename GT>
 int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, int64_t ldo, const GT* G, int64_t ldg,
                   const int32_t* nbr, const float* w, int n, int64_t d, float lr, int delay_mode, bool want_cd,
-                  double* cd_out, void* stream, int deg = 3, bool no_alloc = false) {
+                  double* cd_out, void* stream, int deg = 3, bool no_alloc = false, const Produce* prod = nullptr) {
     clear_error();
     if (!X || !X_out || !G || !nbr || !w || (want_cd && !cd_out)) return fail(PSGD_EINVAL, "%s: null pointer", name);
     if (n < 1 || n > PSGD_MAX_N) return fail(PSGD_EINVAL, "%s: n=%d outside 1..%d", name, n, (int)PSGD_MAX_N);
@@ -443,8 +470,8 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const bool ring = deg == 3 && (plan::ring_rows_paced(n, ncg, di->cus) || plan::ring_rows(n, ncg, di->cus, kRingThreads));
     const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
     if (ring) {
-        grid = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials)
-                       : launch_ring<GT, false>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials);
+        grid = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, prod)
+                       : launch_ring<GT, false>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, prod);
         if (grid < 0) return grid;
     } else if (!tiled) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
@@ -490,9 +517,10 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid, cd_out);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "consensus_final_kernel");
-        if (!no_alloc) return release_partials(di, s);
     }
-    return PSGD_OK;
+    if (prod && !ring)
+        if (int rc = enqueue_producer(name, X, ldx, prod->noise, prod->ldn, prod->g, prod->ldg, n, d, prod->c, s)) return rc;
+    return want_cd && !no_alloc ? release_partials(di, s) : PSGD_OK;
 }
 
 template <typename GT>
@@ -722,6 +750,33 @@ int psgd_mix_step_deg(const float* X, int64_t ldx, float* X_out, int64_t ldo, co
                                       w, n, d, lr, delay_mode, cdist_out != nullptr, cdist_out, stream, deg);
 }
 
+int psgd_mix_step_d1d(const float* X, int64_t ldx, float* X_out, int64_t ldo, const float* G, int64_t ldg, const int32_t* nbr,
+                      const float* w, int deg, int n, int64_t d, float lr, const float* noise, int64_t ldn, float* G_next, int64_t ldgn,
+                      float c, double* cdist_out, void* stream) {
+    using namespace psgd;
+    const char* name = "psgd_mix_step_d1d";
+    clear_error();
+    if (!X || !X_out || !G || !noise || !G_next) return fail(PSGD_EINVAL, "%s: null pointer", name);
+    if (n < 1 || n > PSGD_MAX_N || d < 0) return fail(PSGD_EINVAL, "%s: n=%d d=%lld", name, n, (long long)d);
+    if (n > 1 && (ldx < d || ldo < d || ldg < d || ldn < d || ldgn < d)) return fail(PSGD_EINVAL, "%s: a row pitch is smaller than d", name);
+    if (n == 1) ldx = ldo = ldg = ldn = ldgn = d;
+    if (!aligned_to(noise, 4) || !aligned_to(G_next, 4)) return fail(PSGD_EALIGN, "%s: pointer not 4-byte aligned", name);
+    int64_t ldmax = ldn > ldgn ? ldn : ldgn;
+    for (int64_t l : {ldx, ldo, ldg}) ldmax = l > ldmax ? l : ldmax;
+    if (ldmax > 0 && (int64_t)n > INT64_MAX / 8 / ldmax) return fail(PSGD_EINVAL, "%s: n * pitch overflows", name);
+    const size_t row = (size_t)d * sizeof(float);
+    // what is written here and read there, or written twice, at the same time
+    if (rows_overlap(G_next, ldgn * 4, row, X, ldx * 4, row, n) || rows_overlap(G_next, ldgn * 4, row, noise, ldn * 4, row, n) ||
+        rows_overlap(G_next, ldgn * 4, row, G, ldg * 4, row, n) || rows_overlap(G_next, ldgn * 4, row, X_out, ldo * 4, row, n) ||
+        rows_overlap(noise, ldn * 4, row, X_out, ldo * 4, row, n))
+        return fail(PSGD_EALIAS, "%s: an output overlaps another array", name);
+    if (cdist_out && (scalar_overlaps(cdist_out, G_next, ldgn * 4, row, n) || scalar_overlaps(cdist_out, noise, ldn * 4, row, n)))
+        return fail(PSGD_EALIAS, "%s: the distance output overlaps a data buffer", name);
+    const Produce prod{noise, G_next, ldn, ldgn, c};
+    return mix_step_impl<float>(name, X, ldx, X_out, ldo, G, ldg, nbr, w, n, d, lr, 1, cdist_out != nullptr, cdist_out, stream, deg, false,
+                                &prod);
+}
+
 int psgd_mix_full(const float* X, int64_t ldx, float* X_out, int64_t ldo, const void* G, int64_t ldg, int g_is_bf16,
                   int n, int64_t d, float lr, int delay_mode, double* cdist_out, void* stream) {
     if (g_is_bf16 != 0 && g_is_bf16 != 1) {
@@ -808,14 +863,7 @@ int psgd_synth_grad(const float* X_prev, const float* noise, float* G, int64_t c
     if (overlaps(G, bytes, X_prev, bytes) || overlaps(G, bytes, noise, bytes))
         return fail(PSGD_EALIAS, "psgd_synth_grad: G overlaps an input");
     if (count == 0) return PSGD_OK;
-    DeviceInfo* di = nullptr;
-    if (int rc = device_info(&di)) return rc;
-    const int grid = persistent_grid(*di, (count + 3) / 4, 16);
-    hipLaunchKernelGGL(synth_grad_kernel, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), X_prev,
-                       noise, G, count, c);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "synth_grad_kernel");
-    return PSGD_OK;
+    return enqueue_producer("synth_grad_kernel", X_prev, count, noise, count, G, count, 1, count, c, static_cast<hipStream_t>(stream));
 }
 
 int psgd_synth_grad_ex(const float* X_prev, int64_t ldx, const float* noise, int64_t ldn, float* G, int64_t ldg,
@@ -834,19 +882,7 @@ int psgd_synth_grad_ex(const float* X_prev, int64_t ldx, const float* noise, int
     if (rows_overlap(G, ldg * 4, row, X_prev, ldx * 4, row, n) || rows_overlap(G, ldg * 4, row, noise, ldn * 4, row, n))
         return fail(PSGD_EALIAS, "psgd_synth_grad_ex: G overlaps an input");
     if (d == 0) return PSGD_OK;
-    DeviceInfo* di = nullptr;
-    if (int rc = device_info(&di)) return rc;
-    const int grid = persistent_grid(*di, (d + kVec - 1) / kVec, 8);
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (d < kVec)
-        hipLaunchKernelGGL(synth_grad_rows_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X_prev, ldx, noise, ldn, G, ldg,
-                           n, d, c);
-    else
-        hipLaunchKernelGGL(synth_grad_rows_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X_prev, ldx, noise, ldn, G, ldg,
-                           n, d, c);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "synth_grad_rows_kernel");
-    return PSGD_OK;
+    return enqueue_producer("synth_grad_kernel", X_prev, ldx, noise, ldn, G, ldg, n, d, c, static_cast<hipStream_t>(stream));
 }
 
 int psgd_reference_stream(int kind, const float* X, int64_t ldx, float* X_out, int64_t ldo, const void* G, int64_t ldg,

@@ -121,16 +121,26 @@ template <typename T> __device__ __forceinline__ const T* lane_at(const T* base,
     return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(elements * sizeof(T)));
 }
 
+// The gradient producer of the delay-by-one schedule beside the step (Sec. 4, Eq. 14; the stand-in G_next = c X + noise): the walk holds
+// every row of X in registers at the moment its output is made, so the pair moves 20 bytes per element instead of 24.
+struct Produce {
+    const float* noise;
+    float* g;
+    int64_t ldn, ldg;
+    float c;
+};
+
 // All rows of the workgroup's column groups, sweep by sweep, as one stream of items: item q is position q mod n of sweep q / n.
 // The X rows arrive in the order 0, n-1, 1, 2, .. n-2 of every sweep, so that at item q the stream stands at q + 2; loads, X and
 // gradient, are issued D items ahead, and across sweeps nothing drains.  Loads and stores are unconditional (the waits
 // then count operations instead of waiting for all of them); the stores of lanes that own nothing are dropped by the buffer's
 // bounds check.  An item's addresses and weights are worked out behind the item before it, so that a row's place is free for the
 // next load as soon as it has arrived: with them in between (LDS reads, 64-bit products) two rows took 2.3 us, not 1.6.
-template <typename GT, bool CD, bool RAGGED, int D>
+// PROD: also the next gradients; noise travels with the gradients.
+template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const GT* __restrict__ G, const RingEnt* ring, int n,
                                             int64_t d, Pitch ld, float neg_lr, const Sweeps& sweeps, int64_t my_sweeps, Pace* pace,
-                                            double inv_n) {
+                                            double inv_n, const Produce& prod) {
     typedef typename RawG<GT>::T GR;
     const int64_t ncg = (d + kVec - 1) / kVec;
     int64_t sw = 0;
@@ -152,22 +162,29 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
         const bool over = p >= n;
         return G + ((uint64_t)(uint32_t)ring_row(ring + (over ? p - n : p)) * (uint64_t)ld.g + (uint64_t)(over ? next_col : col));
     };
+    auto noise_at = [&](int p) __attribute__((always_inline)) {
+        const int64_t col = now.col, next_col = nxt.col;
+        const bool over = p >= n;
+        return prod.noise + ((uint64_t)(uint32_t)ring_row(ring + (over ? p - n : p)) * (uint64_t)prod.ldn + (uint64_t)(over ? next_col : col));
+    };
     auto lane_of = [&](int p) __attribute__((always_inline)) {
         const uint32_t at = now.at, next_at = nxt.at;
         return p >= n ? next_at : at;
     };
     f32x4 first = ld_x(lane_at(x_at(0), now.at)), last = ld_x(lane_at(x_at(1), now.at)), prev = last, cur = first, ahead = first;
-    f32x4 x[D];
+    f32x4 x[D], noise[PROD ? D : 1];
     GR g[D];
 #pragma unroll
     for (int u = 0; u < D; ++u) {
         x[u] = ld_x(lane_at(x_at(u + 2), lane_of(u + 2)));
         g[u] = ld_g_raw(lane_at(g_at(u), now.at));
+        if (PROD) noise[u] = ld_x(lane_at(noise_at(u), now.at));
     }
     // The next item: where its loads come from, where its output goes, its weights.
     const float* from_x;
     const GT* from_g;
-    float* to;
+    const float* from_noise = nullptr;
+    float *to, *to_g = nullptr;
     RingEnt e;
     int p = 0, items = 0;
     auto prepare = [&]() __attribute__((always_inline)) {
@@ -175,10 +192,14 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
         to = Xout + ((uint64_t)(uint32_t)e.row * (uint64_t)ld.o + (uint64_t)now.col);
         from_x = x_at(p + 2 + D);
         from_g = g_at(p + D);
+        if (PROD) {
+            from_noise = noise_at(p + D);
+            to_g = prod.g + ((uint64_t)(uint32_t)e.row * (uint64_t)prod.ldg + (uint64_t)now.col);
+        }
     };
     prepare();
     bool paced = true;
-    auto item = [&](f32x4& xu, GR& gu) __attribute__((always_inline)) {
+    auto item = [&](f32x4& xu, GR& gu, f32x4& nu) __attribute__((always_inline)) {
         if (paced) {
             int spin = 0;
             while (lds_peek(&pace->allowed) < 4 * items && ++spin < plan::kPaceSpins) __builtin_amdgcn_s_sleep(1);
@@ -187,8 +208,11 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
         __builtin_amdgcn_sched_barrier(0);
         const f32x4 in = set_apart(xu);
         const GR grad = set_apart(gu);
+        f32x4 next_g;
+        if (PROD) next_g = vfma(prod.c, cur, nu);
         xu = ld_x(lane_at(from_x, lane_of(p + 2 + D)));
         gu = ld_g_raw(lane_at(from_g, lane_of(p + D)));
+        if (PROD) nu = ld_x(lane_at(from_noise, lane_of(p + D)));
         ++items;
         if (threadIdx.x == 0) lds_poke(&pace->done, items);
         __builtin_amdgcn_sched_barrier(0);
@@ -196,11 +220,14 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
         if (p >= n - 2) right = pick(p == n - 2, last, first);
         const f32x4 out = mix_one(e.w0, e.w1, e.w2, cur, prev, right, widen_g(grad), neg_lr);
         st_row(to, now.to, out);
+        if (PROD) st_row(to_g, now.to, next_g);
         if (RAGGED && now.lo > 0 && now.lo < 4) {                  // one lane of the launch
-            float* mine = to + now.at;
 #pragma unroll
             for (int k = 1; k < 4; ++k)
-                if (k >= now.lo) __builtin_nontemporal_store(out[k], mine + k);
+                if (k >= now.lo) {
+                    __builtin_nontemporal_store(out[k], to + now.at + k);
+                    if (PROD) __builtin_nontemporal_store(next_g[k], to_g + now.at + k);
+                }
         }
         if (CD) stats.add(out);
         prev = cur;
@@ -224,17 +251,41 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
     // The first D items apart: a wait that they shared with the loop would count the operations since the start, which are fewer.
     const int64_t all = my_sweeps * n;
 #pragma unroll
-    for (int u = 0; u < D; ++u) item(x[u], g[u]);
+    for (int u = 0; u < D; ++u) item(x[u], g[u], noise[PROD ? u : 0]);
     for (int64_t i = D; i + D <= all; i += D)
 #pragma unroll
-        for (int u = 0; u < D; ++u) item(x[u], g[u]);
+        for (int u = 0; u < D; ++u) item(x[u], g[u], noise[PROD ? u : 0]);
     const int more = (int)(all % D);
 #pragma unroll
     for (int u = 0; u + 1 < D; ++u)
-        if (u < more) item(x[u], g[u]);
+        if (u < more) item(x[u], g[u], noise[PROD ? u : 0]);
     return total;
 }
 
+
+// The next gradients alone, for tables that are not walked: the same columns, row by row.
+template <bool RAGGED>
+__device__ __forceinline__ void produce_rows(const float* X, int n, int64_t d, int64_t ldx, const Sweeps& sweeps, int64_t my_sweeps,
+                                             const Produce& prod) {
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    for (int64_t sw = 0; sw < my_sweeps; ++sw) {
+        const WalkCols c = walk_cols<RAGGED>(sweeps, sw, ncg, d);
+        const ColGroup own{0, c.lo, 4};
+        const int64_t at = c.col + c.at;
+        for (int r0 = 0; r0 < n; r0 += 4) {
+            f32x4 x[4], z[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t r = row_or_last(r0 + u, n);
+                x[u] = ld_x(X + r * ldx + at);
+                z[u] = ld_x(prod.noise + r * prod.ldn + at);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r0 + u < n) st_cols(prod.g + (int64_t)(r0 + u) * prod.ldg + at, vfma(prod.c, x[u], z[u]), own);
+        }
+    }
+}
 
 // The step on long rows for any 3-slot table, one launch.  The workgroups stage and classify the table alike; one ring is walked, any
 // other table goes through tiles (short_tiles; Tiles: how), an invalid one raises the flag and nothing is written.  A
@@ -243,16 +294,16 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
 // CD = also reduce the consensus distance of the outputs into partials[blockIdx.x].
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
 // same number of sweeps; the wavefronts that neither a sweep nor the tiles need are not launched.
-// RAGGED: 4 may not divide d.  D: rows on their way per lane.
+// RAGGED: 4 may not divide d.  D: rows on their way per lane.  PROD: the next gradients too, whatever the table.
 struct Tiles {
     int rows, cached, logc, nrg, tab_bytes, tile_bytes;
 };
-template <typename GT, bool CD, bool RAGGED, int D>
+template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                                          const int32_t* __restrict__ nbr,
                                                                          const float* __restrict__ w, int n, int64_t d, Pitch ld,
                                                                          float neg_lr, Sweeps sweeps, int lanes, int slot, int lead,
-                                                                         Tiles tiles, double* __restrict__ partials) {
+                                                                         Tiles tiles, Produce prod, double* __restrict__ partials) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[(plan::kRingLanes + 64) / 64];
     __shared__ int lds_bad[(plan::kRingLanes + 64) / 64];
@@ -261,6 +312,10 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     const Lds l = carve(lds_raw, n);
     if (tid == 0) pace = Pace{0, lead};
     const int kind = stage_table(nbr, w, n, l, blockDim.x);      // contains barriers
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    int64_t my_sweeps = sweeps.count;
+    while (my_sweeps > 0 && sweeps.base(my_sweeps - 1) >= ncg) --my_sweeps;   // uniform
+    if (PROD && kind != kTableRing && tid < lanes) produce_rows<RAGGED>(X, n, d, ld.x, sweeps, my_sweeps, prod);
     if (kind == kTableBad) {
         if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
         if (CD && tid == 0) partials[blockIdx.x] = __builtin_nan("");
@@ -289,13 +344,10 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
         return;
     }
     if (tid >= lanes + 64) return;                               // whole wavefronts
-    const int64_t ncg = (d + kVec - 1) / kVec;
     double total = 0.0;
-    int64_t my_sweeps = sweeps.count;
-    while (my_sweeps > 0 && sweeps.base(my_sweeps - 1) >= ncg) --my_sweeps;   // uniform
     if (my_sweeps > 0) {
         if (tid >= lanes) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
-        else total = ring_walk<GT, CD, RAGGED, D>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n);
+        else total = ring_walk<GT, CD, RAGGED, D, PROD>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n, prod);
     }
     if (CD) {
         const double bs = block_sum_any(total, lds_waves, lanes + 64);

@@ -317,36 +317,19 @@ __global__ __launch_bounds__(kThreads) void consensus_final_kernel(const double*
     if (threadIdx.x == 0) out[0] = bs;
 }
 
-__global__ __launch_bounds__(kThreads) void synth_grad_kernel(const float* __restrict__ xp,
-                                                              const float* __restrict__ noise, float* __restrict__ g,
-                                                              int64_t count, float c) {
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    const int64_t tid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t groups = count / 4;
-    for (int64_t i = tid; i < groups; i += stride) st_x(g + 4 * i, vfma(c, ld_x(xp + 4 * i), ld_x(noise + 4 * i)));
-    for (int64_t i = groups * 4 + tid; i < count; i += stride) g[i] = vfma(c, xp[i], noise[i]);
-}
-
-// Row-pitched form: a lane owns one column group and walks the n rows.  FEW: rows of fewer than four columns.
+// The stand-in gradient producer: row blockIdx.y, a lane per column group.  FEW: rows of fewer than four columns.
 template <bool FEW>
-__global__ __launch_bounds__(kThreads) void synth_grad_rows_kernel(const float* __restrict__ xp, int64_t ldx,
-                                                                   const float* __restrict__ noise, int64_t ldn,
-                                                                   float* __restrict__ g, int64_t ldg, int n,
-                                                                   int64_t d, float c) {
+__global__ __launch_bounds__(kThreads) void synth_grad_kernel(const float* __restrict__ xp, int64_t ldx,
+                                                              const float* __restrict__ noise, int64_t ldn,
+                                                              float* __restrict__ g, int64_t ldg, int64_t d, float c) {
     const int64_t ncg = (d + kVec - 1) / kVec;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
+    xp += (int64_t)blockIdx.y * ldx;
+    noise += (int64_t)blockIdx.y * ldn;
+    g += (int64_t)blockIdx.y * ldg;
     for (int64_t cg = (int64_t)blockIdx.x * kThreads + threadIdx.x; cg < ncg; cg += stride) {
         const ColGroup at = col_group(cg, d);
-        const float* xc = xp + at.col;
-        const float* nc = noise + at.col;
-        float* gc = g + at.col;
-        if (!FEW && at.lo == 0) {                                // all but the ragged end: the stores are unconditional
-#pragma unroll 4
-            for (int r = 0; r < n; ++r) st_x(gc + (int64_t)r * ldg, vfma(c, ld_x(xc + (int64_t)r * ldx), ld_x(nc + (int64_t)r * ldn)));
-        } else {
-            for (int r = 0; r < n; ++r)
-                st_cols(gc + (int64_t)r * ldg, vfma(c, ld_cols<FEW>(xc + (int64_t)r * ldx, d), ld_cols<FEW>(nc + (int64_t)r * ldn, d)), at);
-        }
+        st_cols(g + at.col, vfma(c, ld_cols<FEW>(xp + at.col, d), ld_cols<FEW>(noise + at.col, d)), at);
     }
 }
 

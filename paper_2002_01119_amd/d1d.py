@@ -14,6 +14,10 @@ carry the three dependencies that exist:
 Three X buffers rotate (X_{k-1}, X_k, X_{k+1}); X_k is read by mix k and by producer k+1 at the same time
 and written by neither, which is why delay_mode 1 forbids mixing in place.  X_{-1} := X_0.
 
+With the noise a tensor and no producer stream of the caller's, mix k and producer k+1 are one kernel on the mix stream
+(`psgd.mix_step_d1d`): both read X_k, and either alone already takes all the HBM gives, so side by side they share its
+rate while one pass moves five arrays instead of six.
+
 Only enqueue order lives here: every arithmetic step is a kernel of the library.
 """
 import torch
@@ -27,7 +31,10 @@ class DelayByOne:
     X holds X_0 on entry; Y and X_prev are scratch of the same shape (X_prev is overwritten with X_0).
     `noise` is an [n, d] tensor (used every step) or a callable k -> tensor.  `table` is a callable
     k -> (nbr_dev, w_dev), or None for global averaging (psgd.mix_full).  With overlap=False everything is
-    enqueued on `mix_stream` in the serial order producer k, mix k.
+    enqueued on `mix_stream` in the serial order producer k, mix k.  With overlap and a `producer_stream` the producer
+    runs there.  Without one it runs in the mix kernel where `noise` is a tensor, a table is given and producer_repeat is 1
+    (`producer_stream` is then the mix stream, and `before_mix` / `after_mix` of a step bracket both), else on a stream of
+    its own.
     """
 
     def __init__(self, X, Y, X_prev, Gs, noise, table, lr, c, *, overlap=True, mix_stream=None,
@@ -35,18 +42,24 @@ class DelayByOne:
         if len(Gs) != 2:
             raise ValueError("two gradient buffers are needed")
         self.X, self.Y, self.X_prev, self.Gs = X, Y, X_prev, list(Gs)
+        one_pass = overlap and producer_stream is None and isinstance(noise, torch.Tensor) and table is not None and producer_repeat <= 1
         self.noise = noise if callable(noise) else (lambda k: noise)
         self.table, self.lr, self.c = table, lr, c
         self.overlap = overlap
         self.mix_stream = mix_stream or torch.cuda.current_stream()
+        if one_pass:
+            producer_stream = self.mix_stream
         self.producer_stream = producer_stream or (torch.cuda.Stream(device=X.device) if overlap else None)
+        self._one_pass = one_pass
         self.producer_repeat = max(int(producer_repeat), 1)   # > 1 rewrites the same G again: a slower producer
         self.k = 0
         self._mix_done = {}          # step -> event recorded behind mix k
         self._produced = {}          # step -> event recorded behind the producer of G_k
         with torch.cuda.stream(self.mix_stream):
             self.X_prev.copy_(self.X)                         # X_{-1} := X_0
-        if overlap:
+        if one_pass:
+            psgd.synth_grad(self.X_prev, noise, self.Gs[0], c, stream=self.mix_stream)
+        elif overlap:
             start = torch.cuda.Event()
             start.record(self.mix_stream)
             self.producer_stream.wait_event(start)
@@ -68,6 +81,8 @@ class DelayByOne:
         that holds X_{k+1}."""
         k, ms = self.k, self.mix_stream
         G = self.Gs[k % 2]
+        if self._one_pass:
+            return self._step_in_one_pass(k, G, cdist_out, before_mix, after_mix, more)
         if self.overlap:
             ms.wait_event(self._produced.pop(k))
         else:
@@ -96,9 +111,25 @@ class DelayByOne:
         self.k += 1
         return self.X
 
+    def _step_in_one_pass(self, k, G, cdist_out, before_mix, after_mix, more):
+        ms = self.mix_stream
+        nbr, w = self.table(k)
+        if before_mix:
+            before_mix(ms)
+        if more:
+            psgd.mix_step_d1d(self.X, self.Y, G, nbr, w, self.lr, self.noise(k + 1), self.Gs[(k + 1) % 2], self.c, stream=ms,
+                              cdist_out=cdist_out)
+        else:
+            psgd.mix_step(self.X, self.Y, G, nbr, w, self.lr, delay_mode=1, stream=ms, cdist_out=cdist_out)
+        if after_mix:
+            after_mix(ms)
+        self.X_prev, self.X, self.Y = self.X, self.Y, self.X_prev
+        self.k += 1
+        return self.X
+
     def finish(self):
         """Make the mix stream wait for everything enqueued on the producer stream."""
-        if self.overlap:
+        if self.overlap and not self._one_pass:
             ev = torch.cuda.Event()
             ev.record(self.producer_stream)
             self.mix_stream.wait_event(ev)

@@ -24,7 +24,7 @@ _lib = None
 
 EXPORTS = (
     "psgd_build_mixing", "psgd_build_mixing_device", "psgd_mix_step", "psgd_mix_step_bf16g", "psgd_mix_step_cd",
-    "psgd_mix_step_cd_bf16g", "psgd_mix_step_ex", "psgd_mix_step_cd_static", "psgd_mix_step_deg", "psgd_mix_full", "psgd_consensus_dist", "psgd_consensus_dist_ex",
+    "psgd_mix_step_cd_bf16g", "psgd_mix_step_ex", "psgd_mix_step_cd_static", "psgd_mix_step_deg", "psgd_mix_step_d1d", "psgd_mix_full", "psgd_consensus_dist", "psgd_consensus_dist_ex",
     "psgd_consensus_dist_async", "psgd_synth_grad", "psgd_synth_grad_ex", "psgd_reference_stream", "psgd_spread_alloc", "psgd_spread_free", "psgd_interleaved_alloc", "psgd_interleaved_free", "psgd_device_status", "psgd_last_error",
     "psgd_version",
 )
@@ -73,6 +73,10 @@ def load(reload=False):
     lib.psgd_mix_step_deg.argtypes = [vp, ctypes.c_int64, vp, ctypes.c_int64, vp, ctypes.c_int64, ctypes.c_int,
                                       vp, vp, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_float,
                                       ctypes.c_int, vp, vp]
+    lib.psgd_mix_step_d1d.restype = ctypes.c_int
+    lib.psgd_mix_step_d1d.argtypes = [vp, ctypes.c_int64, vp, ctypes.c_int64, vp, ctypes.c_int64, vp, vp, ctypes.c_int,
+                                      ctypes.c_int, ctypes.c_int64, ctypes.c_float, vp, ctypes.c_int64, vp,
+                                      ctypes.c_int64, ctypes.c_float, vp, vp]
     lib.psgd_mix_full.restype = ctypes.c_int
     lib.psgd_mix_full.argtypes = [vp, ctypes.c_int64, vp, ctypes.c_int64, vp, ctypes.c_int64, ctypes.c_int,
                                   ctypes.c_int, ctypes.c_int64, ctypes.c_float, ctypes.c_int, vp, vp]
@@ -237,6 +241,31 @@ def mix_step(X, X_out, G, nbr, w, lr, delay_mode=0, stream=None, cdist_out=None)
         fn = lib.psgd_mix_step_cd_bf16g if bf16 else lib.psgd_mix_step_cd
         _check(fn(X.data_ptr(), X_out.data_ptr(), G.data_ptr(), nbr.data_ptr(), w.data_ptr(), n, d,
                   float(lr), int(delay_mode), cd_ptr, sh))
+
+
+def mix_step_d1d(X, X_out, G, nbr, w, lr, noise, G_next, c, stream=None, cdist_out=None):
+    """Enqueue the step X_out = mix(X) - lr * G of the delay-by-one schedule and, from the same rows of X, the next
+    gradients G_next = c * X + noise, in one pass (psgd_mix_step_d1d).  Tensors as in mix_step, gradients and noise float32."""
+    import torch
+    n, d, ldx = _rows_cols_pitch(X)
+    lds = [ldx]
+    for t in (X_out, G, noise, G_next):
+        nt, dt, ld = _rows_cols_pitch(t)
+        if (nt, dt) != (n, d):
+            raise ValueError("X, X_out, G, noise and G_next must have one shape")
+        lds.append(ld)
+    if any(t.dtype != torch.float32 for t in (X, X_out, G, noise, G_next)):
+        raise ValueError("X, X_out, G, noise and G_next must be float32")
+    if nbr.dtype != torch.int32 or w.dtype != torch.float32 or nbr.numel() % n or nbr.numel() != w.numel() \
+            or not nbr.is_contiguous() or not w.is_contiguous():
+        raise ValueError("nbr must be int32 [n,deg] and w float32 [n,deg], contiguous")
+    if cdist_out is not None and (cdist_out.dtype != torch.float64 or cdist_out.numel() < 1 or cdist_out.device != X.device):
+        raise ValueError("cdist_out must be a float64 device tensor")
+    _on_current_device(X, X_out, G, nbr, w, noise, G_next, cdist_out)
+    _check(load().psgd_mix_step_d1d(X.data_ptr(), lds[0], X_out.data_ptr(), lds[1], G.data_ptr(), lds[2], nbr.data_ptr(),
+                                    w.data_ptr(), nbr.numel() // n, n, d, float(lr), noise.data_ptr(), lds[3],
+                                    G_next.data_ptr(), lds[4], float(c), cdist_out.data_ptr() if cdist_out is not None else None,
+                                    _stream_handle(stream)))
 
 
 def mix_step_cd_static(X, X_out, G, nbr, w, lr, cdist_out, delay_mode=0, stream=None):
