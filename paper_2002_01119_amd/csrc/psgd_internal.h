@@ -125,6 +125,17 @@ inline bool ring_rows_paced(int n, int64_t ncg, int cus) {
     return n > 8 && ncg >= from * cus;
 }
 
+// Global averaging with the workgroups of a die in step, in column groups per compute unit, and how far ahead of the mean a workgroup
+// may be, in quarter rows: more than in the ring walk, as half of the rows are only read.  us, lanes walking alone or rows spread over
+// lanes / in step: 9 x 1.5 M 32.4 / 32.9 (bf16 gradients, no distance 25.2 / 27.5), x 3 M 63.8 / 59.3, 16 x 0.82 M 33.7 / 31.1, x 0.4 M bf16
+// 11.7 / 14.8, 32 x 0.5 M 34.9 / 36.4, 64 x 0.22 M 34.6 / 37.8, x 0.31 M 51 / 46, x 0.6 M 97 / 80, 512 x 0.31 M 390 / 331.  Lead with two rows on
+// their way, 64 x 25.6 M: 10 quarters 3326, 14 3306, 16 3313, 20 3441.
+inline bool full_rows_paced(int n, int64_t ncg, int cus) {
+    const int64_t from = n < 16 ? 2400 : n < 32 ? 800 : n < 48 ? 560 : 300;
+    return n > 8 && ncg >= from * cus;
+}
+inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
+
 // LDS of the tiled kernel (long rows, tables that are not one ring): the slot table (8 bytes per slot), TWO tile
 // buffers of n rows x lpr lanes x 16 bytes (the next tile is staged while the current one is read), and, when the
 // consensus distance is gathered in the same pass, the merge slots of the column sums: a double and a float (the row

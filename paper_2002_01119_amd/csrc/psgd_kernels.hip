@@ -39,6 +39,7 @@
 static __device__ __align__(256) double scratch[PSGD_STATIC_SLOTS];
 
 #include "psgd_device.h"
+#include "psgd_pace.h"
 #include "psgd_short.h"
 #include "psgd_tiled.h"
 #include "psgd_ring_walk.h"
@@ -331,7 +332,8 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
 
 // Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.  Returns the number of workgroups (partial
 // sums with the distance) or a negative status.
-std::atomic<unsigned> g_ring_launches{0};   // each takes the next of the pace words
+std::atomic<unsigned> g_paced_launches{0};   // each takes the next of the pace words
+int next_pace_slot() { return (int)(g_paced_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots); }
 template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp, int cached, hipStream_t s, const float* X, float* X_out,
                   const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
@@ -343,7 +345,7 @@ int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp
     const int threads = lanes + 64 > tp.threads ? lanes + 64 : tp.threads;
     hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D, PROD>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
                        Sweeps{sp.count, sp.chunk}, lanes,
-                       (int)(g_ring_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots), plan::pace_lead(D, PROD),
+                       next_pace_slot(), plan::pace_lead(D, PROD),
                        Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, prod, partials);
     return grid;
 }
@@ -569,9 +571,26 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const float neg_lr = -lr;
     const bool big = long_rows(*di, ncg, 2);
     const plan::RowsPlan rp = plan::full_rows_plan(n, d, di->cus, want_cd);
-    const bool split = !big && rp.threads != 0;
+    const bool walk = plan::full_rows_paced(n, ncg, di->cus);
+    const bool split = !walk && !big && rp.threads != 0;
     int grid = 0;
-    if (split) {
+    if (walk) {
+        grid = di->cus < kMaxGrid ? di->cus : kMaxGrid;
+        const plan::SweepPlan sp = plan::sweep_plan(ncg, grid, plan::kRingLanes);
+        const int lanes = plan::ring_threads({1, sp.chunk}, plan::kRingLanes);
+#define PSGD_LAUNCH_WALK(CD, D)                                                                                            \
+    do {                                                                                                                   \
+        if (int rc = allow_lds(reinterpret_cast<const void*>(mix_full_walk_kernel<GT, CD, D>), plan::kRingLds)) return rc;  \
+        hipLaunchKernelGGL((mix_full_walk_kernel<GT, CD, D>), dim3(grid), dim3(lanes + 64), plan::kRingLds, s, X, X_out, G, \
+                           n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk}, lanes, next_pace_slot(), plan::full_lead(D),       \
+                           partials);                                                                                      \
+    } while (0)
+        if (sp.chunk >= 576 && want_cd) PSGD_LAUNCH_WALK(true, 2);
+        else if (sp.chunk >= 576) PSGD_LAUNCH_WALK(false, 2);
+        else if (want_cd) PSGD_LAUNCH_WALK(true, 4);
+        else PSGD_LAUNCH_WALK(false, 4);
+#undef PSGD_LAUNCH_WALK
+    } else if (split) {
         grid = (int)(rp.tiles < kMaxGrid ? rp.tiles : kMaxGrid);
         const size_t lds = (size_t)rp.threads * (want_cd ? 48 : 32) + (16 << rp.logc);
 #define PSGD_LAUNCH_ROWS(CD, FEW)                                                                                          \

@@ -5,7 +5,7 @@
 #ifndef PSGD_STREAMS_H
 #define PSGD_STREAMS_H
 
-#include "psgd_device.h"
+#include "psgd_pace.h"
 
 namespace psgd {
 namespace {
@@ -84,6 +84,121 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
     if (CD) {
         const double bs = block_sum<T>(total, lds_waves, blockDim.x);
         if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+    }
+}
+
+// The same on long rows, paced as the ring walk is (psgd_pace.h): a sweep is n items that add an X row and n items that read a
+// gradient row and write an output row; loads are D items ahead, the first gradients travelling under the last X rows and the next
+// sweep's first X rows under the last outputs.  Rows beyond n (where D does not divide it) repeat the last one; they add nothing and
+// their stores are dropped.  All X loads of a lane's columns precede its first store, so X_out may alias X.
+// us, dense (lockstep batches of eight rows before): 64 x 25.6 M fp32 with the distance 3703 -> 3313, 64 x 1 M bf16 122 -> 112, 64 x 600 k
+// 97 -> 80, 512 x 310 k 390 -> 331.
+template <typename GT, bool CD, int D>
+__device__ __forceinline__ double full_walk(const float* X, float* Xout, const GT* __restrict__ G, int n, int64_t d, Pitch ld,
+                                            float neg_lr, const Sweeps& sweeps, int64_t my_sweeps, Pace* pace) {
+    typedef typename RawG<GT>::T GR;
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    const double inv_n = 1.0 / (double)n;
+    WalkCols now = walk_cols<true>(sweeps, 0, ncg, d);
+    double total = 0.0;
+    int items = 0;
+    bool paced = true;
+    f32x4 x[D];
+    GR g[D];
+#pragma unroll
+    for (int u = 0; u < D; ++u) x[u] = ld_x(lane_at(X + ((int64_t)row_or_last(u, n) * ld.x + now.col), now.at));
+    auto done = [&]() __attribute__((always_inline)) {
+        ++items;
+        if (threadIdx.x == 0) lds_poke(&pace->done, items);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int64_t sw = 0; sw < my_sweeps; ++sw) {
+        const WalkCols nxt = walk_cols<true>(sweeps, sw + 1 < my_sweeps ? sw + 1 : sw, ncg, d);
+        double sum[kVec] = {0.0, 0.0, 0.0, 0.0};
+        int r = 0;
+        for (; r + D < n; r += D) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                wait_for_pace(pace, items, paced);
+                __builtin_amdgcn_sched_barrier(0);
+                const f32x4 in = set_apart(x[u]);
+                x[u] = ld_x(lane_at(X + ((int64_t)row_or_last(r + u + D, n) * ld.x + now.col), now.at));
+                done();
+                add_to(sum, in);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            wait_for_pace(pace, items, paced);
+            __builtin_amdgcn_sched_barrier(0);
+            const f32x4 in = set_apart(x[u]);
+            g[u] = ld_g_raw(lane_at(G + ((int64_t)row_or_last(u, n) * ld.g + now.col), now.at));
+            done();
+            if (r + u < n) add_to(sum, in);
+        }
+        const f32x4 mean = mean_of(sum, inv_n);
+        ColStats<true> stats;
+        if (CD) stats.reset();
+        auto put = [&](int row, GR grad) __attribute__((always_inline)) {
+            const f32x4 out = vfma(neg_lr, widen_g(grad), mean);
+            float* to = Xout + ((int64_t)row_or_last(row, n) * ld.o + now.col);
+            st_row(to, row < n ? now.to : kDropStore, out);
+            if (now.lo > 0 && now.lo < 4 && row < n) {           // one lane of the launch
+#pragma unroll
+                for (int k = 1; k < 4; ++k)
+                    if (k >= now.lo) __builtin_nontemporal_store(out[k], to + now.at + k);
+            }
+            if (CD && row < n) stats.add(out);
+        };
+        auto mid = [&](int at) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                wait_for_pace(pace, items, paced);
+                __builtin_amdgcn_sched_barrier(0);
+                const GR grad = set_apart(g[u]);
+                g[u] = ld_g_raw(lane_at(G + ((int64_t)row_or_last(at + u + D, n) * ld.g + now.col), now.at));
+                done();
+                put(at + u, grad);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        mid(0);                                                  // apart: its waits count no stores yet (n > D)
+        for (r = D; r + D < n; r += D) mid(r);
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            wait_for_pace(pace, items, paced);
+            __builtin_amdgcn_sched_barrier(0);
+            const GR grad = set_apart(g[u]);
+            x[u] = ld_x(lane_at(X + ((int64_t)row_or_last(u, n) * ld.x + nxt.col), nxt.at));
+            done();
+            put(r + u, grad);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (CD) total += stats.result(inv_n, ColGroup{0, now.lo, 4});
+        now = nxt;
+    }
+    return total;
+}
+template <typename GT, bool CD, int D>
+__global__ __launch_bounds__(plan::kRingThreadsMost) void mix_full_walk_kernel(const float* X, float* Xout, const GT* __restrict__ G,
+                                                                               int n, int64_t d, Pitch ld, float neg_lr,
+                                                                               Sweeps sweeps, int lanes, int slot, int lead,
+                                                                               double* __restrict__ partials) {
+    __shared__ double lds_waves[plan::kRingThreadsMost / 64];
+    __shared__ Pace pace;
+    const int tid = threadIdx.x;
+    if (tid == 0) pace = Pace{0, lead};
+    __syncthreads();
+    const int64_t my_sweeps = sweeps_of(sweeps, (d + kVec - 1) / kVec);
+    const int items = 2 * ((n + D - 1) / D) * D;                 // of a sweep
+    double total = 0.0;
+    if (my_sweeps > 0) {
+        if (tid >= lanes) keep_pace(&pace, slot, lead, (int)my_sweeps * items, items);
+        else total = full_walk<GT, CD, D>(X, Xout, G, n, d, ld, neg_lr, sweeps, my_sweeps, &pace);
+    }
+    if (CD) {
+        const double bs = block_sum_any(total, lds_waves, lanes + 64);
+        if (tid == 0) partials[blockIdx.x] = bs;
     }
 }
 

@@ -92,6 +92,33 @@ def test_other_tables_on_the_same_rows(psgd, n, d, gkind):
     assert torch.equal(Xd, before) and torch.isnan(c).all() and psgd.device_status() == 1
 
 
+# global averaging in step: two and four rows on their way, counts of rows that these divide or not, several sweeps, ragged rows
+@pytest.mark.parametrize("n,d,gkind", [
+    (9, 2_457_600, "f32"), (9, 2_500_003, "bf16"), (16, 819_201, "f32"), (17, 820_002, "bf16"), (31, 1_100_004, "f32"), (33, 600_001, "f32"),
+    (48, 310_001, "bf16"), (49, 307_200, "f32"), (50, 590_003, "bf16"), (65, 330_004, "f32"), (130, 307_201, "bf16"), (511, 310_000, "f32")])
+def test_global_averaging_every_element(psgd, n, d, gkind):
+    X, G, _, _, _ = _inputs(psgd, n, d, gkind, 17 + n)
+    g = G if gkind == "f32" else (G.astype(np.uint32) << 16).view(np.float32)
+    lr = np.float64(np.float32(0.2))
+    mean = X.mean(axis=0, dtype=np.float64)
+    # the mean's rounding to fp32 and the last fused operation's, each on a value no larger than this
+    tol = 2.0 ** -24 * (2 * float(np.abs(mean).max()) + 0.2 * float(np.abs(g).max()))
+    Xd = torch.from_numpy(X).to("cuda:0")
+    Gd = torch.from_numpy(G.view(np.int16) if gkind == "bf16" else G).to("cuda:0")
+    for form in ("plain", "distance", "in place"):
+        Y = torch.full_like(Xd, float("nan")) if form != "in place" else Xd
+        c = torch.full((1,), float("nan"), dtype=torch.float64, device="cuda:0") if form != "plain" else None
+        psgd.mix_full(Xd, Y, Gd, 0.2, cdist_out=c)
+        torch.cuda.synchronize()
+        got = Y.cpu().numpy()
+        for i in range(0, n, 8):
+            assert np.abs(got[i:i + 8] - (mean - lr * g[i:i + 8])).max() <= tol, form
+        if c is not None:
+            ref = orc.sparse_consensus_dist(got.astype(np.float64), threads=4)
+            assert abs(c.item() - ref) <= 1e-9 * ref, form
+    assert psgd.device_status() == 0
+
+
 def test_launches_that_overlap_and_share_pace_words(psgd):
     """Three streams with 100 launches each, so that launches under way at once share words; the bits are those of a launch alone."""
     n, d = 64, 1_000_004
