@@ -3,10 +3,14 @@
 Device buffers are torch tensors (PyTorch is used for HBM allocation and streams); every
 step of the computation runs in the library's HIP kernels.  There is no fallback: if the
 shared library is missing or a call fails, an exception is raised.
+
+Calls that are plainly in order take the short way of the _call extension (csrc/psgd_call.cpp), which checks the same and passes
+them to the same library functions; whatever it does not answer with success goes through the checks below.
 """
 import ctypes
 import math
 import os
+import sys
 
 import numpy as np
 
@@ -21,6 +25,9 @@ OK, EINVAL, EALIAS, EALIGN, EHIP = 0, -1, -2, -3, -4
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libpsgd.so")
 _lib = None
+_call = None             # the extension, once bound to the library's functions
+_call_tried = False
+_CALLS = ("psgd_mix_step_deg", "psgd_mix_step_d1d", "psgd_mix_full", "psgd_build_mixing_device", "psgd_consensus_dist_ex", "psgd_synth_grad_ex")
 
 EXPORTS = (
     "psgd_build_mixing", "psgd_build_mixing_device", "psgd_mix_step", "psgd_mix_step_bf16g", "psgd_mix_step_cd",
@@ -110,7 +117,22 @@ def load(reload=False):
     lib.psgd_version.restype = ctypes.c_int
     lib.psgd_version.argtypes = []
     _lib = lib
+    if "torch" in sys.modules:
+        _bind()
     return lib
+
+
+def _bind():
+    """Hand the extension the addresses of the loaded library's functions.  It needs torch in the process."""
+    global _call, _call_tried
+    _call_tried = True
+    try:
+        from . import _call as ext
+    except ImportError:
+        _call = None
+        return
+    ext.bind(*(ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in _CALLS))
+    _call = ext
 
 
 def last_error():
@@ -125,6 +147,8 @@ def _check(rc):
 def _stream_handle(stream):
     """hipStream_t of a torch stream (None = torch's current stream on the current GPU)."""
     import torch
+    if not _call_tried and _lib is not None:
+        _bind()
     if stream is not None:
         return stream.cuda_stream
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # 0.1 us; building the Stream object takes 2.5
@@ -179,6 +203,8 @@ def build_mixing_device(topology, n, seed, nbr, w, step_dev=None, step_offset=0,
     """Enqueue the construction of the same table in device memory: nbr int32 [n,3], w float32
     [n,3] (device tensors, written).  The iteration is step_offset plus, if given, the value of
     step_dev (device int64 / uint64 tensor, >= 1 element), which is then advanced by `advance`."""
+    if _call is not None and _call.build_mixing_device(topology, n, seed, nbr, w, step_dev, step_offset, advance, stream) == OK:
+        return
     import torch
     if nbr.dtype != torch.int32 or w.dtype != torch.float32 or nbr.numel() != 3 * n or w.numel() != 3 * n \
             or not nbr.is_contiguous() or not w.is_contiguous():
@@ -201,6 +227,8 @@ def mix_step(X, X_out, G, nbr, w, lr, delay_mode=0, stream=None, cdist_out=None)
     stride along d; their rows may be pitched (stride(0) >= d), which selects
     psgd_mix_step_ex.  With cdist_out (device float64 tensor, >= 1 element) the fused
     variant also writes the consensus distance of X_out there."""
+    if _call is not None and _call.mix_step(X, X_out, G, nbr, w, lr, delay_mode, stream, cdist_out) == OK:
+        return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
     no, do, ldo = _rows_cols_pitch(X_out)
@@ -246,6 +274,8 @@ def mix_step(X, X_out, G, nbr, w, lr, delay_mode=0, stream=None, cdist_out=None)
 def mix_step_d1d(X, X_out, G, nbr, w, lr, noise, G_next, c, stream=None, cdist_out=None):
     """Enqueue the step X_out = mix(X) - lr * G of the delay-by-one schedule and, from the same rows of X, the next
     gradients G_next = c * X + noise, in one pass (psgd_mix_step_d1d).  Tensors as in mix_step, gradients and noise float32."""
+    if _call is not None and _call.mix_step_d1d(X, X_out, G, nbr, w, lr, noise, G_next, c, stream, cdist_out) == OK:
+        return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
     lds = [ldx]
@@ -298,6 +328,8 @@ def mix_step_cd_static(X, X_out, G, nbr, w, lr, cdist_out, delay_mode=0, stream=
 
 def mix_full(X, X_out, G, lr, delay_mode=0, stream=None, cdist_out=None):
     """Enqueue X_out[i] = mean_j X[j] - lr * G[i] (global averaging, T_u).  Tensors as in mix_step."""
+    if _call is not None and _call.mix_full(X, X_out, G, lr, delay_mode, stream, cdist_out) == OK:
+        return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
     no, do, ldo = _rows_cols_pitch(X_out)
@@ -339,6 +371,8 @@ def consensus_dist(X):
 
 def consensus_dist_async(X, out, stream=None):
     """Enqueue the consensus distance of X into out (device float64 tensor, 1 element)."""
+    if _call is not None and _call.consensus_dist_async(X, out, stream) == OK:
+        return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
     _on_current_device(X, out)
@@ -355,6 +389,8 @@ def consensus_dist_async(X, out, stream=None):
 def synth_grad(X_prev, noise, G, c, stream=None):
     """Enqueue G = c * X_prev + noise (fp32, elementwise) for the delay-by-one workload.
     Contiguous tensors of any shape, or [n, d] tensors with pitched rows."""
+    if _call is not None and _call.synth_grad(X_prev, noise, G, c, stream) == OK:
+        return
     import torch
     if X_prev.shape != noise.shape or X_prev.shape != G.shape:
         raise ValueError("X_prev, noise and G must have one shape")
