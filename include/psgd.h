@@ -115,10 +115,9 @@ int psgd_build_mixing_device(int topology, int n, uint64_t seed, uint64_t* step_
  *
  * Enqueues its work on `stream` and returns without waiting.  The table lives in device memory,
  * so only the device can tell whether it is one ring (every table of Sec. 3 is) or a general
- * 3-slot table.  Most shapes: one kernel that serves any table.  Long rows of nine and more
- * learners (9 to 28 learners: from about 6.3 M columns; up to 47: 1.2 M; up to 95: 1 M; up to 255:
- * 0.31 M; above: 0.2 M): two kernels, the ring walk and behind it one for any other table (LDS tiles);
- * both classify the table and the one it does not belong to exits at once (4 to 7 us).
+ * 3-slot table.  One kernel either way: on short rows one that serves any table alike, on long rows of nine and
+ * more learners (9 learners: from about 3.7 M columns; 16: 1.6 M; 24: 0.8 M; 32: 0.6 M; 48: 0.4 M; 96: 0.34 M;
+ * 200: 0.24 M) one that classifies the table and walks the ring, or takes any other table through LDS tiles.
  * Errors: PSGD_EINVAL;
  * PSGD_EALIAS (X_out partially overlaps X, X_out overlaps G, or X_out == X with
  * delay_mode 1); PSGD_EALIGN (X, X_out, G not 4-byte aligned); PSGD_EHIP.  A table entry
@@ -198,8 +197,8 @@ int psgd_mix_step_ex(const float* X, int64_t ldx, float* X_out, int64_t ldo,
  * call makes no hipMalloc / hipFree and creates no event or stream.
  *
  * Limit: a launch uses one partial per workgroup.  Most shapes loop over their tiles within the
- * array; the ring walk takes one workgroup per compute unit and the kernel behind it what is left.  If the ring walk alone would need PSGD_STATIC_SLOTS or more the call fails with PSGD_EINVAL
- * and launches nothing.  n, d and the pitches are limited as in psgd_mix_step_ex.
+ * array; on long rows there is one workgroup per compute unit.  A device on which that is more than PSGD_STATIC_SLOTS
+ * is refused with PSGD_EINVAL and nothing is launched.  n, d and the pitches are limited as in psgd_mix_step_ex.
  * Every call on a GPU uses that GPU's one array, which keeps the previous call's partials (each
  * launch overwrites the slots it reads, so nothing needs clearing).  Calls that overlap in time
  * on one GPU (two streams, or two graphs launched side by side) race on it: the caller orders
