@@ -23,6 +23,7 @@ struct Library {
     decltype(&psgd_build_mixing_device) build_mixing_device = nullptr;
     decltype(&psgd_consensus_dist_ex) consensus_dist_ex = nullptr;
     decltype(&psgd_synth_grad_ex) synth_grad_ex = nullptr;
+    decltype(&psgd_consensus_dist) consensus_dist = nullptr;
 } lib;
 
 // A plain strided tensor on device `dev` whose pointer means what it says: no subclass, no tensor of a transform or a trace.
@@ -233,6 +234,25 @@ PyObject* consensus_dist_async(PyObject*, PyObject* const* a, Py_ssize_t count) 
     });
 }
 
+// consensus_dist(X): the value, or None where the call is not answered here
+PyObject* consensus_dist(PyObject*, PyObject* const* a, Py_ssize_t count) {
+    double v = 0.0;
+    bool mine = false;
+    try {
+        const int dev = device();
+        int64_t n = -1, d = 0;
+        Rows x;
+        if (count == 1 && dev >= 0 && rows(a[0], dev, at::kFloat, n, d, x) && THPVariable_Unpack(a[0]).is_contiguous()) {
+            Unlocked run;
+            v = lib.consensus_dist(static_cast<float*>(x.p), static_cast<int>(n), d);
+            mine = true;
+        }
+    } catch (...) {
+    }
+    if (!mine) Py_RETURN_NONE;
+    return PyFloat_FromDouble(v);
+}
+
 // synth_grad(X_prev, noise, G, c, stream)
 PyObject* synth_grad(PyObject*, PyObject* const* a, Py_ssize_t count) {
     return guarded([&]() -> long {
@@ -250,11 +270,11 @@ PyObject* synth_grad(PyObject*, PyObject* const* a, Py_ssize_t count) {
     });
 }
 
-// bind(addresses of the six functions, in the order of struct Library)
+// bind(addresses of the functions, in the order of struct Library)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t count) {
-    void* p[6];
-    if (count != 6) return answer(NOT_MINE);
-    for (int i = 0; i < 6; ++i) {
+    void* p[7];
+    if (count != 7) return answer(NOT_MINE);
+    for (int i = 0; i < 7; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
         if (PyErr_Occurred()) return nullptr;
     }
@@ -264,12 +284,13 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t count) {
     lib.build_mixing_device = reinterpret_cast<decltype(lib.build_mixing_device)>(p[3]);
     lib.consensus_dist_ex = reinterpret_cast<decltype(lib.consensus_dist_ex)>(p[4]);
     lib.synth_grad_ex = reinterpret_cast<decltype(lib.synth_grad_ex)>(p[5]);
+    lib.consensus_dist = reinterpret_cast<decltype(lib.consensus_dist)>(p[6]);
     return answer(0);
 }
 
 #define PSGD_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {PSGD_METHOD(mix_step),  PSGD_METHOD(mix_full), PSGD_METHOD(mix_step_d1d), PSGD_METHOD(build_mixing_device),
-                         PSGD_METHOD(consensus_dist_async), PSGD_METHOD(synth_grad), PSGD_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
+                         PSGD_METHOD(consensus_dist_async), PSGD_METHOD(consensus_dist), PSGD_METHOD(synth_grad), PSGD_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

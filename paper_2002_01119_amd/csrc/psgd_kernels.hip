@@ -58,7 +58,8 @@ struct DeviceInfo {
     hipStream_t partials_stream = nullptr;  // the stream (not under capture) that used `partials` last
     bool partials_used = false;
     double* static_partials = nullptr;  // device address of ::scratch on this GPU (psgd_mix_step_cd_static)
-    double* host_result = nullptr;      // pinned host memory, hipHostMalloc'ed on first use (psgd_consensus_dist)
+    double* host_result = nullptr;      // pinned host memory, hipHostMalloc'ed on first use (psgd_consensus_dist),
+    double* host_result_dev = nullptr;  // and its address on the device
     std::mutex host_result_mutex;       // held from the launch until the word has been read
 };
 constexpr int kMaxDevices = 64;
@@ -853,11 +854,12 @@ double psgd_consensus_dist(const float* X, int n, int64_t d) {
             return NAN;
         }
     }
-    double* out_dev = nullptr;
-    e = hipHostGetDevicePointer(reinterpret_cast<void**>(&out_dev), di->host_result, 0);
-    if (e != hipSuccess) { hip_fail(e, "hipHostGetDevicePointer(result)"); return NAN; }
+    if (!di->host_result_dev) {
+        e = hipHostGetDevicePointer(reinterpret_cast<void**>(&di->host_result_dev), di->host_result, 0);
+        if (e != hipSuccess) { di->host_result_dev = nullptr; hip_fail(e, "hipHostGetDevicePointer(result)"); return NAN; }
+    }
     *di->host_result = NAN;
-    if (consensus_enqueue(X, d, n, d, out_dev, nullptr) != PSGD_OK) return NAN;
+    if (consensus_enqueue(X, d, n, d, di->host_result_dev, nullptr) != PSGD_OK) return NAN;
     e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) { hip_fail(e, "hipStreamSynchronize"); return NAN; }
     return *static_cast<volatile double*>(di->host_result);

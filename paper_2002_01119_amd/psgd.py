@@ -27,7 +27,8 @@ _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libpsgd.so
 _lib = None
 _call = None             # the extension, once bound to the library's functions
 _call_tried = False
-_CALLS = ("psgd_mix_step_deg", "psgd_mix_step_d1d", "psgd_mix_full", "psgd_build_mixing_device", "psgd_consensus_dist_ex", "psgd_synth_grad_ex")
+_CALLS = ("psgd_mix_step_deg", "psgd_mix_step_d1d", "psgd_mix_full", "psgd_build_mixing_device", "psgd_consensus_dist_ex", "psgd_synth_grad_ex",
+          "psgd_consensus_dist")
 
 EXPORTS = (
     "psgd_build_mixing", "psgd_build_mixing_device", "psgd_mix_step", "psgd_mix_step_bf16g", "psgd_mix_step_cd",
@@ -356,12 +357,14 @@ def mix_full(X, X_out, G, lr, delay_mode=0, stream=None, cdist_out=None):
 
 def consensus_dist(X):
     """Synchronous sum_i ||x_i - xbar||^2 of a device tensor [n, d]."""
-    import torch
-    n, d = _rows_cols(X)
-    _on_current_device(X)
-    if X.dtype != torch.float32:
-        raise ValueError("X must be float32")
-    v = load().psgd_consensus_dist(X.data_ptr(), n, d)
+    v = _call.consensus_dist(X) if _call is not None else None
+    if v is None:
+        import torch
+        n, d = _rows_cols(X)
+        _on_current_device(X)
+        if X.dtype != torch.float32:
+            raise ValueError("X must be float32")
+        v = load().psgd_consensus_dist(X.data_ptr(), n, d)
     if math.isnan(v):
         err = last_error()
         if err:

@@ -60,7 +60,7 @@ def test_results_are_the_same(psgd, monkeypatch, n, d, deg, g, wide):
             psgd.mix_step_d1d(X, P, Z, nbr, w, 0.25, Z, F, 0.5, stream=st, cdist_out=c[3])
             psgd.build_mixing_device(1, n, -5, t, u, step_dev=k, step_offset=3, advance=2, stream=st)
             torch.cuda.synchronize()
-            out[st is None] = [v.clone() for v in (Y, F, H, P, t, u, k, *c)]
+            out[st is None] = [v.clone() for v in (Y, F, H, P, t, u, k, *c, torch.tensor(psgd.consensus_dist(H)))]
         return out
 
     a, b = _both(psgd, monkeypatch, run)
@@ -82,7 +82,7 @@ def test_the_same_calls_are_refused(psgd, monkeypatch):
         lambda: psgd.mix_step(X, Y, G, nbr.long(), w, 0.1), lambda: psgd.mix_step(X, Y, G, nbr, w[:2], 0.1),
         lambda: psgd.mix_step(X, Y, G, nbr, w, 0.1, delay_mode=7), lambda: psgd.mix_step(X, Y, G, nbr, w, 0.1, cdist_out=cd.float()),
         lambda: psgd.mix_step(X.t(), Y.t(), G.t(), nbr, w, 0.1), lambda: psgd.mix_step(X, Y, G, nbr, w, "x"),
-        lambda: psgd.mix_full(X, X[:2], G, 0.1), lambda: psgd.consensus_dist_async(X, None), lambda: psgd.consensus_dist_async(X, X),
+        lambda: psgd.mix_full(X, X[:2], G, 0.1), lambda: psgd.consensus_dist_async(X, None), lambda: psgd.consensus_dist_async(X, X), lambda: psgd.consensus_dist(X.t()), lambda: psgd.consensus_dist(X.half()),
         lambda: psgd.build_mixing_device(2, n, 1, nbr, w), lambda: psgd.build_mixing_device(0, 5, 1, nbr, w),
         lambda: psgd.synth_grad(X, Y, X, 0.1), lambda: psgd.synth_grad(X, Y, G[:2], 0.1), lambda: psgd.mix_step(None, Y, G, nbr, w, 0.1),
     ]
