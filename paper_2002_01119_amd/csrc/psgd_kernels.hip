@@ -1,10 +1,10 @@
 // libpsgd's HIP translation unit (gfx950 / CDNA4): the launchers and C entry points for the model-averaging step
 //     X_out[i,:] = sum_s w[i,s] * X[nbr[i,s],:] - lr * G[i,:]            (Sec. 2, Eq. 2)
 // and for the consensus distance sum_i ||x_i - xbar||^2 (Sec. 3).  The kernels live in the headers included
-// below: psgd_device.h (shared building blocks), psgd_short.h (any table: short rows, few or many learners, rows off
-// the lines), psgd_ring_walk.h (long rows of nine and more learners, ring tables, registers only), psgd_tiled.h (long rows
-// of 9 to 128 learners, any other table, LDS tiles), psgd_streams.h (global averaging, distance, gradient producer,
-// reference streams, table builder).
+// below: psgd_device.h (shared building blocks), psgd_pace.h (workgroups of a die in step), psgd_short.h (any table: short rows, few
+// learners, rows off the lines), psgd_ring_walk.h (3-slot tables on long rows of nine and more learners, rings in registers only),
+// psgd_tiled.h (long rows of 9 to 128 learners, other slot counts, LDS tiles), psgd_streams.h (global averaging, distance,
+// gradient producer, reference streams, table builder).
 //
 // The step is bound by HBM traffic (about 7 flops against 10-12 bytes per element), so the
 // design goal is to touch every X, G and X_out byte exactly once:

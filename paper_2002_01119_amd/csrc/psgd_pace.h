@@ -22,8 +22,9 @@ namespace {
 // The wait decides nothing but when the loads go out: it is bounded, and after one that ran out the wavefront walks on unpaced (a
 // workgroup that shares the chip with other kernels, or whose neighbours have not started).
 // ---------------------------------------------------------------------------------------
-// One word per launch slot and die, in a line of its own: the progress of the workgroups under way (upper 40 bits), those started and
-// those done (12 bits each).  The last one done puts it back to zero.
+// One word per launch slot and die, in a line of its own: the progress of the workgroups under way (upper 32 bits), those started and
+// those done (16 bits each).  The last one done puts it back to zero; only launches on one slot that overlapped without a gap 2000
+// times over would run out of the counts, and then lose the pace, not a result.
 __device__ unsigned long long g_pace[plan::kPaceSlots][kXcds][16];
 
 // The operations are performed by the L2 of the die the workgroup runs on, which is what they are meant to reach: no more than
@@ -42,23 +43,23 @@ struct Pace {
 
 // The pacing wavefront: ends when the workers have made all `total` items; `sweep` items are one sweep.
 __device__ __forceinline__ void keep_pace(Pace* pace, int slot, int lead, int total, int sweep) {
-    constexpr unsigned long long kStarted = 1ull << 12, kProgress = 1ull << 24;
+    constexpr unsigned long long kStarted = 1ull << 16, kProgress = 1ull << 32;
     const int die = __builtin_amdgcn_s_getreg(20 | 31 << 11) & (kXcds - 1);   // hwreg XCC_ID: which die this is
     if ((threadIdx.x & 63) != 0) return;
     unsigned long long* word = g_pace[slot][die];
     unsigned long long v = pace_add(word, kStarted);
-    auto started = [&] { return (unsigned)(v >> 12) & 0xFFFu; };
-    auto done = [&] { return (unsigned)v & 0xFFFu; };
+    auto started = [&] { return (unsigned)(v >> 16) & 0xFFFFu; };
+    auto done = [&] { return (unsigned)v & 0xFFFFu; };
     // A workgroup that starts late counts from the sweep the others are in, so that it neither holds them up nor falls out of step.
     const unsigned before = started() - 1 - done();
-    const int from = before ? (int)((unsigned)(v >> 24) / before) / sweep * sweep : 0;
+    const int from = before ? (int)((unsigned)(v >> 32) / before) / sweep * sweep : 0;
     int at = 0;
     for (int now = from;;) {
         v = pace_add(word, (unsigned long long)(now - at) * kProgress);   // one operation whether there is progress or not: a plain
         at = now;                                                        // load might be served by the compute unit's own cache
         if (now - from >= total) break;
         const unsigned under_way = started() - done();
-        if (under_way) lds_poke(&pace->allowed, (int)(4u * (unsigned)(v >> 24) / under_way) - 4 * from + lead);
+        if (under_way) lds_poke(&pace->allowed, (int)(4u * (unsigned)(v >> 32) / under_way) - 4 * from + lead);
         __builtin_amdgcn_s_sleep(1);
         now = from + lds_peek(&pace->done);
     }

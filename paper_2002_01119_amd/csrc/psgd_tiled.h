@@ -1,5 +1,5 @@
-// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows of 9 to 128 learners, for mixing tables that are
-// not one ring, and its kernel mix_deg_kernel (rows on lines, with two exceptions: see the rule in mix_step_impl).  Included by psgd_kernels.hip only.
+// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows of 9 to 128 learners, for mixing tables of other than three
+// slots, and its kernel mix_deg_kernel (rows on lines, with two exceptions: see the rule in mix_step_impl).  Included by psgd_kernels.hip only.
 #ifndef PSGD_TILED_H
 #define PSGD_TILED_H
 
@@ -9,7 +9,7 @@ namespace psgd {
 namespace {
 
 // ---------------------------------------------------------------------------------------
-// Tiled path for tables that are not a single ring (any number of slots per row).
+// Tiled path (any number of slots per row).
 //
 // The workgroup's T lanes form T / lpr row groups of lpr lanes; a tile is n rows by lpr column groups and lives
 // in LDS, so a neighbour read is an LDS read and every X element crosses the HBM interface once.  Lane (rg,
@@ -410,7 +410,7 @@ __device__ double tile_remainder(const float* X, float* Xout, const GT* __restri
 }
 
 // Any table with `deg` slots per row (sparse doubly stochastic matrices beyond the ring: more neighbours, lazy
-// walks, products of several mixing rounds, and 3-slot tables that are not one ring).
+// walks, products of several mixing rounds).
 // LDS: TileSlot tab[deg n] | two tile buffers | merge slots (plan::tile_plan).
 //
 // UQ: a row group is whole wavefronts (lpr >= 64).
