@@ -1,7 +1,7 @@
 // The Python binding's short way into libpsgd: the calls of a training loop with plain device tensors, checked and passed on
 // without building Python objects for every shape and pointer (psgd.py's own way takes 2.5 to 3 us of a 5.5 to 10 us call).
 // A call that is not plainly in order is not answered here: NOT_MINE sends it psgd.py's way, which checks it argument by argument
-// and raises what there is to raise.  Nothing is kept between calls but the addresses of the library's functions.
+// and raises what there is to raise, as it does for the library's refusals of an argument; other failures psgd.py raises at once.  Nothing is kept between calls but the addresses of the library's functions.
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>

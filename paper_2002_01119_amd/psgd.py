@@ -5,7 +5,8 @@ step of the computation runs in the library's HIP kernels.  There is no fallback
 shared library is missing or a call fails, an exception is raised.
 
 Calls that are plainly in order take the short way of the _call extension (csrc/psgd_call.cpp), which checks the same and passes
-them to the same library functions; whatever it does not answer with success goes through the checks below.
+them to the same library functions; what it does not take, and what the library refuses before any work is enqueued, goes through
+the checks below.
 """
 import ctypes
 import math
@@ -145,6 +146,17 @@ def _check(rc):
         raise PsgdError(rc, last_error())
 
 
+def _answered(rc):
+    """Whether the short way has made the call.  Not if it did not take it (a positive status), nor if the library refused an
+    argument, which it does before it enqueues anything: the long way says why.  Any other failure may come from behind work that
+    is already enqueued (a step in place, a counter that was advanced), so it is raised and the call not made again."""
+    if rc == OK:
+        return True
+    if rc > 0 or rc in (EINVAL, EALIAS, EALIGN):
+        return False
+    raise PsgdError(rc, last_error())
+
+
 def _stream_handle(stream):
     """hipStream_t of a torch stream (None = torch's current stream on the current GPU)."""
     import torch
@@ -204,7 +216,7 @@ def build_mixing_device(topology, n, seed, nbr, w, step_dev=None, step_offset=0,
     """Enqueue the construction of the same table in device memory: nbr int32 [n,3], w float32
     [n,3] (device tensors, written).  The iteration is step_offset plus, if given, the value of
     step_dev (device int64 / uint64 tensor, >= 1 element), which is then advanced by `advance`."""
-    if _call is not None and _call.build_mixing_device(topology, n, seed, nbr, w, step_dev, step_offset, advance, stream) == OK:
+    if _call is not None and _answered(_call.build_mixing_device(topology, n, seed, nbr, w, step_dev, step_offset, advance, stream)):
         return
     import torch
     if nbr.dtype != torch.int32 or w.dtype != torch.float32 or nbr.numel() != 3 * n or w.numel() != 3 * n \
@@ -228,7 +240,7 @@ def mix_step(X, X_out, G, nbr, w, lr, delay_mode=0, stream=None, cdist_out=None)
     stride along d; their rows may be pitched (stride(0) >= d), which selects
     psgd_mix_step_ex.  With cdist_out (device float64 tensor, >= 1 element) the fused
     variant also writes the consensus distance of X_out there."""
-    if _call is not None and _call.mix_step(X, X_out, G, nbr, w, lr, delay_mode, stream, cdist_out) == OK:
+    if _call is not None and _answered(_call.mix_step(X, X_out, G, nbr, w, lr, delay_mode, stream, cdist_out)):
         return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
@@ -275,7 +287,7 @@ def mix_step(X, X_out, G, nbr, w, lr, delay_mode=0, stream=None, cdist_out=None)
 def mix_step_d1d(X, X_out, G, nbr, w, lr, noise, G_next, c, stream=None, cdist_out=None):
     """Enqueue the step X_out = mix(X) - lr * G of the delay-by-one schedule and, from the same rows of X, the next
     gradients G_next = c * X + noise, in one pass (psgd_mix_step_d1d).  Tensors as in mix_step, gradients and noise float32."""
-    if _call is not None and _call.mix_step_d1d(X, X_out, G, nbr, w, lr, noise, G_next, c, stream, cdist_out) == OK:
+    if _call is not None and _answered(_call.mix_step_d1d(X, X_out, G, nbr, w, lr, noise, G_next, c, stream, cdist_out)):
         return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
@@ -329,7 +341,7 @@ def mix_step_cd_static(X, X_out, G, nbr, w, lr, cdist_out, delay_mode=0, stream=
 
 def mix_full(X, X_out, G, lr, delay_mode=0, stream=None, cdist_out=None):
     """Enqueue X_out[i] = mean_j X[j] - lr * G[i] (global averaging, T_u).  Tensors as in mix_step."""
-    if _call is not None and _call.mix_full(X, X_out, G, lr, delay_mode, stream, cdist_out) == OK:
+    if _call is not None and _answered(_call.mix_full(X, X_out, G, lr, delay_mode, stream, cdist_out)):
         return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
@@ -374,7 +386,7 @@ def consensus_dist(X):
 
 def consensus_dist_async(X, out, stream=None):
     """Enqueue the consensus distance of X into out (device float64 tensor, 1 element)."""
-    if _call is not None and _call.consensus_dist_async(X, out, stream) == OK:
+    if _call is not None and _answered(_call.consensus_dist_async(X, out, stream)):
         return
     import torch
     n, d, ldx = _rows_cols_pitch(X)
@@ -392,7 +404,7 @@ def consensus_dist_async(X, out, stream=None):
 def synth_grad(X_prev, noise, G, c, stream=None):
     """Enqueue G = c * X_prev + noise (fp32, elementwise) for the delay-by-one workload.
     Contiguous tensors of any shape, or [n, d] tensors with pitched rows."""
-    if _call is not None and _call.synth_grad(X_prev, noise, G, c, stream) == OK:
+    if _call is not None and _answered(_call.synth_grad(X_prev, noise, G, c, stream)):
         return
     import torch
     if X_prev.shape != noise.shape or X_prev.shape != G.shape:
