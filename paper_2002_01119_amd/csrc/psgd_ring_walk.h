@@ -213,10 +213,17 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     if (kind == kTableGeneral) {
         if (tid >= tiles.nrg << tiles.logc) return;              // whole wavefronts
         lds_barrier();                                           // the staged table has been read
+        // Every form starts from values of its own.  With common ones the compiler hoists what the forms share to the front of the
+        // choice and holds it through all of them: up to 27 vector registers spilled, in the tiles' loop too (us, so / now, fp32: 16 x 2 M
+        // with the distance 80.3 / 75.6, 40 x 700 k 73.3 / 70.8, 24 x 6 M without 319 / 314, 32 x 1.4 M 109.4 / 105.3).
 #define PSGD_TILES(R, CACHED)                                                                                              \
-    short_tiles<GT, CD, 3, R, false, CACHED, false>(X, Xout, G, nbr, w, 3, n, d, ld, neg_lr, tiles.logc, tiles.nrg,        \
-                                                    tiles.tab_bytes, tiles.tile_bytes, partials,                          \
-                                                    ShortLds{lds_raw, lds_waves, lds_bad})
+    do {                                                                                                                   \
+        int t = tid, rows = n, logc = tiles.logc, nrg = tiles.nrg;                                                         \
+        asm volatile("; tiles of %4 rows per lane, accesses %5" : "+v"(t), "+s"(rows), "+s"(logc), "+s"(nrg) : "n"(R), "n"(CACHED)); \
+        short_tiles<GT, CD, 3, R, false, CACHED, false>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
+                                                        tiles.tab_bytes, tiles.tile_bytes, partials,                       \
+                                                        ShortLds{lds_raw, lds_waves, lds_bad});                            \
+    } while (0)
         constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
         if (tiles.rows <= 2) {
             if (tiles.cached == kBoth) PSGD_TILES(2, kBoth);

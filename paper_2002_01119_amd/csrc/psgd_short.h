@@ -36,15 +36,15 @@ namespace {
 // ---------------------------------------------------------------------------------------
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (two or up to eight rows per lane: nothing is
 // loaded ahead, so those registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
-// FEW: rows of fewer than four columns.  Run by nrg << logc lanes of the workgroup, the others having ended.
+// FEW: rows of fewer than four columns.  Run by nrg << logc lanes of the workgroup, lane `tid` of them, the others having ended.
 struct ShortLds {
     char* dynamic;                           // plan::ShortPlan::lds bytes
     double* waves;                           // one per wavefront
     int* bad;                                // the same
 };
 template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
-__device__ __forceinline__ void short_tiles(const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr,
-                                            const float* __restrict__ w, int deg_any, int n, int64_t d, Pitch ld, float neg_lr,
+__device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout, const GT* __restrict__ G,
+                                            const int32_t* __restrict__ nbr, const float* __restrict__ w, int deg_any, int n, int64_t d, Pitch ld, float neg_lr,
                                             int logc, int nrg, int tab_bytes, int tile_bytes, double* __restrict__ partials,
                                             const ShortLds& lds) {
     typedef typename RawG<GT>::T GR;
@@ -52,7 +52,7 @@ __device__ __forceinline__ void short_tiles(const float* X, float* Xout, const G
     double* lds_waves = lds.waves;
     int* lds_bad = lds.bad;
     const int deg = DEG ? DEG : deg_any;
-    const int T = nrg << logc, C = 1 << logc, tid = threadIdx.x, lane = tid & (C - 1), lane16 = lane * 16;
+    const int T = nrg << logc, C = 1 << logc, lane = tid & (C - 1), lane16 = lane * 16;
     int rg = tid >> logc;
     TileSlot* tab = reinterpret_cast<TileSlot*>(lds_raw);       // slot: byte offset of the source row in the tile, weight
     char* tile = lds_raw + tab_bytes;
@@ -221,8 +221,8 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
     __shared__ int lds_bad[plan::kShortThreads / 64];
-    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW>(X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes, tile_bytes,
-                                                  partials, ShortLds{lds_raw, lds_waves, lds_bad});
+    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW>(threadIdx.x, X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes,
+                                                  tile_bytes, partials, ShortLds{lds_raw, lds_waves, lds_bad});
 }
 
 }  // namespace
