@@ -116,8 +116,8 @@ int psgd_build_mixing_device(int topology, int n, uint64_t seed, uint64_t* step_
  * Enqueues its work on `stream` and returns without waiting.  The table lives in device memory,
  * so only the device can tell whether it is one ring (every table of Sec. 3 is) or a general
  * 3-slot table.  One kernel either way: on short rows one that serves any table alike, on long rows of nine and
- * more learners (9 learners: from about 3.7 M columns; 16: 1.6 M; 24: 0.8 M; 32: 0.6 M; 48: 0.4 M; 96: 0.34 M;
- * 200: 0.24 M) one that classifies the table and walks the ring, or takes any other table through LDS tiles.
+ * more learners (9 learners: from about 3.7 M columns; 16: 1.6 M; 24: 0.8 M; 32: 0.6 M; 48: 0.4 M; 96: 0.31 M;
+ * 200: 0.24 M; 256: 0.2 M) one that classifies the table and walks the ring, or takes any other table through LDS tiles.
  * Errors: PSGD_EINVAL;
  * PSGD_EALIAS (X_out partially overlaps X, X_out overlaps G, or X_out == X with
  * delay_mode 1); PSGD_EALIGN (X, X_out, G not 4-byte aligned); PSGD_EHIP.  A table entry

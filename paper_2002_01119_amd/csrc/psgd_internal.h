@@ -106,22 +106,15 @@ inline int ring_threads(const SweepPlan& s, int threads) {
 }
 
 // Whether a 3-slot table on n rows of `ncg` column groups takes mix_step_kernel (the ring walk, tiles for any other table) instead
-// of the short-row kernel, by the lines of the ring walk without pacing; paced it is ahead from ring_rows_paced on.  In sweeps of
-// one 768-lane workgroup per compute unit.
-inline bool ring_rows(int n, int64_t ncg, int cus, int threads) {
-    if (n <= 8) return false;
-    const int64_t sweep = (int64_t)cus * threads;
-    return ncg * 4 >= (n < 29 ? 32 * sweep : n < 48 ? 6 * sweep : n < 96 ? 5 * sweep : n < 256 ? 8 * sweep / 5 : sweep);
-}
-
-// The same with the workgroups of a die in step, in column groups per compute unit.  The walk takes 0.45 us a row and sweep however
+// of the short-row kernel; in column groups per compute unit.  The walk takes 0.45 us a row and sweep however
 // few columns there are, and stages and classifies the table first; the short-row kernel reads and writes all rows of a tile at once,
 // which holds its rate to 5.0-5.3 TB/s once the arrays do not fit the last-level cache.  us, short-row kernel / ring walk, fp32 with the
 // distance: 9 x 2.5 M 52.5 / 51 (bf16 gradients 43 / 45), 12 x 1.5 M 42.6 / 44.7, 16 x 1.5 M 56.0 / 56.1, x 2.9 M 106 / 95, 24 x 0.66 M 37.5 / 39.2, x 0.82 M 48.1 / 46.8,
 // 32 x 0.51 M 41.3 / 41.2, x 0.82 M 66 / 59, 64 x 0.33 M 51 / 54, x 0.41 M 64 / 60, x 0.66 M 97 / 88, 128 x 0.26 M 78 / 75 (bf16 gradients, no
-// distance, 0.19 M 53 / 66, 0.33 M 93 / 86), 200 x 0.26 M 135 / 113.
-inline bool ring_rows_paced(int n, int64_t ncg, int cus) {
-    const int64_t from = n < 12 ? 3600 : n < 16 ? 2500 : n < 24 ? 1600 : n < 32 ? 800 : n < 48 ? 560 : n < 96 ? 400 : n < 200 ? 330 : 230;
+// distance, 0.19 M 53 / 66; with it 0.33 M 94.8 / 86.8), x 0.32 M 103.9 / 92.3, 96 x 0.33 M bf16, no distance, 69.3 / 58.9, 199 x 325 001 174 / 150, 200 x 0.26 M
+// 135 / 113, 256 x 0.2 M 139.8 / 122.9, 512 x 0.2 M 266.8 / 236.5, x 230 001 331 / 273 (300 x 0.2 M with bf16 gradients 133.6 / 142.9).
+inline bool ring_rows(int n, int64_t ncg, int cus) {
+    const int64_t from = n < 12 ? 3600 : n < 16 ? 2500 : n < 24 ? 1600 : n < 32 ? 800 : n < 48 ? 560 : n < 96 ? 400 : n < 200 ? 307 : n < 256 ? 230 : 192;
     return n > 8 && ncg >= from * cus;
 }
 

@@ -458,7 +458,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const Pitch ld{ldx, ldo, ldg};
     int grid = 0;        // partial sums written so far (the fused distance sums this many)
     const int64_t ncg = (d + kVec - 1) / kVec;
-    // 3-slot tables: from plan::ring_rows_paced on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
+    // 3-slot tables: from plan::ring_rows on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
     // through tiles; below it the short-row kernel.
     // Tables of other slot counts: on long rows the tiled kernel is as good or a little better while
     // its row segments are wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5
@@ -470,7 +470,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // with 13 slots 236 / 220).
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
     const bool wide = n > 8 && n <= 128 && (rows_on_lines(X, X_out, ld) || (n > 28 && n <= 32));
-    const bool ring = deg == 3 && (plan::ring_rows_paced(n, ncg, di->cus) || plan::ring_rows(n, ncg, di->cus, kRingThreads));
+    const bool ring = deg == 3 && plan::ring_rows(n, ncg, di->cus);
     const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
     if (ring) {
         grid = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, prod)

@@ -161,18 +161,39 @@ int main() {
         CHECK(tile_plan(256, 3, 1024, false, large, 4).lpr == 16, "n = 256: 256-byte row segments");
         CHECK(tile_plan(257, 3, 1024, false, large, 4).lpr == 0, "n = 257: no plan");
     }
-    // where the ring walk runs: the lines of each band of learners (in column groups, 256 compute units of 768 lanes), and what
-    // the short-row kernel behind it is built for there
-    const struct { int lo, hi; int64_t line; } bands[] = {{9, 28, 1572864}, {29, 47, 294912}, {48, 95, 245760}, {96, 255, 78643}, {256, 512, 49152}};
-    for (const auto& b : bands)
-        for (int n : {b.lo, (b.lo + b.hi) / 2, b.hi})
-            for (int64_t ncg : {b.line - 1, b.line, b.line * 3 + 1}) {
-                CHECK(ring_rows(n, ncg, 256, 768) == (ncg >= b.line), "ring walk: n=%d, %lld column groups", n, (long long)ncg);
-                const ShortPlan p = short_plan(n, 3, ncg, 256, n & 1, true);
-                CHECK(ncg < b.line || (!p.one && p.rows >= 2 && p.rows <= 4 && short_grid(p, 256, kShortSlots - 256) >= 1),
-                      "n=%d, %lld column groups: %d rows per lane behind the ring walk", n, (long long)ncg, p.rows);
-            }
-    for (int n : {1, 8}) CHECK(!ring_rows(n, (int64_t)1 << 32, 256, 768), "no ring walk for %d learners", n);
+    // where the ring walk and the paced global averaging run: each band of learners from its line on (column groups per compute unit)
+    const struct { int lo, hi; int64_t line; } bands[] = {{9, 11, 3600}, {12, 15, 2500}, {16, 23, 1600}, {24, 31, 800}, {32, 47, 560},
+                                                          {48, 95, 400}, {96, 199, 307}, {200, 255, 230}, {256, 512, 192}};
+    const struct { int lo, hi; int64_t line; } full_bands[] = {{9, 15, 2400}, {16, 31, 800}, {32, 47, 560}, {48, 512, 300}};
+    for (int cus : {64, 256, 304})
+        for (const auto& b : bands)
+            for (int n = b.lo; n <= b.hi; ++n)
+                for (int64_t ncg : {b.line * cus - 1, b.line * cus, b.line * cus + 1, b.line * cus * 3 + 7, b.line * cus * 40 + 1}) {
+                    CHECK(ring_rows(n, ncg, cus) == (ncg >= b.line * cus), "ring walk: n=%d, %lld column groups", n, (long long)ncg);
+                    if (!ring_rows(n, ncg, cus)) continue;
+                    const SweepPlan p = sweep_plan(ncg, cus, kRingLanes);
+                    const int depth = ring_depth(p, n), produce = ring_depth_produce(p);
+                    CHECK(p.chunk <= kRingLanes && depth <= n - 2 && (produce == 1 || produce == 2) && produce <= n - 2,
+                          "ring walk: n=%d, depths %d and %d", n, depth, produce);
+                    CHECK(pace_lead(produce, true) >= 4 * produce, "with the next gradients: a lead that the loads on their way need");
+                    CHECK(p.count * n < (int64_t)1 << 29, "ring walk: %lld items, counted in quarters in 32 bits", (long long)(p.count * n));
+                    // any other table in the same launch: looping tiles of two to four rows per lane on the same workgroups, one partial
+                    // sum and at least one tile each
+                    for (bool cd : {false, true}) {
+                        const ShortPlan t = short_loop_plan(n, 3, ncg, cd);
+                        CHECK(!t.one && t.rows >= 2 && t.rows <= 4 && t.nrg * t.rows >= n && t.threads == t.nrg << t.logc &&
+                                  t.threads % 64 == 0 && t.threads <= kRingThreadsMost && t.lds <= kShortLds,
+                              "n=%d: tiles of %d rows per lane, %d lanes, %zu bytes of LDS", n, t.rows, t.threads, t.lds);
+                        CHECK(t.tiles >= cus && t.tiles << t.logc >= ncg, "n=%d, %lld column groups: %lld tiles", n, (long long)ncg, (long long)t.tiles);
+                    }
+                }
+    for (int cus : {64, 256, 304})
+        for (const auto& b : full_bands)
+            for (int n = b.lo; n <= b.hi; ++n)
+                for (int64_t ncg : {b.line * cus - 1, b.line * cus, b.line * cus + 1, b.line * cus * 40 + 1})
+                    CHECK(full_rows_paced(n, ncg, cus) == (ncg >= b.line * cus), "global averaging in step: n=%d, %lld column groups", n, (long long)ncg);
+    for (int n : {1, 8}) CHECK(!ring_rows(n, (int64_t)1 << 32, 256) && !full_rows_paced(n, (int64_t)1 << 32, 256), "no walk for %d learners", n);
+    for (int depth : {2, 4}) CHECK(depth < 9 && full_lead(depth) >= 4 * depth, "global averaging: lead %d of depth %d", full_lead(depth), depth);
     // short rows: whole wavefronts, the rows covered, the LDS within a compute unit's, the grid within the buffer
     for (int n : {1, 2, 3, 5, 8, 9, 16, 17, 33, 64, 65, 100, 128, 200, 256, 257, 300, 511, 512})
         for (int deg : {1, 3, 8, 13, 32})
