@@ -85,9 +85,10 @@ constexpr int kPaceSlots = 64;
 constexpr int kPaceSpins = 400;
 // Rows on their way per lane, and how far ahead of the mean a workgroup may be, in quarter rows.  The narrower the chunk, the more rows: about 900 lanes times rows keep the memory busy, and
 // what is beyond that costs more in order than it gains (us; one row each 64 x 1.2 M 154, two 153; 128 x 500 k 138 / 129; two / four
-// 130 x 200 k with a distance 79 / 68, 256 x 280 k with bf16 gradients 154 / 135; four / eight 512 x 205 k 242 / 235, 256 x 210 k bf16
-// 112 / 105).  Lead: one row 1.25 / 1.5 / 1.75 / 2 rows 64 x 25.6 M 3134 / 3136 / 3186 / 3289; four rows of lead or none
-// for a depth of one: 3500 / 3800.
+// 130 x 200 k with a distance 79 / 68, 256 x 280 k with bf16 gradients 154 / 135; four / six 512 x 205 k 244.7 / 237.0, without the distance 222.8 /
+// 212.9, 300 x 210 k 147.9 / 143.3, 256 x 220 001 bf16 143.8 / 141.1, 512 x 240 k bf16 226.0 / 207.8, 200 x 260 k bf16 94.8 / 92.1; from 240 to 260 fp32
+// alone would stay at four: 512 x 240 k 252.1 / 258.1, 256 x 260 k 138.5 / 142.6).  Lead: one row 1.25 / 1.5 / 1.75 / 2 rows 64 x 25.6 M
+// 3134 / 3136 / 3186 / 3289; four rows of lead or none for a depth of one: 3500 / 3800.
 inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 6; }
 constexpr int kRingThreadsMost = kRingLanes + 64;   // of the workgroup
 // With the producer of the next gradients in the walk five arrays are on their way, not three: fewer rows, less lead (pairs, us: one row

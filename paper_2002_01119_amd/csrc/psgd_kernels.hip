@@ -366,7 +366,7 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
                                            prod ? *prod : Produce{})
     const int depth = plan::ring_depth(sp, n);
     // With one or two rows on their way the ragged form costs nothing (64 x 25.6 M 3137 / 3129 us); with more, a lane's own work shows
-    // (512 x 205 k with six: 246, ragged 265).
+    // (512 x 205 k with six rows, in one run: whole groups 246, the ragged form 265).
     if constexpr (sizeof(GT) == 4) {
         if (prod) {
             return plan::ring_depth_produce(sp) == 1 ? PSGD_RING(true, 1, true) : PSGD_RING(true, 2, true);

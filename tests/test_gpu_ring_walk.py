@@ -10,7 +10,7 @@ from paper_2002_01119_amd import inputs as inp
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-# n, d, gradients: depth 1 (several sweeps, the last one not for every workgroup), 2, 4 and 8; even and odd counts of rows
+# n, d, gradients: depth 1 (several sweeps, the last one not for every workgroup), 2, 4 and 6; even and odd counts of rows
 CASES = [
     (9, 6_300_004, "f32"), (9, 6_291_459, "bf16"), (15, 6_400_001, "bf16"), (31, 1_180_003, "f32"), (64, 1_966_084, "f32"),
     (65, 990_001, "bf16"), (100, 450_001, "bf16"), (101, 590_000, "f32"), (100, 409_604, "f32"), (128, 330_003, "bf16"),
