@@ -54,11 +54,12 @@ class DelayByOne:
         self.producer_repeat = max(int(producer_repeat), 1)   # > 1 rewrites the same G again: a slower producer
         self.k = 0
         self._mix_done = {}          # step -> event recorded behind mix k
-        self._produced = {}          # step -> event recorded behind the producer of G_k
+        self._produced = {}          # step -> event recorded behind the producer of G_k (in one pass: None, the stream orders it)
         with torch.cuda.stream(self.mix_stream):
             self.X_prev.copy_(self.X)                         # X_{-1} := X_0
         if one_pass:
             psgd.synth_grad(self.X_prev, noise, self.Gs[0], c, stream=self.mix_stream)
+            self._produced[0] = None
         elif overlap:
             start = torch.cuda.Event()
             start.record(self.mix_stream)
@@ -77,8 +78,8 @@ class DelayByOne:
     def step(self, cdist_out=None, before_mix=None, after_mix=None, more=True):
         """Enqueue step k: X_{k+1} = mix(X_k) - lr * G_k with G_k = c * X_{k-1} + noise_k.  `before_mix` /
         `after_mix` are called with the mix stream right around the mix call (for timing events).  `more`
-        = False says no further step follows, so no further gradient is produced.  Returns the tensor
-        that holds X_{k+1}."""
+        = False says no further step follows, so no further gradient is produced: on the overlapped schedules a step after
+        that raises KeyError.  Returns the tensor that holds X_{k+1}."""
         k, ms = self.k, self.mix_stream
         G = self.Gs[k % 2]
         if self._one_pass:
@@ -113,16 +114,19 @@ class DelayByOne:
 
     def _step_in_one_pass(self, k, G, cdist_out, before_mix, after_mix, more):
         ms = self.mix_stream
+        self._produced[k]                                     # KeyError: the step before said that none would follow
         nbr, w = self.table(k)
         if before_mix:
             before_mix(ms)
         if more:
             psgd.mix_step_d1d(self.X, self.Y, G, nbr, w, self.lr, self.noise(k + 1), self.Gs[(k + 1) % 2], self.c, stream=ms,
                               cdist_out=cdist_out)
+            self._produced[k + 1] = None
         else:
             psgd.mix_step(self.X, self.Y, G, nbr, w, self.lr, delay_mode=1, stream=ms, cdist_out=cdist_out)
         if after_mix:
             after_mix(ms)
+        del self._produced[k]
         self.X_prev, self.X, self.Y = self.X, self.Y, self.X_prev
         self.k += 1
         return self.X
