@@ -76,8 +76,8 @@ def test_variants_run_and_report(flags):
 @pytest.mark.gpu
 def test_default_form_reports_the_legs_it_is_read_against():
     """Without flags the line also carries the same step in place and on dense arrays, tables that are not one ring
-    (the tiled kernel), the distance as a pass of its own, the reference streams (read-only, write-only, x + a g
-    in the step kernel's access pattern) and the runtime's device copy."""
+    (tiles, under keys of one name), the distance as a pass of its own, the reference streams (read-only, write-only, x + a g
+    in the form of a walk of the rows) and the runtime's device copy."""
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -114,9 +114,24 @@ def test_overlapped_schedule_long_rows_kernels_really_overlap(mods):
         _check(got, cdist, want, steps)
 
 
-def test_workload4_overlapped_on_sampled_columns(mods):
+def test_overlapped_schedule_beside_the_ring_walk(mods):
+    """Enough learners for the ring walk, whose workgroups keep pace while the producer of the other stream takes compute units from
+    them; every element against the oracle, and the bits of the serial order; the slower producer variant too."""
+    n, d, steps = 100, 420_001, 5
+    serial, cs, want = _run(mods, n, d, steps, orc.TOPO_RAND_RING, overlap=False, seed=60)
+    for rep in (1, 4):
+        got, cdist, _ = _run(mods, n, d, steps, orc.TOPO_RAND_RING, overlap=True, producer_repeat=rep, seed=60)
+        for k in range(steps):
+            assert np.array_equal(got[k].view(np.uint32), serial[k].view(np.uint32)), (rep, k)
+        assert np.array_equal(cdist, cs)
+    _check(got, cdist, want, steps)
+
+
+@pytest.mark.parametrize("two_streams", [True, False])
+def test_workload4_overlapped_on_sampled_columns(mods, two_streams):
     """Workload 4 at full size (n = 128, d = 8 M, randomized ring, G = 0.01 X_{k-1} + N(0, 1e-3^2)) in the
-    benchmark's pitched layout and overlapped schedule, 40 steps, sampled columns against the oracle."""
+    benchmark's pitched layout and overlapped schedule (a producer stream of the caller's; without one, the one-pass form), 40
+    steps, sampled columns against the oracle."""
     psgd, d1d = mods
     from paper_2002_01119_amd import placement as plc
     wl = inp.workload(4)
@@ -140,7 +155,9 @@ def test_workload4_overlapped_on_sampled_columns(mods):
     torch.cuda.synchronize()
     ms = torch.cuda.Stream()
     run = d1d.DelayByOne(X, views["Y"], views["Xprev"], [views["G0"], views["G1"]], noise, lambda k: tabs_dev[k],
-                         wl.lr, wl.grad_pull, overlap=True, mix_stream=ms)
+                         wl.lr, wl.grad_pull, overlap=True, mix_stream=ms,
+                         producer_stream=torch.cuda.Stream() if two_streams else None)
+    assert (run.producer_stream is not ms) == two_streams
     snaps = {}
     for k in range(steps):
         out = run.step(cdist_out=cd[k:k + 1], more=k + 1 < steps)

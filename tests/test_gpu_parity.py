@@ -679,10 +679,9 @@ def test_steps_captured_in_a_hip_graph_replay_exactly(psgd):
 
 @pytest.mark.parametrize("n,d", [(16, 1_600_004), (40, 1_600_032), (40, 1_200_003)])
 def test_long_row_kernels_captured_in_a_hip_graph_replay_exactly(psgd, n, d):
-    """The same on rows long enough for the large workgroups: the ring walk with the kernel for any other table enqueued
-    behind it (d on 128-byte lines: the tiled one, else the short-row one), a 5-slot table through the same kernel
-    (tiled: more than 64 KB of LDS) and global averaging, every one with the fused distance, captured once after an
-    eager pass and replayed between eager work.  n = 16 takes one pass per table only."""
+    """The same on rows long enough for the large workgroups: the ring walk (more than 64 KB of LDS), a 5-slot table (d on
+    128-byte lines: the tiled kernel, else the short-row one) and global averaging, every one with the fused distance, captured
+    once after an eager pass and replayed between eager work.  n = 16 takes one pass per table only."""
     rng = np.random.default_rng(5)
     X0 = dev(inp.host_normal_f32((n, d), 1.0, 23))
     G = dev(inp.host_normal_f32((n, d), 0.1, 24))
@@ -815,8 +814,8 @@ def test_binding_checks_dtypes_and_devices(psgd):
                                   (40, 1_500_001)])
 def test_many_sweeps_per_workgroup(psgd, kind, n, d):
     """Rows long enough that the workgroups of the short-row kernel and of global averaging stride over many
-    tiles / column groups (the small shapes finish in one), with a ragged last tile; n = 40 takes the ring walk and,
-    on its lines, the tiled kernel.  Every element is compared."""
+    tiles / column groups (the small shapes finish in one), with a ragged last tile; n = 40 takes the ring walk and, for
+    more than three slots on its lines, the tiled kernel.  Every element is compared."""
     lr = 0.1
     rng = np.random.default_rng(d % 1000 + len(kind))
     X = inp.host_normal_f32((n, d), 1.0, 61)
@@ -870,8 +869,7 @@ def test_global_average_large_workgroups_every_element(psgd, gkind):
 
 @pytest.mark.parametrize("n,d", [(4, 2_000_000), (64, 1_000_064), (33, 1_200_003)])
 def test_status_flag_is_sticky_until_cleared_and_long_rows_refuse_bad_tables(psgd, n, d):
-    """Four learners take the short-row kernel, 64 and 33 the ring walk with the tiled and the short-row kernel behind
-    it: a bad table is written off by one of the two, and only once."""
+    """Four learners take the short-row kernel, 64 and 33 the ring walk's: each writes off a bad table, and raises the flag."""
     nbr, w = psgd.build_mixing(psgd.TOPO_RING, n)
     bad = nbr.copy()
     bad[1, 2] = -1
@@ -972,7 +970,7 @@ _LONG_ROW_CASES = (
        (16, 1_900_004, "two_rings", "bf16"), (16, 1_900_004, "deg5", "f32"),
        (5, 2_000_004, "deg5", "f32"), (5, 2_000_004, "deg13", "bf16"),
        (48, 1_600_003, "two_rings", "f32"), (48, 1_600_003, "deg5", "bf16")]
-    # rows on 128-byte lines: the tiled kernel (behind the ring walk for the two rings)
+    # rows on 128-byte lines: the tiled kernel (for the two rings the tiles of the ring walk's kernel)
     + [(64, 1_600_032, k, g) for k in ("two_rings", "deg5", "deg13") for g in ("f32", "bf16")]
     + [(128, 1_600_032, "two_rings", "bf16"), (128, 1_600_032, "deg5", "f32"), (128, 1_600_032, "deg13", "bf16"),
        (33, 1_700_032, "deg5", "f32"), (33, 1_700_032, "deg13", "bf16"), (30, 1_600_003, "two_rings", "bf16"),
@@ -982,11 +980,11 @@ _LONG_ROW_CASES = (
 
 @pytest.mark.parametrize("n,d,kind,gkind", _LONG_ROW_CASES)
 def test_general_tables_long_rows_every_element(psgd, n, d, kind, gkind):
-    """Long rows and tables that are not one ring.  On 128-byte lines (and for n = 29 to 32) the tiled kernel: merge
+    """Long rows and tables that are not one ring.  More than three slots on 128-byte lines (and for n = 29 to 32): the tiled kernel, merge
     slots of the distance inside the consumed tile buffer at 16 B per lane; wider rows for n = 16 and 10; an odd row
     count per row group for n = 33; narrower rows for n = 70 and n = 128; 16-byte accesses on the lines and, for n = 30
     off them, one column per lane at the ragged end.  Off the lines and for n <= 8 the short-row kernel over many
-    tiles, behind the ring walk for 3 slots from its line on.  Every element and the fused distance against the
+    tiles.  The two rings: its tiles in the ring walk's kernel.  Every element and the fused distance against the
     oracle, out of place and in place, ragged last tile included."""
     rng = np.random.default_rng(n + d % 1000)
     if kind == "two_rings":
@@ -1013,8 +1011,8 @@ def test_general_tables_long_rows_every_element(psgd, n, d, kind, gkind):
 
 @pytest.mark.parametrize("n,kind,gkind", [(200, "deg5", "bf16"), (256, "two_rings", "f32")])
 def test_general_tables_long_rows_many_learners(psgd, n, kind, gkind):
-    """More than 128 learners on long rows: the short-row kernel over many tiles, behind the ring walk for the two
-    rings; every element and the fused distance against the oracle."""
+    """More than 128 learners on long rows: the short-row kernel over many tiles, for the two rings in the ring walk's
+    kernel; every element and the fused distance against the oracle."""
     d = 1_580_004
     rng = np.random.default_rng(n)
     nbr, w = _two_rings_table(n) if kind == "two_rings" else _perm_sum_table(n, 5, rng)
@@ -1059,12 +1057,13 @@ def test_tiled_kernel_long_rows_widest_tables(psgd, n, deg, gkind, d):
 
 @pytest.mark.parametrize("n", [16, 64, 128])
 @pytest.mark.parametrize("d", [1_600_004, 1_600_032])
-def test_general_tables_long_rows_distance_corner_cases(psgd, n, d):
+@pytest.mark.parametrize("slots", [3, 5])
+def test_general_tables_long_rows_distance_corner_cases(psgd, n, d, slots):
     """The row groups of a tile each measure against their own pivot and the merge brings them to a common one:
     replicas far from the origin and close together must still give the distance to 1e-6, and identical outputs must
-    give exactly 0.  Rows off the 128-byte lines and n = 16 take the short-row kernel, 64 and 128 learners on the
-    lines the tiled one."""
-    nbr, w = _two_rings_table(n)
+    give exactly 0.  Two rings: n = 16 takes the short-row kernel, 64 and 128 learners its tiles in the ring walk's kernel; five
+    slots: the short-row kernel off the 128-byte lines, the tiled one on them."""
+    nbr, w = _two_rings_table(n) if slots == 3 else _perm_sum_table(n, slots, np.random.default_rng(n))
     base = inp.host_normal_f32((1, d), 100.0, 3)
     X = (np.tile(base, (n, 1)) + inp.host_normal_f32((n, d), 1e-3, 4)).astype(np.float32)
     G = np.full((n, d), 7.0, np.float32)

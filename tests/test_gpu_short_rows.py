@@ -18,14 +18,20 @@ CASES = [
     (512, 6_001, 8, "bf16", (1, 2, 7)), (100, 50_002, 3, "f32", None),
     (8, 1_048_578, 3, "f32", None), (8, 1_200_003, 3, "bf16", (2, 3, 1)), (5, 1_570_001, 4, "f32", None),
     (9, 1_100_002, 3, "bf16", None), (16, 700_001, 5, "f32", (1, 2, 3)), (64, 200_003, 3, "bf16", (3, 1, 1)),
-    # the ring walk, whose last column group is ragged too, in one sweep; n = 64 is not a ring: the short-row kernel behind it
+    # the ring walk, whose last column group is ragged too, in one sweep
     (128, 589_821, 3, "f32", (1, 2, 3)), (128, 589_825, 3, "bf16", (3, 1, 2)), (200, 600_002, 3, "f32", None),
     (64, 2_359_299, 3, "bf16", None),
-    # either side of the line to the ring walk, in each band of learners
+    # either side of the line to the ring walk, in each band of learners (the ragged end is the column group that makes the difference)
+    (9, 3_686_396, 3, "f32", None), (9, 3_686_397, 3, "bf16", None), (12, 2_559_996, 3, "bf16", None), (12, 2_559_997, 3, "f32", None),
+    (16, 1_638_396, -3, "f32", None), (16, 1_638_397, -3, "bf16", None), (24, 819_196, 3, "bf16", (3, 1, 2)), (24, 819_197, 3, "f32", None),
+    (32, 573_436, 3, "f32", None), (32, 573_437, 3, "bf16", None), (48, 409_596, 3, "bf16", None), (48, 409_597, 3, "f32", (1, 2, 3)),
+    (96, 314_364, 3, "f32", None), (96, 314_365, 3, "bf16", None), (200, 235_516, -3, "bf16", None), (200, 235_517, -3, "f32", None),
+    (256, 196_604, 3, "f32", None), (256, 196_605, 3, "bf16", None),
+    # the ring walk and, for other tables, the tiles beside it, above their lines
     (9, 6_291_452, 3, "bf16", None), (9, 6_291_453, 3, "bf16", None), (32, 1_179_644, 3, "f32", None), (32, 1_179_645, 3, "bf16", None),
     (64, 983_036, -3, "bf16", None), (64, 983_037, -3, "f32", (1, 2, 3)), (128, 314_568, 3, "bf16", (3, 1, 2)),
-    (128, 314_569, 3, "f32", (1, 2, 3)), (256, 196_604, 3, "f32", None), (256, 196_605, 3, "bf16", None),
-    # 3-slot tables that are not one ring above it (-3): on lines the tiled kernel, its ragged end apart; else the short-row kernel
+    (128, 314_569, 3, "f32", (1, 2, 3)),
+    # 3-slot tables that are not one ring on such rows (-3): tiles of two, three and four rows per lane, on and off lines
     (33, 1_200_000, -3, "f32", None), (33, 1_200_002, -3, "bf16", (30, 62, 0)), (30, 1_200_003, -3, "f32", None),
     (10, 6_300_003, -3, "bf16", None), (13, 6_300_001, -3, "f32", None), (100, 400_004, -3, "bf16", None), (136, 330_016, -3, "f32", None),
     (200, 320_001, -3, "bf16", (1, 2, 3)), (257, 200_003, -3, "f32", None), (300, 200_032, -3, "bf16", None), (301, 200_032, -3, "f32", None),

@@ -437,8 +437,8 @@ def test_rows_longer_than_2_31_elements(psgd):
 
 @pytest.mark.parametrize("d", [2 ** 31 + 1088, 2 ** 31 + 1027])
 def test_rows_longer_than_2_31_elements_ring_walk_and_the_kernel_behind_it(psgd, d):
-    """The same for the kernels of long rows, which take nine learners: the ring walk, and for two rings the kernel
-    behind it (rows on 128-byte lines: the tiled one; ragged rows: the short-row one), on sampled columns; the fused
+    """The same for the kernel of long rows, which takes nine learners: the ring walk, and for two rings its tiles (rows on
+    128-byte lines; ragged rows), on sampled columns; the fused
     distance against the pass of its own (both add a column's n squares in fp32: at most (n + 2) 2^-24 relative)."""
     n, lr = 9, 0.25
     X = inp.device_normal_f32((n, d), 1.0, 74)

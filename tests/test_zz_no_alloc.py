@@ -86,8 +86,7 @@ def test_static_entry_point_twice_second_call_smaller(lib):
 
 @pytest.mark.parametrize("n,d,gkind", [(64, 1_000_064, "bf16"), (33, 1_200_003, "f32"), (200, 400_004, "bf16")])
 def test_static_entry_point_behind_the_ring_walk(lib, n, d, gkind):
-    """From the ring walk's line on two kernels share the array: the ring walk, and behind it the tiled kernel (64
-    learners, rows on 128-byte lines) or the short-row kernel."""
+    """From the ring walk's line on: one partial sum per compute unit, rows on 128-byte lines (64 learners) and off them."""
     _case(lib, n, d, gkind, orc.TOPO_RAND_RING, n, pitched=False)
 
 
