@@ -13,7 +13,7 @@ ring (the configuration the 80 %-of-HBM target is quoted on).
 After the timed region the default run also measures, in the same process and on the same box, what the
 headline has to be read against (`legs` and `reference_streams` in the JSON): the same step in place, on plain
 dense arrays through the entry points the baseline names, on the other workloads, and the traffic of the step
-with the mixing taken out (read-only, write-only and x + a g streams in the step kernel's own access pattern),
+with the mixing taken out (read-only, write-only and x + a g streams in the form of a walk that is not kept in step),
 plus the runtime's device-to-device copy.
 
 Prints ONE JSON line on stdout; progress and per-kernel detail go to stderr.
@@ -367,7 +367,7 @@ def main():
         nbr_dev[k].copy_(nbr_host[k], non_blocking=True)
         w_dev[k].copy_(w_host[k], non_blocking=True)
 
-    # Delay-by-one workloads run through the two-stream schedule of d1d.DelayByOne (overlap or serial order);
+    # Delay-by-one workloads run through d1d.DelayByOne, on two streams (--overlap) or in serial order, never in one pass;
     # its table callback uploads the iteration's table on the mix stream right before the mix.
     delayed = None
     if wl.delay:
@@ -576,12 +576,12 @@ def main():
         return r
 
     def reference_streams(w_, Xr, Yr, Gr, layout):
-        """Read-only, write-only and x + a g traffic of the step's own access pattern on these buffers."""
+        """Read-only, write-only and x + a g traffic of a walk of the rows on these buffers."""
         nd = w_.n * w_.d
         gb = 2 if w_.g_dtype == "bf16" else 4
         out = {"layout": layout, "workload": w_.name,
-               "note": "psgd_reference_stream: the step kernel's lane/column ownership, lockstep row batches and "
-                       "persistent grid, without the mixing"}
+               "note": "psgd_reference_stream: the ring walk's lane/column ownership in lockstep row batches on a persistent "
+                       "grid, its workgroups not kept in step, without the mixing"}
         for name, kind, per in (("read_x_and_g", psgd.REF_READ, 4 + gb), ("write_x_out", psgd.REF_WRITE, 4),
                                 ("axpy_x_plus_a_g", psgd.REF_AXPY, 8 + gb)):
             ms = timed(lambda s_: psgd.reference_stream(kind, Xr, Yr, Gr, 0.5, stream=s_))
@@ -611,10 +611,11 @@ def main():
             legs["pitched_in_place"] = leg("pitched, in place", wl, mix_bytes, ms, layout="pitched", in_place=True,
                                            entry_point="psgd_mix_step_ex")
         if not wl.delay and n % 2 == 0 and n >= 13:
-            # ---- tables that are not one ring (the LDS-tiled kernel), and the distance as a pass of its own
+            # ---- tables that are not one ring (two rings: the tiles of the ring walk's kernel; 13 slots: the LDS-tiled kernel), and the
+            # distance as a pass of its own
             nb3, w3 = psgd.build_mixing(wl.topology, n, wl.seed_perm, total - 1)
             for key, label, (nb_, ww_) in (
-                    ("tiled_two_rings_pitched", "two disjoint rings (tiled kernel)", (split_in_two(nb3), w3)),
+                    ("tiled_two_rings_pitched", "two disjoint rings (tiles in the ring walk's kernel)", (split_in_two(nb3), w3)),
                     ("tiled_degree13_pitched", "13 neighbours per learner (tiled kernel)", widen(nb3, 13))):
                 nb_, ww_ = torch.from_numpy(nb_).to(dev), torch.from_numpy(ww_).to(dev)
                 ms = timed(lambda s_: psgd.mix_step(Xa, Ya, Ga, nb_, ww_, wl.lr, stream=s_, cdist_out=cd1))

@@ -281,7 +281,7 @@ int psgd_synth_grad_ex(const float* X_prev, int64_t ldx, const float* noise, int
  *     X_out[i,:] = sum_s w[i,s] * X[nbr[i,s],:] - lr * G[i,:]
  * of psgd_mix_step_deg (fp32 gradients, delay_mode 1, `deg` slots, optional distance) and the producer of the next
  * gradients, G_next = fma(c, X, noise) as psgd_synth_grad_ex computes it, from the same rows of X.  Same values as the
- * two calls one after the other.  Row pitches in elements.  No output may overlap another array (PSGD_EALIAS).  The next
+ * two calls one after the other.  Row pitches in elements.  No output may overlap X, G, noise or another output (PSGD_EALIAS).  The next
  * gradients are written whatever the table holds, the step only if it is valid.
  */
 int psgd_mix_step_d1d(const float* X, int64_t ldx, float* X_out, int64_t ldo, const float* G, int64_t ldg,
@@ -291,10 +291,10 @@ int psgd_mix_step_d1d(const float* X, int64_t ldx, float* X_out, int64_t ldo, co
 
 /*
  * psgd_reference_stream - measurement support, not a step of the method: the memory traffic of
- * the fused step with the mixing taken out, issued exactly as the step's kernel issues it (a lane
+ * the fused step with the mixing taken out, issued as a walk of the rows that nothing keeps in step issues it (a lane
  * per 128-bit column group walking the n rows, workgroups sweeping the rows in lockstep batches,
- * the same persistent grid).  The rate it reaches on a given placement of the arrays is the
- * ceiling the step is compared with in the benchmark.
+ * a persistent grid).  The benchmark reads the step against it; the ring walk, whose workgroups keep pace with one
+ * another, is ahead of kind 2.
  *
  *   kind 0  read X and G, write nothing          (4 + 2 or 4 + 4 bytes per element)
  *   kind 1  write X_out[i, j] = a, read nothing   (4 bytes per element)

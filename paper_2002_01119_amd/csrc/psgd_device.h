@@ -329,9 +329,8 @@ __device__ __forceinline__ void floats_of(f32x4 x, float* f) {
 
 // Running sums of one lane's column group; the first value it is given becomes the pivot (kept as
 // the fp32 value it is).  Unless the group may be owned in part (RAGGED) the squares of its columns share one
-// accumulator: only their total is needed, and three fp64 accumulators less are six registers less in the ring walk
-// (142 against 148), of which a kernel on another stream may find the room; the time of a delay-by-one pair does not
-// tell the two apart (128 x 8 M: 4.96 and 4.99 ms, where runs differ by more).
+// accumulator: only their total is needed, and three fp64 accumulators less are five to seven registers less in the ring walk
+// (without the tiles beside it 103 against 110 with four rows on their way, 121 against 126 with six).
 template <bool RAGGED>
 struct ColStats {
     f32x4 s;

@@ -130,7 +130,7 @@ inline bool full_rows_paced(int n, int64_t ncg, int cus) {
 }
 inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
 
-// LDS of the tiled kernel (long rows, tables that are not one ring): the slot table (8 bytes per slot), TWO tile
+// LDS of the tiled kernel (long rows, tables of other than three slots): the slot table (8 bytes per slot), TWO tile
 // buffers of n rows x lpr lanes x 16 bytes (the next tile is staged while the current one is read), and, when the
 // consensus distance is gathered in the same pass, the merge slots of the column sums: a double and a float (the row
 // group's own pivot) per column and row group.  They go into the buffer that has just been read (one more barrier per tile)

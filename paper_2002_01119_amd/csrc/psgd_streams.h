@@ -450,11 +450,11 @@ __global__ __launch_bounds__(kThreads) void synth_grad_kernel(const float* __res
 
 // ---------------------------------------------------------------------------------------
 // Reference streams (measurement support, not a step of the method): the memory traffic of the step with the
-// mixing taken out, in the very form the step kernels give it -- a lane owns one 128-bit column group and
+// mixing taken out, as a walk that nothing keeps in step issues it -- a lane owns one 128-bit column group and
 // walks the n rows, the workgroup's wavefronts sweep the rows in lockstep batches, the column groups are split
 // evenly over a persistent grid.  KIND 0 only reads X and G, KIND 1 only writes X_out, KIND 2 is
 // X_out = X + a * G (the step's 4 + 2 + 4 or 4 + 4 + 4 bytes per element, no neighbours).  The rate these
-// reach is what the chip's memory system gives this access pattern; the step is measured against it.
+// reach is what the chip's memory system gives that access pattern; the paced walks are ahead of KIND 2 (psgd_pace.h).
 // ---------------------------------------------------------------------------------------
 enum { kRefRead = 0, kRefWrite = 1, kRefAxpy = 2 };
 
