@@ -201,21 +201,37 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     const int tid = threadIdx.x;
     const Lds l = carve(lds_raw, n);
     if (tid == 0) pace = Pace{0, lead};
-    const int kind = stage_table(nbr, w, n, l, blockDim.x);      // contains barriers
+    // Uniform, but the compiler is told so only for bf16 gradients with the distance: it lays the walk out otherwise then (us, told / not:
+    // 24 x 3 M 126.6 / 129.4, 16 x 4 100 003 117.8 / 119.6, 28 x 1.5 M 77.6 / 79.8; without the distance 24 x 3 M 126.1 / 121.8, fp32 128 x 8 M
+    // with the next gradients 3476 / 3415).
+    const int staged = stage_table(nbr, w, n, l, blockDim.x);    // contains barriers
+    const int kind = CD && sizeof(GT) == 2 ? __builtin_amdgcn_readfirstlane(staged) : staged;
     const int64_t ncg = (d + kVec - 1) / kVec;
     const int64_t my_sweeps = sweeps_of(sweeps, ncg);            // uniform
     if (PROD && kind != kTableRing && tid < lanes) produce_rows<RAGGED>(X, n, d, ld.x, sweeps, my_sweeps, prod);
+    if (kind == kTableRing) {
+        if (tid >= lanes + 64) return;                           // whole wavefronts
+        double total = 0.0;
+        if (my_sweeps > 0) {
+            if (tid >= lanes) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
+            else total = ring_walk<GT, CD, RAGGED, D, PROD>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n, prod);
+        }
+        if (CD) {
+            const double bs = block_sum_any(total, lds_waves, lanes + 64);
+            if (tid == 0) partials[blockIdx.x] = bs;
+        }
+        return;
+    }
     if (kind == kTableBad) {
         if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
         if (CD && tid == 0) partials[blockIdx.x] = __builtin_nan("");
         return;
     }
-    if (kind == kTableGeneral) {
-        if (tid >= tiles.nrg << tiles.logc) return;              // whole wavefronts
-        lds_barrier();                                           // the staged table has been read
-        // Every form starts from values of its own.  With common ones the compiler hoists what the forms share to the front of the
-        // choice and holds it through all of them: up to 27 vector registers spilled, in the tiles' loop too (us, so / now, fp32: 16 x 2 M
-        // with the distance 80.3 / 75.6, 40 x 700 k 73.3 / 70.8, 24 x 6 M without 319 / 314, 32 x 1.4 M 109.4 / 105.3).
+    if (tid >= tiles.nrg << tiles.logc) return;                  // whole wavefronts
+    lds_barrier();                                               // the staged table has been read
+    // Every form starts from values of its own.  With common ones the compiler hoists what the forms share to the front of the
+    // choice and holds it through all of them: up to 27 vector registers spilled, in the tiles' loop too (us, so / now, fp32: 16 x 2 M
+    // with the distance 80.3 / 75.6, 40 x 700 k 73.3 / 70.8, 24 x 6 M without 319 / 314, 32 x 1.4 M 109.4 / 105.3).
 #define PSGD_TILES(R, CACHED)                                                                                              \
     do {                                                                                                                   \
         int t = tid, rows = n, logc = tiles.logc, nrg = tiles.nrg;                                                         \
@@ -224,31 +240,19 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
                                                         tiles.tab_bytes, tiles.tile_bytes, partials,                       \
                                                         ShortLds{lds_raw, lds_waves, lds_bad});                            \
     } while (0)
-        constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
-        if (tiles.rows <= 2) {
-            if (tiles.cached == kBoth) PSGD_TILES(2, kBoth);
-            else PSGD_TILES(2, 0);
-        } else if (tiles.rows == 3) {
-            if (tiles.cached == kBoth) PSGD_TILES(3, kBoth);
-            else PSGD_TILES(3, 0);
-        } else {
-            if (tiles.cached == kBoth) PSGD_TILES(4, kBoth);
-            else if (sizeof(GT) == 2 && tiles.cached) PSGD_TILES(4, plan::kCachedLoads);
-            else PSGD_TILES(4, 0);
-        }
+    constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
+    if (tiles.rows <= 2) {
+        if (tiles.cached == kBoth) PSGD_TILES(2, kBoth);
+        else PSGD_TILES(2, 0);
+    } else if (tiles.rows == 3) {
+        if (tiles.cached == kBoth) PSGD_TILES(3, kBoth);
+        else PSGD_TILES(3, 0);
+    } else {
+        if (tiles.cached == kBoth) PSGD_TILES(4, kBoth);
+        else if (sizeof(GT) == 2 && tiles.cached) PSGD_TILES(4, plan::kCachedLoads);
+        else PSGD_TILES(4, 0);
+    }
 #undef PSGD_TILES
-        return;
-    }
-    if (tid >= lanes + 64) return;                               // whole wavefronts
-    double total = 0.0;
-    if (my_sweeps > 0) {
-        if (tid >= lanes) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
-        else total = ring_walk<GT, CD, RAGGED, D, PROD>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n, prod);
-    }
-    if (CD) {
-        const double bs = block_sum_any(total, lds_waves, lanes + 64);
-        if (tid == 0) partials[blockIdx.x] = bs;
-    }
 }
 
 }  // namespace
