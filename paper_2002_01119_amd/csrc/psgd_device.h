@@ -287,29 +287,90 @@ __device__ __forceinline__ int stage_table(const int32_t* __restrict__ nbr, cons
 // fp64 unless their exponents are more than 29 apart, and because the pivot is one of the
 // points the subtraction cancels at most a factor n).
 // ---------------------------------------------------------------------------------------
+// Sum over a wavefront, all of whose lanes take part; every lane gets it.  Lane to lane through the vector unit's own shifts (a row of 16
+// lanes, then row to row): through LDS (64-bit shuffles) the six steps were 0.3 us of every small launch with a distance.
+template <int CTRL, int ROWS> __device__ __forceinline__ double add_shifted(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xF, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xF, true);
+    return v + __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);   // lanes without a source add zero
+}
+__device__ __forceinline__ double row_sum(double v) {           // of 16 lanes, in the last of them
+    v = add_shifted<0x111, 0xF>(v);
+    v = add_shifted<0x112, 0xF>(v);
+    v = add_shifted<0x114, 0xF>(v);
+    return add_shifted<0x118, 0xF>(v);
+}
+__device__ __forceinline__ double from_lane(double v, int lane) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, lane), hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
+    v = row_sum(v);
+    v = add_shifted<0x142, 0xA>(v);                              // lane 15 to row 1, lane 47 to row 3
+    v = add_shifted<0x143, 0xC>(v);                              // lane 31 to rows 2 and 3
+    return from_lane(v, 63);
 }
 
-// Sum over the workgroup (T threads, or the first `lanes` of them: whole wavefronts); the per-wavefront sums are read at
-// once and added in a fixed order.
-template <int T = kThreads>
-__device__ __forceinline__ double block_sum(double v, double* lds_waves, int lanes = T) {
+// Sum over the workgroup's T lanes (whole wavefronts, at most 16 of them), valid in its first wavefront; the per-wavefront sums are
+// added in a fixed order.
+__device__ __forceinline__ double block_sum(double v, double* lds_waves, int T) {
     v = wave_sum(v);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) lds_waves[wave] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int i = 0; i < T / 64; i += 2)
-            r += (64 * i < lanes ? lds_waves[i] : 0.0) + (64 * (i + 1) < lanes ? lds_waves[i + 1] : 0.0);
-    }
-    return r;  // valid in thread 0
+    const int tid = threadIdx.x;
+    if ((tid & 63) == 0) lds_waves[tid >> 6] = v;
+    lds_barrier();
+    return tid < 64 ? from_lane(row_sum(tid < T / 64 ? lds_waves[tid] : 0.0), 15) : 0.0;
 }
 
+// ---------------------------------------------------------------------------------------
+// The distance's last sum, over the workgroups, by the workgroup that is done last.  Every workgroup writes its partial sum past the caches and then draws a ticket: from the launch's counter, or where
+// many workgroups would queue at it (16 ns each) from one of kTicketLeaves first, whose last one goes on to it.  The last of
+// all reads the partial sums, adds them in a fixed order whichever workgroup it is, and puts the counters back to zero.  Nobody waits.
+// Against the second kernel (us of a launch of 256 lanes a workgroup and little work): 64 workgroups 4.3 / 4.3, 157 4.1 / 4.2, 256 of 8 us 9.3 / 8.8, 512
+// 6.8 / 6.6: as long on the device, but a launch less, which is 2.6 us of host time on calls that are bound by it.
+// ---------------------------------------------------------------------------------------
+constexpr int kTicketLeaves = 16;
+__device__ unsigned g_tickets[plan::kTicketSlots][kTicketLeaves + 1][32];   // a counter in each 128-byte line
+struct Gather {
+    double* partials;
+    double* out;
+    int slot;
+};
+__device__ __forceinline__ void last_sum(const Gather& g, double mine) {       // `mine`: of the workgroup, in its first wavefront
+    const int tid = threadIdx.x;
+    if (tid >= 64) return;
+    const unsigned count = gridDim.x, leaves = count <= 64 ? 0u : (unsigned)kTicketLeaves;
+    unsigned (*tickets)[32] = g_tickets[g.slot];
+    auto draw = [&](unsigned* at, unsigned of) {                  // whether this is the last of `of` to come
+        if (__hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != of - 1) return false;
+        __hip_atomic_store(at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    };
+    int last = 0;
+    if (tid == 0) {
+        __hip_atomic_store(g.partials + blockIdx.x, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // written before the ticket is drawn
+        const unsigned leaf = blockIdx.x % kTicketLeaves;
+        last = (leaves == 0 || draw(tickets[1 + leaf], (count - leaf + kTicketLeaves - 1) / kTicketLeaves)) &&
+               draw(tickets[0], leaves ? leaves : count);
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    asm volatile("" ::: "memory");
+    double sum = 0.0;
+    for (unsigned from = 0; from < count; from += 512) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const unsigned at = from + 64 * k + tid;
+            v[k] = at < count ? __hip_atomic_load(g.partials + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += v[k];
+    }
+    sum = wave_sum(sum);
+    if (tid == 0) *g.out = sum;
+}
 __device__ __forceinline__ void acc_diff(double* a, double* b, f32x4 x, const double* s) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -434,17 +495,6 @@ __device__ __forceinline__ double row_group_distance(double* sums, float* pivots
     }
     lds_barrier();
     return total + row_group_merge<false>(sums, pivots, logc, nrg, n, T, inv_n, first, d);
-}
-
-// block_sum for a workgroup of T lanes known at run time (whole wavefronts).
-__device__ __forceinline__ double block_sum_any(double v, double* lds_waves, int T) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) lds_waves[threadIdx.x >> 6] = v;
-    lds_barrier();
-    double r = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < T / 64; ++i) r += lds_waves[i];
-    return r;  // valid in thread 0
 }
 
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the

@@ -273,28 +273,27 @@ inline bool rows_start_on(int bytes, const float* X, const float* X_out, const P
 }
 inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) { return rows_start_on(128, X, X_out, ld); }
 
-// Short rows: one launch of the short-row kernel.  Returns the number of partial sums (0 without the distance) or a
-// negative status.
+// Short rows: one launch of the short-row kernel.
 template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
 int launch_short_t(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
-                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather) {
     const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>);
     if (int rc = allow_lds(fn, p.lds)) return rc;
     const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? plan::kShortSlots : INT32_MAX);
     hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X,
-                       X_out, G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, partials);
-    return CD ? grid : 0;
+                       X_out, G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, gather);
+    return PSGD_OK;
 }
 
 template <typename GT, bool CD, int DEG>
 int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
-                 const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, double* partials) {
+                 const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather) {
     static_assert(plan::kShortSlots <= PSGD_STATIC_SLOTS && plan::kShortSlots <= kMaxGrid, "one partial per workgroup");
     const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
 #define PSGD_SHORT(DEG, R, ONE, CACHED, FEW)                                                                              \
-    return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials)
+    return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather)
     // Only what the plan asks for is built: four rows and one tile are three or four learners on wide tiles, one row and
     // several tiles a single learner; without a variant the accesses keep their hints.
 #define PSGD_SHORT_ONE(R)                                                                                                 \
@@ -331,13 +330,16 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
     return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane", p.rows);
 }
 
-// Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.  Returns the number of workgroups (partial
-// sums with the distance) or a negative status.
+// Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.
 std::atomic<unsigned> g_paced_launches{0};   // each takes the next of the pace words
+std::atomic<unsigned> g_gathers{0};          // each takes the next tickets
+Gather make_gather(double* partials, double* out) {
+    return Gather{partials, out, out ? (int)(g_gathers.fetch_add(1, std::memory_order_relaxed) % plan::kTicketSlots) : 0};
+}
 int next_pace_slot() { return (int)(g_paced_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots); }
 template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp, int cached, hipStream_t s, const float* X, float* X_out,
-                  const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials,
+                  const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather,
                   const Produce& prod) {
     size_t lds = tp.lds > plan::kRingLds ? tp.lds : plan::kRingLds;
     if (lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
@@ -347,12 +349,12 @@ int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp
     hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D, PROD>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
                        Sweeps{sp.count, sp.chunk}, lanes,
                        next_pace_slot(), plan::pace_lead(D, PROD),
-                       Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, prod, partials);
-    return grid;
+                       Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, prod, gather);
+    return PSGD_OK;
 }
 template <typename GT, bool CD>
 int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const float* X, float* X_out, const GT* G, const int32_t* nbr,
-                const float* w, int n, int64_t d, Pitch ld, float neg_lr, double* partials, const Produce* prod) {
+                const float* w, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather, const Produce* prod) {
     const int64_t ncg = (d + kVec - 1) / kVec;
     const int grid = di.cus < kMaxGrid ? di.cus : kMaxGrid;   // the sweeps split any row evenly
     if (CD && grid > plan::kShortSlots)                       // one partial per workgroup must fit the smallest buffer
@@ -362,7 +364,7 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
     const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
 #define PSGD_RING(RAGGED, D, PROD)                                                                                         \
-    launch_ring_t<GT, CD, RAGGED, D, PROD>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials,      \
+    launch_ring_t<GT, CD, RAGGED, D, PROD>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather,        \
                                            prod ? *prod : Produce{})
     const int depth = plan::ring_depth(sp, n);
     // With one or two rows on their way the ragged form costs nothing (64 x 25.6 M 3137 / 3129 us); with more, a lane's own work shows
@@ -449,14 +451,14 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         }
     }
     if (d == 0) {
-        hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, 0, cd_out);
+        hipLaunchKernelGGL(no_distance_kernel, dim3(1), dim3(1), 0, s, cd_out);
         const hipError_t e0 = hipGetLastError();
-        if (e0 != hipSuccess) return hip_fail(e0, "consensus_final_kernel");
+        if (e0 != hipSuccess) return hip_fail(e0, "no_distance_kernel");
         return no_alloc ? PSGD_OK : release_partials(di, s);
     }
     const float neg_lr = -lr;
     const Pitch ld{ldx, ldo, ldg};
-    int grid = 0;        // partial sums written so far (the fused distance sums this many)
+    const Gather gather = make_gather(partials, cd_out);
     const int64_t ncg = (d + kVec - 1) / kVec;
     // 3-slot tables: from plan::ring_rows on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
     // through tiles; below it the short-row kernel.
@@ -473,17 +475,18 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const bool ring = deg == 3 && plan::ring_rows(n, ncg, di->cus);
     const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
     if (ring) {
-        grid = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, prod)
-                       : launch_ring<GT, false>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, partials, prod);
-        if (grid < 0) return grid;
+        if (int rc = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, prod)
+                             : launch_ring<GT, false>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, prod))
+            return rc;
     } else if (!tiled) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
                                          : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
-        if (want_cd && deg == 3) grid = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else if (want_cd) grid = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else if (deg == 3) grid = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        else grid = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, partials);
-        if (grid < 0) return grid;
+        int rc;
+        if (want_cd && deg == 3) rc = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
+        else if (want_cd) rc = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
+        else if (deg == 3) rc = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
+        else rc = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
+        if (rc) return rc;
     } else {
         // 1024 lanes without the distance, 512 with it.
         const int threads = want_cd ? kTileThreads : kDeepThreads;
@@ -502,11 +505,11 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         if (int rc = allow_lds(fn, lds_bytes)) return rc;                                                                 \
         int per_cu = resident_per_cu(fn, lds_bytes, T);                                                                   \
         if (per_cu > 2 * kGridPerCu) per_cu = 2 * kGridPerCu;                                                             \
-        grid = deg_grid(ntiles, di->cus, per_cu);                                                                         \
+        int grid = deg_grid(ntiles, di->cus, per_cu);                                                                       \
         /* one partial per workgroup: a smaller persistent grid still covers every tile */                                \
         if (CD && grid > (int)plan::kShortSlots) grid = (int)plan::kShortSlots;                                           \
         hipLaunchKernelGGL((mix_deg_kernel<GT, CD, T, UQ>), dim3(grid), dim3(T), lds_bytes, s, X, X_out, G, nbr, w, deg,  \
-                           n, d, ld, neg_lr, tp.lpr, tp.comb_in_tile ? 1 : 0, partials);                                  \
+                           n, d, ld, neg_lr, tp.lpr, tp.comb_in_tile ? 1 : 0, gather);                                    \
     } while (0)
         if (want_cd && tp.lpr >= 64) PSGD_DEG_LAUNCH(true, true);
         else if (want_cd) PSGD_DEG_LAUNCH(true, false);
@@ -516,11 +519,6 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
-    if (want_cd) {
-        hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid, cd_out);
-        e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "consensus_final_kernel");
-    }
     if (prod && !ring)
         if (int rc = enqueue_producer(name, X, ldx, prod->noise, prod->ldn, prod->g, prod->ldg, n, d, prod->c, s)) return rc;
     return want_cd && !no_alloc ? release_partials(di, s) : PSGD_OK;
@@ -562,9 +560,9 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     if (want_cd)
         if (int rc = acquire_partials(di, s, &partials)) return rc;
     if (d == 0) {
-        hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, 0, cd_out);
+        hipLaunchKernelGGL(no_distance_kernel, dim3(1), dim3(1), 0, s, cd_out);
         const hipError_t e0 = hipGetLastError();
-        if (e0 != hipSuccess) return hip_fail(e0, "consensus_final_kernel");
+        if (e0 != hipSuccess) return hip_fail(e0, "no_distance_kernel");
         return release_partials(di, s);
     }
     const int64_t ncg = (d + kVec - 1) / kVec;
@@ -574,6 +572,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const plan::RowsPlan rp = plan::full_rows_plan(n, d, di->cus, want_cd);
     const bool walk = plan::full_rows_paced(n, ncg, di->cus);
     const bool split = !walk && !big && rp.threads != 0;
+    const Gather gather = make_gather(partials, cd_out);
     int grid = 0;
     if (walk) {
         grid = di->cus < kMaxGrid ? di->cus : kMaxGrid;
@@ -584,7 +583,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         if (int rc = allow_lds(reinterpret_cast<const void*>(mix_full_walk_kernel<GT, CD, D>), plan::kRingLds)) return rc;  \
         hipLaunchKernelGGL((mix_full_walk_kernel<GT, CD, D>), dim3(grid), dim3(lanes + 64), plan::kRingLds, s, X, X_out, G, \
                            n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk}, lanes, next_pace_slot(), plan::full_lead(D),       \
-                           partials);                                                                                      \
+                           gather);                                                                                        \
     } while (0)
         if (sp.chunk >= 576 && want_cd) PSGD_LAUNCH_WALK(true, 2);
         else if (sp.chunk >= 576) PSGD_LAUNCH_WALK(false, 2);
@@ -596,7 +595,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         const size_t lds = (size_t)rp.threads * (want_cd ? 48 : 32) + (16 << rp.logc);
 #define PSGD_LAUNCH_ROWS(CD, FEW)                                                                                          \
     hipLaunchKernelGGL((mix_full_rows_kernel<GT, CD, FEW>), dim3(grid), dim3(rp.threads), lds, s, X, X_out, G, n, d, ld,    \
-                       neg_lr, rp.logc, rp.nrg, partials)
+                       neg_lr, rp.logc, rp.nrg, gather)
         if (d < kVec && want_cd) PSGD_LAUNCH_ROWS(true, true);
         else if (d < kVec) PSGD_LAUNCH_ROWS(false, true);
         else if (want_cd) PSGD_LAUNCH_ROWS(true, false);
@@ -609,10 +608,10 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         const Sweeps sw = make_sweeps(ncg, grid, T, n > 8);                                                                \
         if (d % kVec)                                                                                                      \
             hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, true>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, X_out, G,  \
-                               n, d, ld, neg_lr, sw, partials);                                                            \
+                               n, d, ld, neg_lr, sw, gather);                                                              \
         else                                                                                                               \
             hipLaunchKernelGGL((mix_full_kernel<GT, CD, T, false>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, X_out, G, \
-                               n, d, ld, neg_lr, sw, partials);                                                            \
+                               n, d, ld, neg_lr, sw, gather);                                                              \
     } while (0)
         if (big && want_cd) PSGD_LAUNCH_FULL(true, kRingThreads);
         else if (big) PSGD_LAUNCH_FULL(false, kRingThreads);
@@ -620,15 +619,9 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         else PSGD_LAUNCH_FULL(false, kThreads);
     }
 #undef PSGD_LAUNCH_FULL
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
-    if (want_cd) {
-        hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid, cd_out);
-        e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "consensus_final_kernel");
-        return release_partials(di, s);
-    }
-    return PSGD_OK;
+    return want_cd ? release_partials(di, s) : PSGD_OK;
 }
 
 int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out_dev, hipStream_t s) {
@@ -636,44 +629,42 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
     if (int rc = device_info(&di)) return rc;
     double* partials = nullptr;
     if (int rc = acquire_partials(di, s, &partials)) return rc;
-    int grid = 0;
+    const Gather gather = make_gather(partials, out_dev);
     if (d > 0) {
         const int64_t ncg = (d + kVec - 1) / kVec;
         if (long_rows(*di, ncg)) {
-            grid = persistent_grid(*di, ncg, 1, kRingThreads);
+            const int grid = persistent_grid(*di, ncg, 1, kRingThreads);
             const Sweeps sw = make_sweeps(ncg, grid, kRingThreads);
             if (d % kVec)
                 hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads, true>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d,
-                                   ldx, sw, partials);
+                                   ldx, sw, gather);
             else
                 hipLaunchKernelGGL((consensus_sweep_kernel<kRingThreads, false>), dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d,
-                                   ldx, sw, partials);
+                                   ldx, sw, gather);
         } else {
             const plan::RowsPlan rp = plan::distance_rows_plan(n, d, di->cus);
             if (rp.threads != 0) {
-                grid = (int)(rp.tiles < kMaxGrid ? rp.tiles : kMaxGrid);
+                const int grid = (int)(rp.tiles < kMaxGrid ? rp.tiles : kMaxGrid);
                 const size_t lds = (size_t)rp.threads * 48;
                 if (d < kVec)
                     hipLaunchKernelGGL(consensus_rows_kernel<true>, dim3(grid), dim3(rp.threads), lds, s, X, n, d, ldx, rp.logc,
-                                       rp.nrg, partials);
+                                       rp.nrg, gather);
                 else
                     hipLaunchKernelGGL(consensus_rows_kernel<false>, dim3(grid), dim3(rp.threads), lds, s, X, n, d, ldx, rp.logc,
-                                       rp.nrg, partials);
+                                       rp.nrg, gather);
             } else {
-                grid = persistent_grid(*di, ncg, 8);  // light kernel: 32 waves per CU
+                const int grid = persistent_grid(*di, ncg, 8);  // light kernel: 32 waves per CU
                 if (d % kVec)
-                    hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+                    hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, gather);
                 else
-                    hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, partials);
+                    hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, gather);
             }
         }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "consensus_partial_kernel");
+    } else {
+        hipLaunchKernelGGL(no_distance_kernel, dim3(1), dim3(1), 0, s, out_dev);
     }
-    // d = 0: nothing to reduce, the final kernel over zero partials writes 0
-    hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid, out_dev);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "consensus_final_kernel");
+    if (e != hipSuccess) return hip_fail(e, "consensus_partial_kernel");
     return release_partials(di, s);
 }
 

@@ -181,7 +181,7 @@ __device__ __forceinline__ void produce_rows(const float* X, int n, int64_t d, i
 // other table goes through tiles (short_tiles; Tiles: how), an invalid one raises the flag and nothing is written.  A
 // kernel of its own behind this one for the other tables, which for a ring classified the table once more and ended, took 4.5 to 7 us
 // of every launch.
-// CD = also reduce the consensus distance of the outputs into partials[blockIdx.x].
+// CD = also reduce the consensus distance of the outputs into *gather.out.
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
 // same number of sweeps; the wavefronts that neither a sweep nor the tiles need are not launched.
 // RAGGED: 4 may not divide d.  D: rows on their way per lane.  PROD: the next gradients too, whatever the table.
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
                                                                          const int32_t* __restrict__ nbr,
                                                                          const float* __restrict__ w, int n, int64_t d, Pitch ld,
                                                                          float neg_lr, Sweeps sweeps, int lanes, int slot, int lead,
-                                                                         Tiles tiles, Produce prod, double* __restrict__ partials) {
+                                                                         Tiles tiles, Produce prod, Gather gather) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[(plan::kRingLanes + 64) / 64];
     __shared__ int lds_bad[(plan::kRingLanes + 64) / 64];
@@ -216,15 +216,12 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
             if (tid >= lanes) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
             else total = ring_walk<GT, CD, RAGGED, D, PROD>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n, prod);
         }
-        if (CD) {
-            const double bs = block_sum_any(total, lds_waves, lanes + 64);
-            if (tid == 0) partials[blockIdx.x] = bs;
-        }
+        if (CD) last_sum(gather, block_sum(total, lds_waves, lanes + 64));
         return;
     }
     if (kind == kTableBad) {
         if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
-        if (CD && tid == 0) partials[blockIdx.x] = __builtin_nan("");
+        if (CD) last_sum(gather, __builtin_nan(""));
         return;
     }
     if (tid >= tiles.nrg << tiles.logc) return;                  // whole wavefronts
@@ -237,7 +234,7 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
         int t = tid, rows = n, logc = tiles.logc, nrg = tiles.nrg;                                                         \
         asm volatile("; tiles of %4 rows per lane, accesses %5" : "+v"(t), "+s"(rows), "+s"(logc), "+s"(nrg) : "n"(R), "n"(CACHED)); \
         short_tiles<GT, CD, 3, R, false, CACHED, false>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
-                                                        tiles.tab_bytes, tiles.tile_bytes, partials,                       \
+                                                        tiles.tab_bytes, tiles.tile_bytes, gather,                         \
                                                         ShortLds{lds_raw, lds_waves, lds_bad});                            \
     } while (0)
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;

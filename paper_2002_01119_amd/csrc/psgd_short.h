@@ -45,7 +45,7 @@ struct ShortLds {
 template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
 __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout, const GT* __restrict__ G,
                                             const int32_t* __restrict__ nbr, const float* __restrict__ w, int deg_any, int n, int64_t d, Pitch ld, float neg_lr,
-                                            int logc, int nrg, int tab_bytes, int tile_bytes, double* __restrict__ partials,
+                                            int logc, int nrg, int tab_bytes, int tile_bytes, const Gather& gather,
                                             const ShortLds& lds) {
     typedef typename RawG<GT>::T GR;
     char* lds_raw = lds.dynamic;
@@ -110,7 +110,7 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
         for (int i = 0; i < T / 64; ++i) any |= lds_bad[i];
         if (any) {                                              // nothing is written
             if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
-            if (CD && tid == 0) partials[blockIdx.x] = __builtin_nan("");
+            if (CD) last_sum(gather, __builtin_nan(""));
             return;
         }
     }
@@ -207,22 +207,19 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
         cg = next;
     }
     if (t < ntiles) one_tile(std::false_type{}, cg);
-    if (CD) {
-        const double bs = block_sum_any(total, lds_waves, T);
-        if (tid == 0) partials[blockIdx.x] = bs;
-    }
+    if (CD) last_sum(gather, block_sum(total, lds_waves, T));
 }
 
 template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
 __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
     const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
     int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
-    double* __restrict__ partials) {
+    Gather gather) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
     __shared__ int lds_bad[plan::kShortThreads / 64];
     short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW>(threadIdx.x, X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes,
-                                                  tile_bytes, partials, ShortLds{lds_raw, lds_waves, lds_bad});
+                                                  tile_bytes, gather, ShortLds{lds_raw, lds_waves, lds_bad});
 }
 
 }  // namespace

@@ -31,7 +31,7 @@ __device__ __forceinline__ f32x4 mean_of(const double* s, double inv_n) {
 template <typename GT, bool CD, int T, bool RAGGED>
 __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout, const GT* __restrict__ G, int n,
                                                      int64_t d, Pitch ld, float neg_lr, Sweeps sweeps,
-                                                     double* __restrict__ partials) {
+                                                     Gather gather) {
     typedef f32x4 V;
     __shared__ double lds_waves[T / 64];
     const int64_t ncg = (d + kVec - 1) / kVec;
@@ -81,10 +81,7 @@ __global__ __launch_bounds__(T) void mix_full_kernel(const float* X, float* Xout
         }
         if (CD) total += stats.result(inv_n, c);
     }
-    if (CD) {
-        const double bs = block_sum<T>(total, lds_waves, blockDim.x);
-        if (threadIdx.x == 0) partials[blockIdx.x] = bs;
-    }
+    if (CD) last_sum(gather, block_sum(total, lds_waves, blockDim.x));
 }
 
 // The same on long rows, paced as the ring walk is (psgd_pace.h): a sweep is n items that add an X row and n items that read a
@@ -183,7 +180,7 @@ template <typename GT, bool CD, int D>
 __global__ __launch_bounds__(plan::kRingThreadsMost) void mix_full_walk_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                                                int n, int64_t d, Pitch ld, float neg_lr,
                                                                                Sweeps sweeps, int lanes, int slot, int lead,
-                                                                               double* __restrict__ partials) {
+                                                                               Gather gather) {
     __shared__ double lds_waves[plan::kRingThreadsMost / 64];
     __shared__ Pace pace;
     const int tid = threadIdx.x;
@@ -196,10 +193,7 @@ __global__ __launch_bounds__(plan::kRingThreadsMost) void mix_full_walk_kernel(c
         if (tid >= lanes) keep_pace(&pace, slot, lead, (int)my_sweeps * items, items);
         else total = full_walk<GT, CD, D>(X, Xout, G, n, d, ld, neg_lr, sweeps, my_sweeps, &pace);
     }
-    if (CD) {
-        const double bs = block_sum_any(total, lds_waves, lanes + 64);
-        if (tid == 0) partials[blockIdx.x] = bs;
-    }
+    if (CD) last_sum(gather, block_sum(total, lds_waves, lanes + 64));
 }
 
 // The same where the columns alone do not fill the chip: a tile is all n rows x C column groups on nrg row groups of C
@@ -211,7 +205,7 @@ template <typename GT, bool CD, bool FEW>
 __global__ __launch_bounds__(plan::kShortThreads, 4) void mix_full_rows_kernel(const float* X, float* Xout,
                                                                                const GT* __restrict__ G, int n, int64_t d,
                                                                                Pitch ld, float neg_lr, int logc, int nrg,
-                                                                               double* __restrict__ partials) {
+                                                                               Gather gather) {
     typedef typename RawG<GT>::T GR;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
@@ -287,17 +281,14 @@ __global__ __launch_bounds__(plan::kShortThreads, 4) void mix_full_rows_kernel(c
         if (CD) total += row_group_distance(sums, pivots, logc, nrg, n, T, rg, lane, inv_n, a, sq, pv, c, t * C, d);
         lds_barrier();                                           // the merge slots are free again
     }
-    if (CD) {
-        const double bs = block_sum_any(total, lds_waves, T);
-        if (tid == 0) partials[blockIdx.x] = bs;
-    }
+    if (CD) last_sum(gather, block_sum(total, lds_waves, T));
 }
 
 // Consensus-distance kernels (the per-column arithmetic is defined above the ring walk).
 template <bool RAGGED>
 __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float* __restrict__ X, int n,
                                                                      int64_t d, int64_t ldx,
-                                                                     double* __restrict__ partials) {
+                                                                     Gather gather) {
     typedef f32x4 V;
     __shared__ double lds4[4];
     const int64_t ncg = (d + kVec - 1) / kVec;
@@ -332,15 +323,14 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float
         for (int k = 0; k < kVec; ++k)
             if (!RAGGED || k >= c.lo) total += b[k] - a[k] * a[k] * inv_n;
     }
-    const double bs = block_sum(total, lds4);
-    if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+    last_sum(gather, block_sum(total, lds4, kThreads));
 }
 
 // The same where the columns alone do not fill the chip: rows spread over row groups of lanes as in the short-row kernel.
 template <bool FEW>
 __global__ __launch_bounds__(plan::kShortThreads, 4) void consensus_rows_kernel(const float* __restrict__ X, int n, int64_t d,
                                                                                 int64_t ldx, int logc, int nrg,
-                                                                                double* __restrict__ partials) {
+                                                                                Gather gather) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
     const int T = nrg << logc, C = 1 << logc, tid = threadIdx.x, lane = tid & (C - 1), rg = tid >> logc;
@@ -369,8 +359,7 @@ __global__ __launch_bounds__(plan::kShortThreads, 4) void consensus_rows_kernel(
         total += row_group_distance(sums, pivots, logc, nrg, n, T, rg, lane, inv_n, a, sq, pv, c, t * C, d);
         lds_barrier();                                           // the merge slots are free again
     }
-    const double bs = block_sum_any(total, lds_waves, T);
-    if (tid == 0) partials[blockIdx.x] = bs;
+    last_sum(gather, block_sum(total, lds_waves, T));
 }
 
 // The same distance for long rows, in the form of the step kernels: one large workgroup per compute unit whose
@@ -378,7 +367,7 @@ __global__ __launch_bounds__(plan::kShortThreads, 4) void consensus_rows_kernel(
 // persistent grid.  A lane owns one column group per sweep.
 template <int T, bool RAGGED>
 __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restrict__ X, int n, int64_t d, int64_t ldx,
-                                                            Sweeps sweeps, double* __restrict__ partials) {
+                                                            Sweeps sweeps, Gather gather) {
     typedef f32x4 V;
     __shared__ double lds_waves[T / 64];
     const int64_t ncg = (d + kVec - 1) / kVec;
@@ -416,21 +405,11 @@ __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restr
         for (int k = 0; k < kVec; ++k)
             if (RAGGED ? k >= c.lo && k < c.hi : c.lo == 0) total += b[k] - a[k] * a[k] * inv_n;
     }
-    const double bs = block_sum<T>(total, lds_waves, blockDim.x);
-    if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+    last_sum(gather, block_sum(total, lds_waves, blockDim.x));
 }
 
-// Fixed-order sum of the per-workgroup partials: lane t adds entries t, t+256, ... and the
-// 256 lane sums go through the same shuffle/LDS tree, so the result does not depend on
-// scheduling.
-__global__ __launch_bounds__(kThreads) void consensus_final_kernel(const double* __restrict__ partials, int count,
-                                                                   double* __restrict__ out) {
-    __shared__ double lds4[4];
-    double v = 0.0;
-    for (int i = threadIdx.x; i < count; i += kThreads) v += partials[i];
-    const double bs = block_sum(v, lds4);
-    if (threadIdx.x == 0) out[0] = bs;
-}
+// The distance of rows without columns.
+__global__ void no_distance_kernel(double* out) { *out = 0.0; }
 
 // The stand-in gradient producer: row blockIdx.y, a lane per column group.  FEW: rows of fewer than four columns.
 template <bool FEW>

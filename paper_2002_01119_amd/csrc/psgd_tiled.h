@@ -418,7 +418,7 @@ template <typename GT, bool CD, int T, bool UQ>
 __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                     const int32_t* __restrict__ nbr, const float* __restrict__ w,
                                                     int deg, int n, int64_t d, Pitch ld, float neg_lr, int lpr,
-                                                    int comb_in_tile, double* __restrict__ partials) {
+                                                    int comb_in_tile, Gather gather) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[T / 64];
     const size_t tab_bytes = (((size_t)n * deg * sizeof(TileSlot)) + 15) & ~(size_t)15;
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout,
     }
     if (!__syncthreads_and(ok)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&g_status_word, 1);
-        if (CD && threadIdx.x == 0) partials[blockIdx.x] = __builtin_nan("");
+        if (CD) last_sum(gather, __builtin_nan(""));
         return;
     }
     const double inv_n = 1.0 / (double)n;
@@ -441,8 +441,7 @@ __global__ __launch_bounds__(T) void mix_deg_kernel(const float* X, float* Xout,
         total += tile_remainder<GT, CD, T>(X, Xout, G, nbr, w, reinterpret_cast<float*>(lds_raw + tab_bytes), n, deg, ld, d,
                                            neg_lr, inv_n);
     if (CD) {
-        const double bs = block_sum<T>(total, lds_waves);
-        if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+        last_sum(gather, block_sum(total, lds_waves, T));
     }
 }
 
