@@ -90,7 +90,7 @@ constexpr int kTicketSlots = 256;   // launches with a distance under way at a t
 // 212.9, 300 x 210 k 147.9 / 143.3, 256 x 220 001 bf16 143.8 / 141.1, 512 x 240 k bf16 226.0 / 207.8, 200 x 260 k bf16 94.8 / 92.1; from 240 to 260 fp32
 // alone would stay at four: 512 x 240 k 252.1 / 258.1, 256 x 260 k 138.5 / 142.6).  Lead: one row 1.25 / 1.5 / 1.75 / 2 rows 64 x 25.6 M
 // 3134 / 3136 / 3186 / 3289; four rows of lead or none for a depth of one: 3500 / 3800.
-inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 6; }
+inline int ring_depth(const SweepPlan& s, int n) { return s.chunk >= 576 || n < 4 ? 1 : s.chunk >= 400 || n < 16 ? 2 : s.chunk >= 260 ? 4 : 6; }
 constexpr int kRingThreadsMost = kRingLanes + 64;   // of the workgroup
 // With the producer of the next gradients in the walk five arrays are on their way, not three: fewer rows, less lead (pairs, us: one row
 // of lead 5, 6 and 7 quarters 128 x 8 M 3414 / 3494 / 3674; one row or two of depth 128 x 520 k 223 / 235, two or four 113 x 328 k 134 / 171,
@@ -118,6 +118,17 @@ inline int ring_threads(const SweepPlan& s, int threads) {
 inline bool ring_rows(int n, int64_t ncg, int cus) {
     const int64_t from = n < 12 ? 3600 : n < 16 ? 2500 : n < 24 ? 1600 : n < 32 ? 800 : n < 48 ? 560 : n < 96 ? 400 : n < 200 ? 307 : n < 256 ? 230 : 192;
     return n > 8 && ncg >= from * cus;
+}
+// The same for all calls of a 3-slot table.
+//   - Three to eight learners, whose rows the short-row kernel holds in one lane, or with the distance spreads over two: by the column groups
+//     of all learners together (us, short-row kernel / ring walk, fp32 with the distance 3 x 12 M 76.0 / 73.2, 4 x 8 M 69.0 / 66.3, 5 x 6 M 68.9 / 62.9,
+//     7 x 4 M 63.4 / 59.6, 8 x 3.1 M 57.1 / 53.7, 8 x 12 M 201 / 184, bf16 gradients 6 x 5 M 56.5 / 55.9, 7 x 32 M 424 / 361; 3 x 3 M 20.5 / 24.6, 8 x 1 M 17.8 / 22).
+//     Without the distance later, and not for the fewest: 8 x 24 M 412 / 362, bf16 338 / 307, 6 x 24 M 304 / 273; 7 x 7 M 97.3 / 95.9, where other tables'
+//     tiles lose more than rings gain; 5 x 12 M 117.1 / 116.8, 3 x 32 M 182 / 183.
+inline bool walk_rows(int n, int64_t ncg, int cus, bool cd) {
+    if (n > 8) return ring_rows(n, ncg, cus);
+    const int64_t all = n * ncg;
+    return cd ? n > 2 && all >= 24000 * (int64_t)cus : n > 5 && all >= 100000 * (int64_t)cus;
 }
 
 // Global averaging with the workgroups of a die in step, in column groups per compute unit, and how far ahead of the mean a workgroup
@@ -186,6 +197,7 @@ struct ShortPlan {
     int64_t tiles;
     size_t lds;
 };
+PSGD_HOST_DEVICE inline int short_table_bytes(int n, int deg) { return (n * deg * 8 + 15) & ~15; }
 inline ShortPlan short_shape(int n, int deg, int64_t ncg, bool cd, bool one, int logc, int rows) {
     ShortPlan p;
     p.one = one;
@@ -195,7 +207,7 @@ inline ShortPlan short_shape(int n, int deg, int64_t ncg, bool cd, bool one, int
     p.rows = (n + p.nrg - 1) / p.nrg;
     if (one) p.rows = (p.rows + 1) & ~1;
     p.threads = p.nrg * c;
-    p.tab_bytes = (n * deg * 8 + 15) & ~15;
+    p.tab_bytes = short_table_bytes(n, deg);
     p.tile_bytes = n * c * 16;
     p.tiles = (ncg + c - 1) >> logc;
     const int merge = cd && p.nrg > 1 ? p.threads * 48 : 0;
@@ -320,6 +332,12 @@ inline ShortPlan short_loop_plan(int n, int deg, int64_t ncg, bool cd) {
             best = p;
     }
     return best;
+}
+// The tiles of a table that is not one ring, on rows that the ring walk would take.  Up to eight learners: 512 lanes of four rows (us, by
+// 1024 lanes of two / so / short_plan's, which it was: 3 x 9 M 74.4 / 56.8 / 58.7, 4 x 6 M 56.5 / 52.1 / 54.2, 5 x 6 M 74.2 / 72.7 / 69.3, 7 x 6 M
+// 97.7 / 96.5 / 95.8, 8 x 24 M 413 / 391 / 408).
+inline ShortPlan ring_tiles(int n, int64_t ncg, bool cd) {
+    return n < 9 ? short_widest(n, 3, ncg, cd, false, 512, 4) : short_loop_plan(n, 3, ncg, cd);
 }
 // Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
 //   - few columns: two rows per lane, on as few lanes as leave a row segment of a 128-byte line.  A lane reads its rows'

@@ -343,13 +343,13 @@ int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp
                   const Produce& prod) {
     size_t lds = tp.lds > plan::kRingLds ? tp.lds : plan::kRingLds;
     if (lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
-    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D, PROD>), lds)) return rc;
     const int lanes = plan::ring_threads({1, sp.chunk}, plan::kRingLanes);
     const int threads = lanes + 64 > tp.threads ? lanes + 64 : tp.threads;
+    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D, PROD>), lds)) return rc;
     hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D, PROD>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
                        Sweeps{sp.count, sp.chunk}, lanes,
                        next_pace_slot(), plan::pace_lead(D, PROD),
-                       Tiles{tp.rows, cached, tp.logc, tp.nrg, tp.tab_bytes, tp.tile_bytes}, prod, gather);
+                       Tiles{tp.rows | cached << 4 | tp.logc << 8, tp.nrg}, prod, gather);
     return PSGD_OK;
 }
 template <typename GT, bool CD>
@@ -360,7 +360,7 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
     if (CD && grid > plan::kShortSlots)                       // one partial per workgroup must fit the smallest buffer
         return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, grid, (int)plan::kShortSlots);
     const plan::SweepPlan sp = plan::sweep_plan(ncg, grid, plan::kRingLanes);
-    const plan::ShortPlan tp = plan::short_loop_plan(n, 3, ncg, CD);
+    const plan::ShortPlan tp = plan::ring_tiles(n, ncg, CD);
     const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
 #define PSGD_RING(RAGGED, D, PROD)                                                                                         \
@@ -472,7 +472,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // with 13 slots 236 / 220).
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
     const bool wide = n > 8 && n <= 128 && (rows_on_lines(X, X_out, ld) || (n > 28 && n <= 32));
-    const bool ring = deg == 3 && plan::ring_rows(n, ncg, di->cus);
+    const bool ring = deg == 3 && plan::walk_rows(n, ncg, di->cus, want_cd);
     const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
     if (ring) {
         if (int rc = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, prod)

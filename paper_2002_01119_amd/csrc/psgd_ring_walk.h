@@ -186,7 +186,8 @@ __device__ __forceinline__ void produce_rows(const float* X, int n, int64_t d, i
 // same number of sweeps; the wavefronts that neither a sweep nor the tiles need are not launched.
 // RAGGED: 4 may not divide d.  D: rows on their way per lane.  PROD: the next gradients too, whatever the table.
 struct Tiles {
-    int rows, cached, logc, nrg, tab_bytes, tile_bytes;
+    int form;                                                     // rows | cached << 4 | logc << 8: few scalar registers
+    int nrg;
 };
 template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
@@ -198,13 +199,19 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     __shared__ double lds_waves[(plan::kRingLanes + 64) / 64];
     __shared__ int lds_bad[(plan::kRingLanes + 64) / 64];
     __shared__ Pace pace;
+    __shared__ int found;
     const int tid = threadIdx.x;
-    const Lds l = carve(lds_raw, n);
+    RingEnt* ring = reinterpret_cast<RingEnt*>(lds_raw);
     if (tid == 0) pace = Pace{0, lead};
     // Uniform, but the compiler is told so only for bf16 gradients with the distance: it lays the walk out otherwise then (us, told / not:
     // 24 x 3 M 126.6 / 129.4, 16 x 4 100 003 117.8 / 119.6, 28 x 1.5 M 77.6 / 79.8; without the distance 24 x 3 M 126.1 / 121.8, fp32 128 x 8 M
     // with the next gradients 3476 / 3415).
-    const int staged = stage_table(nbr, w, n, l, blockDim.x);    // contains barriers
+    if (tid < 64) {
+        const int k = n <= 64 ? stage_table<1>(nbr, w, n, lds_raw, tid) : stage_table<8>(nbr, w, n, lds_raw, tid);
+        if (tid == 0) found = k;
+    }
+    lds_barrier();
+    const int staged = found;
     const int kind = CD && sizeof(GT) == 2 ? __builtin_amdgcn_readfirstlane(staged) : staged;
     const int64_t ncg = (d + kVec - 1) / kVec;
     const int64_t my_sweeps = sweeps_of(sweeps, ncg);            // uniform
@@ -214,39 +221,40 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
         double total = 0.0;
         if (my_sweeps > 0) {
             if (tid >= lanes) keep_pace(&pace, slot, lead, (int)(my_sweeps * n), n);
-            else total = ring_walk<GT, CD, RAGGED, D, PROD>(X, Xout, G, l.ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n, prod);
+            else total = ring_walk<GT, CD, RAGGED, D, PROD>(X, Xout, G, ring, n, d, ld, neg_lr, sweeps, my_sweeps, &pace, 1.0 / (double)n, prod);
         }
         if (CD) last_sum(gather, block_sum(total, lds_waves, lanes + 64));
         return;
     }
+    const int tile_rows = tiles.form & 15, cached = tiles.form >> 4 & 15, logc_all = tiles.form >> 8;
     if (kind == kTableBad) {
         if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
         if (CD) last_sum(gather, __builtin_nan(""));
         return;
     }
-    if (tid >= tiles.nrg << tiles.logc) return;                  // whole wavefronts
+    if (tid >= tiles.nrg << logc_all) return;                     // whole wavefronts
     lds_barrier();                                               // the staged table has been read
     // Every form starts from values of its own.  With common ones the compiler hoists what the forms share to the front of the
     // choice and holds it through all of them: up to 27 vector registers spilled, in the tiles' loop too (us, so / now, fp32: 16 x 2 M
     // with the distance 80.3 / 75.6, 40 x 700 k 73.3 / 70.8, 24 x 6 M without 319 / 314, 32 x 1.4 M 109.4 / 105.3).
 #define PSGD_TILES(R, CACHED)                                                                                              \
     do {                                                                                                                   \
-        int t = tid, rows = n, logc = tiles.logc, nrg = tiles.nrg;                                                         \
+        int t = tid, rows = n, logc = logc_all, nrg = tiles.nrg;                                                         \
         asm volatile("; tiles of %4 rows per lane, accesses %5" : "+v"(t), "+s"(rows), "+s"(logc), "+s"(nrg) : "n"(R), "n"(CACHED)); \
         short_tiles<GT, CD, 3, R, false, CACHED, false>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
-                                                        tiles.tab_bytes, tiles.tile_bytes, gather,                         \
+                                                        plan::short_table_bytes(rows, 3), rows << (logc + 4), gather,            \
                                                         ShortLds{lds_raw, lds_waves, lds_bad});                            \
     } while (0)
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
-    if (tiles.rows <= 2) {
-        if (tiles.cached == kBoth) PSGD_TILES(2, kBoth);
+    if (tile_rows <= 2) {
+        if (cached == kBoth) PSGD_TILES(2, kBoth);
         else PSGD_TILES(2, 0);
-    } else if (tiles.rows == 3) {
-        if (tiles.cached == kBoth) PSGD_TILES(3, kBoth);
+    } else if (tile_rows == 3) {
+        if (cached == kBoth) PSGD_TILES(3, kBoth);
         else PSGD_TILES(3, 0);
     } else {
-        if (tiles.cached == kBoth) PSGD_TILES(4, kBoth);
-        else if (sizeof(GT) == 2 && tiles.cached) PSGD_TILES(4, plan::kCachedLoads);
+        if (cached == kBoth) PSGD_TILES(4, kBoth);
+        else if (sizeof(GT) == 2 && cached) PSGD_TILES(4, plan::kCachedLoads);
         else PSGD_TILES(4, 0);
     }
 #undef PSGD_TILES
