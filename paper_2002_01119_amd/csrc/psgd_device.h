@@ -167,6 +167,15 @@ struct Pitch {
     int64_t x, o, g;
 };
 
+// The gradient producer of the delay-by-one schedule beside the step (Sec. 4, Eq. 14; the stand-in G_next = c X + noise): the step has
+// every row of X at hand when its output is made, so the pair moves 20 bytes per element instead of 24.
+struct Produce {
+    const float* noise;
+    float* g;
+    int64_t ldn, ldg;
+    float c;
+};
+
 // One ring position, packed so the walk fetches it with a single 128-bit LDS read.
 struct __attribute__((aligned(16))) RingEnt {
     int row;

@@ -125,9 +125,14 @@ inline bool ring_rows(int n, int64_t ncg, int cus) {
 //     7 x 4 M 63.4 / 59.6, 8 x 3.1 M 57.1 / 53.7, 8 x 12 M 201 / 184, bf16 gradients 6 x 5 M 56.5 / 55.9, 7 x 32 M 424 / 361; 3 x 3 M 20.5 / 24.6, 8 x 1 M 17.8 / 22).
 //     Without the distance later, and not for the fewest: 8 x 24 M 412 / 362, bf16 338 / 307, 6 x 24 M 304 / 273; 7 x 7 M 97.3 / 95.9, where other tables'
 //     tiles lose more than rings gain; 5 x 12 M 117.1 / 116.8, 3 x 32 M 182 / 183.
-inline bool walk_rows(int n, int64_t ncg, int cus, bool cd) {
-    if (n > 8) return ring_rows(n, ncg, cus);
+//   - With the next gradients of the delay-by-one schedule, five arrays: earlier (32 x 500 k 62.8 / 58.9, 64 x 250 k 67.6 / 61.1, 128 x 250 k 132.9 / 116.6,
+//     16 x 1 M 61.2 / 58.7, 12 x 2 M 90.7 / 83.3; 9 x 1 M 35.8 / 36.6, 24 x 500 k 46.1 / 45.9, 64 x 160 k 43.3 / 51.0); 5 x 6 M 119 / 103, 8 x 3 M 87.6 / 83.5, without the
+//     distance 4 x 6 M 78.9 / 81.1.
+inline bool walk_rows(int n, int64_t ncg, int cus, bool cd, bool produce) {
+    if (n > 8 && !produce) return ring_rows(n, ncg, cus);
+    if (n > 8) return ncg >= (n < 12 ? 1500 : n < 16 ? 1200 : n < 24 ? 900 : n < 48 ? 440 : n < 256 ? 220 : 192) * (int64_t)cus;
     const int64_t all = n * ncg;
+    if (produce) return n >= (cd ? 4 : 5) && all >= 24000 * (int64_t)cus;
     return cd ? n > 2 && all >= 24000 * (int64_t)cus : n > 5 && all >= 100000 * (int64_t)cus;
 }
 
@@ -335,9 +340,11 @@ inline ShortPlan short_loop_plan(int n, int deg, int64_t ncg, bool cd) {
 }
 // The tiles of a table that is not one ring, on rows that the ring walk would take.  Up to eight learners: 512 lanes of four rows (us, by
 // 1024 lanes of two / so / short_plan's, which it was: 3 x 9 M 74.4 / 56.8 / 58.7, 4 x 6 M 56.5 / 52.1 / 54.2, 5 x 6 M 74.2 / 72.7 / 69.3, 7 x 6 M
-// 97.7 / 96.5 / 95.8, 8 x 24 M 413 / 391 / 408).
-inline ShortPlan ring_tiles(int n, int64_t ncg, bool cd) {
-    return n < 9 ? short_widest(n, 3, ncg, cd, false, 512, 4) : short_loop_plan(n, 3, ncg, cd);
+// 97.7 / 96.5 / 95.8, 8 x 24 M 413 / 391 / 408).  With the next gradients at most three rows: more than that the registers do not hold.
+inline ShortPlan ring_tiles(int n, int64_t ncg, bool cd, bool produce) {
+    if (n < 9) return produce ? short_widest(n, 3, ncg, cd, false, kShortThreads, 2) : short_widest(n, 3, ncg, cd, false, 512, 4);
+    const ShortPlan p = short_loop_plan(n, 3, ncg, cd);
+    return produce && p.rows > 3 ? short_widest(n, 3, ncg, cd, false, kShortThreads, 3) : p;
 }
 // Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
 //   - few columns: two rows per lane, on as few lanes as leave a row segment of a 128-byte line.  A lane reads its rows'
@@ -386,6 +393,11 @@ inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, bool 
     }
     return short_loop_plan(n, deg, ncg, cd);
 }
+
+// Whether the short-row kernel also makes the next gradients of the delay-by-one schedule, or a producer behind it does: not on one round of
+// large workgroups whose row segments are 256 bytes or less, five arrays of which lie badly (us, 512 x 15 000 in one pass / two launches 41.1 / 39.4,
+// without the distance 39.6 / 35.5; 400 x 15 000 30.6 / 33.5, 29.1 / 28.8; 300 x 10 000, smaller workgroups, 15.0 / 21.8).
+inline bool short_produces(const ShortPlan& p) { return p.one ? p.threads <= 768 || p.logc > 4 : p.rows > 1; }
 
 }  // namespace plan
 }  // namespace psgd

@@ -274,20 +274,22 @@ inline bool rows_start_on(int bytes, const float* X, const float* X_out, const P
 inline bool rows_on_lines(const float* X, const float* X_out, const Pitch& ld) { return rows_start_on(128, X, X_out, ld); }
 
 // Short rows: one launch of the short-row kernel.
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool PROD = false>
 int launch_short_t(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
-                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather) {
-    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>);
+                   const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather,
+                   const Produce& prod = {}) {
+    const void* fn = reinterpret_cast<const void*>(mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW, PROD>);
     if (int rc = allow_lds(fn, p.lds)) return rc;
     const int grid = ONE ? (int)p.tiles : plan::short_grid(p, di.cus, CD ? plan::kShortSlots : INT32_MAX);
-    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW>), dim3(grid), dim3(p.threads), p.lds, s, X,
-                       X_out, G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, gather);
+    hipLaunchKernelGGL((mix_short_kernel<GT, CD, DEG, R, ONE, CACHED, FEW, PROD>), dim3(grid), dim3(p.threads), p.lds, s, X,
+                       X_out, G, nbr, w, deg, n, d, ld, neg_lr, p.logc, p.nrg, p.tab_bytes, p.tile_bytes, gather, prod);
     return PSGD_OK;
 }
 
 template <typename GT, bool CD, int DEG>
 int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, const float* X, float* X_out, const GT* G,
-                 const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather) {
+                 const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather,
+                 const Produce* prod) {
     static_assert(plan::kShortSlots <= PSGD_STATIC_SLOTS && plan::kShortSlots <= kMaxGrid, "one partial per workgroup");
     const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
@@ -308,6 +310,40 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
         if constexpr (R != 1 || CD)                                                                                       \
             if (cached == plan::kCachedLoads) PSGD_SHORT(DEG, R, false, plan::kCachedLoads, false);                       \
         PSGD_SHORT(DEG, R, false, 0, false)
+    if constexpr (sizeof(GT) == 4 && DEG == 3) {
+        if (prod) {
+#define PSGD_SHORT_PROD(R, ONE, CACHED)                                                                                   \
+    return launch_short_t<GT, CD, 3, R, ONE, CACHED, false, true>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather, *prod)
+#define PSGD_SHORT_PROD_ONE(R)                                                                                            \
+    case R:                                                                                                               \
+        if constexpr (R != 4)                                                                                             \
+            if (cached) PSGD_SHORT_PROD(R, true, kBoth);                                                                  \
+        PSGD_SHORT_PROD(R, true, 0)
+#define PSGD_SHORT_PROD_LOOP(R)                                                                                           \
+    case R:                                                                                                               \
+        if (cached == kBoth) PSGD_SHORT_PROD(R, false, kBoth);                                                            \
+        if (cached == plan::kCachedLoads) PSGD_SHORT_PROD(R, false, plan::kCachedLoads);                                  \
+        PSGD_SHORT_PROD(R, false, 0)
+            if (p.one) {
+                switch (p.rows) {
+                    PSGD_SHORT_PROD_ONE(2);
+                    PSGD_SHORT_PROD_ONE(4);
+                    PSGD_SHORT_PROD_ONE(6);
+                    PSGD_SHORT_PROD_ONE(8);
+                }
+            } else {
+                switch (p.rows) {
+                    PSGD_SHORT_PROD_LOOP(2);
+                    PSGD_SHORT_PROD_LOOP(3);
+                    PSGD_SHORT_PROD_LOOP(4);
+                }
+            }
+            return fail(PSGD_EINVAL, "no short-row kernel of %d rows per lane with the next gradients", p.rows);
+#undef PSGD_SHORT_PROD_LOOP
+#undef PSGD_SHORT_PROD_ONE
+#undef PSGD_SHORT_PROD
+        }
+    }
     if (d < kVec) PSGD_SHORT(0, 2, true, 0, true);
     if (p.one) {
         switch (p.rows) {
@@ -360,7 +396,7 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
     if (CD && grid > plan::kShortSlots)                       // one partial per workgroup must fit the smallest buffer
         return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, grid, (int)plan::kShortSlots);
     const plan::SweepPlan sp = plan::sweep_plan(ncg, grid, plan::kRingLanes);
-    const plan::ShortPlan tp = plan::ring_tiles(n, ncg, CD);
+    const plan::ShortPlan tp = plan::ring_tiles(n, ncg, CD, prod != nullptr);
     const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
 #define PSGD_RING(RAGGED, D, PROD)                                                                                         \
@@ -472,8 +508,9 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // with 13 slots 236 / 220).
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
     const bool wide = n > 8 && n <= 128 && (rows_on_lines(X, X_out, ld) || (n > 28 && n <= 32));
-    const bool ring = deg == 3 && plan::walk_rows(n, ncg, di->cus, want_cd);
+    const bool ring = deg == 3 && plan::walk_rows(n, ncg, di->cus, want_cd, prod != nullptr);
     const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
+    bool produced = ring;                                        // the next gradients, by the same kernel
     if (ring) {
         if (int rc = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, prod)
                              : launch_ring<GT, false>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, prod))
@@ -481,11 +518,13 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     } else if (!tiled) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
                                          : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
+        const Produce* beside = prod && deg == 3 && d >= kVec && plan::short_produces(sp) ? prod : nullptr;
+        produced = beside != nullptr;
         int rc;
-        if (want_cd && deg == 3) rc = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
-        else if (want_cd) rc = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
-        else if (deg == 3) rc = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
-        else rc = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather);
+        if (want_cd && deg == 3) rc = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather, beside);
+        else if (want_cd) rc = launch_short<GT, true, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather, beside);
+        else if (deg == 3) rc = launch_short<GT, false, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather, beside);
+        else rc = launch_short<GT, false, 0>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather, beside);
         if (rc) return rc;
     } else {
         // 1024 lanes without the distance, 512 with it.
@@ -519,7 +558,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
-    if (prod && !ring)
+    if (prod && !produced)
         if (int rc = enqueue_producer(name, X, ldx, prod->noise, prod->ldn, prod->g, prod->ldg, n, d, prod->c, s)) return rc;
     return want_cd && !no_alloc ? release_partials(di, s) : PSGD_OK;
 }

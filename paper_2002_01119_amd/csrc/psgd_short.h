@@ -34,19 +34,32 @@ namespace {
 // The distance (CD): every lane measures its outputs against its first one, in fp64, and the row groups' sums meet in
 // LDS, where they are brought to row group 0's pivot exactly (row_group_merge).
 // ---------------------------------------------------------------------------------------
+// The next gradients alone, where the table is invalid: the workgroup's tiles, row by row.
+__device__ __forceinline__ void produce_tiles(int tid, const float* X, int n, int64_t d, int64_t ldx, int logc, int nrg, const Produce& prod) {
+    const int C = 1 << logc, lane = tid & (C - 1);
+    const int64_t ntiles = (((d + 3) >> 2) + C - 1) >> logc;
+    for (int64_t t = plan::die_contiguous_slot(blockIdx.x, gridDim.x, kXcds); t < ntiles; t += gridDim.x) {
+        const ColGroup c = col_group(t * C + lane, d);
+        for (int r = tid >> logc; r < n; r += nrg)
+            st_cols(prod.g + (int64_t)r * prod.ldg + c.col,
+                    vfma(prod.c, ld_x(X + (int64_t)r * ldx + c.col), ld_x(prod.noise + (int64_t)r * prod.ldn + c.col)), c);
+    }
+}
+
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (two or up to eight rows per lane: nothing is
 // loaded ahead, so those registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
-// FEW: rows of fewer than four columns.  Run by nrg << logc lanes of the workgroup, lane `tid` of them, the others having ended.
+// FEW: rows of fewer than four columns.  PROD: also the next gradients of the delay-by-one schedule, of the rows as they were.
+// Run by nrg << logc lanes of the workgroup, lane `tid` of them, the others having ended.
 struct ShortLds {
     char* dynamic;                           // plan::ShortPlan::lds bytes
     double* waves;                           // one per wavefront
     int* bad;                                // the same
 };
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool PROD>
 __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout, const GT* __restrict__ G,
                                             const int32_t* __restrict__ nbr, const float* __restrict__ w, int deg_any, int n, int64_t d, Pitch ld, float neg_lr,
                                             int logc, int nrg, int tab_bytes, int tile_bytes, const Gather& gather,
-                                            const ShortLds& lds) {
+                                            const ShortLds& lds, const Produce& prod) {
     typedef typename RawG<GT>::T GR;
     char* lds_raw = lds.dynamic;
     double* lds_waves = lds.waves;
@@ -88,6 +101,21 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
     for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW, CL>(X + (int64_t)row_of(u) * ld.x + cg.col, d);
 #pragma unroll
     for (int u = 0; u < R; ++u) g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + cg.col, d);
+    // The noise of the next gradients travels with them where registers allow (few rows per lane: the launches whose latency shows).
+    // More rows take the registers of the first few in turn.
+    constexpr bool EARLY = PROD && R <= 4;
+    constexpr int NR = !PROD ? 1 : R <= 4 ? R : CD && R == 8 ? 2 : 4;
+    f32x4 noise[NR];
+    auto load_noise = [&](int u, const ColGroup& at) __attribute__((always_inline)) {
+        noise[u % NR] = ld_x<CL>(prod.noise + (int64_t)row_of(u) * prod.ldn + at.col);
+    };
+    auto own_row = [&](int u) __attribute__((always_inline)) {
+        return *reinterpret_cast<const f32x4*>(tile + ((row_of(u) << (logc + 4)) + lane16));
+    };
+    if (EARLY) {
+#pragma unroll
+        for (int u = 0; u < NR; ++u) load_noise(u, cg);
+    }
     int bad = 0;
 #pragma unroll
     for (int i = 0; i < TE; ++i) {
@@ -108,8 +136,9 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
     {
         int any = 0;
         for (int i = 0; i < T / 64; ++i) any |= lds_bad[i];
-        if (any) {                                              // nothing is written
+        if (any) {                                              // nothing of the step is written
             if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
+            if (PROD) produce_tiles(tid, X, n, d, ld.x, logc, nrg, prod);
             if (CD) last_sum(gather, __builtin_nan(""));
             return;
         }
@@ -128,13 +157,19 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
 #pragma unroll
             for (int u = 0; u < R; ++u) x[u] = ld_cols<FEW, CL>(X + (int64_t)row_of(u) * ld.x + next.col, d);
         }
+        if (PROD && !EARLY) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < NR; ++u) load_noise(u, cg);
+        }
         // SB rows' slot chains advance together (a table read, then a tile read that depends on it, per slot).
-        constexpr int SB = R < 4 ? R : 4;
+        constexpr int SB = PROD && !ONE ? 2 : R < 4 ? R : 4;           // two where registers go to the noise too
         double a[4] = {0.0, 0.0, 0.0, 0.0}, sq[4] = {0.0, 0.0, 0.0, 0.0};
         f32x4 pv;
 #pragma unroll
         for (int j = 0; j < R; j += SB) {
             __builtin_amdgcn_sched_barrier(0);
+            if (PROD) asm volatile("" : "+v"(rg));
             const TileSlot* tp[SB];
             f32x4 out[SB];
 #pragma unroll
@@ -164,13 +199,20 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
                 const int u = j + i;
                 if (u >= R) break;
                 const f32x4 o = vfma(neg_lr, widen_g(g[u]), out[i]);
+                if (PROD && !EARLY) asm volatile("" : "+v"(rg));
                 float* to = Xout + (int64_t)row_of(u) * ld.o + cg.col;
                 if (FULL) {
                     st_x<CS>(to, o);
+                    if (PROD) {
+                        st_x<CS>(prod.g + (int64_t)row_of(u) * prod.ldg + cg.col, vfma(prod.c, own_row(u), noise[u % NR]));
+                        load_noise(u, next);
+                    }
                     g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + next.col, d);
                 } else if (rg + u * nrg < n) {
                     st_cols<CS>(to, o, cg);
+                    if (PROD) st_cols<CS>(prod.g + (int64_t)row_of(u) * prod.ldg + cg.col, vfma(prod.c, own_row(u), noise[u % NR]), cg);
                 }
+                if (PROD && u + NR < R) load_noise(u + NR, cg);
                 if (CD && u == 0) pv = o;
                 if (CD && u > 0 && rg + u * nrg < n) {
 #pragma unroll
@@ -210,16 +252,16 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
     if (CD) last_sum(gather, block_sum(total, lds_waves, T));
 }
 
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool PROD>
 __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) void mix_short_kernel(
     const float* X, float* Xout, const GT* __restrict__ G, const int32_t* __restrict__ nbr, const float* __restrict__ w,
     int deg_any, int n, int64_t d, Pitch ld, float neg_lr, int logc, int nrg, int tab_bytes, int tile_bytes,
-    Gather gather) {
+    Gather gather, Produce prod) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
     __shared__ int lds_bad[plan::kShortThreads / 64];
-    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW>(threadIdx.x, X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes,
-                                                  tile_bytes, gather, ShortLds{lds_raw, lds_waves, lds_bad});
+    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW, PROD>(threadIdx.x, X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes,
+                                                  tile_bytes, gather, ShortLds{lds_raw, lds_waves, lds_bad}, prod);
 }
 
 }  // namespace

@@ -1,12 +1,15 @@
-"""The ring walk of three to eight learners, at the edges of where it is used and with tables that are not one ring.  Every element against
-the oracle."""
+"""The ring walk of three to eight learners, at the edges of where it is used and with tables that are not one ring, and the next gradients of
+the delay-by-one schedule from the short-row kernel in each of its forms.  Every element against the oracle, or against the two separate
+calls."""
 import pytest
 
+import test_gpu_d1d_one_pass
 import test_gpu_short_rows
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 psgd = test_gpu_short_rows.psgd
+mods = test_gpu_d1d_one_pass.mods
 
 
 # learners times column groups: 24 000 per compute unit with the distance, 100 000 without (256 compute units)
@@ -18,3 +21,19 @@ psgd = test_gpu_short_rows.psgd
     (8, 12_800_004, -3, "f32", None)])
 def test_ring_walk_of_few_learners(psgd, n, d, deg, gkind, extra):
     test_gpu_short_rows.test_short_rows_every_element(psgd, n, d, deg, gkind, extra)
+
+
+@pytest.mark.parametrize("n,d,deg,extra", [
+    # a tile per workgroup: two, four, six and eight rows per lane; four, five and seven columns
+    (2, 4, 3, 0), (3, 5, 3, 2), (7, 7, -3, 0), (16, 20_003, 3, 1), (4, 1_100_001, 3, 0), (5, 700_002, -3, 3), (6, 1_000_000, 3, 0),
+    (8, 600_003, 3, 1), (12, 250_001, 3, 0), (64, 100_002, -3, 1), (300, 10_001, 3, 0),
+    # large workgroups on narrow tiles, which leave it to the producer
+    (512, 15_003, 3, 0),
+    # looping: two, three and four rows per lane, whole tiles and a ragged last one, rows off the lines
+    (8, 2_900_000, 3, 0), (7, 3_400_003, -3, 1), (13, 900_004, 3, 0), (33, 300_001, 3, 2), (64, 160_000, 3, 0), (64, 160_001, -3, 1), (128, 120_003, 3, 0),
+    (300, 60_001, 3, 3), (512, 40_000, -3, 0),
+    # the ring walk from its line for this schedule on, rings and other tables
+    (4, 6_144_001, 3, 0), (5, 4_915_205, 3, 1), (8, 3_072_004, 3, 0), (8, 3_072_001, -3, 0), (9, 1_536_001, 3, 0), (12, 1_228_804, -3, 0),
+    (16, 921_601, 3, 2), (32, 450_563, 3, 0), (64, 225_284, -3, 0), (128, 225_281, 3, 1), (128, 225_285, -3, 0)])
+def test_next_gradients_beside_the_step(mods, n, d, deg, extra):
+    test_gpu_d1d_one_pass.test_one_pass_is_the_two_calls(mods, n, d, deg, extra)
