@@ -28,6 +28,16 @@ inline int persistent_grid(int cus, int64_t work_items, int per_cu, int threads)
     return (int)(g < 1 ? 1 : g);
 }
 
+// The same with as many workgroups on each compute unit, of fewer lanes, where more than half of the units would have one: with the last of
+// them short of a round, the others wait for the few that have one more, or idle.  Left alone where that is a few of many.  us, workgroups of 256
+// lanes / even: global averaging 512 x 140 k 192 / 155, 402 x 151 673 167 / 140, 100 x 150 k 43.3 / 37.4, 32 x 300 k 24.7 / 20.9, 73 x 202 100 36.7 / 34.3; distance
+// 128 x 300 k 32.4 / 26.5, 64 x 300 k 18.1 / 15.5, 64 x 550 k 29.0 / 25.7 (16 x 700 k, 684 workgroups, 23.7 / 24.1).
+inline int even_grid(int64_t work_items, int cus, int per_cu, int threads) {
+    const int g = persistent_grid(cus, work_items, per_cu, threads);
+    const int even = (g + cus - 1) / cus * cus;
+    return g > cus / 2 && even <= kMaxGrid && (g <= 2 * cus || even - g > cus / 3) ? even : g;
+}
+
 // Grid of the degree-K kernel: one workgroup per tile up to what is resident, within the same bound.
 inline int deg_grid(int64_t ntiles, int cus, int per_cu) {
     int64_t cap = (int64_t)cus * per_cu;

@@ -641,7 +641,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         else PSGD_LAUNCH_ROWS(false, false);
 #undef PSGD_LAUNCH_ROWS
     } else {
-        grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : persistent_grid(*di, ncg, kGridPerCu);
+        grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : plan::even_grid(ncg, di->cus, kGridPerCu, kThreads);
 #define PSGD_LAUNCH_FULL(CD, T)                                                                                            \
     do {                                                                                                                   \
         const Sweeps sw = make_sweeps(ncg, grid, T, n > 8);                                                                \
@@ -692,11 +692,14 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
                     hipLaunchKernelGGL(consensus_rows_kernel<false>, dim3(grid), dim3(rp.threads), lds, s, X, n, d, ldx, rp.logc,
                                        rp.nrg, gather);
             } else {
-                const int grid = persistent_grid(*di, ncg, 8);  // light kernel: 32 waves per CU
+                const int grid = plan::even_grid(ncg, di->cus, 8, kThreads);  // light kernel: 32 waves per CU
+                const Sweeps sw = make_sweeps(ncg, grid, kThreads);
                 if (d % kVec)
-                    hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, gather);
+                    hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d, ldx, (int)sw.chunk,
+                                       gather);
                 else
-                    hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(kThreads), 0, s, X, n, d, ldx, gather);
+                    hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d, ldx, (int)sw.chunk,
+                                       gather);
             }
         }
     } else {

@@ -287,15 +287,15 @@ __global__ __launch_bounds__(plan::kShortThreads, 4) void mix_full_rows_kernel(c
 // Consensus-distance kernels (the per-column arithmetic is defined above the ring walk).
 template <bool RAGGED>
 __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float* __restrict__ X, int n,
-                                                                     int64_t d, int64_t ldx,
+                                                                     int64_t d, int64_t ldx, int chunk,
                                                                      Gather gather) {
     typedef f32x4 V;
     __shared__ double lds4[4];
     const int64_t ncg = (d + kVec - 1) / kVec;
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    const int64_t stride = (int64_t)gridDim.x * chunk;
     const double inv_n = 1.0 / (double)n;
     double total = 0.0;
-    for (int64_t cg = (int64_t)blockIdx.x * kThreads + threadIdx.x; cg < ncg; cg += stride) {
+    for (int64_t cg = (int)threadIdx.x < chunk ? (int64_t)blockIdx.x * chunk + threadIdx.x : ncg; cg < ncg; cg += stride) {
         const ColGroup c = col_group_of<RAGGED>(cg, ncg, d);
         const float* xc = X + c.col;
         double s[kVec], a[kVec], b[kVec];
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float
         for (int k = 0; k < kVec; ++k)
             if (!RAGGED || k >= c.lo) total += b[k] - a[k] * a[k] * inv_n;
     }
-    last_sum(gather, block_sum(total, lds4, kThreads));
+    last_sum(gather, block_sum(total, lds4, blockDim.x));
 }
 
 // The same where the columns alone do not fill the chip: rows spread over row groups of lanes as in the short-row kernel.
