@@ -155,6 +155,14 @@ inline bool full_rows_paced(int n, int64_t ncg, int cus) {
     const int64_t from = n < 16 ? 2400 : n < 32 ? 800 : n < 48 ? 560 : 300;
     return n > 8 && ncg >= from * cus;
 }
+// Three to eight learners by the column groups of all of them (us, fp32 / bf16 gradients with the distance: 5 x 2.5 M 32.1 / 29.1, 35.1 / 28.1, 7 x 1.8 M
+// 34.4 / 29.1, 36.0 / 27.3, 8 x 30 M 529 / 474, 437 / 403, 3 x 30 M 195 / 182, 191 / 159; 3 x 3 M 22.1 / 22.7, 23.9 / 23.0).
+inline bool walk_full_rows(int n, int64_t ncg, int cus) {
+    return n > 8 ? full_rows_paced(n, ncg, cus) : n > 2 && n * ncg >= 12000 * (int64_t)cus;
+}
+// The distance of two or three learners on long rows: small workgroups by themselves, not swept in batches of eight rows that they do not
+// have (us, swept / alone: 2 x 30 M 57.4 / 47.3, 3 x 30 M 65.8 / 57.9, 2 x 8 M 19.4 / 17.1; 3 x 6.5 M 19.3 / 19.5, 4 x 8 M 24.3 / 24.4, 5 x 8 M 27.6 / 28.9).
+inline bool distance_alone(int n, int64_t ncg, int cus) { return n < 4 && ncg >= 7500 * (int64_t)cus; }
 inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
 
 // LDS of the tiled kernel (long rows, tables of other than three slots): the slot table (8 bytes per slot), TWO tile

@@ -609,7 +609,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const float neg_lr = -lr;
     const bool big = long_rows(*di, ncg, 2);
     const plan::RowsPlan rp = plan::full_rows_plan(n, d, di->cus, want_cd);
-    const bool walk = plan::full_rows_paced(n, ncg, di->cus);
+    const bool walk = plan::walk_full_rows(n, ncg, di->cus);
     const bool split = !walk && !big && rp.threads != 0;
     const Gather gather = make_gather(partials, cd_out);
     int grid = 0;
@@ -624,8 +624,8 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
                            n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk}, lanes, next_pace_slot(), plan::full_lead(D),       \
                            gather);                                                                                        \
     } while (0)
-        if (sp.chunk >= 576 && want_cd) PSGD_LAUNCH_WALK(true, 2);
-        else if (sp.chunk >= 576) PSGD_LAUNCH_WALK(false, 2);
+        if ((n < 6 || sp.chunk >= 576) && want_cd) PSGD_LAUNCH_WALK(true, 2);   // n > D
+        else if (n < 6 || sp.chunk >= 576) PSGD_LAUNCH_WALK(false, 2);
         else if (want_cd) PSGD_LAUNCH_WALK(true, 4);
         else PSGD_LAUNCH_WALK(false, 4);
 #undef PSGD_LAUNCH_WALK
@@ -671,7 +671,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
     const Gather gather = make_gather(partials, out_dev);
     if (d > 0) {
         const int64_t ncg = (d + kVec - 1) / kVec;
-        if (long_rows(*di, ncg)) {
+        if (long_rows(*di, ncg) && !plan::distance_alone(n, ncg, di->cus)) {
             const int grid = persistent_grid(*di, ncg, 1, kRingThreads);
             const Sweeps sw = make_sweeps(ncg, grid, kRingThreads);
             if (d % kVec)

@@ -1,5 +1,6 @@
-"""The ring walk of three to eight learners, at the edges of where it is used and with tables that are not one ring, and the next gradients of
-the delay-by-one schedule from the short-row kernel in each of its forms.  Every element against the oracle, or against the two separate
+"""The ring walk of three to eight learners, at the edges of where it is used and with tables that are not one ring, the next gradients of
+the delay-by-one schedule from the short-row kernel in each of its forms, global averaging of few learners in step, and workgroups spread
+evenly over the compute units.  Every element against the oracle, or against the two separate
 calls."""
 import pytest
 
@@ -37,3 +38,14 @@ def test_ring_walk_of_few_learners(psgd, n, d, deg, gkind, extra):
     (16, 921_601, 3, 2), (32, 450_563, 3, 0), (64, 225_284, -3, 0), (128, 225_281, 3, 1), (128, 225_285, -3, 0)])
 def test_next_gradients_beside_the_step(mods, n, d, deg, extra):
     test_gpu_d1d_one_pass.test_one_pass_is_the_two_calls(mods, n, d, deg, extra)
+
+
+# global averaging in step from 12 000 column groups of all learners per compute unit on; workgroups that are not a multiple of the compute
+# units (198, 293, 684, 977 of 256 lanes); the distance of two and three learners on either side of 7500 column groups per compute unit
+@pytest.mark.parametrize("n,d,gkind,extra", [
+    (3, 4_095_996, "f32", None), (3, 4_096_001, "bf16", (1, 2, 3)), (4, 3_072_003, "f32", None), (5, 2_457_602, "bf16", None),
+    (6, 2_048_004, "f32", (3, 1, 2)), (7, 1_755_431, "f32", None), (8, 1_536_001, "bf16", None), (8, 1_535_996, "f32", None),
+    (73, 202_100, "bf16", None), (33, 300_003, "f32", (1, 2, 3)), (16, 700_000, "f32", None), (9, 1_000_001, "bf16", None), (20, 524_289, "f32", None),
+    (2, 7_679_996, "f32", None), (2, 7_680_001, "f32", None), (3, 7_680_004, "f32", None), (3, 7_700_003, "f32", (1, 0, 2))])
+def test_global_average_and_distance(psgd, n, d, gkind, extra):
+    test_gpu_short_rows.test_global_average_and_distance_with_rows_spread_over_lanes(psgd, n, d, gkind, extra)
