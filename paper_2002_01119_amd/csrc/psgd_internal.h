@@ -200,6 +200,22 @@ inline TilePlan tile_plan(int n, int deg, int threads, bool cd, size_t cap, int 
     return p;
 }
 
+// Whether long rows (two column groups for every lane of 768 per compute unit) of a table of other than three slots take the tiled
+// kernel.  `room`: 2, every row of X and X_out starts on a 128-byte line; 1, on 16 bytes, and there are twice as many columns; 0, neither.
+// Its tiles are a power of two of column groups wide, and as deep as a power of two of row groups: learners that fill them, 13 to 16, 29 to 32,
+// 53 to 64 and 105 to 128, are as well off there or better, tables of many slots with the distance most (us, short-row / tiled: 64 x 2 M with 16
+// slots and the distance 296 / 270, 30 x 3.2 M with 20 and bf16 gradients 303 / 215); the others leave places empty (on lines, with the distance, tiled /
+// short-row: 9 x 6 M with 5 slots 156 / 119, with 32 264 / 190, 12 x 4 M 123 / 108, 20 x 4 M 204 / 178, 24 x 4 M 226 / 214, 33 x 3 M 276 / 225, 40 x 2 M 202 / 178, 48 x 2 M
+// 225 / 213; off them, 16 slots and more, in times: 10 x 8 M 1.1 to 1.5, 24 x 4 M 1.02 to 1.2, 40 x 4 M 1.03 to 1.35).  13 to 16 learners on lines: only
+// with the distance and 16 slots (14 x 6 M with 4 slots and none 193 / 180, with 16 and the distance 205 / 206).  65 to 104: from 16 slots (96 and 100 x
+// 1.6 M with fewer 1.00 to 1.03 times).  The largest tables halve the tile (128 x 1.6 M with 32 slots 1.6 to 1.8 times).  Off the lines few slots
+// keep to it with 29 to 32 learners only (32 x 3 M with 13, short-row / tiled 236 / 220).
+inline bool tiled_rows(int n, int deg, bool cd, int room) {
+    if (n < 13 || (n > 16 && n < 29) || (n > 32 && n < 49) || n > 128 || n * deg > 3840) return false;
+    if (room < 2) return (n > 28 && n < 33) || (room == 1 && n <= 64 && deg >= 16);
+    return n < 17 ? cd && deg >= 16 : n < 65 || n > 104 || deg >= 16;
+}
+
 // The short-row kernel's tile: all n rows x `1 << logc` column groups on `nrg` row groups of as many lanes (a multiple
 // of 64 lanes in all), `rows` rows per lane, and its LDS: slot table (8 bytes per slot), the tile, and with the distance
 // the merge slots (48 bytes per lane).

@@ -2,8 +2,8 @@
 //     X_out[i,:] = sum_s w[i,s] * X[nbr[i,s],:] - lr * G[i,:]            (Sec. 2, Eq. 2)
 // and for the consensus distance sum_i ||x_i - xbar||^2 (Sec. 3).  The kernels live in the headers included
 // below: psgd_device.h (shared building blocks), psgd_pace.h (workgroups of a die in step), psgd_short.h (any table: short rows, few
-// learners, rows off the lines), psgd_ring_walk.h (3-slot tables on long rows of nine and more learners, rings in registers only),
-// psgd_tiled.h (long rows of 9 to 128 learners, other slot counts, LDS tiles), psgd_streams.h (global averaging, distance,
+// learners, most tables of other than three slots), psgd_ring_walk.h (3-slot tables on long rows, rings in registers only),
+// psgd_tiled.h (long rows, other slot counts, numbers of learners that fill its LDS tiles), psgd_streams.h (global averaging, distance,
 // gradient producer, reference streams, table builder).
 //
 // The step is bound by HBM traffic (about 7 flops against 10-12 bytes per element), so the
@@ -498,18 +498,11 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const int64_t ncg = (d + kVec - 1) / kVec;
     // 3-slot tables: from plan::ring_rows on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
     // through tiles; below it the short-row kernel.
-    // Tables of other slot counts: on long rows the tiled kernel is as good or a little better while
-    // its row segments are wide and start on lines (64 x 100 M pitched, 13 slots with the distance 72.7 against 65.9 % of 8 TB/s; 5
-    // slots 76.6 / 76.0), else the short-row kernel (us, short-row / tiled: 64 x 6 400 001 with 5 slots 1034 / 1121, 200 x 1 600 001
-    // 838 / 1322, 300 x 1.6 M 1392 / 1556, 512 x 1.6 M with 8 slots 2367 / 4141, 5 x 20 M 239 / 279).  Tables of 16 slots and more, bound by LDS
-    // reads, on 9 to 64 learners also where rows start on 16 bytes only (64 x 3 200 004 with 32 slots 674 / 599, 16 x 12 000 004 601 /
-    // 559), not on shorter rows (9 x 2.3 M with bf16 gradients 80 / 112).  29 to 32 learners, whose
-    // short-row tile is 128 column groups wide, are ahead on the tiled kernel off the lines too (32 x 3 000 016
-    // with 13 slots 236 / 220).
+    // Tables of other slot counts: the short-row kernel, but for long rows where plan::tiled_rows says so.
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
-    const bool wide = n > 8 && n <= 128 && (rows_on_lines(X, X_out, ld) || (n > 28 && n <= 32));
+    const int room = !long_rows(*di, ncg) ? 0 : rows_on_lines(X, X_out, ld) ? 2 : quads && long_rows(*di, ncg, 4) ? 1 : 0;
     const bool ring = deg == 3 && plan::walk_rows(n, ncg, di->cus, want_cd, prod != nullptr);
-    const bool tiled = deg != 3 && long_rows(*di, ncg) && (wide || (n > 8 && n <= 64 && deg >= 16 && quads && long_rows(*di, ncg, 4)));
+    const bool tiled = deg != 3 && long_rows(*di, ncg) && plan::tiled_rows(n, deg, want_cd, room);
     bool produced = ring;                                        // the next gradients, by the same kernel
     if (ring) {
         if (int rc = want_cd ? launch_ring<GT, true>(*di, name, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, prod)

@@ -1,5 +1,5 @@
-// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows of 9 to 128 learners, for mixing tables of other than three
-// slots, and its kernel mix_deg_kernel (rows on lines, with two exceptions: see the rule in mix_step_impl).  Included by psgd_kernels.hip only.
+// The LDS-tiled form of the model-averaging step (Sec. 2, Eq. 2) on long rows, for mixing tables of other than three slots and numbers of learners
+// that fill its tiles (plan::tiled_rows), and its kernel mix_deg_kernel.  Included by psgd_kernels.hip only.
 #ifndef PSGD_TILED_H
 #define PSGD_TILED_H
 
