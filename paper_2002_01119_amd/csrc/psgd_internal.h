@@ -93,7 +93,7 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads, bool even = true
 constexpr int kRingLanes = 960;
 constexpr int kPaceSlots = 64;
 constexpr int kPaceSpins = 400;
-constexpr int kTicketSlots = 256;   // launches with a distance under way at a time whose tickets are their own
+constexpr int kTicketSlots = 256;   // counters of the distance's last sum: half for each array of partial sums, launch by launch in turn
 // Rows on their way per lane, and how far ahead of the mean a workgroup may be, in quarter rows.  The narrower the chunk, the more rows: about 900 lanes times rows keep the memory busy, and
 // what is beyond that costs more in order than it gains (us; one row each 64 x 1.2 M 154, two 153; 128 x 500 k 138 / 129; two / four
 // 130 x 200 k with a distance 79 / 68, 256 x 280 k with bf16 gradients 154 / 135; four / six 512 x 205 k 244.7 / 237.0, without the distance 222.8 /

@@ -8,7 +8,7 @@ from paper_2002_01119_amd import psgd
 
 pytestmark = pytest.mark.gpu
 LANES, COLS = 256, 4          # of a workgroup of the distance kernel for few learners; columns of a lane
-TICKETS = 256                 # launches before a counter is used again
+TICKETS = 256                 # more launches than that use a counter again
 
 
 def _reference(X):
@@ -72,3 +72,32 @@ def test_graph_replays_between_eager_calls():
         torch.cuda.synchronize()
         assert float(c) == want and float(e) == want, k
         assert torch.equal(Y, Z)
+
+
+def test_graph_with_the_fixed_array_beside_calls_with_the_other():
+    """Two arrays of partial sums, hence two streams that may run side by side, one of them a graph whose tickets stay as captured:
+    over as many calls as there are tickets each gets its own distance, also when the launches' workgroup counts differ."""
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    X, G = torch.randn(6, 300_001, device="cuda:0", generator=gen), torch.randn(6, 300_001, device="cuda:0", generator=gen)
+    V = torch.randn(3, 500_000, device="cuda:0", generator=gen)
+    Y, want_v = torch.empty_like(X), _reference(V)
+    nbr, w = [torch.from_numpy(np.ascontiguousarray(t)).to("cuda:0") for t in psgd.build_mixing(psgd.TOPO_RAND_RING, 6, 3, 0)]
+    c = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    psgd.mix_step_cd_static(X, Y, G, nbr, w, 0.1, c)
+    want = float(c)
+    rounds = 2 * TICKETS
+    got, got_v = [torch.full((rounds,), float("nan"), dtype=torch.float64, device="cuda:0") for _ in range(2)]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        psgd.mix_step_cd_static(X, Y, G, nbr, w, 0.1, c)
+    torch.cuda.synchronize()
+    for k in range(rounds):
+        with torch.cuda.stream(side):
+            g.replay()
+            got[k:k + 1].copy_(c)
+        psgd.consensus_dist_async(V, got_v[k:k + 1])
+    torch.cuda.synchronize()
+    assert bool((got == want).all())
+    assert bool((got_v == got_v[0]).all()) and abs(float(got_v[0]) - want_v) <= V.numel() * 2.0 ** -53 * want_v
