@@ -382,6 +382,13 @@ __device__ __forceinline__ void last_sum(const Gather& g, double mine) {       /
     sum = wave_sum(sum);
     if (tid == 0) *g.out = sum;
 }
+// The same, or left to sum_partials_kernel behind this one.
+__device__ __forceinline__ void last_sum_or_none(const Gather& g, double mine) {
+    if (g.out)
+        last_sum(g, mine);
+    else if (threadIdx.x == 0)
+        g.partials[blockIdx.x] = mine;
+}
 __device__ __forceinline__ void acc_diff(double* a, double* b, f32x4 x, const double* s) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {

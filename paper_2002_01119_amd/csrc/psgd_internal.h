@@ -161,8 +161,14 @@ inline bool walk_full_rows(int n, int64_t ncg, int cus) {
     return n > 8 ? full_rows_paced(n, ncg, cus) : n > 2 && n * ncg >= 12000 * (int64_t)cus;
 }
 // The distance of two or three learners on long rows: small workgroups by themselves, not swept in batches of eight rows that they do not
-// have (us, swept / alone: 2 x 30 M 57.4 / 47.3, 3 x 30 M 65.8 / 57.9, 2 x 8 M 19.4 / 17.1; 3 x 6.5 M 19.3 / 19.5, 4 x 8 M 24.3 / 24.4, 5 x 8 M 27.6 / 28.9).
-inline bool distance_alone(int n, int64_t ncg, int cus) { return n < 4 && ncg >= 7500 * (int64_t)cus; }
+// have (us, swept / alone, over three buffers in turn: 2 x 12 M 26.0 / 22.7, 2 x 24 M 45.8 / 39.4, 3 x 12 M 29.3 / 27.2, 3 x 30 M 65.8 / 57.6; 2 x 8.4 M, a fifth
+// sweep that is nearly empty, 19.2 / 19.9, 3 x 8.4 M 21.9 / 22.6; 4 x 8 M 24.3 / 24.4, 5 x 8 M 27.6 / 28.9).
+inline bool distance_alone(int n, int64_t ncg, int cus) { return n < 4 && ncg >= 10000 * (int64_t)cus; }
+// Whether the partial sums of the distance's small workgroups are added up by a kernel of its own, not by the workgroup that is done last:
+// from 64 MB of X on, where its launch is hidden behind the reading, and for more workgroups than two on each compute unit, which queue longer
+// at the tickets.  us of the synchronous call, last workgroup / kernel of its own: 64 x 1 M (977 workgroups) 53.6 / 52.9; of 256 to 512: 128 x 300 k 37.7 /
+// 38.1, 16 x 4 M 53.6 / 53.9, 8 x 2.6 M 27.2 / 27.6.
+inline bool distance_summed_apart(int grid, int n, int64_t d, int cus) { return grid > 2 * cus && n * d >= (int64_t)1 << 24; }
 inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
 
 // LDS of the tiled kernel (long rows, tables of other than three slots): the slot table (8 bytes per slot), TWO tile

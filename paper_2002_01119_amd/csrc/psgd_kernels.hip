@@ -665,7 +665,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
     if (int rc = device_info(&di)) return rc;
     double* partials = nullptr;
     if (int rc = acquire_partials(di, s, &partials)) return rc;
-    const Gather gather = make_gather(partials, out_dev, false);
+    Gather gather = make_gather(partials, out_dev, false);
     if (d > 0) {
         const int64_t ncg = (d + kVec - 1) / kVec;
         if (long_rows(*di, ncg) && !plan::distance_alone(n, ncg, di->cus)) {
@@ -691,12 +691,15 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
             } else {
                 const int grid = plan::even_grid(ncg, di->cus, 8, kThreads);  // light kernel: 32 waves per CU
                 const Sweeps sw = make_sweeps(ncg, grid, kThreads);
+                const bool apart = plan::distance_summed_apart(grid, n, d, di->cus);
+                if (apart) gather.out = nullptr;
                 if (d % kVec)
                     hipLaunchKernelGGL(consensus_partial_kernel<true>, dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d, ldx, (int)sw.chunk,
                                        gather);
                 else
                     hipLaunchKernelGGL(consensus_partial_kernel<false>, dim3(grid), dim3(sweep_threads(sw)), 0, s, X, n, d, ldx, (int)sw.chunk,
                                        gather);
+                if (apart) hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(kThreads), 0, s, partials, grid, out_dev);
             }
         }
     } else {

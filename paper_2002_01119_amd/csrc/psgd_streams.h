@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(const float
         for (int k = 0; k < kVec; ++k)
             if (!RAGGED || k >= c.lo) total += b[k] - a[k] * a[k] * inv_n;
     }
-    last_sum(gather, block_sum(total, lds4, blockDim.x));
+    last_sum_or_none(gather, block_sum(total, lds4, blockDim.x));
 }
 
 // The same where the columns alone do not fill the chip: rows spread over row groups of lanes as in the short-row kernel.
@@ -406,6 +406,15 @@ __global__ __launch_bounds__(T) void consensus_sweep_kernel(const float* __restr
             if (RAGGED ? k >= c.lo && k < c.hi : c.lo == 0) total += b[k] - a[k] * a[k] * inv_n;
     }
     last_sum(gather, block_sum(total, lds_waves, blockDim.x));
+}
+
+// The distance's last sum where the workgroups leave it (plan::distance_summed_apart), in a fixed order.
+__global__ __launch_bounds__(kThreads) void sum_partials_kernel(const double* __restrict__ partials, int count, double* __restrict__ out) {
+    __shared__ double lds_waves[kThreads / 64];
+    double v = 0.0;
+    for (int i = threadIdx.x; i < count; i += kThreads) v += partials[i];
+    v = block_sum(v, lds_waves, kThreads);
+    if (threadIdx.x == 0) *out = v;
 }
 
 // The distance of rows without columns.

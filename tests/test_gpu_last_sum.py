@@ -32,6 +32,19 @@ def test_workgroup_counts(groups, odd):
     assert got == [got[0]] * 4
 
 
+@pytest.mark.parametrize("n, d", [(32, 524_284), (32, 524_288), (31, 541_201), (29, 578_527), (64, 1_000_003)])
+def test_around_the_kernel_of_its_own(n, d):
+    """Both sides of 2^24 elements and of two workgroups on each compute unit, from which on a kernel behind makes the last sum."""
+    X = torch.randn(n, d, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(n))
+    want = _reference(X)
+    out = torch.full((3,), float("nan"), dtype=torch.float64, device="cuda:0")
+    for k in range(3):
+        psgd.consensus_dist_async(X, out[k:k + 1])
+    got = out.tolist()
+    assert abs(got[0] - want) <= n * d * 2.0 ** -53 * want
+    assert got == [got[0]] * 3 and psgd.consensus_dist(X) == got[0]
+
+
 def test_more_launches_than_tickets():
     n = 5
     sizes = [1000, 70_001, 400_000]
