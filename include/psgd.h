@@ -154,7 +154,8 @@ int psgd_mix_step_bf16g(const float* X, float* X_out, const uint16_t* G_bf16,
  * library orders them on the device (a call that comes on another stream than the previous one
  * makes its stream wait for everything enqueued so far on that previous stream), so they
  * serialise instead of racing.  Work captured into graphs is exempt: graph launches that use
- * the buffer must be ordered by the caller.
+ * the buffer must be ordered by the caller.  Where they overlap all the same, the distances of the calls that
+ * overlapped are wrong or not written; X_out and later calls are not touched by it.
  * All other arguments, modes and errors are those of psgd_mix_step; d = 0 writes 0.
  */
 int psgd_mix_step_cd(const float* X, float* X_out, const float* G,
@@ -200,9 +201,10 @@ int psgd_mix_step_ex(const float* X, int64_t ldx, float* X_out, int64_t ldo,
  * array; on long rows there is one workgroup per compute unit.  A device on which that is more than PSGD_STATIC_SLOTS
  * is refused with PSGD_EINVAL and nothing is launched.  n, d and the pitches are limited as in psgd_mix_step_ex.
  * Every call on a GPU uses that GPU's one array, which keeps the previous call's partials (each
- * launch overwrites the slots it reads, so nothing needs clearing).  Calls that overlap in time
- * on one GPU (two streams, or two graphs launched side by side) race on it: the caller orders
- * them.  It does not share the buffer of psgd_mix_step_cd / psgd_consensus_dist_async.
+ * launch overwrites the slots it reads, and leaves the counters that tell its last workgroup at zero, so nothing needs
+ * clearing).  Calls that overlap in time on one GPU (two streams, or two graphs launched side by side) race on it:
+ * the caller orders them, or the distances of the calls that overlapped are wrong or not written (X_out and later calls are not touched).
+ * It does not share the buffer of psgd_mix_step_cd / psgd_consensus_dist_async.
  */
 int psgd_mix_step_cd_static(const float* X, int64_t ldx, float* X_out, int64_t ldo,
                             const void* G, int64_t ldg, int g_is_bf16,

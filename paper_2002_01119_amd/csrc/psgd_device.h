@@ -335,36 +335,31 @@ __device__ __forceinline__ double block_sum(double v, double* lds_waves, int T) 
 }
 
 // ---------------------------------------------------------------------------------------
-// The distance's last sum, over the workgroups, by the workgroup that is done last.  Every workgroup writes its partial sum past the caches and then draws a ticket: from the launch's counter, or where
-// many workgroups would queue at it (16 ns each) from one of kTicketLeaves first, whose last one goes on to it.  The last of
-// all reads the partial sums, adds them in a fixed order whichever workgroup it is, and puts the counters back to zero.  Nobody waits.
+// The distance's last sum, over the workgroups, by the workgroup that is done last.  Every workgroup writes its partial sum past the caches and then
+// draws a ticket: from one counter, or where many workgroups would queue at it (16 ns each) from one of plan::kTicketLeaves first, whose
+// last one goes on to it.  The last of all reads the partial sums and adds them in a fixed order whichever workgroup it is.  Nobody waits,
+// and every counter ends at zero (plan::Ticket).
 // Against the second kernel (us of a launch of 256 lanes a workgroup and little work): 64 workgroups 4.3 / 4.3, 157 4.1 / 4.2, 256 of 8 us 9.3 / 8.8, 512
 // 6.8 / 6.6: as long on the device, but a launch less, which is 2.6 us of host time on calls that are bound by it.
 // ---------------------------------------------------------------------------------------
-constexpr int kTicketLeaves = 16;
-__device__ unsigned g_tickets[plan::kTicketSlots][kTicketLeaves + 1][32];   // a counter in each 128-byte line
+__device__ unsigned g_tickets[2][plan::kTicketCounters][32];   // for each array of partial sums; a counter in each 128-byte line
 struct Gather {
     double* partials;
     double* out;
-    int slot;
+    int array;
 };
 __device__ __forceinline__ void last_sum(const Gather& g, double mine) {       // `mine`: of the workgroup, in its first wavefront
     const int tid = threadIdx.x;
     if (tid >= 64) return;
-    const unsigned count = gridDim.x, leaves = count <= 64 ? 0u : (unsigned)kTicketLeaves;
-    unsigned (*tickets)[32] = g_tickets[g.slot];
-    auto draw = [&](unsigned* at, unsigned of) {                  // whether this is the last of `of` to come
-        if (__hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != of - 1) return false;
-        __hip_atomic_store(at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return true;
+    const unsigned count = gridDim.x;
+    auto draw = [&](plan::Ticket t) {                             // whether this is the last of t.of to come
+        return atomicInc(&g_tickets[g.array][t.at][0], (unsigned)t.of - 1) == (unsigned)t.of - 1;
     };
     int last = 0;
     if (tid == 0) {
         __hip_atomic_store(g.partials + blockIdx.x, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // written before the ticket is drawn
-        const unsigned leaf = blockIdx.x % kTicketLeaves;
-        last = (leaves == 0 || draw(tickets[1 + leaf], (count - leaf + kTicketLeaves - 1) / kTicketLeaves)) &&
-               draw(tickets[0], leaves ? leaves : count);
+        last = (!plan::ticket_leaves(count) || draw(plan::ticket_leaf(blockIdx.x, count))) && draw(plan::ticket_root(count));
     }
     if (!__builtin_amdgcn_readfirstlane(last)) return;
     asm volatile("" ::: "memory");

@@ -88,12 +88,32 @@ inline SweepPlan sweep_plan(int64_t ncg, int grid, int threads, bool even = true
     return s;
 }
 
+// The counters that the workgroups of a launch with a distance draw tickets from (last_sum): the one that draws the last ticket adds the partial
+// sums up.  A draw adds one to its counter, or puts it back to zero at the last of `of`, in one access.  Every counter is used with one
+// `of` only, whatever the launch: then any number of launches, in order or by a caller's mistake at the same time, ends with the
+// counter at zero, and what such a mistake spoils are the distances of those launches, not of a later one.
+// Up to 64 workgroups draw at one counter, its `of` being its place; more draw at one of 16 leaves each, of a size of its own, and the last of
+// each leaf at the counter of 16.
+constexpr int kTicketLeaves = 16, kTicketQueue = 64;
+constexpr int kTicketCounters = kTicketQueue + 1 + kTicketLeaves * (kMaxGrid / kTicketLeaves);
+struct Ticket {
+    int at, of;
+};
+PSGD_HOST_DEVICE inline bool ticket_leaves(int grid) { return grid > kTicketQueue; }
+PSGD_HOST_DEVICE inline Ticket ticket_leaf(int block, int grid) {
+    const int leaf = block % kTicketLeaves, of = (grid - leaf + kTicketLeaves - 1) / kTicketLeaves;
+    return Ticket{kTicketQueue + 1 + leaf + kTicketLeaves * (of - 1), of};
+}
+PSGD_HOST_DEVICE inline Ticket ticket_root(int grid) {
+    const int of = ticket_leaves(grid) ? kTicketLeaves : grid;
+    return Ticket{of, of};
+}
+
 // The ring walk: most lanes that have columns (one more wavefront keeps the pace), words to keep it with (launches under way at a
 // time that do not share one), and how often a wavefront asks before it walks on by itself (about 30 us).
 constexpr int kRingLanes = 960;
 constexpr int kPaceSlots = 64;
 constexpr int kPaceSpins = 400;
-constexpr int kTicketSlots = 256;   // counters of the distance's last sum: half for each array of partial sums, launch by launch in turn
 // Rows on their way per lane, and how far ahead of the mean a workgroup may be, in quarter rows.  The narrower the chunk, the more rows: about 900 lanes times rows keep the memory busy, and
 // what is beyond that costs more in order than it gains (us; one row each 64 x 1.2 M 154, two 153; 128 x 500 k 138 / 129; two / four
 // 130 x 200 k with a distance 79 / 68, 256 x 280 k with bf16 gradients 154 / 135; four / six 512 x 205 k 244.7 / 237.0, without the distance 222.8 /

@@ -368,14 +368,6 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
 
 // Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.
 std::atomic<unsigned> g_paced_launches{0};   // each takes the next of the pace words
-// Each launch with a distance takes the next tickets of those that go with its array of partial sums: what is enqueued on one array is in
-// order, but a graph, whose tickets stay as captured, may run beside calls that use the other.
-std::atomic<unsigned> g_gathers{0};
-Gather make_gather(double* partials, double* out, bool fixed_array) {
-    constexpr unsigned kEach = plan::kTicketSlots / 2;
-    const unsigned next = out ? g_gathers.fetch_add(1, std::memory_order_relaxed) % kEach : 0;
-    return Gather{partials, out, (int)(fixed_array ? kEach + next : next)};
-}
 int next_pace_slot() { return (int)(g_paced_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots); }
 template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
 int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp, int cached, hipStream_t s, const float* X, float* X_out,
@@ -498,7 +490,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     }
     const float neg_lr = -lr;
     const Pitch ld{ldx, ldo, ldg};
-    const Gather gather = make_gather(partials, cd_out, no_alloc);
+    const Gather gather{partials, cd_out, no_alloc ? 1 : 0};
     const int64_t ncg = (d + kVec - 1) / kVec;
     // 3-slot tables: from plan::ring_rows on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
     // through tiles; below it the short-row kernel.
@@ -608,7 +600,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const plan::RowsPlan rp = plan::full_rows_plan(n, d, di->cus, want_cd);
     const bool walk = plan::walk_full_rows(n, ncg, di->cus);
     const bool split = !walk && !big && rp.threads != 0;
-    const Gather gather = make_gather(partials, cd_out, false);
+    const Gather gather{partials, cd_out, 0};
     int grid = 0;
     if (walk) {
         grid = di->cus < kMaxGrid ? di->cus : kMaxGrid;
@@ -665,7 +657,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
     if (int rc = device_info(&di)) return rc;
     double* partials = nullptr;
     if (int rc = acquire_partials(di, s, &partials)) return rc;
-    Gather gather = make_gather(partials, out_dev, false);
+    Gather gather{partials, out_dev, 0};
     if (d > 0) {
         const int64_t ncg = (d + kVec - 1) / kVec;
         if (long_rows(*di, ncg) && !plan::distance_alone(n, ncg, di->cus)) {

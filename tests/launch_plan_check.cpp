@@ -51,7 +51,54 @@ static void check_cover(int64_t ncg, int grid, int threads, bool even = true) {
     }
 }
 
+// The counters of the distance's last sum as the kernels use them: a draw adds one, or puts back to zero at the last of `of`.
+struct Counters {
+    std::vector<int> value = std::vector<int>(kTicketCounters, 0), of = std::vector<int>(kTicketCounters, 0);
+    bool draw(Ticket t) {
+        CHECK(t.at >= 0 && t.at < kTicketCounters && t.of >= 1 && (of[t.at] == 0 || of[t.at] == t.of), "counter %d drawn from as of %d and of %d", t.at, of[t.at], t.of);
+        if (t.at < 0 || t.at >= kTicketCounters) return false;
+        of[t.at] = t.of;
+        const int old = value[t.at];
+        value[t.at] = old >= t.of - 1 ? 0 : old + 1;
+        return old == t.of - 1;
+    }
+    bool last(int block, int grid) { return (!ticket_leaves(grid) || draw(ticket_leaf(block, grid))) && draw(ticket_root(grid)); }
+};
+static void check_tickets() {
+    std::srand(1);
+    Counters c;
+    // launches that a caller let overlap, their workgroups interleaved, and behind them launches in order: every one of these has one last
+    // workgroup, and it is the one that came last
+    for (int round = 0; round < 400; ++round) {
+        std::vector<int> grids, blocks;
+        for (int k = 0; k < 2 + round % 3; ++k) {
+            const int g = round % 5 == 4 ? kMaxGrid - k : 1 + std::rand() % (round % 2 ? 80 : 700);
+            grids.push_back(k && round % 4 == 0 ? grids[0] : g);
+            blocks.push_back(0);
+        }
+        for (;;) {
+            std::vector<int> open;
+            for (size_t k = 0; k < grids.size(); ++k)
+                if (blocks[k] < grids[k]) open.push_back((int)k);
+            if (open.empty()) break;
+            const int k = open[std::rand() % open.size()];
+            (void)c.last(blocks[k]++, grids[k]);
+        }
+        for (int g : {grids[0], grids[1], 1 + std::rand() % kMaxGrid, 16, 64, 65, 66, 80, 512}) {
+            int lasts = 0, where = -1;
+            const int first = std::rand() % g;                  // in any order
+            for (int b = 0; b < g; ++b)
+                if (c.last((first + b) % g, g)) { ++lasts; where = b; }
+            CHECK(lasts == 1 && where == g - 1, "%d workgroups: %d of them the last, place %d", g, lasts, where);
+        }
+    }
+    for (int g = 1; g <= kMaxGrid; ++g)
+        for (int b = 0; b < g; ++b) (void)c.last(b, g);
+    for (int k = 0; k < kTicketCounters; ++k) CHECK(c.value[k] == 0, "counter %d ends at %d", k, c.value[k]);
+}
+
 int main() {
+    check_tickets();
     // the five workloads' rows in 128-bit column groups, the grids an MI355X gives them, and odd neighbours
     const int64_t rows[] = {250000, 8000000, 6400000, 2000000, 25000000, 1, 15, 16, 17, 767, 768, 769, 196608, 196609,
                             786431, 786432, 786433, 123456789, (1ll << 31) + 257, (1ll << 33) + 5};

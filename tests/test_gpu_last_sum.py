@@ -1,5 +1,5 @@
 """The distance's last sum, made by the workgroup that is done last: workgroup counts on both sides of where tickets are drawn in two
-steps, launches beyond the tickets that exist, graph replays between eager calls."""
+steps, the same counters launch after launch, graph replays between eager calls, and calls behind some that overlapped by mistake."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +8,7 @@ from paper_2002_01119_amd import psgd
 
 pytestmark = pytest.mark.gpu
 LANES, COLS = 256, 4          # of a workgroup of the distance kernel for few learners; columns of a lane
-TICKETS = 256                 # more launches than that use a counter again
+TICKETS = 256                 # draws and launches enough that a counter left off zero would show
 
 
 def _reference(X):
@@ -88,8 +88,8 @@ def test_graph_replays_between_eager_calls():
 
 
 def test_graph_with_the_fixed_array_beside_calls_with_the_other():
-    """Two arrays of partial sums, hence two streams that may run side by side, one of them a graph whose tickets stay as captured:
-    over as many calls as there are tickets each gets its own distance, also when the launches' workgroup counts differ."""
+    """Two arrays of partial sums, hence two streams that may run side by side, one of them a graph:
+    over many calls each gets its own distance, also when the launches' workgroup counts differ."""
     gen = torch.Generator(device="cuda:0").manual_seed(3)
     X, G = torch.randn(6, 300_001, device="cuda:0", generator=gen), torch.randn(6, 300_001, device="cuda:0", generator=gen)
     V = torch.randn(3, 500_000, device="cuda:0", generator=gen)
@@ -114,3 +114,45 @@ def test_graph_with_the_fixed_array_beside_calls_with_the_other():
     torch.cuda.synchronize()
     assert bool((got == want).all())
     assert bool((got_v == got_v[0]).all()) and abs(float(got_v[0]) - want_v) <= V.numel() * 2.0 ** -53 * want_v
+
+
+def test_calls_behind_overlapping_ones():
+    """Calls of one array of partial sums that run side by side, the caller's mistake: their own distances may be wrong or missing, those of
+    later calls in order are right, whichever workgroup counts overlapped."""
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    shapes = [(6, 300_001), (8, 40_000), (6, 300_001), (16, 20_003)]
+    data = [[torch.randn(n, d, device="cuda:0", generator=gen) for _ in range(2)] for n, d in shapes]
+    data = [(X, torch.empty_like(X), G) for X, G in data]
+    tables = [[torch.from_numpy(np.ascontiguousarray(t)).to("cuda:0") for t in psgd.build_mixing(psgd.TOPO_RAND_RING, n, 3, 0)] for n, _ in shapes]
+    cd = [torch.zeros(1, dtype=torch.float64, device="cuda:0") for _ in shapes]
+
+    def step(i):
+        X, Y, G = data[i]
+        psgd.mix_step_cd_static(X, Y, G, *tables[i], 0.1, cd[i])
+
+    want = []
+    for i in range(len(shapes)):
+        step(i)
+        want.append(float(cd[i]))
+        assert abs(want[i] - _reference(data[i][1])) <= shapes[i][0] * shapes[i][1] * 2.0 ** -53 * want[i]
+    streams = [torch.cuda.Stream() for _ in shapes]
+    graphs = []
+    for i, s in enumerate(streams):
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[i], stream=s):
+            step(i)
+    torch.cuda.synchronize()
+    for _ in range(60):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                step(i)
+                graphs[i].replay()
+    torch.cuda.synchronize()
+    for k in range(3):
+        for i in range(len(shapes)):
+            cd[i].fill_(float("nan"))
+            step(i)
+            assert float(cd[i]) == want[i], (k, i)
+            cd[i].fill_(float("nan"))
+            graphs[i].replay()
+            assert float(cd[i]) == want[i], (k, i)
