@@ -28,14 +28,25 @@ inline int persistent_grid(int cus, int64_t work_items, int per_cu, int threads)
     return (int)(g < 1 ? 1 : g);
 }
 
-// The same with as many workgroups on each compute unit, of fewer lanes, where more than half of the units would have one: with the last of
-// them short of a round, the others wait for the few that have one more, or idle.  Left alone where that is a few of many.  us, workgroups of 256
-// lanes / even: global averaging 512 x 140 k 192 / 155, 402 x 151 673 167 / 140, 100 x 150 k 43.3 / 37.4, 32 x 300 k 24.7 / 20.9, 73 x 202 100 36.7 / 34.3; distance
-// 128 x 300 k 32.4 / 26.5, 64 x 300 k 18.1 / 15.5, 64 x 550 k 29.0 / 25.7 (16 x 700 k, 684 workgroups, 23.7 / 24.1).
-inline int even_grid(int64_t work_items, int cus, int per_cu, int threads) {
-    const int g = persistent_grid(cus, work_items, per_cu, threads);
-    const int even = (g + cus - 1) / cus * cus;
-    return g > cus / 2 && even <= kMaxGrid && (g <= 2 * cus || even - g > cus / 3) ? even : g;
+// The same with as many workgroups on each compute unit, of fewer lanes: `g` workgroups short of a whole round leave compute units idle, or
+// waiting for the few that have one more.
+inline int even_grid(int g, int cus) { return (g + cus - 1) / cus * cus; }
+// Global averaging: from 16 learners on, where under 3/4 of the even grid would be there, from 96 learners on 85 %; beyond two on each compute
+// unit, where half a round is missing.  us, workgroups of 256 lanes / even: 29 x 298 099 26.9 / 23.9, 120 x 299 507 with the distance 81.2 % of the time, 320 x 140 877 85.8 %,
+// 39 x 529 933 88.4 %; not 33 x 198 253 19.4 / 20.3, 52 x 242 112 29.6 / 30.8, 23 x 414 464 + 4.5 %, nor few learners (4 x 458 912 7.5 / 8.3, 6 x
+// 266 400 8.9 / 10.0, 7 x 475 009 with the distance 13.8 / 14.8, 9 x 475 584 10.9 / 11.9), whose lanes wait for one row after the other.
+inline int full_grid(int n, int64_t work_items, int cus, int per_cu, int threads) {
+    const int g = persistent_grid(cus, work_items, per_cu, threads), even = even_grid(g, cus);
+    if (n < 16 || g <= cus / 2 || even > kMaxGrid) return g;
+    if (g > 2 * cus) return even - g > cus / 2 ? even : g;
+    return 4 * g < 3 * even || (n >= 96 && 20 * g < 17 * even) ? even : g;
+}
+// The distance: from 25 learners on, for more than one on each compute unit.  77 x 271 744 85.9 % of the time, 131 x 294 771 82.7, 70 x 326 464 91.4, 104 x
+// 393 203 96.5, 124 x 792 365 90.8; fewer learners 102 to 112 % (11 x 147 227, 5 x 554 592, 7 x 1 049 335), one on each 101 to 105 (23 x 154 816, 74 x 164 288).
+inline int distance_grid(int n, int64_t work_items, int cus, int per_cu, int threads) {
+    const int g = persistent_grid(cus, work_items, per_cu, threads), even = even_grid(g, cus);
+    if (n < 25 || g <= cus || even > kMaxGrid) return g;
+    return even - g > (g > 2 * cus ? cus / 3 : cus / 8) ? even : g;
 }
 
 // Grid of the degree-K kernel: one workgroup per tile up to what is resident, within the same bound.

@@ -630,7 +630,7 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         else PSGD_LAUNCH_ROWS(false, false);
 #undef PSGD_LAUNCH_ROWS
     } else {
-        grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : plan::even_grid(ncg, di->cus, kGridPerCu, kThreads);
+        grid = big ? persistent_grid(*di, ncg, 1, kRingThreads) : plan::full_grid(n, ncg, di->cus, kGridPerCu, kThreads);
 #define PSGD_LAUNCH_FULL(CD, T)                                                                                            \
     do {                                                                                                                   \
         const Sweeps sw = make_sweeps(ncg, grid, T, n > 8);                                                                \
@@ -681,7 +681,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
                     hipLaunchKernelGGL(consensus_rows_kernel<false>, dim3(grid), dim3(rp.threads), lds, s, X, n, d, ldx, rp.logc,
                                        rp.nrg, gather);
             } else {
-                const int grid = plan::even_grid(ncg, di->cus, 8, kThreads);  // light kernel: 32 waves per CU
+                const int grid = plan::distance_grid(n, ncg, di->cus, 8, kThreads);  // light kernel: 32 waves per CU
                 const Sweeps sw = make_sweeps(ncg, grid, kThreads);
                 const bool apart = plan::distance_summed_apart(grid, n, d, di->cus);
                 if (apart) gather.out = nullptr;

@@ -167,6 +167,23 @@ int main() {
             }
         }
     CHECK(persistent_grid(256, 25000000, 1, 768) == 256, "workload 5 grid");
+    // global averaging and the distance with the columns spread over workgroups: within the buffer, every column group once, evened out
+    // only where measured to gain
+    for (int cus : {1, 64, 256, 304, 1024})
+        for (int n : {1, 2, 9, 15, 16, 24, 25, 64, 95, 96, 512})
+            for (int64_t ncg : {1, 257, 16384, 33000, 50704, 68560, 99999, 118750, 140000, 199999, 262144, 393215})
+                for (int g : {full_grid(n, ncg, cus, 4, 256), distance_grid(n, ncg, cus, 8, 256)}) {
+                    CHECK(g >= 1 && g <= kMaxGrid, "n=%d ncg=%lld: grid %d", n, (long long)ncg, g);
+                    check_cover(ncg, g, 256);
+                    check_cover(ncg, g, 256, false);
+                }
+    const struct { int n; int64_t d; int full, distance; } evened[] = {
+        {4, 458912, 449, 449}, {6, 266400, 261, 261}, {9, 475584, 465, 465}, {15, 299507, 293, 293}, {16, 299507, 512, 293}, {17, 402112, 393, 393},
+        {23, 414464, 405, 405}, {25, 299507, 512, 512}, {33, 198253, 194, 194}, {33, 160000, 256, 157}, {52, 242112, 237, 237}, {39, 529933, 768, 768},
+        {28, 690496, 675, 768}, {144, 209472, 256, 205}, {192, 226815, 222, 222}, {64, 1000000, 977, 977}, {77, 271744, 512, 512}, {74, 164288, 256, 161}};
+    for (const auto& e : evened)
+        CHECK(full_grid(e.n, (e.d + 3) / 4, 256, 4, 256) == e.full && distance_grid(e.n, (e.d + 3) / 4, 256, 8, 256) == e.distance, "n=%d d=%lld: %d and %d workgroups",
+              e.n, (long long)e.d, full_grid(e.n, (e.d + 3) / 4, 256, 4, 256), distance_grid(e.n, (e.d + 3) / 4, 256, 8, 256));
     CHECK(persistent_grid(256, 1000, 4, 256) == 4, "short rows take one workgroup per 256 items");
     CHECK(deg_grid(1 << 30, 1024, 8) == kMaxGrid, "deg_grid clamp");
     // LDS plan of the tiled path: the widest power-of-two lane count whose slot table, two tile buffers and merge slots

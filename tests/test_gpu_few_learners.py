@@ -40,12 +40,13 @@ def test_next_gradients_beside_the_step(mods, n, d, deg, extra):
     test_gpu_d1d_one_pass.test_one_pass_is_the_two_calls(mods, n, d, deg, extra)
 
 
-# global averaging in step from 12 000 column groups of all learners per compute unit on; workgroups that are not a multiple of the compute
-# units (198, 293, 684, 977 of 256 lanes); the distance of two and three learners on either side of 10 000 column groups per compute unit
+# global averaging in step from 12 000 column groups of all learners per compute unit on; workgroups spread evenly over the
+# compute units (one, two and three on each) and left at 198, 293, 684 and 977 of 256 lanes; the distance of two and three learners on either side of 10 000 column groups per compute unit
 @pytest.mark.parametrize("n,d,gkind,extra", [
     (3, 4_095_996, "f32", None), (3, 4_096_001, "bf16", (1, 2, 3)), (4, 3_072_003, "f32", None), (5, 2_457_602, "bf16", None),
     (6, 2_048_004, "f32", (3, 1, 2)), (7, 1_755_431, "f32", None), (8, 1_536_001, "bf16", None), (8, 1_535_996, "f32", None),
     (73, 202_100, "bf16", None), (33, 300_003, "f32", (1, 2, 3)), (16, 700_000, "f32", None), (9, 1_000_001, "bf16", None), (20, 524_289, "f32", None),
+    (21, 538_821, "bf16", None), (77, 271_744, "f32", (1, 0, 3)), (120, 150_001, "bf16", None), (25, 420_003, "f32", None),
     (2, 10_239_996, "f32", None), (2, 10_240_001, "f32", None), (3, 10_240_004, "f32", None), (3, 10_260_003, "f32", (1, 0, 2))])
 def test_global_average_and_distance(psgd, n, d, gkind, extra):
     test_gpu_short_rows.test_global_average_and_distance_with_rows_spread_over_lanes(psgd, n, d, gkind, extra)
