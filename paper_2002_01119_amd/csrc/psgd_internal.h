@@ -196,10 +196,11 @@ inline bool walk_full_rows(int n, int64_t ncg, int cus) {
 // sweep that is nearly empty, 19.2 / 19.9, 3 x 8.4 M 21.9 / 22.6; 4 x 8 M 24.3 / 24.4, 5 x 8 M 27.6 / 28.9).
 inline bool distance_alone(int n, int64_t ncg, int cus) { return n < 4 && ncg >= 10000 * (int64_t)cus; }
 // Whether the partial sums of the distance's small workgroups are added up by a kernel of its own, not by the workgroup that is done last:
-// from 64 MB of X on, where its launch is hidden behind the reading, and for more workgroups than two on each compute unit, which queue longer
-// at the tickets.  us of the synchronous call, last workgroup / kernel of its own: 64 x 1 M (977 workgroups) 53.6 / 52.9; of 256 to 512: 128 x 300 k 37.7 /
-// 38.1, 16 x 4 M 53.6 / 53.9, 8 x 2.6 M 27.2 / 27.6.
-inline bool distance_summed_apart(int grid, int n, int64_t d, int cus) { return grid > 2 * cus && n * d >= (int64_t)1 << 24; }
+// from 192 MB of X on, where its launch is hidden behind the reading, and for more workgroups than three on each compute unit, which queue longer at
+// the tickets.  us, last workgroup / kernel of its own: 117 x 1 320 544 98.6 / 93.9, 31 x 1 552 672 33.7 / 32.6, 42 x 1 383 552 40.1 / 39.2, 262 x 1 111 648
+// 176.7 / 173.1, 202 x 860 489 113.6 / 112.4; the synchronous call 40 x 1 420 419 55.0 / 52.6, 75 x 1 126 016 70.4 / 67.6, 64 x 1 M 53.6 / 53.2.  Even at the line: 62 x
+// 864 096 35.7 / 35.9, 59 x 996 255 41.4 / 41.9.  Below it: 27 x 786 464 16.7 / 17.7, 30 x 1 089 152 23.8 / 24.6, 66 x 603 168 (590 workgroups) 28.2 / 28.8.
+inline bool distance_summed_apart(int grid, int n, int64_t d, int cus) { return grid > 3 * cus && n * d >= 48000000; }
 inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
 
 // LDS of the tiled kernel (long rows, tables of other than three slots): the slot table (8 bytes per slot), TWO tile

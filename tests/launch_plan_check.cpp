@@ -177,6 +177,10 @@ int main() {
                     check_cover(ncg, g, 256);
                     check_cover(ncg, g, 256, false);
                 }
+    const struct { int n; int64_t d; bool apart; } summed[] = {{27, 786464, false}, {30, 1089152, false}, {40, 1149088, false}, {31, 1552672, true}, {66, 603168, false},
+                                                               {178, 671232, false}, {64, 1000000, true}, {117, 1320544, true}, {16, 1000000, false}};
+    for (const auto& e : summed)
+        CHECK(distance_summed_apart(distance_grid(e.n, (e.d + 3) / 4, 256, 8, 256), e.n, e.d, 256) == e.apart, "n=%d d=%lld: last sum", e.n, (long long)e.d);
     const struct { int n; int64_t d; int full, distance; } evened[] = {
         {4, 458912, 449, 449}, {6, 266400, 261, 261}, {9, 475584, 465, 465}, {15, 299507, 293, 293}, {16, 299507, 512, 293}, {17, 402112, 393, 393},
         {23, 414464, 405, 405}, {25, 299507, 512, 512}, {33, 198253, 194, 194}, {33, 160000, 256, 157}, {52, 242112, 237, 237}, {39, 529933, 768, 768},

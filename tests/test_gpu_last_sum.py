@@ -32,9 +32,10 @@ def test_workgroup_counts(groups, odd):
     assert got == [got[0]] * 4
 
 
-@pytest.mark.parametrize("n, d", [(32, 524_284), (32, 524_288), (31, 541_201), (29, 578_527), (64, 1_000_003)])
+@pytest.mark.parametrize("n, d", [(32, 524_284), (32, 524_288), (31, 541_201), (29, 578_527), (64, 1_000_003),
+                                  (48, 999_999), (48, 1_000_000), (61, 786_432), (61, 786_881), (31, 1_552_673)])
 def test_around_the_kernel_of_its_own(n, d):
-    """Both sides of 2^24 elements and of two workgroups on each compute unit, from which on a kernel behind makes the last sum."""
+    """Both sides of 48 M elements and of three workgroups on each compute unit, from which on a kernel behind makes the last sum."""
     X = torch.randn(n, d, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(n))
     want = _reference(X)
     out = torch.full((3,), float("nan"), dtype=torch.float64, device="cuda:0")
