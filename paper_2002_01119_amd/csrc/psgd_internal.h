@@ -468,8 +468,19 @@ inline ShortPlan short_plan(int n, int deg, int64_t ncg, int cus, bool cd, bool 
 
 // Whether the short-row kernel also makes the next gradients of the delay-by-one schedule, or a producer behind it does: not on one round of
 // large workgroups whose row segments are 256 bytes or less, five arrays of which lie badly (us, 512 x 15 000 in one pass / two launches 41.1 / 39.4,
-// without the distance 39.6 / 35.5; 400 x 15 000 30.6 / 33.5, 29.1 / 28.8; 300 x 10 000, smaller workgroups, 15.0 / 21.8).
-inline bool short_produces(const ShortPlan& p) { return p.one ? p.threads <= 768 || p.logc > 4 : p.rows > 1; }
+// without the distance 39.6 / 35.5; 400 x 15 000 30.6 / 33.5, 29.1 / 28.8; 300 x 10 000, smaller workgroups, 15.0 / 21.8); nor off the lines in loops over
+// segments as short, from where five arrays are more than the last-level cache holds (on the arrays of the schedule, in turn: 498 x 43 411 108.7 / 94.2,
+// 257 x 61 035 76.7 / 69.0, 463 x 51 433 125.6 / 112.7, 142 x 130 547 88.5 / 81.2, 306 x 145 227 209 / 206; below it 381 x 33 063 51.1 / 58.4, 173 x 67 547 44.1 / 52.0; on the
+// lines 393 x 80 736 131 / 141, 439 x 86 240 157 / 167).
+inline bool short_produces(const ShortPlan& p, int64_t elements, bool on_lines) {
+    return p.one ? p.threads <= 768 || p.logc > 4 : p.rows > 1 && (on_lines || p.logc > 4 || elements <= 13500000);
+}
+// Bytes that the choice of cached_accesses goes by: X, G and X_out; with the next gradients off the lines noise and G_next too.  With three counted
+// the loads alone were kept from 7 to 11 M elements, where both are better (on the arrays of the schedule, in turn, loads / both: 393 x 24 927 53.2 / 36.0,
+// 148 x 67 855 45.6 / 33.9, 67 x 138 907 41.6 / 35.2; on the lines neither matters, 92 x 93 152 30.0 / 29.9).
+inline int64_t counted_bytes(int64_t elements, int gradient, bool next_gradients, bool on_lines) {
+    return elements * (8 + gradient + (next_gradients && !on_lines ? 8 : 0));
+}
 
 }  // namespace plan
 }  // namespace psgd

@@ -291,8 +291,8 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
                  const int32_t* nbr, const float* w, int deg, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather,
                  const Produce* prod) {
     static_assert(plan::kShortSlots <= PSGD_STATIC_SLOTS && plan::kShortSlots <= kMaxGrid, "one partial per workgroup");
-    const int cached = plan::cached_accesses(p, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
-                                             sizeof(GT) == 2);
+    const bool on_lines = rows_on_lines(X, X_out, ld);
+    const int cached = plan::cached_accesses(p, plan::counted_bytes(n * d, sizeof(GT), prod != nullptr, on_lines), on_lines, sizeof(GT) == 2);
     constexpr int kBoth = plan::kCachedLoads | plan::kCachedStores;
 #define PSGD_SHORT(DEG, R, ONE, CACHED, FEW)                                                                              \
     return launch_short_t<GT, CD, DEG, R, ONE, CACHED, FEW>(di, p, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather)
@@ -507,7 +507,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     } else if (!tiled) {
         const plan::ShortPlan sp = d < 4 ? plan::short_shape(n, deg, 1, want_cd, true, 0, 2)
                                          : plan::short_plan(n, deg, ncg, di->cus, want_cd, quads);
-        const Produce* beside = prod && deg == 3 && d >= kVec && plan::short_produces(sp) ? prod : nullptr;
+        const Produce* beside = prod && deg == 3 && d >= kVec && plan::short_produces(sp, n * d, rows_on_lines(X, X_out, ld)) ? prod : nullptr;
         produced = beside != nullptr;
         int rc;
         if (want_cd && deg == 3) rc = launch_short<GT, true, 3>(*di, sp, s, X, X_out, G, nbr, w, deg, n, d, ld, neg_lr, gather, beside);

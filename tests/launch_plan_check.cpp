@@ -284,6 +284,26 @@ int main() {
                         const int64_t grid = p.one ? p.tiles : short_grid(p, cus, cd ? slots : INT32_MAX);
                         CHECK(grid >= 1 && grid <= p.tiles && (!cd || grid <= slots), "short rows: grid %lld", (long long)grid);
                     }
+    // the next gradients beside the step or by a producer behind it, and what the cache hints go by then
+    const struct { int n; int64_t d; bool cd, lines, beside; } next[] = {
+        {498, 43411, false, false, false}, {257, 61035, false, false, false}, {306, 145227, true, false, false}, {142, 130547, true, false, false},
+        {381, 33063, false, false, true}, {173, 67547, false, false, true}, {393, 24927, false, false, true}, {393, 80736, true, true, true},
+        {439, 86240, true, true, true}, {107, 205493, true, false, true}, {45, 278507, false, false, true}, {512, 15000, true, true, false}, {300, 10000, true, true, true}};
+    for (const auto& e : next)
+        CHECK(short_produces(short_plan(e.n, 3, (e.d + 3) / 4, 256, e.cd, e.d % 4 == 0), e.n * e.d, e.lines) == e.beside, "n=%d d=%lld: next gradients", e.n, (long long)e.d);
+    for (int n : {1, 2, 3, 7, 16, 100, 300, 385, 512})
+        for (int64_t d : {4, 5, 1000, 20003, 100001, 300000, 3000001})
+            for (int form = 0; form < 4; ++form) {
+                const bool cd = form & 1, lines = form & 2;
+                const ShortPlan p = short_plan(n, 3, (d + 3) / 4, 256, cd, d % 4 == 0);
+                if (short_produces(p, n * d, lines))
+                    CHECK(p.rows >= 2 && p.rows <= (p.one ? 8 : 4), "n=%d d=%lld: no kernel of %d rows with the next gradients", n, (long long)d, p.rows);
+            }
+    {
+        const ShortPlan p = short_plan(393, 3, 6232, 256, false, false);
+        CHECK(cached_accesses(p, counted_bytes(393 * 24927, 4, true, false), false, false) == (kCachedLoads | kCachedStores) &&
+                  cached_accesses(p, counted_bytes(393 * 24927, 4, false, false), false, false) == kCachedLoads, "cache hints with the next gradients off the lines");
+    }
     // few columns: two rows per lane, so that a table's slot chain is short and the workgroups are many; wide tables the same
     // on longer rows; row segments stay a 128-byte line wide where the workgroup has room for it
     for (int n : {3, 8, 16, 40, 64, 105, 200})

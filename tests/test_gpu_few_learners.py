@@ -33,6 +33,8 @@ def test_ring_walk_of_few_learners(psgd, n, d, deg, gkind, extra):
     # looping: two, three and four rows per lane, whole tiles and a ragged last one, rows off the lines
     (8, 2_900_000, 3, 0), (7, 3_400_003, -3, 1), (13, 900_004, 3, 0), (33, 300_001, 3, 2), (64, 160_000, 3, 0), (64, 160_001, -3, 1), (128, 120_003, 3, 0),
     (300, 60_001, 3, 3), (512, 40_000, -3, 0),
+    # off the lines on segments of 128 and 256 bytes: on either side of where the producer takes them
+    (500, 26_999, 3, 0), (500, 27_001, -3, 1), (257, 52_529, -3, 0), (257, 52_531, 3, 2), (150, 50_001, 3, 1), (300, 30_002, -3, 3),
     # the ring walk from its line for this schedule on, rings and other tables
     (4, 6_144_001, 3, 0), (5, 4_915_205, 3, 1), (8, 3_072_004, 3, 0), (8, 3_072_001, -3, 0), (9, 1_536_001, 3, 0), (12, 1_228_804, -3, 0),
     (16, 921_601, 3, 2), (32, 450_563, 3, 0), (64, 225_284, -3, 0), (128, 225_281, 3, 1), (128, 225_285, -3, 0)])
