@@ -200,7 +200,8 @@ inline bool distance_alone(int n, int64_t ncg, int cus) { return n < 4 && ncg >=
 // the tickets.  us, last workgroup / kernel of its own: 117 x 1 320 544 98.6 / 93.9, 31 x 1 552 672 33.7 / 32.6, 42 x 1 383 552 40.1 / 39.2, 262 x 1 111 648
 // 176.7 / 173.1, 202 x 860 489 113.6 / 112.4; the synchronous call 40 x 1 420 419 55.0 / 52.6, 75 x 1 126 016 70.4 / 67.6, 64 x 1 M 53.6 / 53.2.  Even at the line: 62 x
 // 864 096 35.7 / 35.9, 59 x 996 255 41.4 / 41.9.  Below it: 27 x 786 464 16.7 / 17.7, 30 x 1 089 152 23.8 / 24.6, 66 x 603 168 (590 workgroups) 28.2 / 28.8.
-inline bool distance_summed_apart(int grid, int n, int64_t d, int cus) { return grid > 3 * cus && n * d >= 48000000; }
+// More than five on each from 120 MB on: 25 x 1 454 523 28.0 / 26.6, 32 x 1 363 200 31.1 / 30.2, 22 x 1 484 000 23.9 / 23.9.
+inline bool distance_summed_apart(int grid, int n, int64_t d, int cus) { return grid > 3 * cus && n * d >= (grid > 5 * cus ? 30000000 : 48000000); }
 inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
 
 // LDS of the tiled kernel (long rows, tables of other than three slots): the slot table (8 bytes per slot), TWO tile

@@ -178,7 +178,8 @@ int main() {
                     check_cover(ncg, g, 256, false);
                 }
     const struct { int n; int64_t d; bool apart; } summed[] = {{27, 786464, false}, {30, 1089152, false}, {40, 1149088, false}, {31, 1552672, true}, {66, 603168, false},
-                                                               {178, 671232, false}, {64, 1000000, true}, {117, 1320544, true}, {16, 1000000, false}};
+                                                               {178, 671232, false}, {64, 1000000, true}, {117, 1320544, true}, {16, 1000000, false},
+                                                               {25, 1454523, true}, {20, 1474931, false}, {30, 1262304, false}};
     for (const auto& e : summed)
         CHECK(distance_summed_apart(distance_grid(e.n, (e.d + 3) / 4, 256, 8, 256), e.n, e.d, 256) == e.apart, "n=%d d=%lld: last sum", e.n, (long long)e.d);
     const struct { int n; int64_t d; int full, distance; } evened[] = {
