@@ -413,11 +413,14 @@ inline ShortPlan short_loop_plan(int n, int deg, int64_t ncg, bool cd) {
 }
 // The tiles of a table that is not one ring, on rows that the ring walk would take.  Up to eight learners: 512 lanes of four rows (us, by
 // 1024 lanes of two / so / short_plan's, which it was: 3 x 9 M 74.4 / 56.8 / 58.7, 4 x 6 M 56.5 / 52.1 / 54.2, 5 x 6 M 74.2 / 72.7 / 69.3, 7 x 6 M
-// 97.7 / 96.5 / 95.8, 8 x 24 M 413 / 391 / 408).  With the next gradients at most three rows: more than that the registers do not hold.
+// 97.7 / 96.5 / 95.8, 8 x 24 M 413 / 391 / 408).  With the next gradients at most three rows: more than that the registers do not hold.  Beyond
+// 384 learners that would leave segments of 64 bytes: the next gradients are made in front of the tiles, which keep four rows (436 x 257 984 620 with them,
+// 523 apart, 446 x 297 344 806 / 668, 470 x 196 608 599 / 512, off the lines 507 x 244 161 705 / 659).
+inline bool tiles_produce(int n) { return n <= 384; }
 inline ShortPlan ring_tiles(int n, int64_t ncg, bool cd, bool produce) {
     if (n < 9) return produce ? short_widest(n, 3, ncg, cd, false, kShortThreads, 2) : short_widest(n, 3, ncg, cd, false, 512, 4);
     const ShortPlan p = short_loop_plan(n, 3, ncg, cd);
-    return produce && p.rows > 3 ? short_widest(n, 3, ncg, cd, false, kShortThreads, 3) : p;
+    return produce && tiles_produce(n) && p.rows > 3 ? short_widest(n, 3, ncg, cd, false, kShortThreads, 3) : p;
 }
 // Which tile a launch takes (fp32 gradients, with the distance unless said otherwise, kernel + final sum):
 //   - few columns: two rows per lane, on as few lanes as leave a row segment of a 128-byte line.  A lane reads its rows'

@@ -369,7 +369,7 @@ int launch_short(const DeviceInfo& di, const plan::ShortPlan& p, hipStream_t s, 
 // Long rows, 3-slot tables: one launch of mix_step_kernel, one workgroup per compute unit.
 std::atomic<unsigned> g_paced_launches{0};   // each takes the next of the pace words
 int next_pace_slot() { return (int)(g_paced_launches.fetch_add(1, std::memory_order_relaxed) % plan::kPaceSlots); }
-template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
+template <typename GT, bool CD, bool RAGGED, int D, bool PROD, bool APART = false>
 int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp, int cached, hipStream_t s, const float* X, float* X_out,
                   const GT* G, const int32_t* nbr, const float* w, int n, int64_t d, Pitch ld, float neg_lr, const Gather& gather,
                   const Produce& prod) {
@@ -377,8 +377,8 @@ int launch_ring_t(const plan::SweepPlan& sp, int grid, const plan::ShortPlan& tp
     if (lds < lds_classify_bytes(n)) lds = lds_classify_bytes(n);
     const int lanes = plan::ring_threads({1, sp.chunk}, plan::kRingLanes);
     const int threads = lanes + 64 > tp.threads ? lanes + 64 : tp.threads;
-    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D, PROD>), lds)) return rc;
-    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D, PROD>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
+    if (int rc = allow_lds(reinterpret_cast<const void*>(mix_step_kernel<GT, CD, RAGGED, D, PROD, APART>), lds)) return rc;
+    hipLaunchKernelGGL((mix_step_kernel<GT, CD, RAGGED, D, PROD, APART>), dim3(grid), dim3(threads), lds, s, X, X_out, G, nbr, w, n, d, ld, neg_lr,
                        Sweeps{sp.count, sp.chunk}, lanes,
                        next_pace_slot(), plan::pace_lead(D, PROD),
                        Tiles{tp.rows | cached << 4 | tp.logc << 8, tp.nrg}, prod, gather);
@@ -395,15 +395,17 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
     const plan::ShortPlan tp = plan::ring_tiles(n, ncg, CD, prod != nullptr);
     const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
                                              sizeof(GT) == 2);
-#define PSGD_RING(RAGGED, D, PROD)                                                                                         \
-    launch_ring_t<GT, CD, RAGGED, D, PROD>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather,        \
-                                           prod ? *prod : Produce{})
+#define PSGD_RING(RAGGED, D, ...)                                                                                         \
+    launch_ring_t<GT, CD, RAGGED, D, __VA_ARGS__>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, \
+                                                  prod ? *prod : Produce{})
     const int depth = plan::ring_depth(sp, n);
     // With one or two rows on their way the ragged form costs nothing (64 x 25.6 M 3137 / 3129 us); with more, a lane's own work shows
     // (512 x 205 k with six rows, in one run: whole groups 246, the ragged form 265).
     if constexpr (sizeof(GT) == 4) {
         if (prod) {
-            return plan::ring_depth_produce(sp) == 1 ? PSGD_RING(true, 1, true) : PSGD_RING(true, 2, true);
+            const bool one = plan::ring_depth_produce(sp) == 1;
+            if (plan::tiles_produce(n)) return one ? PSGD_RING(true, 1, true) : PSGD_RING(true, 2, true);
+            return one ? PSGD_RING(true, 1, true, true) : PSGD_RING(true, 2, true, true);
         }
     }
     switch (depth) {

@@ -144,6 +144,30 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
 }
 
 
+// The next gradients alone, for tables that are not walked: the same columns, row by row.
+template <bool RAGGED>
+__device__ __forceinline__ void produce_rows(const float* X, int n, int64_t d, int64_t ldx, const Sweeps& sweeps, int64_t my_sweeps,
+                                             const Produce& prod) {
+    const int64_t ncg = (d + kVec - 1) / kVec;
+    for (int64_t sw = 0; sw < my_sweeps; ++sw) {
+        const WalkCols c = walk_cols<RAGGED>(sweeps, sw, ncg, d);
+        const ColGroup own{0, c.lo, 4};
+        const int64_t at = c.col + c.at;
+        for (int r0 = 0; r0 < n; r0 += 4) {
+            f32x4 x[4], z[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t r = row_or_last(r0 + u, n);
+                x[u] = ld_x(X + r * ldx + at);
+                z[u] = ld_x(prod.noise + r * prod.ldn + at);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r0 + u < n) st_cols(prod.g + (int64_t)(r0 + u) * prod.ldg + at, vfma(prod.c, x[u], z[u]), own);
+        }
+    }
+}
+
 // The step on long rows for any 3-slot table, one launch.  The workgroups stage and classify the table alike; one ring is walked, any
 // other table goes through tiles (short_tiles; Tiles: how), an invalid one raises the flag and nothing is written.  A
 // kernel of its own behind this one for the other tables, which for a ring classified the table once more and ended, took 4.5 to 7 us
@@ -151,12 +175,13 @@ __device__ __forceinline__ double ring_walk(const float* X, float* Xout, const G
 // CD = also reduce the consensus distance of the outputs into *gather.out.
 // The column groups are split evenly over the persistent grid (plan::sweep_plan): every workgroup makes the
 // same number of sweeps; the wavefronts that neither a sweep nor the tiles need are not launched.
-// RAGGED: 4 may not divide d.  D: rows on their way per lane.  PROD: the next gradients too, whatever the table.
+// RAGGED: 4 may not divide d.  D: rows on their way per lane.  PROD: the next gradients too, whatever the table; APART: in front of the tiles,
+// not with them (plan::tiles_produce).
 struct Tiles {
     int form;                                                     // rows | cached << 4 | logc << 8: few scalar registers
     int nrg;
 };
-template <typename GT, bool CD, bool RAGGED, int D, bool PROD>
+template <typename GT, bool CD, bool RAGGED, int D, bool PROD, bool APART>
 __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const float* X, float* Xout, const GT* __restrict__ G,
                                                                          const int32_t* __restrict__ nbr,
                                                                          const float* __restrict__ w, int n, int64_t d, Pitch ld,
@@ -182,6 +207,8 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     const int kind = CD && sizeof(GT) == 2 ? __builtin_amdgcn_readfirstlane(staged) : staged;
     const int64_t ncg = (d + kVec - 1) / kVec;
     const int64_t my_sweeps = sweeps_of(sweeps, ncg);            // uniform
+    constexpr bool BESIDE = PROD && !APART;
+    if (APART && kind != kTableRing && tid < lanes) produce_rows<RAGGED>(X, n, d, ld.x, sweeps, my_sweeps, prod);
     if (kind == kTableRing) {
         if (tid >= lanes + 64) return;                           // whole wavefronts
         double total = 0.0;
@@ -195,7 +222,7 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     const int tile_rows = tiles.form & 15, cached = tiles.form >> 4 & 15, logc_all = tiles.form >> 8;
     if (kind == kTableBad) {
         if (blockIdx.x == 0 && tid == 0) atomicOr(&g_status_word, 1);
-        if (PROD && tid < tiles.nrg << logc_all) produce_tiles(tid, X, n, d, ld.x, logc_all, tiles.nrg, prod);
+        if (BESIDE && tid < tiles.nrg << logc_all) produce_tiles(tid, X, n, d, ld.x, logc_all, tiles.nrg, prod);
         if (CD) last_sum(gather, __builtin_nan(""));
         return;
     }
@@ -208,7 +235,7 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     do {                                                                                                                   \
         int t = tid, rows = n, logc = logc_all, nrg = tiles.nrg;                                                         \
         asm volatile("; tiles of %4 rows per lane, accesses %5" : "+v"(t), "+s"(rows), "+s"(logc), "+s"(nrg) : "n"(R), "n"(CACHED)); \
-        short_tiles<GT, CD, 3, R, false, CACHED, false, PROD>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
+        short_tiles<GT, CD, 3, R, false, CACHED, false, BESIDE>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
                                                         plan::short_table_bytes(rows, 3), rows << (logc + 4), gather,            \
                                                         ShortLds{lds_raw, lds_waves, lds_bad}, prod);                      \
     } while (0)
@@ -219,7 +246,7 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     } else if (tile_rows == 3) {
         if (cached == kBoth) PSGD_TILES(3, kBoth);
         else PSGD_TILES(3, 0);
-    } else if constexpr (!PROD) {                                // with the noise four rows are more than the registers hold
+    } else if constexpr (!BESIDE) {                              // with the noise four rows are more than the registers hold
         if (cached == kBoth) PSGD_TILES(4, kBoth);
         else if (sizeof(GT) == 2 && cached) PSGD_TILES(4, plan::kCachedLoads);
         else PSGD_TILES(4, 0);

@@ -256,6 +256,19 @@ int main() {
                         CHECK(t.tiles >= cus && t.tiles << t.logc >= ncg, "n=%d, %lld column groups: %lld tiles", n, (long long)ncg, (long long)t.tiles);
                     }
                 }
+    // with the next gradients beside the tiles three rows at most (no kernel has more), on segments no narrower than without them but for
+    // half of them; in front of the tiles the same tiles as without
+    for (int cus : {64, 256, 304})
+        for (int n = 3; n <= 512; ++n)
+            for (int64_t ncg : {192 * (int64_t)cus, 3600 * (int64_t)cus + 1, 30000 * (int64_t)cus + 5})
+                for (bool cd : {false, true}) {
+                    const ShortPlan t = ring_tiles(n, ncg, cd, true), u = ring_tiles(n, ncg, cd, false);
+                    CHECK(!t.one && t.rows >= 1 && t.rows <= (tiles_produce(n) ? 3 : 4) && t.nrg * t.rows >= n && t.threads % 64 == 0 && t.threads <= kRingThreadsMost &&
+                              t.lds <= kShortLds && t.tiles << t.logc >= ncg, "n=%d: tiles of %d rows beside the next gradients", n, t.rows);
+                    CHECK(u.rows <= 4 && u.nrg * u.rows >= n && u.threads <= kRingThreadsMost && u.lds <= kShortLds && u.tiles << u.logc >= ncg, "n=%d: tiles of %d rows", n, u.rows);
+                    CHECK(n < 9 || (tiles_produce(n) ? t.logc >= 3 && t.logc + 1 >= u.logc : t.logc == u.logc), "n=%d: segments of 2^%d groups with the next gradients, 2^%d without",
+                          n, t.logc, u.logc);
+                }
     for (int cus : {64, 256, 304})
         for (const auto& b : full_bands)
             for (int n = b.lo; n <= b.hi; ++n)

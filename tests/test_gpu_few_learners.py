@@ -37,6 +37,8 @@ def test_ring_walk_of_few_learners(psgd, n, d, deg, gkind, extra):
     (500, 26_999, 3, 0), (500, 27_001, -3, 1), (257, 52_529, -3, 0), (257, 52_531, 3, 2), (150, 50_001, 3, 1), (300, 30_002, -3, 3),
     # the ring walk from its line for this schedule on, rings and other tables
     (4, 6_144_001, 3, 0), (5, 4_915_205, 3, 1), (8, 3_072_004, 3, 0), (8, 3_072_001, -3, 0), (9, 1_536_001, 3, 0), (12, 1_228_804, -3, 0),
+    # its other tables' tiles: of three rows up to 384 learners, of four with the next gradients in front of them beyond
+    (384, 196_608, -3, 0), (385, 196_608, -3, 0), (385, 196_613, -3, 1), (512, 196_610, -3, 2), (450, 196_611, 3, 0),
     (16, 921_601, 3, 2), (32, 450_563, 3, 0), (64, 225_284, -3, 0), (128, 225_281, 3, 1), (128, 225_285, -3, 0)])
 def test_next_gradients_beside_the_step(mods, n, d, deg, extra):
     test_gpu_d1d_one_pass.test_one_pass_is_the_two_calls(mods, n, d, deg, extra)
