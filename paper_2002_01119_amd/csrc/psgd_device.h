@@ -352,8 +352,9 @@ __device__ __forceinline__ void last_sum(const Gather& g, double mine) {       /
     const int tid = threadIdx.x;
     if (tid >= 64) return;
     const unsigned count = gridDim.x;
+    unsigned (*counters)[32] = g_tickets[g.array];                // not named in the lambda, which would take its address from a table in memory
     auto draw = [&](plan::Ticket t) {                             // whether this is the last of t.of to come
-        return atomicInc(&g_tickets[g.array][t.at][0], (unsigned)t.of - 1) == (unsigned)t.of - 1;
+        return atomicInc(&counters[t.at][0], (unsigned)t.of - 1) == (unsigned)t.of - 1;
     };
     int last = 0;
     if (tid == 0) {
