@@ -411,14 +411,18 @@ inline ShortPlan short_loop_plan(int n, int deg, int64_t ncg, bool cd) {
     }
     return best;
 }
-// The tiles of a table that is not one ring, on rows that the ring walk would take.  Up to eight learners: 512 lanes of four rows (us, by
-// 1024 lanes of two / so / short_plan's, which it was: 3 x 9 M 74.4 / 56.8 / 58.7, 4 x 6 M 56.5 / 52.1 / 54.2, 5 x 6 M 74.2 / 72.7 / 69.3, 7 x 6 M
-// 97.7 / 96.5 / 95.8, 8 x 24 M 413 / 391 / 408).  With the next gradients at most three rows: more than that the registers do not hold.  Beyond
+// The tiles of a table that is not one ring, on rows that the ring walk would take.  Up to eight learners: 512 lanes of four rows, with the distance
+// and five to seven of them 1024 lanes of two (us, short_plan's, which it was / 512 lanes of four / 1024 of two: 3 x 9 M 58.7 / 56.8 / 74.4, 4 x 6 M 54.2 / 52.1
+// / 56.5, 8 x 24 M 408 / 391 / 413; with the distance 5 x 11.1 M 126.1 / 131.5 / 124.2, bf16 gradients 5 x 24.6 M 230 / 240 / 229, 6 x 21.3 M 232 / 243 / 233, fp32 6 x 6.2 M 79.9 / 80.9
+// / 80.3, off the lines 7 x 15.6 M 254 / 259 / 254; not six of fp32 off the lines, 24.3 M 315 / 305 / 320, nor eight, 14.2 M 242 / 235 / 242; seven without it stay behind, 7 x 31.3 M 451 / 463, bf16 7 x 20 M 239 / 252, where one ring is ahead,
+// 484 / 431).
+// With the next gradients at most three rows: more than that the registers do not hold.  Beyond
 // 384 learners that would leave segments of 64 bytes: the next gradients are made in front of the tiles, which keep four rows (436 x 257 984 620 with them,
 // 523 apart, 446 x 297 344 806 / 668, 470 x 196 608 599 / 512, off the lines 507 x 244 161 705 / 659).
 inline bool tiles_produce(int n) { return n <= 384; }
-inline ShortPlan ring_tiles(int n, int64_t ncg, bool cd, bool produce) {
-    if (n < 9) return produce ? short_widest(n, 3, ncg, cd, false, kShortThreads, 2) : short_widest(n, 3, ncg, cd, false, 512, 4);
+inline ShortPlan ring_tiles(int n, int64_t ncg, bool cd, bool produce, bool fp32_off_lines) {
+    const bool two = cd && (n == 5 || n == 7 || (n == 6 && !fp32_off_lines));
+    if (n < 9) return produce || two ? short_widest(n, 3, ncg, cd, false, kShortThreads, 2) : short_widest(n, 3, ncg, cd, false, 512, 4);
     const ShortPlan p = short_loop_plan(n, 3, ncg, cd);
     return produce && tiles_produce(n) && p.rows > 3 ? short_widest(n, 3, ncg, cd, false, kShortThreads, 3) : p;
 }

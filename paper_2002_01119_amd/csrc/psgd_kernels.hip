@@ -392,9 +392,9 @@ int launch_ring(const DeviceInfo& di, const char* name, hipStream_t s, const flo
     if (CD && grid > plan::kShortSlots)                       // one partial per workgroup must fit the smallest buffer
         return fail(PSGD_EINVAL, "%s: this launch needs %d partial sums, the buffer holds %d", name, grid, (int)plan::kShortSlots);
     const plan::SweepPlan sp = plan::sweep_plan(ncg, grid, plan::kRingLanes);
-    const plan::ShortPlan tp = plan::ring_tiles(n, ncg, CD, prod != nullptr);
-    const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), rows_on_lines(X, X_out, ld),
-                                             sizeof(GT) == 2);
+    const bool on_lines = rows_on_lines(X, X_out, ld);
+    const plan::ShortPlan tp = plan::ring_tiles(n, ncg, CD, prod != nullptr, sizeof(GT) == 4 && !on_lines);
+    const int cached = plan::cached_accesses(tp, (int64_t)n * d * (int64_t)(8 + sizeof(GT)), on_lines, sizeof(GT) == 2);
 #define PSGD_RING(RAGGED, D, ...)                                                                                         \
     launch_ring_t<GT, CD, RAGGED, D, __VA_ARGS__>(sp, grid, tp, cached, s, X, X_out, G, nbr, w, n, d, ld, neg_lr, gather, \
                                                   prod ? *prod : Produce{})

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(plan::kRingLanes + 64) void mix_step_kernel(const f
     do {                                                                                                                   \
         int t = tid, rows = n, logc = logc_all, nrg = tiles.nrg;                                                         \
         asm volatile("; tiles of %4 rows per lane, accesses %5" : "+v"(t), "+s"(rows), "+s"(logc), "+s"(nrg) : "n"(R), "n"(CACHED)); \
-        short_tiles<GT, CD, 3, R, false, CACHED, false, BESIDE>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
+        short_tiles<GT, CD, 3, R, false, CACHED, false, BESIDE, true>(t, X, Xout, G, nbr, w, 3, rows, d, ld, neg_lr, logc, nrg,          \
                                                         plan::short_table_bytes(rows, 3), rows << (logc + 4), gather,            \
                                                         ShortLds{lds_raw, lds_waves, lds_bad}, prod);                      \
     } while (0)

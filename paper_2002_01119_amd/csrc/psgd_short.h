@@ -48,14 +48,15 @@ __device__ __forceinline__ void produce_tiles(int tid, const float* X, int n, in
 
 // DEG: slots per table row, 3 or 0 (any).  ONE: a tile per workgroup (two or up to eight rows per lane: nothing is
 // loaded ahead, so those registers hold rows).  CACHED: which accesses go without the non-temporal hint (plan::cached_accesses).
-// FEW: rows of fewer than four columns.  PROD: also the next gradients of the delay-by-one schedule, of the rows as they were.
+// FEW: rows of fewer than four columns.  PROD: also the next gradients of the delay-by-one schedule, of the rows as they were.  WALK: in the kernel
+// of the ring walk.
 // Run by nrg << logc lanes of the workgroup, lane `tid` of them, the others having ended.
 struct ShortLds {
     char* dynamic;                           // plan::ShortPlan::lds bytes
     double* waves;                           // one per wavefront
     int* bad;                                // the same
 };
-template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool PROD>
+template <typename GT, bool CD, int DEG, int R, bool ONE, int CACHED, bool FEW, bool PROD, bool WALK>
 __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout, const GT* __restrict__ G,
                                             const int32_t* __restrict__ nbr, const float* __restrict__ w, int deg_any, int n, int64_t d, Pitch ld, float neg_lr,
                                             int logc, int nrg, int tab_bytes, int tile_bytes, const Gather& gather,
@@ -164,8 +165,27 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
         }
         // SB rows' slot chains advance together (a table read, then a tile read that depends on it, per slot).
         constexpr int SB = PROD && !ONE ? 2 : R < 4 ? R : 4;           // two where registers go to the noise too
+        // The next gradients' loads behind the outputs' stores: with two rows the compiler puts them in front beside the ring walk, and with bf16 gradients,
+        // and a tile then waits for its gradients where it needs its rows (with the distance, 5 x 14.5 M off the lines bf16 159 / 147 us, 5 x 11.2 M 132 / 125,
+        // 6 slots 5 x 14.9 M bf16 160 / 149; fp32 gradients in the short-row kernel are in that order anyway, and pinning it loses off the lines, 6 x 24.5 M
+        // with 4 slots 316 / 331).
+        constexpr bool LOADS_LAST = R == 2 && !PROD && !ONE && (WALK || sizeof(GT) == 2);
+        // The last place of a lane may have no row: without the distance, where registers allow it, its output is not stored a second time (7 x
+        // 31.3 M 499 / 463 us, 11 x 2.1 M off the lines 55.4 / 52.7, 34 x 475 741 bf16 38.7 / 37.6).
+        constexpr bool CHECKED = R == 4 && !CD && !PROD;
         double a[4] = {0.0, 0.0, 0.0, 0.0}, sq[4] = {0.0, 0.0, 0.0, 0.0};
         f32x4 pv;
+        auto to_distance = [&](int u, const f32x4& o) __attribute__((always_inline)) {
+            if (CD && u == 0) pv = o;
+            if (CD && u > 0 && rg + u * nrg < n) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double df = (double)o[k] - (double)pv[k];
+                    a[k] += df;
+                    sq[k] = fma(df, df, sq[k]);
+                }
+            }
+        };
 #pragma unroll
         for (int j = 0; j < R; j += SB) {
             __builtin_amdgcn_sched_barrier(0);
@@ -202,26 +222,28 @@ __device__ __forceinline__ void short_tiles(int tid, const float* X, float* Xout
                 if (PROD && !EARLY) asm volatile("" : "+v"(rg));
                 float* to = Xout + (int64_t)row_of(u) * ld.o + cg.col;
                 if (FULL) {
-                    st_x<CS>(to, o);
+                    if (!CHECKED || u + 1 < R || rg + u * nrg < n) st_x<CS>(to, o);
                     if (PROD) {
                         st_x<CS>(prod.g + (int64_t)row_of(u) * prod.ldg + cg.col, vfma(prod.c, own_row(u), noise[u % NR]));
                         load_noise(u, next);
                     }
-                    g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + next.col, d);
+                    if (!LOADS_LAST) g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + next.col, d);
                 } else if (rg + u * nrg < n) {
                     st_cols<CS>(to, o, cg);
                     if (PROD) st_cols<CS>(prod.g + (int64_t)row_of(u) * prod.ldg + cg.col, vfma(prod.c, own_row(u), noise[u % NR]), cg);
                 }
                 if (PROD && u + NR < R) load_noise(u + NR, cg);
-                if (CD && u == 0) pv = o;
-                if (CD && u > 0 && rg + u * nrg < n) {
+                if (LOADS_LAST) out[i] = o;
+                else to_distance(u, o);
+            }
+            if (LOADS_LAST) {
+                if (FULL) {
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const double df = (double)o[k] - (double)pv[k];
-                        a[k] += df;
-                        sq[k] = fma(df, df, sq[k]);
-                    }
+                    for (int u = 0; u < R; ++u) g[u] = ld_cols_raw<FEW, CL>(G + (int64_t)row_of(u) * ld.g + next.col, d);
                 }
+#pragma unroll
+                for (int u = 0; u < R; ++u) to_distance(u, out[u]);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -260,7 +282,7 @@ __global__ __launch_bounds__(plan::kShortThreads, plan::kShortThreads / 256) voi
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     __shared__ double lds_waves[plan::kShortThreads / 64];
     __shared__ int lds_bad[plan::kShortThreads / 64];
-    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW, PROD>(threadIdx.x, X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes,
+    short_tiles<GT, CD, DEG, R, ONE, CACHED, FEW, PROD, false>(threadIdx.x, X, Xout, G, nbr, w, deg_any, n, d, ld, neg_lr, logc, nrg, tab_bytes,
                                                   tile_bytes, gather, ShortLds{lds_raw, lds_waves, lds_bad}, prod);
 }
 

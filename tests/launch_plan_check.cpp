@@ -256,13 +256,18 @@ int main() {
                         CHECK(t.tiles >= cus && t.tiles << t.logc >= ncg, "n=%d, %lld column groups: %lld tiles", n, (long long)ncg, (long long)t.tiles);
                     }
                 }
+    for (int n = 3; n < 9; ++n) {
+        const ShortPlan with = ring_tiles(n, 3000000, true, false, false), without = ring_tiles(n, 30000000, false, false, true);
+        CHECK(ring_tiles(6, 3000000, true, false, true).rows == 3, "six learners off the lines");
+        CHECK(with.rows == (n == 3 ? 3 : n == 4 || n == 8 ? 4 : 2) && without.rows == (n < 4 || n == 5 || n == 6 ? 3 : 4), "n=%d: tiles of %d and %d rows", n, with.rows, without.rows);
+    }
     // with the next gradients beside the tiles three rows at most (no kernel has more), on segments no narrower than without them but for
     // half of them; in front of the tiles the same tiles as without
     for (int cus : {64, 256, 304})
         for (int n = 3; n <= 512; ++n)
             for (int64_t ncg : {192 * (int64_t)cus, 3600 * (int64_t)cus + 1, 30000 * (int64_t)cus + 5})
                 for (bool cd : {false, true}) {
-                    const ShortPlan t = ring_tiles(n, ncg, cd, true), u = ring_tiles(n, ncg, cd, false);
+                    const ShortPlan t = ring_tiles(n, ncg, cd, true, ncg & 1), u = ring_tiles(n, ncg, cd, false, ncg & 1);
                     CHECK(!t.one && t.rows >= 1 && t.rows <= (tiles_produce(n) ? 3 : 4) && t.nrg * t.rows >= n && t.threads % 64 == 0 && t.threads <= kRingThreadsMost &&
                               t.lds <= kShortLds && t.tiles << t.logc >= ncg, "n=%d: tiles of %d rows beside the next gradients", n, t.rows);
                     CHECK(u.rows <= 4 && u.nrg * u.rows >= n && u.threads <= kRingThreadsMost && u.lds <= kShortLds && u.tiles << u.logc >= ncg, "n=%d: tiles of %d rows", n, u.rows);

@@ -19,7 +19,9 @@ mods = test_gpu_d1d_one_pass.mods
     (5, 4_915_201, 3, "f32", (3, 1, 2)), (6, 4_096_003, 3, "bf16", None), (6, 17_066_668, 3, "f32", None), (7, 3_510_859, 3, "f32", None),
     (8, 3_071_996, 3, "bf16", None), (8, 12_799_997, 3, "f32", (1, 2, 3)),
     (3, 8_192_004, -3, "f32", None), (4, 6_144_001, -3, "bf16", (1, 2, 3)), (5, 4_915_204, -3, "bf16", None), (7, 3_510_861, -3, "f32", None),
-    (8, 12_800_004, -3, "f32", None)])
+    (8, 12_800_004, -3, "f32", None),
+    # the tiles of those by form: four rows per lane without the distance (the last place of seven learners has no row), two rows with it
+    (6, 4_096_001, -3, "bf16", (1, 2, 3)), (6, 17_066_672, -3, "f32", None), (7, 14_628_576, -3, "f32", None), (7, 14_628_573, -3, "bf16", (1, 2, 3))])
 def test_ring_walk_of_few_learners(psgd, n, d, deg, gkind, extra):
     test_gpu_short_rows.test_short_rows_every_element(psgd, n, d, deg, gkind, extra)
 
