@@ -242,14 +242,23 @@ inline TilePlan tile_plan(int n, int deg, int threads, bool cd, size_t cap, int 
 // Whether long rows (two column groups for every lane of 768 per compute unit) of a table of other than three slots take the tiled
 // kernel.  `room`: 2, every row of X and X_out starts on a 128-byte line; 1, on 16 bytes, and there are twice as many columns; 0, neither.
 // Its tiles are a power of two of column groups wide, and as deep as a power of two of row groups: learners that fill them, 13 to 16, 29 to 32,
-// 53 to 64 and 105 to 128, are as well off there or better, tables of many slots with the distance most (us, short-row / tiled: 64 x 2 M with 16
+// 49 to 64 and 105 to 128, are as well off there or better, tables of many slots with the distance most (us, short-row / tiled: 64 x 2 M with 16
 // slots and the distance 296 / 270, 30 x 3.2 M with 20 and bf16 gradients 303 / 215); the others leave places empty (on lines, with the distance, tiled /
 // short-row: 9 x 6 M with 5 slots 156 / 119, with 32 264 / 190, 12 x 4 M 123 / 108, 20 x 4 M 204 / 178, 24 x 4 M 226 / 214, 33 x 3 M 276 / 225, 40 x 2 M 202 / 178, 48 x 2 M
 // 225 / 213; off them, 16 slots and more, in times: 10 x 8 M 1.1 to 1.5, 24 x 4 M 1.02 to 1.2, 40 x 4 M 1.03 to 1.35).  13 to 16 learners on lines: only
-// with the distance and 16 slots (14 x 6 M with 4 slots and none 193 / 180, with 16 and the distance 205 / 206).  65 to 104: from 16 slots (96 and 100 x
-// 1.6 M with fewer 1.00 to 1.03 times).  The largest tables halve the tile (128 x 1.6 M with 32 slots 1.6 to 1.8 times).  Off the lines few slots
+// with the distance and 16 slots (14 x 6 M with 4 slots and none 193 / 180, with 16 and the distance 205 / 206).  Nearly filled, and without
+// the distance: on lines 25 to 28 with 14 to 23 slots, 23 and 24 from 16, 43 to 48 from 18 (27 x 2.2 M with 23 slots 69 % of the short-row kernel's time, 28 x
+// 2 003 296 bf16 with 21 86.7, 24 x 1 687 520 bf16 with 22 91.7, 27 x 2 890 912 bf16 with 14 83.4, 43 x 2 105 728 bf16 with 19 91.3, 47 x 1 981 024 bf16 with 21 87.7;
+// with 24 a tile per workgroup is ahead, 44 x 2.4 M 253 / 298; 45 x 5 M with 17 103.5, 22 bf16 with 19 and 22 110); off the lines 25 to 28 from 16 on, the others from
+// 20 (27 x 8 M with 22 79, 28 x 5.5 M bf16 with 25 84, 23 x 7 M with 23 95, 47 x 3.4 M bf16 with 24 90).
+// 65 to 104: from 16 slots (with fewer the tiles take
+// 97 to 114 % of the time, 103.5 on average over 60 shapes).  The largest tables halve the tile (128 x 1.6 M with 32 slots 1.6 to 1.8 times).  Off the lines few slots
 // keep to it with 29 to 32 learners only (32 x 3 M with 13, short-row / tiled 236 / 220).
 inline bool tiled_rows(int n, int deg, bool cd, int room) {
+    if ((n > 22 && n < 29) || (n > 42 && n < 49)) {              // nearly filled
+        const int from = n < 25 ? 16 : n < 29 ? 14 : 18;
+        return !cd && (room == 2 ? deg >= from && deg < 24 : room == 1 && deg >= (n > 24 && n < 29 ? 16 : 20));
+    }
     if (n < 13 || (n > 16 && n < 29) || (n > 32 && n < 49) || n > 128 || n * deg > 3840) return false;
     if (room < 2) return (n > 28 && n < 33) || (room == 1 && n <= 64 && deg >= 16);
     return n < 17 ? cd && deg >= 16 : n < 65 || n > 104 || deg >= 16;

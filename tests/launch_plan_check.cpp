@@ -230,6 +230,23 @@ int main() {
         CHECK(tile_plan(256, 3, 1024, false, large, 4).lpr == 16, "n = 256: 256-byte row segments");
         CHECK(tile_plan(257, 3, 1024, false, large, 4).lpr == 0, "n = 257: no plan");
     }
+    // which tables of other than three slots on long rows take the tiled kernel; every one of them has a plan at both sizes of its workgroups
+    const struct { int n, deg; bool cd; int room; bool tiled; } tables[] = {
+        {12, 16, true, 2, false}, {13, 16, true, 2, true}, {14, 15, true, 2, false}, {16, 32, true, 2, true}, {16, 32, false, 2, false}, {16, 5, true, 2, false},
+        {17, 20, true, 2, false}, {22, 20, false, 2, false}, {23, 16, false, 2, true}, {24, 15, false, 2, false}, {25, 14, false, 2, true}, {27, 23, false, 2, true}, {28, 24, false, 2, false}, {28, 20, true, 2, false},
+        {28, 20, false, 1, true}, {28, 32, false, 1, true}, {24, 20, false, 1, true}, {24, 19, false, 1, false}, {44, 20, false, 1, true}, {44, 20, true, 1, false}, {27, 20, false, 0, false}, {29, 4, false, 0, true}, {30, 13, true, 2, true}, {32, 32, true, 1, true}, {33, 20, false, 2, false}, {42, 20, false, 2, false},
+        {43, 18, false, 2, true}, {43, 17, false, 2, false}, {48, 23, false, 2, true}, {48, 24, false, 2, false}, {49, 4, true, 2, true}, {60, 16, true, 1, true}, {60, 15, true, 1, false}, {60, 16, true, 0, false},
+        {64, 13, false, 2, true}, {65, 15, true, 2, false}, {70, 13, false, 2, false}, {100, 16, true, 2, true}, {104, 5, false, 2, false}, {105, 5, true, 2, true}, {113, 5, false, 2, true},
+        {113, 16, false, 1, false}, {120, 32, false, 2, true}, {128, 30, true, 2, true}, {128, 32, false, 2, false}, {129, 5, true, 2, false}};
+    for (const auto& e : tables) CHECK(tiled_rows(e.n, e.deg, e.cd, e.room) == e.tiled, "n=%d deg=%d cd=%d room=%d: tiled kernel", e.n, e.deg, (int)e.cd, e.room);
+    for (int n = 1; n <= 512; ++n)
+        for (int deg = 1; deg <= 32 && n * deg <= 4096; ++deg)
+            for (int form = 0; form < 6; ++form) {
+                const bool cd = form & 1;
+                if (!tiled_rows(n, deg, cd, form >> 1)) continue;
+                const TilePlan p = tile_plan(n, deg, cd ? 512 : 1024, cd, large, cd ? 8 : 4);
+                CHECK(p.lpr >= 16 && p.total <= large, "n=%d deg=%d cd=%d: no tile", n, deg, (int)cd);
+            }
     // where the ring walk and the paced global averaging run: each band of learners from its line on (column groups per compute unit)
     const struct { int lo, hi; int64_t line; } bands[] = {{9, 11, 3600}, {12, 15, 2500}, {16, 23, 1600}, {24, 31, 800}, {32, 47, 560},
                                                           {48, 95, 400}, {96, 199, 307}, {200, 255, 230}, {256, 512, 192}};

@@ -374,7 +374,7 @@ def test_distance_far_from_origin(psgd, n, deg, d):
     """Replicas that agree to 1e-4 but sit at O(1) and move by a common 1000 per step: the distance is measured
     against an output of the same column, so the large common shift must cancel exactly (a pivot taken from the
     inputs would leave only ~4 of the distance's digits).  The short-row kernel on the short rows; on the long ones
-    (on 128-byte lines) the tiled kernel for more than three slots."""
+    (on 128-byte lines) the tiled kernel for 64 learners and more than three slots."""
     rng = np.random.default_rng(n + deg)
     nbr, w = _general_table(n, rng) if deg == 3 else _perm_sum_table(n, deg, rng)
     X = (np.tile(inp.host_normal_f32((1, d), 1.0, 1), (n, 1)) + inp.host_normal_f32((n, d), 1e-4, 2)).astype(np.float32)
@@ -677,10 +677,10 @@ def test_steps_captured_in_a_hip_graph_replay_exactly(psgd):
         assert abs(psgd.consensus_dist(out) - c_eager[-1].item()) <= 1e-9 * c_eager[-1].item()
 
 
-@pytest.mark.parametrize("n,d", [(16, 1_600_004), (40, 1_600_032), (40, 1_200_003)])
+@pytest.mark.parametrize("n,d", [(16, 1_600_004), (40, 1_600_032), (40, 1_200_003), (53, 1_572_896)])
 def test_long_row_kernels_captured_in_a_hip_graph_replay_exactly(psgd, n, d):
-    """The same on rows long enough for the large workgroups: the ring walk (more than 64 KB of LDS), a 5-slot table (d on
-    128-byte lines: the tiled kernel, else the short-row one) and global averaging, every one with the fused distance, captured
+    """The same on rows long enough for the large workgroups: the ring walk (more than 64 KB of LDS), a 5-slot table (n = 53: the
+    tiled kernel, else the short-row one) and global averaging, every one with the fused distance, captured
     once after an eager pass and replayed between eager work.  n = 16 takes one pass per table only."""
     rng = np.random.default_rng(5)
     X0 = dev(inp.host_normal_f32((n, d), 1.0, 23))
@@ -814,8 +814,8 @@ def test_binding_checks_dtypes_and_devices(psgd):
                                   (40, 1_500_001)])
 def test_many_sweeps_per_workgroup(psgd, kind, n, d):
     """Rows long enough that the workgroups of the short-row kernel and of global averaging stride over many
-    tiles / column groups (the small shapes finish in one), with a ragged last tile; n = 40 takes the ring walk and, for
-    more than three slots on its lines, the tiled kernel.  Every element is compared."""
+    tiles / column groups (the small shapes finish in one), with a ragged last tile; n = 40 takes the ring walk.  Every
+    element is compared."""
     lr = 0.1
     rng = np.random.default_rng(d % 1000 + len(kind))
     X = inp.host_normal_f32((n, d), 1.0, 61)
@@ -970,7 +970,7 @@ _LONG_ROW_CASES = (
        (16, 1_900_004, "two_rings", "bf16"), (16, 1_900_004, "deg5", "f32"),
        (5, 2_000_004, "deg5", "f32"), (5, 2_000_004, "deg13", "bf16"),
        (48, 1_600_003, "two_rings", "f32"), (48, 1_600_003, "deg5", "bf16")]
-    # rows on 128-byte lines: the tiled kernel (for the two rings the tiles of the ring walk's kernel)
+    # rows on 128-byte lines: the tiled kernel for 64 and 128 learners (for the two rings the tiles of the ring walk's kernel)
     + [(64, 1_600_032, k, g) for k in ("two_rings", "deg5", "deg13") for g in ("f32", "bf16")]
     + [(128, 1_600_032, "two_rings", "bf16"), (128, 1_600_032, "deg5", "f32"), (128, 1_600_032, "deg13", "bf16"),
        (33, 1_700_032, "deg5", "f32"), (33, 1_700_032, "deg13", "bf16"), (30, 1_600_003, "two_rings", "bf16"),
@@ -980,11 +980,10 @@ _LONG_ROW_CASES = (
 
 @pytest.mark.parametrize("n,d,kind,gkind", _LONG_ROW_CASES)
 def test_general_tables_long_rows_every_element(psgd, n, d, kind, gkind):
-    """Long rows and tables that are not one ring.  More than three slots on 128-byte lines (and for n = 29 to 32): the tiled kernel, merge
-    slots of the distance inside the consumed tile buffer at 16 B per lane; wider rows for n = 16 and 10; an odd row
-    count per row group for n = 33; narrower rows for n = 70 and n = 128; 16-byte accesses on the lines and, for n = 30
-    off them, one column per lane at the ragged end.  Off the lines and for n <= 8 the short-row kernel over many
-    tiles.  The two rings: its tiles in the ring walk's kernel.  Every element and the fused distance against the
+    """Long rows and tables that are not one ring.  More than three slots on 128-byte lines and n = 64 or 128: the tiled kernel, merge
+    slots of the distance inside the consumed tile buffer at 16 B per lane, narrower rows for n = 128.  Off the lines and for the
+    other numbers of learners, which do not fill its tiles, the short-row kernel over many tiles.  The two rings: its tiles in the ring
+    walk's kernel.  Every element and the fused distance against the
     oracle, out of place and in place, ragged last tile included."""
     rng = np.random.default_rng(n + d % 1000)
     if kind == "two_rings":
@@ -1035,8 +1034,7 @@ def test_general_tables_long_rows_many_learners(psgd, n, kind, gkind):
 def test_tiled_kernel_long_rows_widest_tables(psgd, n, deg, gkind, d):
     """32 slots per row on long rows that start on 128-byte lines: the slot table takes 16 KB (32 KB for 128
     learners) of LDS, so the merge slots of the distance no longer fit beside the two tile buffers and live in the
-    buffer that has just been consumed (n = 64), or the rows get narrower (n = 128).  From 16 slots on the kernel also
-    takes longer rows that only start on 16 bytes (n = 9).  Every element and the distance against the oracle."""
+    buffer that has just been consumed (n = 64).  The widest table of 128 learners and 9 learners go to the short-row kernel.  Every element and the distance against the oracle."""
     rng = np.random.default_rng(n + deg)
     nbr, w = _perm_sum_table(n, deg, rng)
     X = inp.host_normal_f32((n, d), 1.0, 740 + n)
@@ -1062,7 +1060,7 @@ def test_general_tables_long_rows_distance_corner_cases(psgd, n, d, slots):
     """The row groups of a tile each measure against their own pivot and the merge brings them to a common one:
     replicas far from the origin and close together must still give the distance to 1e-6, and identical outputs must
     give exactly 0.  Two rings: n = 16 takes the short-row kernel, 64 and 128 learners its tiles in the ring walk's kernel; five
-    slots: the short-row kernel off the 128-byte lines, the tiled one on them."""
+    slots: 64 and 128 learners on the 128-byte lines the tiled kernel, else the short-row one."""
     nbr, w = _two_rings_table(n) if slots == 3 else _perm_sum_table(n, slots, np.random.default_rng(n))
     base = inp.host_normal_f32((1, d), 100.0, 3)
     X = (np.tile(base, (n, 1)) + inp.host_normal_f32((n, d), 1e-3, 4)).astype(np.float32)

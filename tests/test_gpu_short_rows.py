@@ -70,6 +70,11 @@ def _strided(a, extra, shift):
 
 @pytest.mark.parametrize("n,d,deg,gkind,extra", CASES)
 def test_short_rows_every_element(psgd, n, d, deg, gkind, extra):
+    every_element(psgd, n, d, deg, gkind, extra, 1 if extra else 0)
+
+
+def every_element(psgd, n, d, deg, gkind, extra, shift):
+    """shift: elements in front of X, twice as many in front of X_out, three times of G."""
     rng = np.random.default_rng(n + d)
     ring, deg = deg == 3 and n != 64, abs(deg)
     if ring:
@@ -88,7 +93,6 @@ def test_short_rows_every_element(psgd, n, d, deg, gkind, extra):
     # one fp32 rounding per slot and one for the gradient term, each on a partial sum no larger than this
     tol = (deg + 1) * 2.0 ** -24 * (float(np.abs(X).max()) + lr * gmax)
     ex, eo, eg = extra or (0, 0, 0)
-    shift = 1 if extra else 0
     Xd = _strided(X, ex, shift)
     Gd = _strided(G.view(np.int16) if gkind == "bf16" else G, eg, 3 * shift)
     nd, wd = torch.from_numpy(nbr).to("cuda:0"), torch.from_numpy(w).to("cuda:0")
