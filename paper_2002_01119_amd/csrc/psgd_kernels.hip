@@ -57,6 +57,7 @@ struct DeviceInfo {
     hipEvent_t partials_idle = nullptr;     // recorded on the previous user's stream when another stream takes over
     hipStream_t partials_stream = nullptr;  // the stream (not under capture) that used `partials` last
     bool partials_used = false;
+    std::mutex partials_mutex;         // held from acquire_partials until the caller has launched
     double* static_partials = nullptr;  // device address of ::scratch on this GPU (psgd_mix_step_cd_static)
     double* host_result = nullptr;      // pinned host memory, hipHostMalloc'ed on first use (psgd_consensus_dist),
     double* host_result_dev = nullptr;  // and its address on the device
@@ -106,8 +107,10 @@ bool stream_is_capturing(hipStream_t s) {
 // so far on the previous stream and the new stream is made to wait for it (on the device, not on the host), so
 // two streams that both gather a distance are serialised instead of racing.  Streams under capture are left
 // alone: the order of graph launches is the caller's.
-int acquire_partials(DeviceInfo* di, hipStream_t s, double** out) {
-    std::lock_guard<std::mutex> lock(g_dev_mutex);
+// `use` holds the buffer until the caller has launched: a thread that came in between would make its stream wait for what stood on this one
+// before the launch.
+int acquire_partials(DeviceInfo* di, hipStream_t s, double** out, std::unique_lock<std::mutex>* use) {
+    *use = std::unique_lock<std::mutex>(di->partials_mutex);
     if (di->partials && di->partials_used && di->partials_stream == s) {
         *out = di->partials;
         return PSGD_OK;
@@ -143,10 +146,6 @@ int acquire_partials(DeviceInfo* di, hipStream_t s, double** out) {
     di->partials_used = true;
     return PSGD_OK;
 }
-
-// Called after the last kernel that reads the partials has been enqueued on `s` (nothing to do: the next user
-// on another stream records its own event behind this work).
-int release_partials(DeviceInfo*, hipStream_t) { return PSGD_OK; }
 
 // Device address of the static scratch array on the current GPU, looked up once per device.
 int static_partials(DeviceInfo* di, double** out) {
@@ -477,10 +476,11 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     // use, shared by every call on the device, streams serialised), or the static array of the entry point
     // that may not allocate (no serialisation: that would need an event).
     double* partials = nullptr;
+    std::unique_lock<std::mutex> use;
     if (want_cd) {
         if (no_alloc) {
             if (int rc = static_partials(di, &partials)) return rc;
-        } else if (int rc = acquire_partials(di, s, &partials)) {
+        } else if (int rc = acquire_partials(di, s, &partials, &use)) {
             return rc;
         }
     }
@@ -488,7 +488,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
         hipLaunchKernelGGL(no_distance_kernel, dim3(1), dim3(1), 0, s, cd_out);
         const hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return hip_fail(e0, "no_distance_kernel");
-        return no_alloc ? PSGD_OK : release_partials(di, s);
+        return PSGD_OK;
     }
     const float neg_lr = -lr;
     const Pitch ld{ldx, ldo, ldg};
@@ -551,7 +551,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     if (e != hipSuccess) return hip_fail(e, name);
     if (prod && !produced)
         if (int rc = enqueue_producer(name, X, ldx, prod->noise, prod->ldn, prod->g, prod->ldg, n, d, prod->c, s)) return rc;
-    return want_cd && !no_alloc ? release_partials(di, s) : PSGD_OK;
+    return PSGD_OK;
 }
 
 template <typename GT>
@@ -587,13 +587,14 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     if (d == 0 && !want_cd) return PSGD_OK;
     if (int rc = device_info(&di)) return rc;
     double* partials = nullptr;
+    std::unique_lock<std::mutex> use;
     if (want_cd)
-        if (int rc = acquire_partials(di, s, &partials)) return rc;
+        if (int rc = acquire_partials(di, s, &partials, &use)) return rc;
     if (d == 0) {
         hipLaunchKernelGGL(no_distance_kernel, dim3(1), dim3(1), 0, s, cd_out);
         const hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return hip_fail(e0, "no_distance_kernel");
-        return release_partials(di, s);
+        return PSGD_OK;
     }
     const int64_t ncg = (d + kVec - 1) / kVec;
     const Pitch ld{ldx, ldo, ldg};
@@ -651,14 +652,15 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
 #undef PSGD_LAUNCH_FULL
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, name);
-    return want_cd ? release_partials(di, s) : PSGD_OK;
+    return PSGD_OK;
 }
 
 int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out_dev, hipStream_t s) {
     DeviceInfo* di = nullptr;
     if (int rc = device_info(&di)) return rc;
     double* partials = nullptr;
-    if (int rc = acquire_partials(di, s, &partials)) return rc;
+    std::unique_lock<std::mutex> use;
+    if (int rc = acquire_partials(di, s, &partials, &use)) return rc;
     Gather gather{partials, out_dev, 0};
     if (d > 0) {
         const int64_t ncg = (d + kVec - 1) / kVec;
@@ -701,7 +703,7 @@ int consensus_enqueue(const float* X, int64_t ldx, int n, int64_t d, double* out
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "consensus_partial_kernel");
-    return release_partials(di, s);
+    return PSGD_OK;
 }
 
 int consensus_check(const char* name, const float* X, int64_t ldx, int n, int64_t d) {

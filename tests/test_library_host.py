@@ -305,8 +305,7 @@ print("waits that met:", stub.stub_met())
 """
 
 
-def test_synchronous_distance_does_not_serialise_devices(tmp_path):
-    """Two threads asking for the distance on two GPUs wait for them at the same time (runtime calls replaced on the CPU)."""
+def _with_stub(tmp_path, program):
     import shutil
     import subprocess
     import sys
@@ -316,5 +315,39 @@ def test_synchronous_distance_does_not_serialise_devices(tmp_path):
     stub = str(tmp_path / "libhipstub.so")
     subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(ROOT, "tests", "hip_host_stub.cpp"), "-o", stub],
                    check=True)
-    r = subprocess.run([sys.executable, "-c", _TWO_DEVICES, stub, psgd._LIB_PATH], capture_output=True, text=True, timeout=60)
+    return subprocess.run([sys.executable, "-c", program, stub, psgd._LIB_PATH], capture_output=True, text=True, timeout=60)
+
+
+def test_synchronous_distance_does_not_serialise_devices(tmp_path):
+    """Two threads asking for the distance on two GPUs wait for them at the same time (runtime calls replaced on the CPU)."""
+    r = _with_stub(tmp_path, _TWO_DEVICES)
     assert r.returncode == 0 and "waits that met: 2" in r.stdout, r.stdout + r.stderr
+
+
+_TWO_STREAMS = """
+import ctypes, sys, threading
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+f = lib.psgd_consensus_dist_async
+f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
+results = []
+def ask(stream):
+    results.append(f(4096, 4, 1000, 65536, stream))           # no kernel reads or writes the addresses
+ask(16)                                                       # the buffer of partial sums exists, used last on this stream
+stub.stub_hold_launch()
+first = threading.Thread(target=ask, args=(16,))
+first.start()
+stub.stub_wait_for_launch()                                   # the first thread has the buffer and is about to launch
+second = threading.Thread(target=ask, args=(32,))
+second.start()
+first.join()
+second.join()
+print("results", results, "ordered too early:", stub.stub_early())
+"""
+
+
+def test_a_thread_on_another_stream_is_ordered_behind_the_launch_not_in_front_of_it(tmp_path):
+    """One thread takes the shared partial sums and has not launched yet when another thread asks for them on another stream: the second one's
+    stream must be made to wait for that launch, not for what was there before it."""
+    r = _with_stub(tmp_path, _TWO_STREAMS)
+    assert r.returncode == 0 and "results [0, 0, 0] ordered too early: 0" in r.stdout, r.stdout + r.stderr
