@@ -202,6 +202,8 @@ inline bool distance_alone(int n, int64_t ncg, int cus) { return n < 4 && ncg >=
 // 864 096 35.7 / 35.9, 59 x 996 255 41.4 / 41.9.  Below it: 27 x 786 464 16.7 / 17.7, 30 x 1 089 152 23.8 / 24.6, 66 x 603 168 (590 workgroups) 28.2 / 28.8.
 // More than five on each from 120 MB on: 25 x 1 454 523 28.0 / 26.6, 32 x 1 363 200 31.1 / 30.2, 22 x 1 484 000 23.9 / 23.9.
 inline bool distance_summed_apart(int grid, int n, int64_t d, int cus) { return grid > 3 * cus && n * d >= (grid > 5 * cus ? 30000000 : 48000000); }
+// Rows on their way per lane in global averaging's walk, which needs more rows than that.
+inline int full_depth(const SweepPlan& s, int n) { return n < 6 || s.chunk >= 576 ? 2 : 4; }
 inline int full_lead(int depth) { return depth == 2 ? 16 : 7 * depth; }
 
 // LDS of the tiled kernel (long rows, tables of other than three slots): the slot table (8 bytes per slot), TWO tile

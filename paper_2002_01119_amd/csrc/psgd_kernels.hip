@@ -494,7 +494,7 @@ int mix_step_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
     const Pitch ld{ldx, ldo, ldg};
     const Gather gather{partials, cd_out, no_alloc ? 1 : 0};
     const int64_t ncg = (d + kVec - 1) / kVec;
-    // 3-slot tables: from plan::ring_rows on mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
+    // 3-slot tables: where plan::walk_rows says so mix_step_kernel, which walks one ring (every table of Sec. 3) and takes any other table
     // through tiles; below it the short-row kernel.
     // Tables of other slot counts: the short-row kernel, but for long rows where plan::tiled_rows says so.
     const bool quads = d % kVec == 0 && rows_start_on(16, X, X_out, ld);
@@ -616,8 +616,9 @@ int mix_full_impl(const char* name, const float* X, int64_t ldx, float* X_out, i
                            n, d, ld, neg_lr, Sweeps{sp.count, sp.chunk}, lanes, next_pace_slot(), plan::full_lead(D),       \
                            gather);                                                                                        \
     } while (0)
-        if ((n < 6 || sp.chunk >= 576) && want_cd) PSGD_LAUNCH_WALK(true, 2);   // n > D
-        else if (n < 6 || sp.chunk >= 576) PSGD_LAUNCH_WALK(false, 2);
+        const bool two = plan::full_depth(sp, n) == 2;
+        if (two && want_cd) PSGD_LAUNCH_WALK(true, 2);
+        else if (two) PSGD_LAUNCH_WALK(false, 2);
         else if (want_cd) PSGD_LAUNCH_WALK(true, 4);
         else PSGD_LAUNCH_WALK(false, 4);
 #undef PSGD_LAUNCH_WALK

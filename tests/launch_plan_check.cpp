@@ -145,7 +145,7 @@ int main() {
     // further ahead than the end of the next sweep
     for (int cus : {1, 64, 256, 304})
         for (int64_t ncg = 1; ncg < (int64_t)1 << 34; ncg += ncg / 7 + 16)
-            for (int n : {9, 10, 15, 16, 17, 64, 512}) {
+            for (int n : {3, 4, 5, 6, 8, 9, 10, 15, 16, 17, 64, 512}) {
                 const SweepPlan p = sweep_plan(ncg, cus, kRingLanes);
                 const int depth = ring_depth(p, n), t = ring_threads({1, p.chunk}, kRingLanes) + 64;
                 CHECK(t <= kRingThreadsMost && t - 64 >= p.chunk && t % 64 == 0, "ring walk: %d lanes, depth %d, chunk %lld", t, depth,
@@ -266,7 +266,7 @@ int main() {
                     // any other table in the same launch: looping tiles of two to four rows per lane on the same workgroups, one partial
                     // sum and at least one tile each
                     for (bool cd : {false, true}) {
-                        const ShortPlan t = short_loop_plan(n, 3, ncg, cd);
+                        const ShortPlan t = ring_tiles(n, ncg, cd, false, ncg & 1);
                         CHECK(!t.one && t.rows >= 2 && t.rows <= 4 && t.nrg * t.rows >= n && t.threads == t.nrg << t.logc &&
                                   t.threads % 64 == 0 && t.threads <= kRingThreadsMost && t.lds <= kShortLds,
                               "n=%d: tiles of %d rows per lane, %d lanes, %zu bytes of LDS", n, t.rows, t.threads, t.lds);
@@ -296,8 +296,37 @@ int main() {
             for (int n = b.lo; n <= b.hi; ++n)
                 for (int64_t ncg : {b.line * cus - 1, b.line * cus, b.line * cus + 1, b.line * cus * 40 + 1})
                     CHECK(full_rows_paced(n, ncg, cus) == (ncg >= b.line * cus), "global averaging in step: n=%d, %lld column groups", n, (long long)ncg);
-    for (int n : {1, 8}) CHECK(!ring_rows(n, (int64_t)1 << 32, 256) && !full_rows_paced(n, (int64_t)1 << 32, 256), "no walk for %d learners", n);
-    for (int depth : {2, 4}) CHECK(depth < 9 && full_lead(depth) >= 4 * depth, "global averaging: lead %d of depth %d", full_lead(depth), depth);
+    // where the launches walk: three to eight learners too, by the column groups of all of them (per compute unit; 0: never)
+    const struct { int n; int64_t without, with, pair_without, pair_with, full; } few[] = {
+        {1, 0, 0, 0, 0, 0}, {2, 0, 0, 0, 0, 0}, {3, 0, 24000, 0, 0, 12000}, {4, 0, 24000, 0, 24000, 12000}, {5, 0, 24000, 24000, 24000, 12000},
+        {6, 100000, 24000, 24000, 24000, 12000}, {8, 100000, 24000, 24000, 24000, 12000}};
+    for (const auto& f : few)
+        for (int cus : {64, 256})
+            for (int form = 0; form < 5; ++form) {
+                const int64_t lines[] = {f.without, f.with, f.pair_without, f.pair_with, f.full}, at = lines[form] ? (lines[form] * cus + f.n - 1) / f.n : (int64_t)1 << 34;
+                auto walks = [&](int64_t ncg) { return form == 4 ? walk_full_rows(f.n, ncg, cus) : walk_rows(f.n, ncg, cus, form & 1, form & 2); };
+                CHECK(!walks(at - 1) && walks(at) == (lines[form] != 0), "n=%d: walked in form %d around %lld column groups", f.n, form, (long long)at);
+            }
+    // whatever is walked: lanes for every chunk, no load further ahead than the rows allow, and workgroups that keep pace
+    for (int cus : {1, 64, 256, 304})
+        for (int n = 1; n <= 512; ++n)
+            for (int64_t per_cu : {1, 192, 220, 307, 440, 576, 800, 961, 1500, 2400, 3600, 4001, 8001, 33334, 100001})
+                for (int form = 0; form < 5; ++form) {
+                    const int64_t ncg = per_cu * cus - 1;
+                    const bool full = form == 4, produce = !full && form & 2;
+                    if (full ? !walk_full_rows(n, ncg, cus) : !walk_rows(n, ncg, cus, form & 1, produce)) continue;
+                    const SweepPlan p = sweep_plan(ncg, cus, kRingLanes);
+                    const int depth = full ? full_depth(p, n) : produce ? ring_depth_produce(p) : ring_depth(p, n);
+                    CHECK(full ? (depth == 2 || depth == 4) && depth < n : depth <= n - 2 && (depth == 1 || depth == 2 || (!produce && (depth == 4 || depth == 6))),
+                          "n=%d, %lld column groups, form %d: depth %d", n, (long long)ncg, form, depth);
+                    CHECK((full ? full_lead(depth) : pace_lead(depth, produce)) >= 4 * depth, "n=%d, depth %d: a lead that the loads on their way need", n, depth);
+                    CHECK(p.chunk <= kRingLanes && ring_threads({1, p.chunk}, kRingLanes) + 64 <= kRingThreadsMost, "n=%d, %lld column groups: chunks of %lld", n,
+                          (long long)ncg, (long long)p.chunk);
+                    CHECK(2 * p.count * n < (int64_t)1 << 29, "n=%d: %lld items, counted in quarters in 32 bits", n, (long long)(2 * p.count * n));
+                }
+    // distances by small workgroups: two or three learners on long rows only
+    CHECK(distance_alone(2, 2560000, 256) && distance_alone(3, 2560000, 256) && !distance_alone(3, 2559999, 256) && !distance_alone(4, (int64_t)1 << 32, 256),
+          "the distance of two and three learners");
     // short rows: whole wavefronts, the rows covered, the LDS within a compute unit's, the grid within the buffer
     for (int n : {1, 2, 3, 5, 8, 9, 16, 17, 33, 64, 65, 100, 128, 200, 256, 257, 300, 511, 512})
         for (int deg : {1, 3, 8, 13, 32})
